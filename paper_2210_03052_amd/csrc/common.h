@@ -119,4 +119,18 @@ __device__ __forceinline__ int wave_max(int v) {
              max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
 }
 
+// First position in the strictly increasing idx[0..n) (non-negative entries) whose value is >= key, by the whole
+// wavefront: 64 probes at a time, so the range shrinks 64-fold per memory round trip instead of twofold.  Since
+// idx[i] >= i the answer is at most key.  Wave-uniform arguments and result.
+__device__ __forceinline__ int wave_lower_bound(const int32_t* __restrict__ idx, int n, int key, int lane) {
+  int lo = 0, hi = min(n, key);
+  while (lo < hi) {
+    const int stride = (hi - lo + kWave - 1) / kWave, at = lo + lane * stride;
+    const int below = __popcll(__ballot(at < hi && idx[min(at, hi - 1)] < key));  // the first `below` probes
+    hi = min(hi, lo + below * stride);
+    if (below > 0) lo += (below - 1) * stride + 1;
+  }
+  return lo;
+}
+
 }  // namespace bt

@@ -26,20 +26,16 @@ __global__ __launch_bounds__(256) void bias_residual_ln_kernel(
   const float* xpart = static_cast<const float*>(xin);
   // res_rows: the residual of packed row i is row res_rows[i] of `residual` (pack fused into the read).
   // out_idx: y is the padded tensor [out_rows, H]; this wave owns padded row r, which is packed row
-  //   `lo` if out_idx[lo] == r (out_idx is increasing: uniform binary search) and a zero row otherwise
+  //   `lo` if out_idx[lo] == r (out_idx is increasing: one wave-wide search) and a zero row otherwise
   //   (unpack fused into the store, Sec. III-D).
   const int lane = threadIdx.x & 63;
-  int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  int row = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int chunks = H >> 3;
   size_t obase;
   if (out_idx) {
     const int r = row;
     if (r >= out_rows) return;
-    int lo = 0, hi = T;
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (out_idx[mid] < r) lo = mid + 1; else hi = mid;
-    }
+    const int lo = wave_lower_bound(out_idx, T, r, lane);
     obase = (size_t)r * H;
     if (!(lo < T && out_idx[lo] == r)) {
       const half8_t z = {(half_t)0.f, (half_t)0.f, (half_t)0.f, (half_t)0.f, (half_t)0.f, (half_t)0.f, (half_t)0.f, (half_t)0.f};
@@ -173,16 +169,12 @@ __global__ __launch_bounds__(256) void ln_finalize_kernel(const half_t* __restri
   // out_idx: y is the padded tensor [out_rows, H]; this wave owns padded row r, which is packed row `lo` if
   // out_idx[lo] == r and a zero row otherwise (unpack fused into the store, as in bias_residual_ln_kernel).
   const int lane = threadIdx.x & 63;
-  int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  int row = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   size_t obase;
   if (out_idx) {
     const int r = row;
     if (r >= out_rows) return;
-    int lo = 0, hi = T;
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (out_idx[mid] < r) lo = mid + 1; else hi = mid;
-    }
+    const int lo = wave_lower_bound(out_idx, T, r, lane);
     obase = (size_t)r * H;
     if (!(lo < T && out_idx[lo] == r)) {
       const half8_t z = {(half_t)0.f, (half_t)0.f, (half_t)0.f, (half_t)0.f, (half_t)0.f, (half_t)0.f, (half_t)0.f, (half_t)0.f};

@@ -6,122 +6,261 @@
 
 namespace bt {
 
-constexpr int kOffsetsThreads = 1024;  // 16 wavefronts, one per sentence at a time
+constexpr int kOffsetsThreads = 1024;  // 16 wavefronts
+constexpr int kOffsetsWaves = kOffsetsThreads / kWave;
 
-// One workgroup.  Wave w owns sentences w, w+16, ...  (the paper assigns one
-// warp per sentence inside one threadblock; same decomposition, 64-wide).
-//   phase 1: per-sentence valid count (ballot + popcount) -> cu[b+1]
-//   phase 2: wave 0 turns the counts into an inclusive scan, cu[0] = 0
-//   phase 3: per sentence, ballot/mbcnt ranks every valid token and writes
-//            token_idx[cu[b] + rank] = b*S + t
-// A length outside [0,S] or a mask entry outside {0,1} sets cu[B] = -1.
-// host_total (optional): device-visible host memory that receives the total (or -1) as soon as it
-// is known, before the position array is written, so that the host can go on without a stream sync.
-// max_out (optional): device word that receives the largest per-sentence valid count; with host_total
-// it is also stored to host_total[1], before the total, so that a host that sees the total sees it too.
-__global__ __launch_bounds__(kOffsetsThreads) void offsets_kernel(const int32_t* __restrict__ mask,
-                                                                 const int32_t* __restrict__ lengths, int B, int S,
-                                                                 int32_t* __restrict__ cu,
-                                                                 int32_t* __restrict__ token_idx,
-                                                                 int32_t* host_total, int32_t* max_out) {
-  __shared__ int s_bad, s_max;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwave = kOffsetsThreads / kWave;
-  if (threadIdx.x == 0) { s_bad = 0; s_max = 0; }
+// Inclusive prefix sum over the wavefront on data-parallel-primitive moves: shifts by 1, 2, 4, 8 inside each row of
+// 16 lanes, then the last lane of a row broadcast to the rows behind it.
+__device__ __forceinline__ int wave_inclusive_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+  return v;
+}
+
+// Exclusive prefix sum of v over the workgroup (1024 threads); *total receives the sum.  s_part: LDS, 16 words.
+// The caller separates two uses of s_part by a barrier.
+__device__ __forceinline__ int block_exclusive_scan(int v, int* s_part, int* total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int x = wave_inclusive_scan(v);
+  if (lane == kWave - 1) s_part[wave] = x;
   __syncthreads();
+  // every row of 16 lanes scans the 16 wave sums
+  int p = s_part[lane & 15];
+  p += __builtin_amdgcn_update_dpp(0, p, 0x111, 0xf, 0xf, false);
+  p += __builtin_amdgcn_update_dpp(0, p, 0x112, 0xf, 0xf, false);
+  p += __builtin_amdgcn_update_dpp(0, p, 0x114, 0xf, 0xf, false);
+  p += __builtin_amdgcn_update_dpp(0, p, 0x118, 0xf, 0xf, false);
+  *total = __builtin_amdgcn_readlane(p, 15);
+  const int w = __builtin_amdgcn_readfirstlane(wave);
+  return (w ? __builtin_amdgcn_readlane(p, w - 1) : 0) + x - v;
+}
 
-  for (int b = wave; b < B; b += nwave) {
-    int count = 0, bad = 0;
-    if (mask) {
-      for (int t0 = 0; t0 < S; t0 += kWave) {
-        const int t = t0 + lane;
-        const int m = t < S ? mask[(size_t)b * S + t] : 0;
-        bad |= (m != 0 && m != 1);
-        count += __popcll(__ballot(m != 0));
-      }
-      bad = __any(bad);
-    } else {
-      count = lengths[b];
-      bad = count < 0 || count > S;
-      if (bad) count = 0;
+__device__ __forceinline__ void publish_total(int total, int longest, bool bad, int32_t* host_total, int32_t* max_out) {
+  if (max_out) *max_out = longest;
+  if (host_total) {
+    if (max_out) __hip_atomic_store(host_total + 1, longest, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(host_total, bad ? -1 : total, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+}
+
+// Both kernels: an invalid entry (a length outside [0,S], a mask entry outside {0,1}) sets cu[B] = -1.
+// host_total (optional): device-visible host memory that receives the total (or -1) as soon as it is known, so
+// that the host can go on without a stream sync.  max_out (optional): device word that receives the largest
+// per-sentence valid count; with host_total it is also stored to host_total[1], before the total, so that a host
+// that sees the total sees it too.
+
+// Lengths.  Every workgroup scans all lengths (a few KB, 1024 at a time), workgroup 0 writes cu and the total,
+// and each of the grid's wavefronts writes the positions of its own sentences: the T words of token_idx leave
+// through as many compute units as there are groups of 16 sentences instead of through one.
+__global__ __launch_bounds__(kOffsetsThreads) void offsets_lengths_kernel(const int32_t* __restrict__ lengths, int B,
+                                                                         int S, int32_t* __restrict__ cu,
+                                                                         int32_t* __restrict__ token_idx,
+                                                                         int32_t* host_total, int32_t* max_out) {
+  __shared__ int s_part[kOffsetsWaves], s_base[kOffsetsThreads], s_len[kOffsetsThreads], s_bad, s_max;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int gwave = (int)blockIdx.x * kOffsetsWaves + (tid >> 6), nwave = (int)gridDim.x * kOffsetsWaves;
+  if (tid == 0) { s_bad = 0; s_max = 0; }
+  int running = 0;
+  for (int b0 = 0; b0 < B || b0 == 0; b0 += kOffsetsThreads) {
+    const int b = b0 + tid;
+    int len = b < B ? lengths[b] : 0;
+    const bool bad = len < 0 || len > S;
+    if (bad) len = 0;
+    __syncthreads();  // s_bad / s_max are set, the previous round's reads of the LDS arrays are done
+    if (bad) s_bad = 1;
+    if (max_out) {
+      const int m = wave_max(len);
+      if (lane == 0) atomicMax(&s_max, m);
     }
-    if (lane == 0) {
-      cu[b + 1] = count;
-      if (bad) s_bad = 1;
-      atomicMax(&s_max, count);
+    int total;
+    const int base = running + block_exclusive_scan(len, s_part, &total);
+    s_base[tid] = base;
+    s_len[tid] = len;
+    running += total;
+    __syncthreads();
+    if (blockIdx.x == 0) {
+      if (b < B) cu[b] = base;
+      if (b0 + kOffsetsThreads >= B && tid == 0) {
+        cu[B] = s_bad ? -1 : running;
+        publish_total(running, s_max, s_bad != 0, host_total, max_out);
+      }
+    }
+    const int here = min(B - b0, kOffsetsThreads);
+    for (int i = (gwave - b0 % nwave + nwave) % nwave; i < here; i += nwave) {
+      const int at = s_base[i], n = s_len[i], first = (b0 + i) * S;
+      for (int t = lane; t < n; t += kWave) token_idx[at + t] = first + t;
     }
   }
-  __syncthreads();
+}
 
-  if (wave == 0) {
-    int running = 0;
-    for (int b0 = 0; b0 < B; b0 += kWave) {
-      const int b = b0 + lane;
-      int v = b < B ? cu[b + 1] : 0;
+// Mask.  One workgroup; the mask is read once and kept as bits in LDS.  A token's entry in token_idx is its flat
+// index b*S + t, and its position is the number of ones before it in flat order, so the mask is taken as
+// one flat string of 64-bit words whatever S is: one prefix sum over the popcounts of the words gives the base of
+// every word, and cu[b] is the prefix at flat index b*S.  A lane loads four entries at a time with kMaskLoads loads in
+// flight (256 KB over the workgroup).  kMaskWords words per round (131 072 entries).
+// Bound: one compute unit's read rate (~90 GB/s) for large masks, latency for small ones.  128 x 512: 54.7 us when
+// each wavefront walked its sentences one dependent load at a time and read the mask twice.
+constexpr int kMaskWords = 2 * kOffsetsThreads;
+constexpr int kMaskLoads = 16;
+
+__global__ __launch_bounds__(kOffsetsThreads) void offsets_mask_kernel(const int32_t* __restrict__ mask, int B, int S,
+                                                                      int32_t* __restrict__ cu,
+                                                                      int32_t* __restrict__ token_idx,
+                                                                      int32_t* host_total, int32_t* max_out) {
+  typedef int int4_t __attribute__((ext_vector_type(4)));
+  __shared__ unsigned long long s_word[kMaskWords];
+  __shared__ int s_pre[kMaskWords], s_part[kOffsetsWaves], s_bad, s_max;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = B * S;  // < 2^31
+  const bool vec = (reinterpret_cast<uintptr_t>(mask) & 15u) == 0;
+  const int sub = lane >> 4, shift = 4 * (lane & 15);  // this lane's word of a group of four, its nibble's place in it
+  if (tid == 0) { s_bad = 0; s_max = 0; }
+  __syncthreads();
+  int running = 0;
+  for (int f0 = 0; f0 < n; f0 += kMaskWords * kWave) {  // left by the break of the last round
+    const int entries = min(n - f0, kMaskWords * kWave);
+    const int groups = (entries + 4 * kWave - 1) / (4 * kWave);  // of four words
+    const int run = (groups + kOffsetsWaves - 1) / kOffsetsWaves;
+    const int g0 = wave * run, g1 = min(groups, g0 + run);
+    bool bad = false;
+    for (int g = g0; g < g1; g += kMaskLoads) {
+      int4_t m[kMaskLoads];
 #pragma unroll
-      for (int o = 1; o < kWave; o <<= 1) {
-        const int u = __shfl_up(v, o, kWave);
-        if (lane >= o) v += u;
+      for (int k = 0; k < kMaskLoads; ++k) {
+        m[k] = int4_t{0, 0, 0, 0};
+        const int at = (g + k) * 4 * kWave + lane * 4;
+        if (g + k < g1 && at < entries) {
+          if (vec && at + 4 <= entries) {
+            m[k] = *reinterpret_cast<const int4_t*>(mask + f0 + at);
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (at + e < entries) m[k][e] = mask[f0 + at + e];
+          }
+        }
       }
-      if (b < B) cu[b + 1] = running + v;
-      running += __shfl(v, kWave - 1, kWave);
+#pragma unroll
+      for (int k = 0; k < kMaskLoads; ++k) {
+        if (g + k >= g1) break;  // wave-uniform
+        bad |= ((m[k][0] | m[k][1] | m[k][2] | m[k][3]) & ~1) != 0;
+        const unsigned long long nib = (unsigned)((m[k][0] & 1) | (m[k][1] & 1) << 1 | (m[k][2] & 1) << 2 | (m[k][3] & 1) << 3);
+        const unsigned long long w = nib << shift;
+        int lo = (int)(unsigned)w, hi = (int)(unsigned)(w >> 32);
+        lo |= dpp_move<0xB1>(lo);
+        hi |= dpp_move<0xB1>(hi);
+        lo |= dpp_move<0x4E>(lo);
+        hi |= dpp_move<0x4E>(hi);
+        lo |= dpp_move<0x141>(lo);
+        hi |= dpp_move<0x141>(hi);
+        lo |= dpp_move<0x140>(lo);
+        hi |= dpp_move<0x140>(hi);
+        if ((lane & 15) == 0) s_word[(g + k) * 4 + sub] = (unsigned long long)(unsigned)hi << 32 | (unsigned)lo;
+      }
     }
-    if (lane == 0) cu[0] = 0;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    if (max_out) *max_out = s_max;
-    if (host_total) {
-      if (max_out) __hip_atomic_store(host_total + 1, s_max, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-      __hip_atomic_store(host_total, s_bad ? -1 : cu[B], __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (__any(bad) && lane == 0) s_bad = 1;
+    __syncthreads();
+    const int words = groups * 4;
+    const int c0 = 2 * tid < words ? __popcll(s_word[2 * tid]) : 0;
+    const int c1 = 2 * tid < words ? __popcll(s_word[2 * tid + 1]) : 0;
+    int total;
+    const int base = running + block_exclusive_scan(c0 + c1, s_part, &total);
+    s_pre[2 * tid] = base;
+    s_pre[2 * tid + 1] = base + c0;
+    running += total;
+    __syncthreads();
+    auto prefix = [&](int at) {  // ones before flat index f0 + at, at < entries
+      return s_pre[at >> 6] + __popcll(s_word[at >> 6] & ((1ull << (at & 63)) - 1ull));
+    };
+    for (int b = (f0 + S - 1) / S + tid; b < B && (long long)b * S < (long long)f0 + entries; b += kOffsetsThreads)
+      cu[b] = prefix(b * S - f0);  // sentences that start in this round
+    if (entries == n - f0) {  // last round: the total is known
+      if (tid == 0) cu[B] = running;
+      if (max_out) {
+        __syncthreads();
+        int m = 0;
+        for (int b = tid; b < B; b += kOffsetsThreads) m = max(m, cu[b + 1] - cu[b]);  // written by this workgroup
+        m = wave_max(m);
+        if (lane == 0) atomicMax(&s_max, m);
+        __syncthreads();
+      }
+      if (tid == 0) {
+        if (s_bad) cu[B] = -1;
+        publish_total(running, s_max, s_bad != 0, host_total, max_out);
+      }
     }
-  }
-
-  for (int b = wave; b < B; b += nwave) {
-    const int base = cu[b];
-    const int len = mask ? 0 : (cu[b + 1] - base);
-    int running = 0;
-    for (int t0 = 0; t0 < S; t0 += kWave) {
-      const int t = t0 + lane;
-      const bool valid = t < S && (mask ? mask[(size_t)b * S + t] != 0 : t < len);
-      const unsigned long long bal = __ballot(valid);
-      const int rank = __popcll(bal & ((1ull << lane) - 1ull));
-      if (valid) token_idx[base + running + rank] = b * S + t;
-      running += __popcll(bal);
-      if (!mask && t0 + kWave >= len) break;
+    for (int g = g0; g < g1; ++g) {
+      const unsigned long long word = s_word[g * 4 + sub];
+      int at = s_pre[g * 4 + sub] + __popcll(word & ((1ull << shift) - 1ull));
+      const int nib = (int)(word >> shift) & 15, flat = f0 + g * 4 * kWave + lane * 4;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (nib >> e & 1) token_idx[at++] = flat + e;
     }
+    if (entries == n - f0) break;
+    __syncthreads();  // before the next round overwrites the LDS arrays
   }
-  __syncthreads();
-  if (threadIdx.x == 0 && s_bad) cu[B] = -1;
+  if (n == 0 && tid == 0) {
+    cu[0] = 0;
+    publish_total(0, 0, false, host_total, max_out);
+  }
 }
 
-// One 16-byte chunk per thread; a row of H halves is H/8 consecutive threads.
+// A wavefront copies kPackRows packed rows, row by row with all loads of a row group in flight; one scalar read of
+// the row index per row, no per-element index arithmetic.
+constexpr int kPackRows = 4;
 __global__ __launch_bounds__(256) void pack_kernel(const uint4_t* __restrict__ padded,
-                                                   const int32_t* __restrict__ token_idx, size_t total, int chunks,
+                                                   const int32_t* __restrict__ token_idx, int T, int chunks,
                                                    uint4_t* __restrict__ packed) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= total) return;
-  const size_t tok = i / chunks;
-  const int c = (int)(i - tok * chunks);
-  packed[i] = padded[(size_t)token_idx[tok] * chunks + c];
+  const int lane = threadIdx.x & 63;
+  const int r0 = ((int)blockIdx.x * 4 + (threadIdx.x >> 6)) * kPackRows;
+  if (r0 >= T) return;
+  size_t src[kPackRows];
+#pragma unroll
+  for (int k = 0; k < kPackRows; ++k) src[k] = (size_t)token_idx[min(r0 + k, T - 1)] * chunks;
+  for (int c = lane; c < chunks; c += kWave) {
+    uint4_t v[kPackRows];
+#pragma unroll
+    for (int k = 0; k < kPackRows; ++k) v[k] = padded[src[k] + c];
+#pragma unroll
+    for (int k = 0; k < kPackRows; ++k)
+      if (r0 + k < T) packed[(size_t)(r0 + k) * chunks + c] = v[k];
+  }
 }
 
-// One wavefront per padded row.  The row is valid iff it occurs in the strictly
-// increasing token_idx; a uniform binary search finds its packed position.
+// A wavefront writes kUnpackRows consecutive padded rows.  One wave-wide search finds where they start in the
+// strictly increasing token_idx (three rounds of 64 probes for 2^18 tokens), the next kUnpackRows entries say
+// which of the rows are valid and which packed row each one is.
+constexpr int kUnpackRows = 8;
 __global__ __launch_bounds__(256) void unpack_kernel(const uint4_t* __restrict__ packed,
                                                      const int32_t* __restrict__ token_idx, int T, int rows,
                                                      int chunks, uint4_t* __restrict__ padded) {
   const int lane = threadIdx.x & 63;
-  const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (r >= rows) return;
-  int lo = 0, hi = T;  // first position with token_idx[pos] >= r
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (token_idx[mid] < r) lo = mid + 1; else hi = mid;
+  const int r0 = ((int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * kUnpackRows;
+  if (r0 >= rows) return;
+  const int lo = wave_lower_bound(token_idx, T, r0, lane);
+  const int e = lane < kUnpackRows && lo + lane < T ? token_idx[lo + lane] - r0 : kUnpackRows;
+  int src[kUnpackRows];  // packed row of each padded row, -1: padding; wave-uniform
+#pragma unroll
+  for (int k = 0; k < kUnpackRows; ++k) {
+    const unsigned long long hit = __ballot(e == k);
+    src[k] = hit ? lo + __ffsll((long long)hit) - 1 : -1;
   }
-  const bool valid = lo < T && token_idx[lo] == r;
   const uint4_t zero = {0u, 0u, 0u, 0u};
-  for (int c = lane; c < chunks; c += kWave)
-    padded[(size_t)r * chunks + c] = valid ? packed[(size_t)lo * chunks + c] : zero;
+  for (int c = lane; c < chunks; c += kWave) {
+    uint4_t v[kUnpackRows];
+#pragma unroll
+    for (int k = 0; k < kUnpackRows; ++k) {
+      v[k] = zero;
+      if (src[k] >= 0) v[k] = packed[(size_t)src[k] * chunks + c];
+    }
+#pragma unroll
+    for (int k = 0; k < kUnpackRows; ++k)
+      if (r0 + k < rows) padded[(size_t)(r0 + k) * chunks + c] = v[k];
+  }
 }
 
 }  // namespace bt
@@ -158,8 +297,14 @@ static bt_status build_offsets_impl(const int32_t* d_mask, const int32_t* d_leng
   volatile int32_t* slot = h_out;
   if (h_dev) *slot = kPending;
   // B == 0 runs the same kernel: it writes cu[0] = 0 and a total of 0 (no memset, no special case)
-  offsets_kernel<<<1, kOffsetsThreads, 0, st>>>(d_mask, d_lengths, B, S, d_cu_seqlens, d_token_idx, h_dev,
-                                                stats ? d_cu_seqlens + B + 1 : nullptr);
+  int32_t* const d_max = stats ? d_cu_seqlens + B + 1 : nullptr;
+  if (d_mask) {
+    offsets_mask_kernel<<<1, kOffsetsThreads, 0, st>>>(d_mask, B, S, d_cu_seqlens, d_token_idx, h_dev, d_max);
+  } else {  // one wavefront per sentence, up to one workgroup per compute unit
+    const int wgs = (B + kOffsetsWaves - 1) / kOffsetsWaves;
+    offsets_lengths_kernel<<<wgs < 1 ? 1 : (wgs > 256 ? 256 : wgs), kOffsetsThreads, 0, st>>>(
+        d_lengths, B, S, d_cu_seqlens, d_token_idx, h_dev, d_max);
+  }
   if (hipGetLastError() != hipSuccess) return BT_ERR_HIP;
   int32_t res[2] = {kPending, 0};
   if (h_dev) {
@@ -202,12 +347,9 @@ extern "C" bt_status bt_pack(const bt_half* d_padded, const int32_t* d_token_idx
   if (T == 0) return BT_OK;
   if (!d_padded || !d_token_idx || !d_packed || !aligned16(d_padded) || !aligned16(d_packed))
     return BT_ERR_INVALID_ARG;
-  const int chunks = H / 8;
-  const size_t total = (size_t)T * chunks;
-  const size_t blocks = (total + 255) / 256;
-  if (blocks > 0x7fffffffull) return BT_ERR_UNSUPPORTED;
-  pack_kernel<<<(unsigned)blocks, 256, 0, static_cast<hipStream_t>(stream)>>>(
-      reinterpret_cast<const uint4_t*>(d_padded), d_token_idx, total, chunks, reinterpret_cast<uint4_t*>(d_packed));
+  constexpr int per = 4 * kPackRows;
+  pack_kernel<<<(unsigned)(((size_t)T + per - 1) / per), 256, 0, static_cast<hipStream_t>(stream)>>>(
+      reinterpret_cast<const uint4_t*>(d_padded), d_token_idx, T, H / 8, reinterpret_cast<uint4_t*>(d_packed));
   return launch_status();
 }
 
@@ -220,7 +362,8 @@ extern "C" bt_status bt_unpack(const bt_half* d_packed, const int32_t* d_token_i
   if (!d_padded || !aligned16(d_padded)) return BT_ERR_INVALID_ARG;
   if (T > 0 && (!d_packed || !d_token_idx || !aligned16(d_packed))) return BT_ERR_INVALID_ARG;
   const int rows = B * S;
-  unpack_kernel<<<(rows + 3) / 4, 256, 0, static_cast<hipStream_t>(stream)>>>(
+  constexpr int per = 4 * kUnpackRows;
+  unpack_kernel<<<(unsigned)(((size_t)rows + per - 1) / per), 256, 0, static_cast<hipStream_t>(stream)>>>(
       reinterpret_cast<const uint4_t*>(d_packed), d_token_idx, T, rows, H / 8, reinterpret_cast<uint4_t*>(d_padded));
   return launch_status();
 }

@@ -43,7 +43,7 @@ def template_args(name: str):
     return []
 
 
-STREAMING_GRID = 20_000_000     # threads: bench.py's 262 144-token pack launches 25 M of them, the workloads < 2 M
+STREAMING_GRID = 2_000_000      # threads: bench.py's 262 144-token pack launches 4 M of them, the workloads < 0.3 M
 
 
 def role_of(name: str, grid: int = 0):
@@ -73,7 +73,7 @@ def role_of(name: str, grid: int = 0):
         stream = len(a) >= 3 and a[2] == 1
         return ("bias_residual_ln_streaming" if stream else "bias_residual_ln"), f"bias_residual_ln<{','.join(map(str, a[:3]))}>"
     for key, role in (("ln_finalize_kernel", "ln_finalize"), ("unpack_kernel", "unpack"), ("pack_kernel", "pack"),
-                      ("offsets_kernel", "offsets"), ("fold_vectors_kernel", "fold_vectors"),
+                      ("offsets_lengths_kernel", "offsets"), ("offsets_mask_kernel", "offsets"), ("fold_vectors_kernel", "fold_vectors"),
                       ("peak_mfma_kernel", "peak_mfma"), ("peak_read_kernel", "peak_read"),
                       ("copyBuffer", "device_copy")):
         if key in name:

@@ -47,6 +47,28 @@ def test_offsets_any_mask(bt, B, S, p):
     assert np.array_equal(host(cu), rcu) and np.array_equal(host(tok), rtok)
 
 
+@pytest.mark.parametrize("B,S", [(1, 3), (64, 2048), (257, 511), (1500, 90), (33, 4095), (1025, 7)])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_offsets_rounds_and_alignment(bt, B, S, offset):
+    """Masks of exactly one round of the kernel, of more than one (sentences that straddle the rounds), more sentences
+    than a workgroup has threads, a mask that is not 16-byte aligned; and the same batch given as lengths."""
+    import torch
+    rng = np.random.default_rng(B + S)
+    L = rng.integers(0, S + 1, B).astype(np.int32)
+    mask = O.lengths_to_mask(L, S).astype(np.int32)
+    flat = torch.empty(B * S + offset, dtype=torch.int32, device="cuda:0")
+    given = flat[offset:].view(B, S)
+    given.copy_(dev(mask))
+    rcu, rtok, rT = O.build_offsets(mask)
+    for kw in ({"mask": given}, {"lengths": dev(L), "S": S}):
+        cu, tok, T, longest = bt.build_offsets(with_max=True, **kw)
+        assert T == rT and longest == int(L.max())
+        assert np.array_equal(host(cu), rcu) and np.array_equal(host(tok), rtok)
+    given[B - 1, S - 1] = 2
+    with pytest.raises(bt.BtError):
+        bt.build_offsets(mask=given)
+
+
 @pytest.mark.parametrize("name", list(I.WORKLOADS))
 def test_offsets_from_lengths_workloads(bt, name):
     wl = I.WORKLOADS[name]
@@ -133,7 +155,7 @@ def test_offsets_lengths_edge_cases(bt):
         bt.build_offsets(mask=dev(np.array([[1, 2, 0]], np.int32)))         # mask entry not 0/1
 
 
-@pytest.mark.parametrize("B,S,H", [(3, 5, 8), (4, 64, 768), (16, 256, 768), (7, 100, 1024), (2, 33, 72)])
+@pytest.mark.parametrize("B,S,H", [(3, 5, 8), (4, 64, 768), (16, 256, 768), (7, 100, 1024), (2, 33, 72), (1, 1, 8), (90, 100, 520)])
 def test_pack_unpack_bit_exact(bt, B, S, H):
     import torch
     rng = np.random.default_rng(B + S + H)
