@@ -99,30 +99,48 @@ def load_library(path: str | None = None):
 
 
 # ------------------------------------------------------------------ helpers
+# A pass over a small batch is a few microseconds of GPU time, so the host side of a call counts: pointers and the
+# stream are passed as plain integers (the argument types convert them), torch is looked up once, and the raw handle
+# of the current stream is asked for directly (0.1 us; building a torch.cuda.Stream object for it takes 2.7 us).
+_torch_module = None
+_raw_stream = None
+_current_device = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def _stream():
-    return _c.c_void_p(_torch().cuda.current_stream().cuda_stream)
+    """Raw handle (hipStream_t as an integer) of the current stream of the current device."""
+    global _raw_stream, _current_device
+    if _raw_stream is None:
+        torch = _torch()
+        stream = torch.cuda.current_stream().cuda_stream  # also initialises the device
+        _current_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or \
+            (lambda device: torch.cuda.current_stream(device).cuda_stream)
+        return stream
+    return _raw_stream(_current_device())
 
 
 def _ptr(t):
-    return _c.c_void_p(t.data_ptr()) if t is not None else _c.c_void_p(0)
+    return None if t is None else t.data_ptr()
 
 
 def _chk(t, dtype, name, ndim=None):
-    torch = _torch()
-    if not isinstance(t, torch.Tensor) or not t.is_cuda or t.dtype != dtype or not t.is_contiguous():
+    if not isinstance(t, _torch_module.Tensor) or not t.is_cuda or t.dtype != dtype or not t.is_contiguous():
         raise TypeError(f"{name}: expected a contiguous CUDA tensor of dtype {dtype}")
     if ndim is not None and t.dim() != ndim:
         raise TypeError(f"{name}: expected {ndim} dimensions, got {t.dim()}")
 
 
 def _call(name, *args):
-    lib = load_library()
-    st = getattr(lib, name)(*args)
+    st = getattr(_lib or load_library(), name)(*args)
     if st != BT_OK:
         raise BtError(st, name)
 
@@ -143,6 +161,12 @@ def _pinned_total():
     return t
 
 
+def _offsets_buffer(B, S, device):
+    """One int32 allocation for cu_seqlens [B+2] and token_idx [B*S]; returns (buffer, where token_idx starts)."""
+    at = (B + 2 + 3) & ~3  # 16-byte aligned
+    return _torch().empty(at + max(1, B * S), dtype=_torch().int32, device=device), at
+
+
 def build_offsets(mask=None, lengths=None, S=None, pinned=True, with_max=False):
     """bt_build_offsets.  Returns (cu_seqlens int32[B+1], token_idx int32[T], T).
     pinned=True hands the library a pinned host word for T (no stream synchronisation);
@@ -160,22 +184,23 @@ def build_offsets(mask=None, lengths=None, S=None, pinned=True, with_max=False):
         if S is None:
             raise ValueError("S is required with lengths")
         B, dev = lengths.shape[0], lengths.device
-    cu = torch.empty(B + 2, dtype=torch.int32, device=dev)
-    tok = torch.empty(max(1, B * S), dtype=torch.int32, device=dev)
-    cu_view = cu[: B + 1]  # made before the call: it does not depend on the count the host waits for
+    buf, at = _offsets_buffer(B, int(S), dev)
+    cu_view = buf[: B + 1]  # made before the call: it does not depend on the count the host waits for
+    cu = buf.data_ptr()
+    tok = cu + 4 * at
     name = "bt_build_offsets_stats" if with_max else "bt_build_offsets"
     if pinned:
         _, slot_ptr, slot_np = _pinned_total()
-        _call(name, _ptr(mask), _ptr(lengths), B, int(S), _ptr(cu), _ptr(tok), slot_ptr, _stream())
+        _call(name, _ptr(mask), _ptr(lengths), B, int(S), cu, tok, slot_ptr, _stream())
         T, mx = int(slot_np[0]), int(slot_np[1])
     else:
         res = (_c.c_int32 * 2)(-1, -1)
-        _call(name, _ptr(mask), _ptr(lengths), B, int(S), _ptr(cu), _ptr(tok),
+        _call(name, _ptr(mask), _ptr(lengths), B, int(S), cu, tok,
               _c.cast(res, _c.POINTER(_c.c_int32)), _stream())
         T, mx = int(res[0]), int(res[1])
     if with_max:
-        return cu_view, tok[:T], T, mx
-    return cu_view, tok[:T], T
+        return cu_view, buf[at: at + T], T, mx
+    return cu_view, buf[at: at + T], T
 
 
 def pack(padded, token_idx, out=None):
@@ -185,7 +210,7 @@ def pack(padded, token_idx, out=None):
     _chk(token_idx, torch.int32, "token_idx", 1)
     H, T = padded.shape[-1], token_idx.shape[0]
     if out is None:
-        out = torch.empty((T, H), dtype=torch.float16, device=padded.device)
+        out = padded.new_empty((T, H))
     _call("bt_pack", _ptr(padded), _ptr(token_idx), T, H, _ptr(out), _stream())
     return out
 
@@ -197,7 +222,7 @@ def unpack(packed, token_idx, B, S, out=None):
     _chk(token_idx, torch.int32, "token_idx", 1)
     T, H = packed.shape
     if out is None:
-        out = torch.empty((B, S, H), dtype=torch.float16, device=packed.device)
+        out = packed.new_empty((B, S, H))
     _call("bt_unpack", _ptr(packed), _ptr(token_idx), T, B, S, H, _ptr(out), _stream())
     return out
 
@@ -217,11 +242,11 @@ def varlen_mha(qkv, cu_seqlens, max_len, heads, head_dim=64, scale=None, bq=None
     if scale is None:
         scale = head_dim ** -0.5
     if out is None:
-        out = torch.empty((T, HD), dtype=torch.float16, device=qkv.device)
+        out = qkv.new_empty((T, HD))
     base, es = qkv.data_ptr(), qkv.element_size()
-    _call("bt_varlen_mha", _c.c_void_p(base), _c.c_void_p(base + HD * es), _c.c_void_p(base + 2 * HD * es),
+    _call("bt_varlen_mha", base, base + HD * es, base + 2 * HD * es,
           3 * HD, _ptr(bq), _ptr(bk), _ptr(bv), _ptr(cu_seqlens), B, T, int(max_len), heads, head_dim,
-          float(scale), _ptr(out), _c.c_void_p(0), 0, _stream())
+          float(scale), _ptr(out), None, 0, _stream())
     return out
 
 
@@ -236,9 +261,9 @@ def varlen_mha_separate(q, k, v, cu_seqlens, max_len, heads, head_dim=64, scale=
     if scale is None:
         scale = head_dim ** -0.5
     if out is None:
-        out = torch.empty((T, HD), dtype=torch.float16, device=q.device)
+        out = q.new_empty((T, HD))
     _call("bt_varlen_mha", _ptr(q), _ptr(k), _ptr(v), HD, None, None, None, _ptr(cu_seqlens), B, T, int(max_len),
-          heads, head_dim, float(scale), _ptr(out), _c.c_void_p(0), 0, _stream())
+          heads, head_dim, float(scale), _ptr(out), None, 0, _stream())
     return out
 
 
@@ -254,7 +279,7 @@ def gemm_bias_act(a, w, bias=None, act=ACT_NONE, out=None):
     if w.shape[1] != K:
         raise ValueError("w must be [N,K]")
     if out is None:
-        out = torch.empty((M, N), dtype=torch.float16, device=a.device)
+        out = a.new_empty((M, N))
     _call("bt_gemm_bias_act", _ptr(a), _ptr(w), _ptr(bias), M, N, K, int(act), _ptr(out), _stream())
     return out
 
@@ -298,7 +323,7 @@ def gemm_kslices(a, w, out=None, slices=None):
     if slices is None and nbytes:
         slices = torch.empty(nbytes // 4, dtype=torch.float32, device=a.device)
     if out is None and not nbytes:
-        out = torch.empty((M, N), dtype=torch.float16, device=a.device)
+        out = a.new_empty((M, N))
     n = _c.c_int(-1)
     _call("bt_gemm_kslices", _ptr(a), _ptr(w), M, N, K, _ptr(out), _ptr(slices),
           slices.numel() * 4 if slices is not None else 0, _c.byref(n), _stream())
@@ -472,12 +497,12 @@ def encoder_fwd_masked(layers, x_padded, mask=None, lengths=None, out=None, ws=N
         out = torch.empty_like(x_padded)
     if ws is None:
         ws, _ = _workspace(layers[0], max(B * S, 1), B, S, dev)
-    cu = torch.empty(B + 2, dtype=torch.int32, device=dev)
-    tok = torch.empty(max(1, B * S), dtype=torch.int32, device=dev)
-    cu_view = cu[: B + 1]
+    buf, at = _offsets_buffer(B, S, dev)
+    cu_view = buf[: B + 1]
+    cu = buf.data_ptr()
     _, slot_ptr, slot_np = _pinned_total()
     _call("bt_encoder_fwd_masked", _layer_array(layers), len(layers), _ptr(fold), _ptr(x_padded), _ptr(mask),
-          _ptr(lengths), B, S, _ptr(cu), _ptr(tok), slot_ptr, _ptr(out), _ptr(ws), ws.numel(), _stream())
+          _ptr(lengths), B, S, cu, cu + 4 * at, slot_ptr, _ptr(out), _ptr(ws), ws.numel(), _stream())
     T = int(slot_np[0])
-    return out, cu_view, tok[:T], T
+    return out, cu_view, buf[at: at + T], T
 
