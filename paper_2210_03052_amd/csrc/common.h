@@ -41,12 +41,13 @@ __device__ __forceinline__ int xcd_remap(int id, int n) {
 enum { EPI_PLAIN = 0, EPI_FOLD = 1, EPI_RESID = 2, EPI_PARTIAL = 3 };
 struct GemmEpi {
   const int32_t* a_rows = nullptr;  // any form: row m of the product reads row a_rows[m] of A (pack fused into the load)
+  int a_rows_of = 0;                // with a_rows: number of rows of A
   const half_t* bias = nullptr;     // PLAIN / RESID: [N] or null
   // FOLD: the A operand is u = gamma (.) z of a LayerNorm whose row sums are ln_part
   const float2* ln_part = nullptr;  // [M][ln_np]
   int ln_np = 0;
   const float* fold_c = nullptr;    // [N]  W gamma
-  const float* fold_d = nullptr;    // [N]  W beta + bias
+  const float* fold_d = nullptr;    // [N]  W beta + bias; fold_d == fold_c + N
   float inv_h = 0.f, eps = 0.f;     // 1/width and epsilon of that LayerNorm (also used by RESID)
   // RESID: v = acc + bias + residual; C = out_gamma (.) v; part_out[m][p] = (sum v, sum v^2) over column tile p
   const half_t* resid = nullptr;        // [M][N]: plain residual, or u_r if resid_part is set

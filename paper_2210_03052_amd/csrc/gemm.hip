@@ -2,8 +2,11 @@
 // A [M,K] and W [N,K] are both K-contiguous, which is exactly the operand order
 // the gfx950 MFMA wants: every lane feeds 8 consecutive K values of one row.
 //
-// Main kernel (K % 64 == 0): WGM x WGN wavefronts, block tile BM x BN x 64, wave tile
-// (BM/WGM) x (BN/WGN) of 32x32x16 fp16 MFMA blocks with fp32 accumulators.
+// Narrow tiles (K % 64 == 0; 128 x 64 and smaller, and the forms that only they have): WGM x WGN wavefronts, block tile BM x BN x 64, wave tile
+// (BM/WGM) x (BN/WGN) of 16x16x32 fp16 MFMA blocks with fp32 accumulators.  That block shape, not 32x32x16: with
+// every matrix core busy on ordinary data the chip runs at its power limit, and the shape decides how much
+// arithmetic the limit buys -- a register-only loop on normally distributed operands sustains 1 930 TFLOP/s with
+// 16x16x32 (clock 1.92 GHz) against 1 745 with 32x32x16 (1.67 GHz).
 // Operand slabs travel global memory -> LDS directly (global_load_lds_dwordx4: no
 // register staging), NS stages deep, so that NS-1 slabs are in flight while one is
 // multiplied; each wave waits only for its own oldest slab (s_waitcnt vmcnt) and one
@@ -14,6 +17,8 @@
 // with 4 consecutive output columns of one row; bias/activation run in fp32 and the
 // fp16 tile leaves through LDS with 16-byte stores.
 //
+// Wide tiles (96 ... 256 x 128): gemm_wide.h.
+//
 // Fallback kernel (any K % 8 == 0): register-staged, zero-fills the K tail.
 #include <type_traits>
 
@@ -22,6 +27,7 @@
 namespace bt {
 
 constexpr int kGemmThreads = 256;  // fallback kernel
+constexpr int kComputeUnits = 256;
 
 #define BT_AS1 __attribute__((address_space(1)))
 #define BT_AS3 __attribute__((address_space(3)))
@@ -82,7 +88,7 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
-// Shared epilogue.  acc[i][j][4g+t] = C[m][n] with m = m_base + i*32 + l32, n = n_base + j*32 + 8g + 4hf + t.
+// Shared epilogue.  acc[i][j][t] = C[m][n] with m = m_base + i*16 + lane % 16, n = n_base + j*16 + 4 (lane / 16) + t.
 // Three forms, all on the fp32 accumulators, one rounding to fp16:
 //   EPI_PLAIN  C = act(acc + bias)                                         (Sec. III-C2)
 //   EPI_FOLD   C = act(rstd_m (acc - mu_m c_n) + d_n): the A operand was u = gamma (.) z, the scaled
@@ -99,13 +105,13 @@ __device__ __forceinline__ void static_for(F&& f) {
 // The fp16 tile of this wave is then transposed through a private LDS region (rows padded to WN+8
 // halves) so that global memory is written with 16-byte-per-lane stores, 8 lanes covering 128
 // contiguous bytes of an output row.
-// Per-column epilogue operands of one lane (its 4*NI groups of 4 columns).  They do not depend on the
+// Per-column epilogue operands of one lane (its NI groups of 4 columns).  They do not depend on the
 // product, so the kernels request them before the K loop: the L2 is cold at kernel start and a fetch
 // issued in the epilogue would sit fully exposed at the end of every tile.  Unused members are dead code.
 template <int NI>
 struct EpiVecs {
-  half4_t bias[NI][4];             // PLAIN / RESID (accumulator layout: this lane's 4*NI groups of 4 columns)
-  float4_t fc[NI][4], fd[NI][4];   // FOLD: W gamma, W beta + bias
+  half4_t bias[NI];         // PLAIN / RESID (accumulator layout: this lane's NI groups of 4 columns)
+  float4_t fc[NI], fd[NI];  // FOLD: W gamma, W beta + bias
   // RESID, in the layout of the row-contiguous store pass (this lane's 8 consecutive columns):
   half8_t og8, rg8, rb8;           // output gamma; gamma / beta of a folded residual
 };
@@ -113,22 +119,20 @@ struct EpiVecs {
 template <int NI, int EPI>
 __device__ __forceinline__ void load_epi_vecs(const GemmEpi& ep, const half_t* bias /* = ep.bias */, int N,
                                               int n_base, int lane, EpiVecs<NI>& v) {
-  const int hf = lane >> 5;
+  const int quad = lane >> 4;
   const half4_t zero = {(half_t)0.f, (half_t)0.f, (half_t)0.f, (half_t)0.f};
 #pragma unroll
-  for (int j = 0; j < NI; ++j)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int nc = min(n_base + j * 32 + 8 * g + 4 * hf, N - 4);  // columns past N: clamped, never stored
-      if constexpr (EPI == EPI_FOLD) {
-        v.fc[j][g] = *reinterpret_cast<const float4_t*>(ep.fold_c + nc);
-        v.fd[j][g] = *reinterpret_cast<const float4_t*>(ep.fold_d + nc);
-      } else {
-        v.bias[j][g] = bias ? *reinterpret_cast<const half4_t*>(bias + nc) : zero;
-      }
+  for (int j = 0; j < NI; ++j) {
+    const int nc = min(n_base + j * 16 + 4 * quad, N - 4);  // columns past N: clamped, never stored
+    if constexpr (EPI == EPI_FOLD) {
+      v.fc[j] = *reinterpret_cast<const float4_t*>(ep.fold_c + nc);
+      v.fd[j] = *reinterpret_cast<const float4_t*>(ep.fold_d + nc);
+    } else {
+      v.bias[j] = bias ? *reinterpret_cast<const half4_t*>(bias + nc) : zero;
     }
+  }
   if constexpr (EPI == EPI_RESID) {
-    constexpr int LPR = NI * 4;  // lanes per row of the store pass
+    constexpr int LPR = NI * 2;  // lanes per row of the store pass
     const int nc = min(n_base + (lane % LPR) * 8, N - 8);
     v.og8 = *reinterpret_cast<const half8_t*>(ep.out_gamma + nc);
     if (ep.resid_part) {
@@ -142,25 +146,26 @@ __device__ __forceinline__ void load_epi_vecs(const GemmEpi& ep, const half_t* b
 // that layout: pass p, lane (rr, cc) holds the 8 residual values of row p*RPP + rr, columns cc .. cc+7.
 template <int MI, int NI>
 struct ResidTile {
-  static constexpr int LPR = NI * 4, RPP = 64 / LPR, P = MI * 32 / RPP;
+  static constexpr int LPR = NI * 2, RPP = 64 / LPR, P = MI * 16 / RPP;
   uint4_t r[P];
 };
 
 template <int MI, int NI, int WGN, int ACT, int EPI>
-__device__ __forceinline__ void store_tile(const float16_t (&acc)[MI][NI], const GemmEpi& ep, const EpiVecs<NI>& vec,
+__device__ __forceinline__ void store_tile(const float4_t (&acc)[MI][NI], const GemmEpi& ep, const EpiVecs<NI>& vec,
                                            const float (&mu)[MI], const float (&rstd)[MI],
                                            const ResidTile<MI, NI>& rres, int tile_n,
                                            int wn, int row_in_tile, float2* red /* LDS [WGN][rows of the tile] */,
                                            int tile_rows, half_t* __restrict__ C, int M, int N, int m_base,
                                            int n_base, int lane,
-                                           half_t* stage /* this wave's LDS region: MI*32 x (NI*32+8) halves */) {
-  constexpr int WN = NI * 32, LD = WN + 8;
-  const int l32 = lane & 31, hf = lane >> 5;
+                                           half_t* stage /* this wave's LDS region: MI*16 x (NI*16+8) halves */) {
+  constexpr int WN = NI * 16, LD = WN + 8;
+  const int l16 = lane & 15, quad = lane >> 4;
   const bool folded_resid = EPI == EPI_RESID && ep.resid_part != nullptr;
   // rows of this wave's tile in the store pass: WN/8 lanes per row
-  constexpr int LPR = WN / 8, RPP = 64 / LPR;  // lanes per row, rows per pass
+  constexpr int LPR = WN / 8, RPP = 64 / LPR;  // lanes per row, rows per pass (at most the 16 of a block)
+  static_assert(RPP <= 16, "a store pass stays inside a 16-row block");
   const int rr = lane / LPR, cc = (lane % LPR) * 8;
-  // One 32-row block at a time: arithmetic on the accumulators, fp16 block to LDS, then the row-contiguous
+  // One 16-row block at a time: arithmetic on the accumulators, fp16 block to LDS, then the row-contiguous
   // pass straight to memory -- the stores of block i drain while the arithmetic of block i+1 runs.
   // EPI_RESID: the accumulator pass only adds the bias; the residual, the row sums and the output scale live
   // in the row pass, where the residual arrives as whole 16-byte pieces of a row (requested like that, 8 lanes
@@ -170,42 +175,38 @@ __device__ __forceinline__ void store_tile(const float16_t (&acc)[MI][NI], const
   for (int i = 0; i < MI; ++i) {
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
+      float v[4];
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int nl = j * 32 + 8 * g + 4 * hf;
-        float v[4];
+      for (int t = 0; t < 4; ++t) v[t] = acc[i][j][t];
+      if constexpr (EPI == EPI_FOLD) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) v[t] = acc[i][j][4 * g + t];
-        if constexpr (EPI == EPI_FOLD) {
+        for (int t = 0; t < 4; ++t) v[t] = __builtin_fmaf(rstd[i], v[t] - mu[i] * vec.fc[j][t], vec.fd[j][t]);
+      } else {
 #pragma unroll
-          for (int t = 0; t < 4; ++t) v[t] = __builtin_fmaf(rstd[i], v[t] - mu[i] * vec.fc[j][g][t], vec.fd[j][g][t]);
-        } else {
-#pragma unroll
-          for (int t = 0; t < 4; ++t) v[t] += (float)vec.bias[j][g][t];
-        }
-        if constexpr (EPI != EPI_RESID) {
-#pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            if (ACT == BT_ACT_GELU_ERF) v[t] = gelu_erf(v[t]);
-            else if (ACT == BT_ACT_GELU_TANH) v[t] = gelu_tanh(v[t]);
-          }
-        }
-        half4_t o;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) o[t] = (half_t)v[t];
-        *reinterpret_cast<half4_t*>(stage + (i * 32 + l32) * LD + nl) = o;
+        for (int t = 0; t < 4; ++t) v[t] += (float)vec.bias[j][t];
       }
+      if constexpr (EPI != EPI_RESID) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          if (ACT == BT_ACT_GELU_ERF) v[t] = gelu_erf(v[t]);
+          else if (ACT == BT_ACT_GELU_TANH) v[t] = gelu_tanh(v[t]);
+        }
+      }
+      half4_t o;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) o[t] = (half_t)v[t];
+      *reinterpret_cast<half4_t*>(stage + (i * 16 + l16) * LD + j * 16 + 4 * quad) = o;
     }
 #pragma unroll
-    for (int r0 = i * 32; r0 < (i + 1) * 32; r0 += RPP) {
+    for (int r0 = i * 16; r0 < (i + 1) * 16; r0 += RPP) {
       const int mr = m_base + r0 + rr, n = n_base + cc;
       uint4_t out4 = *reinterpret_cast<const uint4_t*>(stage + (r0 + rr) * LD + cc);
       const bool ok = mr < M && n < N;
       if constexpr (EPI == EPI_RESID) {
         const half8_t h8 = __builtin_bit_cast(half8_t, out4);
         const half8_t r8 = __builtin_bit_cast(half8_t, rres.r[r0 / RPP]);
-        // mean and 1/sigma of the residual's row: lane (r0+rr) % 32 holds them in accumulator layout
-        const float mu_r = __shfl(mu[i], (r0 + rr) & 31, kWave), rstd_r = __shfl(rstd[i], (r0 + rr) & 31, kWave);
+        // mean and 1/sigma of the residual's row: lane (r0+rr) % 16 holds them in accumulator layout
+        const float mu_r = __shfl(mu[i], (r0 + rr) & 15, kWave), rstd_r = __shfl(rstd[i], (r0 + rr) & 15, kWave);
         float s0 = 0.f, s1 = 0.f;
         half8_t u8;
 #pragma unroll
@@ -245,10 +246,10 @@ __device__ __forceinline__ void store_tile(const float16_t (&acc)[MI][NI], const
     // Row sums of this wave's columns are in LDS; after the barrier the wavefronts of tile column 0 add the
     // WGN contributions in order and store ONE partial per row and column tile.
     __syncthreads();
-    if (wn == 0 && hf == 0) {
+    if (wn == 0 && quad == 0) {
 #pragma unroll
       for (int i = 0; i < MI; ++i) {
-        const int r = row_in_tile + i * 32 + l32, m = m_base + i * 32 + l32;
+        const int r = row_in_tile + i * 16 + l16, m = m_base + i * 16 + l16;
         float2 t = red[r];
 #pragma unroll
         for (int w = 1; w < WGN; ++w) {
@@ -262,86 +263,81 @@ __device__ __forceinline__ void store_tile(const float16_t (&acc)[MI][NI], const
   }
 }
 
-// Split-K epilogue: the fp32 accumulators of this wave's tile, one 32-row block at a time through a private
+// Split-K epilogue: the fp32 accumulators of this wave's tile, one 16-row block at a time through a private
 // LDS region (rows padded by 4 floats) so that they leave as whole row segments, 16 bytes per lane, WN/4
-// lanes per row, instead of 16-byte pieces scattered over 32 rows.
+// lanes per row, instead of 16-byte pieces scattered over 16 rows.
 template <int MI, int NI>
-__device__ __forceinline__ void store_partial(const float16_t (&acc)[MI][NI], float* __restrict__ P, int M, int N,
+__device__ __forceinline__ void store_partial(const float4_t (&acc)[MI][NI], float* __restrict__ P, int M, int N,
                                               int m_base, int n_base, int lane,
-                                              float* stage /* this wave's LDS region: 32 x (NI*32+4) floats */) {
-  constexpr int WN = NI * 32, LD = WN + 4;
+                                              float* stage /* this wave's LDS region: 16 x (NI*16+4) floats */) {
+  constexpr int WN = NI * 16, LD = WN + 4;
   constexpr int LPR = WN / 4, RPP = 64 / LPR;  // lanes per row, rows per pass
-  const int l32 = lane & 31, hf = lane >> 5;
+  const int l16 = lane & 15, quad = lane >> 4;
   const int rr = lane / LPR, cc = (lane % LPR) * 4;
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
 #pragma unroll
-    for (int j = 0; j < NI; ++j)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        float4_t v;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) v[t] = acc[i][j][4 * g + t];
-        *reinterpret_cast<float4_t*>(stage + l32 * LD + j * 32 + 8 * g + 4 * hf) = v;
-      }
+    for (int j = 0; j < NI; ++j) *reinterpret_cast<float4_t*>(stage + l16 * LD + j * 16 + 4 * quad) = acc[i][j];
     // same wavefront reads what it wrote: LDS operations of a wave complete in order
 #pragma unroll
-    for (int r0 = 0; r0 < 32; r0 += RPP) {
-      const int mr = m_base + i * 32 + r0 + rr, n = n_base + cc;
+    for (int r0 = 0; r0 < 16; r0 += RPP) {
+      const int mr = m_base + i * 16 + r0 + rr, n = n_base + cc;
       const float4_t v = *reinterpret_cast<const float4_t*>(stage + (r0 + rr) * LD + cc);
       if (mr < M && n < N) store_through(P + ((size_t)mr * N + n), v);  // N % 8 == 0: 4 columns all in or all out
     }
   }
 }
 
-// Mean and 1/sigma of the rows m_base + i*32 + l32 from their partial sums, in two steps so that the
+// Mean and 1/sigma of the rows m_base + i*16 + l16 from their partial sums, in two steps so that the
 // loads can be issued ahead of the operand slabs and collected after them:
-//   request_row_sums: the two 32-lane halves each request one half of a row's partials (up to
-//     kMaxHalfParts each, clamped indices, no branches).  Issued through inline assembly so that the
+//   request_row_sums: the four 16-lane quarters each request a quarter of a row's partials (up to
+//     kMaxQuadParts each, clamped indices, no branches).  Issued through inline assembly so that the
 //     compiler does not put a wait for ALL outstanding memory operations in front of their first use;
 //   finish_row_sums: after the caller has waited (s_waitcnt vmcnt), add them in index order,
-//     exchange the halves, derive mu and rstd.
-constexpr int kMaxHalfParts = 4;  // np <= 8: H <= 1024 at 128-wide column tiles; more falls back to a loop
+//     exchange the quarters, derive mu and rstd.
+constexpr int kMaxQuadParts = 2;  // np <= 8: H <= 1024 at 128-wide column tiles; more falls back to a loop
 
 template <int MI>
-__device__ __forceinline__ void request_row_sums(const float2* __restrict__ part, int np, int M, int m_base, int l32,
-                                                 int hf, float2 (&v)[MI][kMaxHalfParts]) {
-  const int half_np = (np + 1) >> 1, p0 = hf * half_np, p1 = min(np, p0 + half_np);
+__device__ __forceinline__ void request_row_sums(const float2* __restrict__ part, int np, int M, int m_base, int l16,
+                                                 int quad, float2 (&v)[MI][kMaxQuadParts]) {
+  const int per = (np + 3) >> 2, p0 = quad * per, p1 = min(np, p0 + per);
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
-    const float2* row = part + (size_t)min(m_base + i * 32 + l32, M - 1) * np;
+    const float2* row = part + (size_t)min(m_base + i * 16 + l16, M - 1) * np;
 #pragma unroll
-    for (int q = 0; q < kMaxHalfParts; ++q) {
-      const float2* src = row + min(p0 + q, max(p1 - 1, 0));
+    for (int q = 0; q < kMaxQuadParts; ++q) {
+      const float2* src = row + max(min(p0 + q, p1 - 1), 0);
       asm volatile("global_load_dwordx2 %0, %1, off" : "=v"(v[i][q]) : "v"(src) : "memory");
     }
   }
 }
 
 template <int MI>
-__device__ __forceinline__ void finish_row_sums(const float2* __restrict__ part, int np, int M, int m_base, int l32,
-                                                int hf, float inv_h, float eps, float2 (&v)[MI][kMaxHalfParts],
+__device__ __forceinline__ void finish_row_sums(const float2* __restrict__ part, int np, int M, int m_base, int l16,
+                                                int quad, float inv_h, float eps, float2 (&v)[MI][kMaxQuadParts],
                                                 float (&mu)[MI], float (&rstd)[MI]) {
-  const int half_np = (np + 1) >> 1, p0 = hf * half_np, p1 = min(np, p0 + half_np);
+  const int per = (np + 3) >> 2, p0 = quad * per, p1 = min(np, p0 + per);
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
     float a = 0.f, b = 0.f;
 #pragma unroll
-    for (int q = 0; q < kMaxHalfParts; ++q) {
+    for (int q = 0; q < kMaxQuadParts; ++q) {
       asm volatile("" : "+v"(v[i][q]));  // ordered after the caller's wait
       if (p0 + q < p1) {
         a += v[i][q].x;
         b += v[i][q].y;
       }
     }
-    if (half_np > kMaxHalfParts) {  // wide rows: the rest with ordinary loads
-      const float2* row = part + (size_t)min(m_base + i * 32 + l32, M - 1) * np;
-      for (int p = p0 + kMaxHalfParts; p < p1; ++p) {
+    if (per > kMaxQuadParts) {  // wide rows: the rest with ordinary loads
+      const float2* row = part + (size_t)min(m_base + i * 16 + l16, M - 1) * np;
+      for (int p = p0 + kMaxQuadParts; p < p1; ++p) {
         const float2 u = row[p];
         a += u.x;
         b += u.y;
       }
     }
+    a += __shfl_xor(a, 16, kWave);
+    b += __shfl_xor(b, 16, kWave);
     a += __shfl_xor(a, 32, kWave);
     b += __shfl_xor(b, 32, kWave);
     mu[i] = a * inv_h;
@@ -393,10 +389,10 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(
     const half_t* __restrict__ A, const half_t* __restrict__ W, const int32_t* __restrict__ a_rows /* = ep.a_rows */,
     const half_t* __restrict__ bias /* = ep.bias */, int M, int N, int K, int tiles_n, int tiles_m, int group_m,
     half_t* __restrict__ C, const GemmEpi ep) {
-  constexpr int BK = 64, KS = BK / 16;
+  constexpr int BK = 64, KS = BK / 32;
   constexpr int NWAVES = WGM * WGN;
   constexpr int WM = BM / WGM, WN = BN / WGN;   // wave tile
-  constexpr int MI = WM / 32, NI = WN / 32;     // 32x32 MFMA blocks per wave tile
+  constexpr int MI = WM / 16, NI = WN / 16;     // 16x16 MFMA blocks per wave tile
   constexpr int CPR = BK / 8;                   // 16-byte chunks per LDS row
   constexpr int RPI = 64 / CPR;                 // rows one DMA instruction (64 lanes x 16 B) fills
   constexpr int LA = BM / RPI / NWAVES, LB = BN / RPI / NWAVES;  // DMA instructions per wave per slab
@@ -405,8 +401,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(
   static_assert(LA * RPI * NWAVES == BM && LB * RPI * NWAVES == BN, "tile rows must split evenly over the waves");
   static_assert(NS >= 2 && (NS - 1) * TOT < 64, "vmcnt range");
 
-  // per-wave epilogue staging: the fp16 wave tile, or (split-K) one 32-row block of fp32 accumulators
-  constexpr int STAGE_HALVES = EPI == EPI_PARTIAL ? 2 * 32 * (WN + 4) : WM * (WN + 8);
+  // per-wave epilogue staging: the fp16 wave tile, or (split-K) one 16-row block of fp32 accumulators
+  constexpr int STAGE_HALVES = EPI == EPI_PARTIAL ? 2 * 16 * (WN + 4) : WM * (WN + 8);
   constexpr int PIPE_HALVES = NS * (BM + BN) * BK;
   constexpr int LDS_HALVES = PIPE_HALVES > NWAVES * STAGE_HALVES ? PIPE_HALVES : NWAVES * STAGE_HALVES;
   __shared__ __attribute__((aligned(1024))) half_t smem[LDS_HALVES];
@@ -431,7 +427,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: LDS DMA bases live in M0
   const int wm = wave / WGN, wn = wave % WGN;
-  const int l32 = lane & 31, hf = lane >> 5;
+  const int l16 = lane & 15, quad = lane >> 4;
 
   // The bias of the plain epilogue is requested right behind the first operand slabs (a cheap broadcast
   // load whose latency then hides behind the K loop).  The folded forms hold more per-column operands than
@@ -440,14 +436,14 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(
   ResidTile<MI, NI> rres;  // dead (and removed by the compiler) in the other epilogue forms
   EpiVecs<NI> vec;
   __shared__ float2 red[EPI == EPI_RESID ? WGN * BM : 1];
-  float2 psum[MI][kMaxHalfParts];
+  float2 psum[MI][kMaxQuadParts];
   constexpr bool kStats = EPI == EPI_FOLD || EPI == EPI_RESID;
   // without statistics (a plain residual) the requests still issue, at a harmless valid address, so that
   // the number of memory instructions in flight is a compile-time constant
   const float2* const stat_src = EPI == EPI_FOLD ? ep.ln_part : (EPI == EPI_RESID ? ep.resid_part : nullptr);
   const float2* const stat_part = stat_src ? stat_src : reinterpret_cast<const float2*>(W);
   const int stat_np = stat_src ? (EPI == EPI_FOLD ? ep.ln_np : ep.resid_np) : 0;
-  constexpr int kLateLoads = (EPI == EPI_RESID ? ResidTile<MI, NI>::P : 0) + (kStats ? MI * kMaxHalfParts : 0);
+  constexpr int kLateLoads = (EPI == EPI_RESID ? ResidTile<MI, NI>::P : 0) + (kStats ? MI * kMaxQuadParts : 0);
   static_assert((NS - 2) * TOT + kLateLoads < 64, "vmcnt range");
 
   // DMA source pointers.  Instruction q of this wave fills LDS rows [r0, r0+8) of the slab; lane i
@@ -487,13 +483,11 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(
     else dma16(gb[q >= LA ? q - LA : 0] + slab * BK, lds_b + stage * (BN * BK * 2) + (q - LA) * (RPI * BK * 2));
   };
 
-  float16_t acc[MI][NI];
+  float4_t acc[MI][NI];
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
-    for (int j = 0; j < NI; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    for (int j = 0; j < NI; ++j) acc[i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
 
   // Slab schedule.  Slab kt lives in stage (kt - pre) mod NS, with pre = (nk - (NS-1)) mod NS, so that
   // the nk slabs split into `pre` leading slabs (stage known at run time only), a steady state of
@@ -517,21 +511,21 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(
   // are loads here -- more than needed, never less, and only for the first slabs.
   if constexpr (EPI == EPI_PLAIN) load_epi_vecs<NI, EPI>(ep, bias, N, n0 + wn * WN, lane, vec);
 
-  // operand read offsets (halves): row*BK + ((2ks+hf) ^ swz(row))*8 ; swz depends on l32 only
-  const int swz = (l32 >> 1) & (CPR - 1);
-  const half_t* const pa0 = sA + (wm * WM + l32) * BK;
-  const half_t* const pb0 = sB + (wn * WN + l32) * BK;
+  // operand read offsets (halves): row*BK + ((4ks+quad) ^ swz(row))*8 ; swz depends on l16 only
+  const int swz = (l16 >> 1) & (CPR - 1);
+  const half_t* const pa0 = sA + (wm * WM + l16) * BK;
+  const half_t* const pb0 = sB + (wn * WN + l16) * BK;
   int co[KS];
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) co[ks] = ((2 * ks + hf) ^ swz) * 8;
+  for (int ks = 0; ks < KS; ++ks) co[ks] = ((4 * ks + quad) ^ swz) * 8;
   half8_t fa[2][MI], fb[2][NI];
   auto read_frags = [&](auto stage, int ks, int slot) {
 #pragma unroll
     for (int i = 0; i < MI; ++i)
-      fa[slot][i] = *reinterpret_cast<const half8_t*>(pa0 + co[ks] + stage * (BM * BK) + i * 32 * BK);
+      fa[slot][i] = *reinterpret_cast<const half8_t*>(pa0 + co[ks] + stage * (BM * BK) + i * 16 * BK);
 #pragma unroll
     for (int j = 0; j < NI; ++j)
-      fb[slot][j] = *reinterpret_cast<const half8_t*>(pb0 + co[ks] + stage * (BN * BK) + j * 32 * BK);
+      fb[slot][j] = *reinterpret_cast<const half8_t*>(pb0 + co[ks] + stage * (BN * BK) + j * 16 * BK);
   };
   auto mfmas = [&](int slot) {
 #pragma unroll
@@ -539,7 +533,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(
 #pragma unroll
       for (int j = 0; j < NI; ++j)
         // transposed product: D[n][m] += W[n][k] * A[m][k]
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fb[slot][j], fa[slot][i], acc[i][j], 0, 0, 0);
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fb[slot][j], fa[slot][i], acc[i][j], 0, 0, 0);
   };
   // One slab.  The fragments of k-step ks+1 are read from LDS while the MFMAs of k-step ks run; the
   // DMA instructions for slab kt+NS-1 (FETCH) are spread over the first KS-1 k-steps into the stage
@@ -599,7 +593,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(
   for (int i = 0; i < MI; ++i) { mu[i] = 0.f; rstd[i] = 1.f; }
   auto late_requests = [&]() {
     if constexpr (EPI == EPI_RESID) request_resid<MI, NI>(ep.resid, rrow, N, n0 + wn * WN, lane, rres);
-    if constexpr (kStats) request_row_sums<MI>(stat_part, stat_np, M, m0 + wm * WM, l32, hf, psum);
+    if constexpr (kStats) request_row_sums<MI>(stat_part, stat_np, M, m0 + wm * WM, l16, quad, psum);
   };
   auto late_collect = [&]() {
     if constexpr (kLateLoads > 0) {
@@ -608,7 +602,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(
 #pragma unroll
         for (int p = 0; p < ResidTile<MI, NI>::P; ++p) asm volatile("" : "+v"(rres.r[p]));  // ordered after the wait
       }
-      finish_row_sums<MI>(stat_part, stat_np, M, m0 + wm * WM, l32, hf, ep.inv_h, ep.eps, psum, mu, rstd);
+      finish_row_sums<MI>(stat_part, stat_np, M, m0 + wm * WM, l16, quad, ep.inv_h, ep.eps, psum, mu, rstd);
     }
   };
   for (int r = 0; r + 1 < rounds; ++r) {  // steady state: compile-time stages
@@ -652,6 +646,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(
   }
 }
 
+#include "gemm_wide.h"
+
 // ---------------------------------------------------------------------------
 // Fallback kernel: register-staged, 64x64x64 tile, padded LDS rows, K tail zero-filled.
 // ---------------------------------------------------------------------------
@@ -666,11 +662,13 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_simple_kernel(const half_t*
   const int tm = blockIdx.x / tiles_n, tn = blockIdx.x - tm * tiles_n;
   const int m0 = tm * BM, n0 = tn * BN;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, hf = lane >> 5;
+  const int wm = wave >> 1, wn = wave & 1, l16 = lane & 15, quad = lane >> 4;
   const int kc = (tid & 7) * 8;
-  float16_t acc[1][1];
+  float4_t acc[2][2];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) acc[0][0][r] = 0.f;
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
   const uint4_t zero4 = {0u, 0u, 0u, 0u};
   for (int k0 = 0; k0 < K; k0 += BK) {
     const bool in = (k0 + kc) < K;  // K % 8 == 0: a chunk is entirely inside or outside
@@ -691,34 +689,86 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_simple_kernel(const half_t*
     }
     __syncthreads();
 #pragma unroll
-    for (int ks = 0; ks < BK / 16; ++ks) {
-      const half8_t fa = *reinterpret_cast<const half8_t*>(&sA[(wm * 32 + l32) * LDS + ks * 16 + hf * 8]);
-      const half8_t fb = *reinterpret_cast<const half8_t*>(&sB[(wn * 32 + l32) * LDS + ks * 16 + hf * 8]);
-      acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fb, fa, acc[0][0], 0, 0, 0);
+    for (int ks = 0; ks < BK / 32; ++ks) {
+      half8_t fa[2], fb[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        fa[i] = *reinterpret_cast<const half8_t*>(&sA[(wm * 32 + i * 16 + l16) * LDS + ks * 32 + quad * 8]);
+        fb[i] = *reinterpret_cast<const half8_t*>(&sB[(wn * 32 + i * 16 + l16) * LDS + ks * 32 + quad * 8]);
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fb[j], fa[i], acc[i][j], 0, 0, 0);
     }
   }
   __syncthreads();  // operand tiles are dead: reuse them as per-wave staging space (32 x 40 halves each)
-  float mu[1] = {0.f}, rstd[1] = {1.f};
-  ResidTile<1, 1> rres;
+  float mu[2] = {0.f, 0.f}, rstd[2] = {1.f, 1.f};
+  ResidTile<2, 2> rres;
   __shared__ float2 red[EPI == EPI_RESID ? 2 * BM : 1];
   const float2* const stat_part = EPI == EPI_FOLD ? ep.ln_part : (EPI == EPI_RESID ? ep.resid_part : nullptr);
   const int stat_np = EPI == EPI_FOLD ? ep.ln_np : ep.resid_np;
   if (EPI != EPI_PLAIN && stat_part) {
-    float2 psum[1][kMaxHalfParts];
-    request_row_sums<1>(stat_part, stat_np, M, m0 + wm * 32, l32, hf, psum);
+    float2 psum[2][kMaxQuadParts];
+    request_row_sums<2>(stat_part, stat_np, M, m0 + wm * 32, l16, quad, psum);
     wait_vmcnt<0>();
-    finish_row_sums<1>(stat_part, stat_np, M, m0 + wm * 32, l32, hf, ep.inv_h, ep.eps, psum, mu, rstd);
+    finish_row_sums<2>(stat_part, stat_np, M, m0 + wm * 32, l16, quad, ep.inv_h, ep.eps, psum, mu, rstd);
   }
-  if constexpr (EPI == EPI_RESID) load_resid<1, 1>(ep.resid, ep.resid_rows, M, N, m0 + wm * 32, n0 + wn * 32, lane, rres);
-  EpiVecs<1> vec;
-  load_epi_vecs<1, EPI>(ep, ep.bias, N, n0 + wn * 32, lane, vec);
-  store_tile<1, 1, 2, ACT, EPI>(acc, ep, vec, mu, rstd, rres, tn, wn, wm * 32, red, BM, C, M, N, m0 + wm * 32, n0 + wn * 32,
+  if constexpr (EPI == EPI_RESID) load_resid<2, 2>(ep.resid, ep.resid_rows, M, N, m0 + wm * 32, n0 + wn * 32, lane, rres);
+  EpiVecs<2> vec;
+  load_epi_vecs<2, EPI>(ep, ep.bias, N, n0 + wn * 32, lane, vec);
+  store_tile<2, 2, 2, ACT, EPI>(acc, ep, vec, mu, rstd, rres, tn, wn, wm * 32, red, BM, C, M, N, m0 + wm * 32, n0 + wn * 32,
                                 lane, (wave < 2 ? sA : sB) + (wave & 1) * 32 * 40);
 }
 
 // act x epilogue combinations that exist: PLAIN and FOLD with any activation, RESID without one.
 static bt_status launch_simple(const half_t* A, const half_t* W, half_t* C, int M, int N, int K, bt_act act, int epi,
                                GemmEpi ep, hipStream_t st, int* np_out);
+
+// Strip height of the tile order: the per-XCD share of tiles (n_tiles/8) should cover a patch with gm*BM ~ gn*BN.
+static int strip_rows(long long n_tiles, int tiles_m, int bm, int bn) {
+  const int gm = (int)(sqrt((double)n_tiles / 8.0 * bn / bm) + 0.5);
+  return gm < 1 ? 1 : (gm > tiles_m ? tiles_m : gm);
+}
+
+template <int BM, int BN>
+static bt_status launch_wide(const half_t* A, const half_t* W, half_t* C, int M, int N, int K, bt_act act, int epi,
+                             GemmEpi ep, hipStream_t st, int* np_out) {
+  const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+  if (np_out) *np_out = tiles_n;
+  const long long n_tiles = (long long)tiles_m * tiles_n;
+  if (n_tiles > 0x7fffffffLL) return BT_ERR_UNSUPPORTED;
+  const int group_m = strip_rows(n_tiles, tiles_m, BM, BN);
+  const dim3 grid((unsigned)(epi == EPI_PLAIN && n_tiles > kComputeUnits ? kComputeUnits : n_tiles)), block(256);
+#define BT_LAUNCH_S(ACT, EPI, SHAPE) \
+  gemm_wide_kernel<BM, BN, ACT, EPI, SHAPE><<<grid, block, 0, st>>>(A, W, ep.a_rows, ep.bias, M, N, K, tiles_n, tiles_m, group_m, C, ep)
+#define BT_LAUNCH(ACT, EPI)                                      \
+  do {                                                           \
+    if constexpr ((ACT) == BT_ACT_NONE) {                        \
+      if (N >= 2 * K) BT_LAUNCH_S(ACT, EPI, 0);                  \
+      else if (K >= 2 * N) BT_LAUNCH_S(ACT, EPI, 2);             \
+      else BT_LAUNCH_S(ACT, EPI, 1);                             \
+    } else {                                                     \
+      BT_LAUNCH_S(ACT, EPI, 1);                                  \
+    }                                                            \
+  } while (0)
+  if (epi == EPI_FOLD) {
+    if constexpr (BM == 256 || BM == 192 || BM == 128) {  // see gemm_shape_ok
+      if (act == BT_ACT_NONE) BT_LAUNCH(BT_ACT_NONE, EPI_FOLD);
+      else if (act == BT_ACT_GELU_ERF) BT_LAUNCH(BT_ACT_GELU_ERF, EPI_FOLD);
+      else BT_LAUNCH(BT_ACT_GELU_TANH, EPI_FOLD);
+    } else {
+      return BT_ERR_UNSUPPORTED;
+    }
+  } else {
+    if (act == BT_ACT_NONE) BT_LAUNCH(BT_ACT_NONE, EPI_PLAIN);
+    else if (act == BT_ACT_GELU_ERF) BT_LAUNCH(BT_ACT_GELU_ERF, EPI_PLAIN);
+    else BT_LAUNCH(BT_ACT_GELU_TANH, EPI_PLAIN);
+  }
+#undef BT_LAUNCH
+#undef BT_LAUNCH_S
+  return launch_status();
+}
 
 template <int BM, int BN, int WGM, int WGN, int NS>
 static bt_status launch_pipe(const half_t* A, const half_t* W, half_t* C, int M, int N, int K, bt_act act, int epi,
@@ -730,9 +780,7 @@ static bt_status launch_pipe(const half_t* A, const half_t* W, half_t* C, int M,
   const long long n_tiles = (long long)tiles_m * tiles_n;
   if (n_tiles > 0x7fffffffLL) return BT_ERR_UNSUPPORTED;
   dim3 grid((unsigned)n_tiles), block(WGM * WGN * 64);
-  // strip height: the per-XCD share of tiles (n_tiles/8) should cover a patch with gm*BM ~ gn*BN
-  int group_m = (int)(sqrt((double)n_tiles / 8.0 * BN / BM) + 0.5);
-  group_m = group_m < 1 ? 1 : (group_m > tiles_m ? tiles_m : group_m);
+  const int group_m = strip_rows(n_tiles, tiles_m, BM, BN);
 #define BT_LAUNCH_S(ACT, EPI, SHAPE) \
   gemm_pipe_kernel<BM, BN, WGM, WGN, NS, ACT, EPI, SHAPE><<<grid, block, 0, st>>>(A, W, ep.a_rows, ep.bias, M, N, K, tiles_n, tiles_m, group_m, C, ep)
   // the shape class is spelled out only where two products of a layer can meet in one instantiation
@@ -754,12 +802,7 @@ static bt_status launch_pipe(const half_t* A, const half_t* W, half_t* C, int M,
     }                                                                           \
   } while (0)
   if (epi == EPI_RESID) {
-    // only for shapes with one 32x32 block per wavefront: the residual tile and the partial row sums wait in
-    // registers across the last slabs, and the two largest shapes have none to spare (they would spill, which
-    // the hand-collected loads do not survive).  128x128 fits (192 registers) but gains nothing where it could
-    // be chosen: folded and plain layers are level from 2 700 to 5 400 tokens of width 768 with it.
-    if constexpr ((BM / WGM) * (BN / WGN) == 32 * 32) BT_LAUNCH(BT_ACT_NONE, EPI_RESID);
-    else return BT_ERR_UNSUPPORTED;
+    BT_LAUNCH(BT_ACT_NONE, EPI_RESID);
   } else if (epi == EPI_FOLD) {
     if (act == BT_ACT_NONE) BT_LAUNCH(BT_ACT_NONE, EPI_FOLD);
     else if (act == BT_ACT_GELU_ERF) BT_LAUNCH(BT_ACT_GELU_ERF, EPI_FOLD);
@@ -798,30 +841,59 @@ static bt_status launch_simple(const half_t* A, const half_t* W, half_t* C, int 
   return launch_status();
 }
 
-// Tile choice by a small cost model.  Every tile shape is bound by how fast a compute unit ingests
-// operand slabs (~85 GB/s here whatever the shape), so one 64-deep slab costs a time proportional to
-// BM+BN, and the grid runs in ceil(tiles / 256) rounds of one tile per compute unit.  slab_us and
-// epi_us (epilogue + pipeline fill) were measured per shape on MI355X; GELU adds to the epilogue.
-// Returns the index into kGemmTiles.  K % 64 == 0.
-struct GemmTile { int bm, bn; float slab_us, epi_us; bool resid_form; };
-static const GemmTile kGemmTiles[6] = {{256, 128, 0.607f, 2.2f, false}, {192, 128, 0.482f, 1.5f, false},
-                                       {128, 128, 0.384f, 1.5f, false}, {128, 64, 0.298f, 0.78f, true},
-                                       {64, 128, 0.287f, 0.84f, true},  {64, 64, 0.183f, 0.4f, true}};
-// Time of one round (one tile per compute unit) of shape t, by the model above.
-static float gemm_round_us(const GemmTile& t, int K, bt_act act) {
-  const float act_us = act != BT_ACT_NONE ? 9e-5f * t.bm * t.bn : 0.f;
-  return (float)(K / 64) * t.slab_us + t.epi_us + act_us;
+// Tile choice by a small cost model, fitted to MI355X measurements of every shape on the products of both layer widths
+// at nine token counts from 640 to 9 894 (kernels in dependent sequence, launch included; the fit is within 3 % rms):
+//   us = start + rounds (slabs slab0 + epi + act) + slabs slab_u (tiles / 256),   rounds = ceil(tiles / 256).
+// slab0 is what a 64-deep slab costs a compute unit that has the chip to itself, slab_u what the other 255 add when all
+// of them fetch operands at once; act_us (one activation per output, vector work that nothing overlaps) adds to epi.
+// Its choice is within 1.1 % of the best shape on average over the measured points.  K % 64 == 0.
+struct GemmTile { int bm, bn; float start_us, slab0_us, slab_u_us, epi_us; bool wide; };
+constexpr int kGemmShapes = 9;
+static const GemmTile kGemmTiles[kGemmShapes] = {
+    {256, 128, 2.1f, 0.459f, 0.318f, 2.76f, true}, {224, 128, 1.6f, 0.402f, 0.242f, 3.2f, true},
+    {192, 128, 1.85f, 0.359f, 0.212f, 2.6f, true}, {160, 128, 1.7f, 0.319f, 0.177f, 2.29f, true},
+    {128, 128, 2.2f, 0.289f, 0.136f, 1.55f, true}, {96, 128, 2.2f, 0.285f, 0.078f, 1.08f, true},
+    {128, 64, 1.5f, 0.223f, 0.068f, 1.6f, false},  {64, 128, 1.55f, 0.224f, 0.059f, 1.61f, false},
+    {64, 64, 2.4f, 0.139f, 0.043f, 0.35f, false}};
+constexpr float kActUs = 0.75e-4f;  // per output of a tile
+
+// gemm_wide_kernel: at least four slabs, 32-bit byte offsets into both operands.  Its residual epilogue does not exist: the
+// residual tile and the partial row sums would wait in registers across the last slabs.
+static bool gemm_wide_ok(long long a_rows, int N, int K, int epi) {
+  return K >= 256 && epi != EPI_RESID && (a_rows + 256) * K * 2 < (1LL << 32) && (N + 128LL) * K * 2 < (1LL << 32);
 }
 
-static int gemm_tile_choice(int M, int N, int K, bt_act act, int epi, float* us_out = nullptr) {
+// The shapes whose row count is not a multiple of 64 smooth the staircase of the others.  160 and 96 rows for short
+// reductions with an activation, and 96 rows for deep reductions, are taken only where their last round of tiles fills at
+// least three quarters of the chip: there they measured 3 to 4 % of a layer, and nothing elsewhere.  FOLD
+// exists for the other three wide shapes.
+static bool gemm_shape_ok(const GemmTile& t, int M, int N, int K, bt_act act, int epi, bool wide_ok) {
+  if (!t.wide) return true;
+  if (!wide_ok) return false;
+  if (epi != EPI_PLAIN && t.bm != 256 && t.bm != 192 && t.bm != 128) return false;
+  if (((t.bm == 160 || t.bm == 96) && act != BT_ACT_NONE && K < 1024) || (t.bm == 96 && K >= 2 * N)) {
+    const long long tiles = (long long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+    return (tiles - 1) % kComputeUnits >= kComputeUnits * 3 / 4;
+  }
+  return true;
+}
+
+// A single round of wide tiles on nearly every compute unit, all of them storing at once, costs more inside an encoder layer
+// than the model says (1.5 to 3.7 us on the products without an activation): full_us.
+static float gemm_shape_us(const GemmTile& t, int M, int N, int K, bt_act act) {
+  const long long tiles = (long long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+  const float rounds = (float)((tiles + kComputeUnits - 1) / kComputeUnits), slabs = (float)(K / 64);
+  const float epi = t.epi_us + (act != BT_ACT_NONE ? kActUs * t.bm * t.bn : 0.f);
+  const float full_us = t.wide && act == BT_ACT_NONE && tiles > 240 && tiles <= kComputeUnits ? 1.5f : 0.f;
+  return t.start_us + rounds * (slabs * t.slab0_us + epi) + slabs * t.slab_u_us * (float)tiles / kComputeUnits + full_us;
+}
+
+static int gemm_tile_choice(int M, int N, int K, bt_act act, int epi, bool wide_ok, float* us_out = nullptr) {
   int best = -1;
   float best_us = 0.f;
-  for (int c = 0; c < 6; ++c) {
-    const GemmTile& t = kGemmTiles[c];
-    if (epi == EPI_RESID && !t.resid_form) continue;  // see launch_pipe
-    const long long tiles = (long long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
-    const long long rounds = (tiles + 255) / 256;
-    const float us = (float)rounds * gemm_round_us(t, K, act);
+  for (int c = 0; c < kGemmShapes; ++c) {
+    if (!gemm_shape_ok(kGemmTiles[c], M, N, K, act, epi, wide_ok)) continue;
+    const float us = gemm_shape_us(kGemmTiles[c], M, N, K, act);
     if (best < 0 || us < best_us) { best = c; best_us = us; }
   }
   if (us_out) *us_out = best_us;
@@ -829,31 +901,30 @@ static int gemm_tile_choice(int M, int N, int K, bt_act act, int epi, float* us_
 }
 
 // The staircase of the round model: a tile grid that needs a little more than a whole number of rounds pays a
-// whole round for its few last tiles (608 tiles of 256 x 128 for the FFN-up product of 4 648 tokens at width
-// 1024: the third round runs 96 tiles on 256 compute units).  Rows are independent, so such a product can run as
+// whole round for its few last tiles.  Rows are independent, so such a product can run as
 // two launches: the rows that fill whole rounds of one shape, then the remaining rows with whatever shape suits
-// them (measured for that product: 49 us against 58.5 us; bit-identical rows where both parts use the shape of the
-// single launch).  Returns the number of leading rows for the first launch and its shape, or 0: one launch.
-// The second launch costs a launch gap, and the model's constants are from single-round runs: a split must
-// promise 5 %.
-constexpr float kLaunchUs = 2.5f;
-static int gemm_msplit_choice(int M, int N, int K, bt_act act, int* main_tile) {
-  float single_us = 0.f;
-  (void)gemm_tile_choice(M, N, K, act, EPI_PLAIN, &single_us);
+// them (bit-identical rows where both parts use the shape of the single launch), where the model finds that faster.
+// Returns the number of leading rows for the first launch and its shape, or 0: one launch.
+static int gemm_msplit_choice(int M, int N, int K, bt_act act, bool wide_ok, int* main_tile) {
+  float best_us = 0.f;
+  (void)gemm_tile_choice(M, N, K, act, EPI_PLAIN, wide_ok, &best_us);
   int best_rows = 0;
-  float best_us = 0.95f * single_us;
-  for (int c = 0; c < 6; ++c) {
+  for (int c = 0; c < kGemmShapes; ++c) {
     const GemmTile& t = kGemmTiles[c];
+    if (!gemm_shape_ok(t, M, N, K, act, EPI_PLAIN, wide_ok)) continue;
     const long long tn = (N + t.bn - 1) / t.bn, tm = (M + t.bm - 1) / t.bm, tiles = tm * tn;
-    const long long full = tiles / 256;
-    if (full < 1 || tiles % 256 == 0 || tn > 256) continue;
-    const long long rows_main = (full * 256 / tn) * t.bm;  // whole tile rows that fit `full` rounds
+    const long long full = tiles / kComputeUnits;
+    if (full < 1 || tiles % kComputeUnits == 0 || tn > kComputeUnits) continue;
+    const long long rows_main = (full * kComputeUnits / tn) * t.bm;  // whole tile rows that fit `full` rounds
     if (rows_main <= 0 || rows_main >= M) continue;
-    const long long rounds_main = ((rows_main / t.bm) * tn + 255) / 256;
     float rest_us = 0.f;
-    (void)gemm_tile_choice((int)(M - rows_main), N, K, act, EPI_PLAIN, &rest_us);
-    const float us = (float)rounds_main * gemm_round_us(t, K, act) + rest_us + kLaunchUs;
-    if (us < best_us) { best_us = us; best_rows = (int)rows_main; *main_tile = c; }
+    (void)gemm_tile_choice((int)(M - rows_main), N, K, act, EPI_PLAIN, wide_ok, &rest_us);
+    const float us = gemm_shape_us(t, (int)rows_main, N, K, act) + rest_us;
+    if (us < (best_rows ? 0.99f : 1.f) * best_us) {  // among equals the larger shape, listed first
+      best_us = us;
+      best_rows = (int)rows_main;
+      *main_tile = c;
+    }
   }
   return best_rows;
 }
@@ -861,15 +932,20 @@ static int gemm_msplit_choice(int M, int N, int K, bt_act act, int* main_tile) {
 static bt_status gemm_launch_tile(int tile, const half_t* a, const half_t* w, half_t* c, int M, int N, int K,
                                   bt_act act, int epi, const GemmEpi& ep, hipStream_t st, int* np_out) {
 #define BT_PIPE(BM, BN, WGM, WGN, NS) launch_pipe<BM, BN, WGM, WGN, NS>(a, w, c, M, N, K, act, epi, ep, st, np_out)
+#define BT_WIDE(BM, BN) launch_wide<BM, BN>(a, w, c, M, N, K, act, epi, ep, st, np_out)
   switch (tile) {
-    case 0: return BT_PIPE(256, 128, 4, 2, 3);
-    case 1: return BT_PIPE(192, 128, 2, 4, 3);
-    case 2: return BT_PIPE(128, 128, 2, 4, 4);
-    case 3: return BT_PIPE(128, 64, 4, 2, 4);
-    case 4: return BT_PIPE(64, 128, 2, 4, 4);
+    case 0: return BT_WIDE(256, 128);
+    case 1: return BT_WIDE(224, 128);
+    case 2: return BT_WIDE(192, 128);
+    case 3: return BT_WIDE(160, 128);
+    case 4: return BT_WIDE(128, 128);
+    case 5: return BT_WIDE(96, 128);
+    case 6: return BT_PIPE(128, 64, 4, 2, 4);
+    case 7: return BT_PIPE(64, 128, 2, 4, 4);
     default: return BT_PIPE(64, 64, 2, 2, 4);
   }
 #undef BT_PIPE
+#undef BT_WIDE
 }
 
 bt_status gemm_dispatch(const bt_half* A, const bt_half* W, int M, int N, int K, bt_act act, int epi,
@@ -879,9 +955,10 @@ bt_status gemm_dispatch(const bt_half* A, const bt_half* W, int M, int N, int K,
   half_t* c = reinterpret_cast<half_t*>(C);
   if (epi == EPI_RESID && act != BT_ACT_NONE) return BT_ERR_INVALID_ARG;
   if ((K % 64) != 0) return launch_simple(a, w, c, M, N, K, act, epi, ep, st, np_out);
+  const bool wide_ok = gemm_wide_ok(ep.a_rows ? ep.a_rows_of : M, N, K, epi);
   if (epi == EPI_PLAIN) {  // nothing of the plain epilogue is indexed by row: the row ranges are independent products
     int main_tile = 0;
-    const int m1 = gemm_msplit_choice(M, N, K, act, &main_tile);
+    const int m1 = gemm_msplit_choice(M, N, K, act, wide_ok, &main_tile);
     if (m1 > 0) {
       const bt_status s = gemm_launch_tile(main_tile, a, w, c, m1, N, K, act, epi, ep, st, np_out);
       if (s != BT_OK) return s;
@@ -891,7 +968,7 @@ bt_status gemm_dispatch(const bt_half* A, const bt_half* W, int M, int N, int K,
                            epi, rest, reinterpret_cast<bt_half*>(c + (size_t)m1 * N), st, np_out);
     }
   }
-  return gemm_launch_tile(gemm_tile_choice(M, N, K, act, epi), a, w, c, M, N, K, act, epi, ep, st, np_out);
+  return gemm_launch_tile(gemm_tile_choice(M, N, K, act, epi, wide_ok), a, w, c, M, N, K, act, epi, ep, st, np_out);
 }
 
 // Split-K for token counts so small that the tile grid leaves most compute units idle and every tile
@@ -924,8 +1001,7 @@ bt_status gemm_splitk_dispatch(const bt_half* A, const bt_half* W, int M, int N,
   GemmEpi ep;
   ep.partial = partial;
   ep.ksplit = ksplit;
-  int group_m = (int)(sqrt((double)n_tiles / 8.0) + 0.5);
-  group_m = group_m < 1 ? 1 : (group_m > tiles_m ? tiles_m : group_m);
+  const int group_m = strip_rows(n_tiles, tiles_m, BM, BN);
   const dim3 grid((unsigned)(n_tiles * ksplit)), block(256);
   const half_t* a = reinterpret_cast<const half_t*>(A);
   const half_t* w = reinterpret_cast<const half_t*>(W);
@@ -982,7 +1058,7 @@ extern "C" bt_status bt_gemm_row_split(int M, int N, int K, bt_act act, int* row
   if (M < 0 || N < 1 || K < 1 || (N % 8) != 0 || (K % 8) != 0 || !rows_first) return BT_ERR_INVALID_ARG;
   if (act != BT_ACT_NONE && act != BT_ACT_GELU_ERF && act != BT_ACT_GELU_TANH) return BT_ERR_INVALID_ARG;
   int tile = 0;
-  *rows_first = (K % 64) != 0 || M < 1 ? 0 : bt::gemm_msplit_choice(M, N, K, act, &tile);
+  *rows_first = (K % 64) != 0 || M < 1 ? 0 : bt::gemm_msplit_choice(M, N, K, act, bt::gemm_wide_ok(M, N, K, bt::EPI_PLAIN), &tile);
   return BT_OK;
 }
 
@@ -991,9 +1067,8 @@ extern "C" bt_status bt_gemm_tile_shape(int M, int N, int K, bt_act act, int* bm
   if (act != BT_ACT_NONE && act != BT_ACT_GELU_ERF && act != BT_ACT_GELU_TANH) return BT_ERR_INVALID_ARG;
   *bm = *bn = 64;  // the register-staged fallback kernel: K not a multiple of 64, or shorter than the pipeline
   if ((K % 64) != 0) return BT_OK;
-  const int c = bt::gemm_tile_choice(M, N, K, act, bt::EPI_PLAIN);
-  const bt::GemmTile& t = bt::kGemmTiles[c];
-  if (K / 64 < (c < 2 ? 3 : 4) - 1) return BT_OK;  // stages of that shape: 3 for the two widest, else 4
+  const bt::GemmTile& t = bt::kGemmTiles[bt::gemm_tile_choice(M, N, K, act, bt::EPI_PLAIN, bt::gemm_wide_ok(M, N, K, bt::EPI_PLAIN))];
+  if (K / 64 < 3) return BT_OK;  // shorter than the four stages of the narrow shapes
   *bm = t.bm;
   *bn = t.bn;
   return BT_OK;

@@ -108,6 +108,7 @@ static bt_status check_stack(const bt_layer* layers, int n_layers) {
 // Where a layer's input rows come from and where its output rows go.  Defaults: packed in, packed out.
 struct LayerIo {
   const int32_t* in_rows = nullptr;   // x is the PADDED tensor; packed row i is its row in_rows[i] (first layer)
+  int in_rows_of = 0;                 // rows of that tensor
   const int32_t* out_idx = nullptr;   // y is the PADDED tensor [out_rows, H]; packed row i goes to row out_idx[i],
   int out_rows = 0;                   // every other row is zero-filled (last layer)
 };
@@ -118,6 +119,7 @@ static bt_status layer_fwd(const bt_layer* l, const bt_half* x, const int32_t* c
   bt_status s;
   GemmEpi ep;
   ep.a_rows = io.in_rows;
+  ep.a_rows_of = io.in_rows_of;
   ep.bias = hp(l->b_qkv);
   if ((s = gemm_dispatch(x, l->w_qkv, T, 3 * H, H, BT_ACT_NONE, EPI_PLAIN, ep, w.qkv, st, nullptr)) != BT_OK) return s;
   const float scale = 1.0f / sqrtf((float)l->head_dim);
@@ -182,6 +184,7 @@ static bt_status stack_fwd_folded(const bt_layer* layers, int n_layers, const fl
       } else {
         ep.bias = hp(l->b_qkv);
         ep.a_rows = io.in_rows;
+        ep.a_rows_of = io.in_rows_of;
       }
       if ((s = gemm_dispatch(in, l->w_qkv, T, 3 * H, H, BT_ACT_NONE, prev ? EPI_FOLD : EPI_PLAIN, ep, w.qkv, st,
                              nullptr)) != BT_OK)
@@ -395,6 +398,7 @@ extern "C" bt_status bt_encoder_fwd_padded(const bt_layer* layers, int n_layers,
   if (d_fold && folded_pays(T, H, layers[0].F)) {
     LayerIo io;
     io.in_rows = d_token_idx;
+    io.in_rows_of = B * S;
     io.out_idx = d_token_idx;
     io.out_rows = B * S;
     return stack_fwd_folded(layers, n_layers, d_fold, d_x_padded, d_cu_seqlens, B, T, S, d_y_padded, w, st, io);
@@ -403,7 +407,7 @@ extern "C" bt_status bt_encoder_fwd_padded(const bt_layer* layers, int n_layers,
   for (int i = 0; i < n_layers; ++i) {
     const bool last = i == n_layers - 1;
     LayerIo io;
-    if (i == 0) io.in_rows = d_token_idx;
+    if (i == 0) { io.in_rows = d_token_idx; io.in_rows_of = B * S; }
     if (last) { io.out_idx = d_token_idx; io.out_rows = B * S; }
     bt_half* outp = last ? d_y_padded : ((i & 1) ? w.pong : w.ping);
     if ((s = layer_fwd(&layers[i], in, d_cu_seqlens, B, T, S, outp, w, st, io)) != BT_OK) return s;

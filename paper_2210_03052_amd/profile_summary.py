@@ -51,9 +51,13 @@ def role_of(name: str, grid: int = 0):
     a = template_args(name)
     if "unpack_kernel" not in name and "pack_kernel" in name and grid >= STREAMING_GRID:
         return "pack_streaming", "pack_kernel (262144 tokens)"
-    if "gemm_pipe_kernel" in name and len(a) >= 8:
-        bm, bn, wgm, wgn, ns, act, epi, shape = a[:8]
-        label = f"gemm_pipe<{bm}x{bn},{wgm}x{wgn} waves,{ns} stages,act={act},epi={epi},shape={shape}>"
+    if ("gemm_pipe_kernel" in name and len(a) >= 8) or ("gemm_wide_kernel" in name and len(a) >= 5):
+        if "gemm_wide_kernel" in name:
+            bm, bn, act, epi, shape = a[:5]
+            label = f"gemm_wide<{bm}x{bn},act={act},epi={epi},shape={shape}>"
+        else:
+            bm, bn, wgm, wgn, ns, act, epi, shape = a[:8]
+            label = f"gemm_pipe<{bm}x{bn},{wgm}x{wgn} waves,{ns} stages,act={act},epi={epi},shape={shape}>"
         if epi == 3:
             return ("gemm3_ffn_down" if shape == 2 else "gemm1_proj"), label
         if epi == 1:   # LayerNorm of the input folded into the epilogue (5-launch pipeline)

@@ -224,6 +224,27 @@ def test_gemm_bias_act(bt, M, N, K, act, bias):
     assert (err <= 1e-3 + 2 ** -10 * np.abs(ref)).mean() > 0.999
 
 
+@pytest.mark.parametrize("tile,M,N,K,act", [
+    (96, 716, 2976, 256, 0), (96, 4491, 2008, 256, 1), (96, 2202, 1240, 768, 0), (128, 3678, 3256, 256, 1),
+    (128, 6832, 1144, 384, 0), (128, 2852, 1344, 320, 2), (160, 7260, 1320, 256, 0), (160, 3583, 2768, 320, 2),
+    (160, 4395, 856, 768, 0), (192, 6783, 1704, 256, 0), (192, 7870, 1376, 320, 2), (192, 3998, 1296, 768, 1),
+    (224, 6686, 2088, 256, 0), (224, 8623, 1440, 320, 1), (224, 2010, 3040, 448, 2), (256, 4452, 3304, 256, 0),
+    (256, 6309, 2360, 256, 1), (256, 2599, 2568, 576, 0)])
+def test_gemm_wide_tiles(bt, tile, M, N, K, act):
+    """Every wide tile shape: rows and columns that do not fill the last tile, the shortest reduction (four slabs) and
+    longer ones of every residue modulo the three stages, one tile per workgroup and several in turn."""
+    assert bt.gemm_tile_shape(M, N, K, act) == (tile, 128) and bt.gemm_row_split(M, N, K, act) == 0
+    rng = np.random.default_rng(M + N + K)
+    a = rng.normal(0, 1, (M, K)).astype(np.float16)
+    w = rng.normal(0, 0.05, (N, K)).astype(np.float16)
+    b = rng.normal(0, 0.5, N).astype(np.float16)
+    ref = a.astype(np.float32) @ w.astype(np.float32).T + b.astype(np.float32)
+    if act:
+        ref = (O.gelu if act == 1 else O.gelu_tanh)(ref.astype(np.float64))
+    got = host(bt.gemm_bias_act(dev(a), dev(w), dev(b), act)).astype(np.float64)
+    assert np.abs(got - ref).max() <= 2e-3 * max(1.0, np.abs(ref).max())
+
+
 @pytest.mark.parametrize("act", [1, 2])
 def test_gelu_epilogue_over_every_fp16_input(bt, act):
     """The activation alone: with A = identity the product hands each weight through unchanged
