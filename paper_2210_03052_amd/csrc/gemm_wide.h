@@ -36,6 +36,9 @@ __device__ __forceinline__ void dma16_sv(const void* sbase, uint32_t voff, uint3
   asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(sbase), "n"(OFF)
                : "memory", "m0", "scc");
 }
+__device__ __forceinline__ void dma4_sv(const void* sbase, uint32_t voff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(voff), "s"(sbase) : "memory", "m0");
+}
 
 template <int BM, int BN>
 struct WideTile {
@@ -106,12 +109,14 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(
     if constexpr (Q < LA) dma16_sv<Q * 1024>(fa_base, va[Q], dma_a + fstage);
     else dma16_sv<(Q - LA) * 1024>(fb_base, vb[Q - LA], dma_b + fstage);
   };
-  // The tile's per-column operands for the epilogue (columns past N: clamped, never stored).  PLAIN: BN bias values, one DMA
-  // instruction (lanes past them repeat the last ones).  FOLD: BN values of fold_c, then BN of fold_d = fold_c + N.
+  // The tile's per-column operands for the epilogue (columns past N: clamped, never stored), one DMA instruction.
+  // PLAIN: BN bias values, a pair per lane (a bias is 8-byte aligned, not 16).  FOLD: BN values of fold_c, then BN of
+  // fold_d = fold_c + N.
   auto request_bias = [&](int n_first, int parity) {
     const uint32_t to = lds0 + T::NS * STAGE + 4 * T::EPI_BYTES + parity * T::BIAS_BYTES;
     if constexpr (EPI == EPI_PLAIN) {
-      if (bias && wave == 0) dma16_sv<0>(bias, (uint32_t)min(n_first + lane * 8, N - 8) * 2u, to);
+      static_assert(BN == 128, "one DMA instruction: 64 pairs");
+      if (bias && wave == 0) dma4_sv(bias, (uint32_t)min(n_first + lane * 2, N - 2) * 2u, to);
     } else {
       static_assert(BN == 128, "one DMA instruction: 32 lanes for each vector");
       if (wave == 0) dma16_sv<0>(ep.fold_c, (uint32_t)((lane >> 5) * N + min(n_first + (lane & 31) * 4, N - 4)) * 4u, to);

@@ -245,6 +245,22 @@ def test_gemm_wide_tiles(bt, tile, M, N, K, act):
     assert np.abs(got - ref).max() <= 2e-3 * max(1.0, np.abs(ref).max())
 
 
+@pytest.mark.parametrize("tile,M,N,K", [(96, 716, 2976, 256), (128, 3678, 3256, 256), (256, 4452, 3304, 256)])
+def test_gemm_wide_tiles_bias_alignment(bt, tile, M, N, K):
+    """A bias that starts 8 bytes past a 16-byte boundary, the least alignment that is accepted: same bits."""
+    import torch
+    assert bt.gemm_tile_shape(M, N, K, 1) == (tile, 128) or bt.gemm_tile_shape(M, N, K, 0) == (tile, 128)
+    act = 0 if bt.gemm_tile_shape(M, N, K, 0) == (tile, 128) else 1
+    rng = np.random.default_rng(M + N)
+    a, w = dev(rng.normal(0, 1, (M, K)).astype(np.float16)), dev(rng.normal(0, 0.05, (N, K)).astype(np.float16))
+    b = dev(rng.normal(0, 0.5, N).astype(np.float16))
+    room = torch.empty(N + 4, dtype=torch.float16, device="cuda:0")
+    shifted = room[4:]
+    shifted.copy_(b)
+    assert b.data_ptr() % 16 == 0 and shifted.data_ptr() % 16 == 8
+    assert torch.equal(bt.gemm_bias_act(a, w, shifted, act), bt.gemm_bias_act(a, w, b, act))
+
+
 @pytest.mark.parametrize("act", [1, 2])
 def test_gelu_epilogue_over_every_fp16_input(bt, act):
     """The activation alone: with A = identity the product hands each weight through unchanged
