@@ -31,7 +31,10 @@ FLAGS = [
 
 # Per-file extras.  The attention kernel runs VALU softmax directly on MFMA results: keep MFMA
 # operands and results in VGPRs so that no v_accvgpr_read/write copies sit in its inner loop.
-EXTRA_FLAGS = {"mha.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+# GEMM epilogue: the last fused multiply-add of an activation and its conversion to fp16 become one instruction with one
+# rounding.  The SLP vectoriser pairs some of the conversions first, which leaves those elements two roundings, other
+# ones in every tile shape; without it the result of an element does not depend on the tile that holds it.
+EXTRA_FLAGS = {"mha.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"], "gemm.hip": ["-fno-slp-vectorize"]}
 
 
 def _compile(src: str) -> str:
