@@ -290,58 +290,101 @@ __device__ __forceinline__ void store_partial(const float4_t (&acc)[MI][NI], flo
 
 // Mean and 1/sigma of the rows m_base + i*16 + l16 from their partial sums, in two steps so that the
 // loads can be issued ahead of the operand slabs and collected after them:
-//   request_row_sums: the four 16-lane quarters each request a quarter of a row's partials (up to
-//     kMaxQuadParts each, clamped indices, no branches).  Issued through inline assembly so that the
-//     compiler does not put a wait for ALL outstanding memory operations in front of their first use;
-//   finish_row_sums: after the caller has waited (s_waitcnt vmcnt), add them in index order,
-//     exchange the quarters, derive mu and rstd.
-constexpr int kMaxQuadParts = 2;  // np <= 8: H <= 1024 at 128-wide column tiles; more falls back to a loop
+//   request_row_sums: a row's partials form two halves; the 16-lane quarters 0 and 2 request the front of a half,
+//     quarters 1 and 3 what follows (up to QP each, clamped indices, no branches).  Issued through
+//     inline assembly so that the compiler does not put a wait for ALL outstanding memory operations in front of their
+//     first use;
+//   finish_row_sums: after the caller has waited (s_waitcnt vmcnt), each half in index order (a back quarter goes on
+//     where its front quarter stopped), then the two halves; ln_finalize_kernel adds in the same order.
+// QP requests a lane cover 4 QP partials of a row, more of them are fetched behind the wait.  The 64 x 64 tile, which runs
+// where 64-wide tiles wrote 12 or 16 partials (width 768, 1024), has QP = 4, the others 2 (8 partials: width 1024 at 128-wide
+// tiles): requests that nobody needs cost, with 4 in every shape six folded layers of width 768 take 440 us instead of
+// 424 at 2 308 tokens.
+constexpr int row_sum_requests(int bm, int bn) { return bm * bn == 64 * 64 ? 4 : 2; }
 
-template <int MI>
+struct RowSumRange { int p0, p1; };  // the partials of a row that this lane adds
+template <int QP>
+__device__ __forceinline__ RowSumRange row_sum_range(int np, int quad) {
+  const int half_np = (np + 1) >> 1, h0 = (quad >> 1) * half_np, h1 = min(np, h0 + half_np);
+  return quad & 1 ? RowSumRange{h0 + QP, h1} : RowSumRange{h0, min(h1, h0 + QP)};
+}
+
+// Quarters 0 and 2 of the wavefront copied over quarters 1 and 3.
+__device__ __forceinline__ float even_quarter(float v) {
+  const unsigned u = __builtin_bit_cast(unsigned, v);
+  return __builtin_bit_cast(float, __builtin_amdgcn_permlane16_swap(u, u, false, false)[0]);
+}
+// Quarter 1 + quarter 3, in every lane.
+__device__ __forceinline__ float sum_of_odd_quarters(float v) {
+  const unsigned u = __builtin_bit_cast(unsigned, v);
+  const unsigned h = __builtin_amdgcn_permlane16_swap(u, u, false, false)[1];
+  const auto t = __builtin_amdgcn_permlane32_swap(h, h, false, false);
+  return __builtin_bit_cast(float, (unsigned)t[0]) + __builtin_bit_cast(float, (unsigned)t[1]);
+}
+
+template <int MI, int QP>
 __device__ __forceinline__ void request_row_sums(const float2* __restrict__ part, int np, int M, int m_base, int l16,
-                                                 int quad, float2 (&v)[MI][kMaxQuadParts]) {
-  const int per = (np + 3) >> 2, p0 = quad * per, p1 = min(np, p0 + per);
+                                                 int quad, float2 (&v)[MI][QP]) {
+  const RowSumRange r = row_sum_range<QP>(np, quad);
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
     const float2* row = part + (size_t)min(m_base + i * 16 + l16, M - 1) * np;
 #pragma unroll
-    for (int q = 0; q < kMaxQuadParts; ++q) {
-      const float2* src = row + max(min(p0 + q, p1 - 1), 0);
+    for (int q = 0; q < QP; ++q) {
+      const float2* src = row + max(min(r.p0 + q, r.p1 - 1), 0);
       asm volatile("global_load_dwordx2 %0, %1, off" : "=v"(v[i][q]) : "v"(src) : "memory");
     }
   }
 }
 
-template <int MI>
+template <int MI, int QP>
 __device__ __forceinline__ void finish_row_sums(const float2* __restrict__ part, int np, int M, int m_base, int l16,
-                                                int quad, float inv_h, float eps, float2 (&v)[MI][kMaxQuadParts],
+                                                int quad, float inv_h, float eps, float2 (&v)[MI][QP],
                                                 float (&mu)[MI], float (&rstd)[MI]) {
-  const int per = (np + 3) >> 2, p0 = quad * per, p1 = min(np, p0 + per);
+  const RowSumRange r = row_sum_range<QP>(np, quad);
+  float a[MI], b[MI];
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
-    float a = 0.f, b = 0.f;
 #pragma unroll
-    for (int q = 0; q < kMaxQuadParts; ++q) {
-      asm volatile("" : "+v"(v[i][q]));  // ordered after the caller's wait
-      if (p0 + q < p1) {
-        a += v[i][q].x;
-        b += v[i][q].y;
-      }
+    for (int q = 0; q < QP; ++q) asm volatile("" : "+v"(v[i][q]));  // ordered after the caller's wait
+    auto add = [&]() {
+#pragma unroll
+      for (int q = 0; q < QP; ++q)
+        if (r.p0 + q < r.p1) {
+          a[i] += v[i][q].x;
+          b[i] += v[i][q].y;
+        }
+    };
+    a[i] = b[i] = 0.f;
+    add();
+    a[i] = even_quarter(a[i]);  // a back quarter goes on where its front quarter stopped
+    b[i] = even_quarter(b[i]);
+    add();
+  }
+  if (np > 4 * QP) {  // wide rows: the rest of the back quarters with ordinary loads, kBatch of a row in flight
+    constexpr int kBatch = MI > 2 ? 2 : 4;
+    const int rest = ((np + 1) >> 1) - 2 * QP;
+    for (int k = 0; k < rest; k += kBatch) {
+      const int p = r.p0 + QP + k;
+      float2 u[MI][kBatch];
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) u[i][q] = part[(size_t)min(m_base + i * 16 + l16, M - 1) * np + min(p + q, np - 1)];
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q)
+          if (p + q < r.p1) {
+            a[i] += u[i][q].x;
+            b[i] += u[i][q].y;
+          }
     }
-    if (per > kMaxQuadParts) {  // wide rows: the rest with ordinary loads
-      const float2* row = part + (size_t)min(m_base + i * 16 + l16, M - 1) * np;
-      for (int p = p0 + kMaxQuadParts; p < p1; ++p) {
-        const float2 u = row[p];
-        a += u.x;
-        b += u.y;
-      }
-    }
-    a += __shfl_xor(a, 16, kWave);
-    b += __shfl_xor(b, 16, kWave);
-    a += __shfl_xor(a, 32, kWave);
-    b += __shfl_xor(b, 32, kWave);
-    mu[i] = a * inv_h;
-    rstd[i] = rsqrtf(fmaxf(b * inv_h - mu[i] * mu[i], 0.f) + eps);
+  }
+#pragma unroll
+  for (int i = 0; i < MI; ++i) {
+    mu[i] = sum_of_odd_quarters(a[i]) * inv_h;
+    rstd[i] = rsqrtf(fmaxf(sum_of_odd_quarters(b[i]) * inv_h - mu[i] * mu[i], 0.f) + eps);
   }
 }
 
@@ -436,14 +479,15 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(
   ResidTile<MI, NI> rres;  // dead (and removed by the compiler) in the other epilogue forms
   EpiVecs<NI> vec;
   __shared__ float2 red[EPI == EPI_RESID ? WGN * BM : 1];
-  float2 psum[MI][kMaxQuadParts];
+  constexpr int QP = row_sum_requests(BM, BN);
+  float2 psum[MI][QP];
   constexpr bool kStats = EPI == EPI_FOLD || EPI == EPI_RESID;
   // without statistics (a plain residual) the requests still issue, at a harmless valid address, so that
   // the number of memory instructions in flight is a compile-time constant
   const float2* const stat_src = EPI == EPI_FOLD ? ep.ln_part : (EPI == EPI_RESID ? ep.resid_part : nullptr);
   const float2* const stat_part = stat_src ? stat_src : reinterpret_cast<const float2*>(W);
   const int stat_np = stat_src ? (EPI == EPI_FOLD ? ep.ln_np : ep.resid_np) : 0;
-  constexpr int kLateLoads = (EPI == EPI_RESID ? ResidTile<MI, NI>::P : 0) + (kStats ? MI * kMaxQuadParts : 0);
+  constexpr int kLateLoads = (EPI == EPI_RESID ? ResidTile<MI, NI>::P : 0) + (kStats ? MI * QP : 0);
   static_assert((NS - 2) * TOT + kLateLoads < 64, "vmcnt range");
 
   // DMA source pointers.  Instruction q of this wave fills LDS rows [r0, r0+8) of the slab; lane i
@@ -593,7 +637,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(
   for (int i = 0; i < MI; ++i) { mu[i] = 0.f; rstd[i] = 1.f; }
   auto late_requests = [&]() {
     if constexpr (EPI == EPI_RESID) request_resid<MI, NI>(ep.resid, rrow, N, n0 + wn * WN, lane, rres);
-    if constexpr (kStats) request_row_sums<MI>(stat_part, stat_np, M, m0 + wm * WM, l16, quad, psum);
+    if constexpr (kStats) request_row_sums(stat_part, stat_np, M, m0 + wm * WM, l16, quad, psum);
   };
   auto late_collect = [&]() {
     if constexpr (kLateLoads > 0) {
@@ -602,7 +646,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(
 #pragma unroll
         for (int p = 0; p < ResidTile<MI, NI>::P; ++p) asm volatile("" : "+v"(rres.r[p]));  // ordered after the wait
       }
-      finish_row_sums<MI>(stat_part, stat_np, M, m0 + wm * WM, l16, quad, ep.inv_h, ep.eps, psum, mu, rstd);
+      finish_row_sums(stat_part, stat_np, M, m0 + wm * WM, l16, quad, ep.inv_h, ep.eps, psum, mu, rstd);
     }
   };
   for (int r = 0; r + 1 < rounds; ++r) {  // steady state: compile-time stages
@@ -709,10 +753,10 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_simple_kernel(const half_t*
   const float2* const stat_part = EPI == EPI_FOLD ? ep.ln_part : (EPI == EPI_RESID ? ep.resid_part : nullptr);
   const int stat_np = EPI == EPI_FOLD ? ep.ln_np : ep.resid_np;
   if (EPI != EPI_PLAIN && stat_part) {
-    float2 psum[2][kMaxQuadParts];
-    request_row_sums<2>(stat_part, stat_np, M, m0 + wm * 32, l16, quad, psum);
+    float2 psum[2][row_sum_requests(BM, BN)];
+    request_row_sums(stat_part, stat_np, M, m0 + wm * 32, l16, quad, psum);
     wait_vmcnt<0>();
-    finish_row_sums<2>(stat_part, stat_np, M, m0 + wm * 32, l16, quad, ep.inv_h, ep.eps, psum, mu, rstd);
+    finish_row_sums(stat_part, stat_np, M, m0 + wm * 32, l16, quad, ep.inv_h, ep.eps, psum, mu, rstd);
   }
   if constexpr (EPI == EPI_RESID) load_resid<2, 2>(ep.resid, ep.resid_rows, M, N, m0 + wm * 32, n0 + wn * 32, lane, rres);
   EpiVecs<2> vec;
@@ -888,7 +932,24 @@ static float gemm_shape_us(const GemmTile& t, int M, int N, int K, bt_act act) {
   return t.start_us + rounds * (slabs * t.slab0_us + epi) + slabs * t.slab_u_us * (float)tiles / kComputeUnits + full_us;
 }
 
+// The residual form: narrow shapes, a round of tiles takes slabs slab + epi.  Its epilogue outlasts the plain one, so it
+// has costs of its own; a product near the border of two shapes (1 376 to 1 760 tokens of width 768) taken by the costs above
+// made a folded layer 3 % slower.  The choice also fixes how a row's sums are grouped.
+static int gemm_resid_tile_choice(int M, int N, int K) {
+  static const struct { int tile; float slab_us, epi_us; } kCosts[] = {{6, 0.298f, 0.78f}, {7, 0.287f, 0.84f}, {8, 0.183f, 0.4f}};
+  int best = -1;
+  float best_us = 0.f;
+  for (const auto& c : kCosts) {
+    const GemmTile& t = kGemmTiles[c.tile];
+    const long long tiles = (long long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+    const float us = (float)((tiles + kComputeUnits - 1) / kComputeUnits) * ((float)(K / 64) * c.slab_us + c.epi_us);
+    if (best < 0 || us < best_us) { best = c.tile; best_us = us; }
+  }
+  return best;
+}
+
 static int gemm_tile_choice(int M, int N, int K, bt_act act, int epi, bool wide_ok, float* us_out = nullptr) {
+  if (epi == EPI_RESID) return gemm_resid_tile_choice(M, N, K);
   int best = -1;
   float best_us = 0.f;
   for (int c = 0; c < kGemmShapes; ++c) {

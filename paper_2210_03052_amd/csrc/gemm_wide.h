@@ -266,10 +266,10 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(
       }
     }
     if constexpr (EPI == EPI_FOLD) {
-      float2 psum[MI][kMaxQuadParts];
-      request_row_sums<MI>(ep.ln_part, ep.ln_np, M, m_base, l16, quad, psum);
+      float2 psum[MI][row_sum_requests(BM, BN)];
+      request_row_sums(ep.ln_part, ep.ln_np, M, m_base, l16, quad, psum);
       wait_vmcnt<0>();
-      finish_row_sums<MI>(ep.ln_part, ep.ln_np, M, m_base, l16, quad, ep.inv_h, ep.eps, psum, mu, rstd);
+      finish_row_sums(ep.ln_part, ep.ln_np, M, m_base, l16, quad, ep.inv_h, ep.eps, psum, mu, rstd);
     }
     half4_t out[MI][NI];
     auto arithmetic = [&](int i) {

@@ -159,7 +159,7 @@ __global__ __launch_bounds__(256) void bias_residual_ln_kernel(
 // Normalisation of a row whose scaled values u = gamma (.) z and partial sums (sum z, sum z^2) were
 // produced by a GEMM epilogue (EPI_RESID): y = rstd (u - mu gamma) + beta.  Used once, at the end of a
 // stack whose inner LayerNorms are folded into the GEMMs that follow them.  The partial sums are added
-// in the order the GEMMs add them (four quarters in index order, then the quarters in pairs), so the statistics
+// in the order the GEMMs add them (two halves in index order, then the two halves), so the statistics
 // are the ones the folded GEMMs used.
 __global__ __launch_bounds__(256) void ln_finalize_kernel(const half_t* __restrict__ u, const float2* __restrict__ part,
                                                           int np, const half_t* __restrict__ gamma,
@@ -187,24 +187,18 @@ __global__ __launch_bounds__(256) void ln_finalize_kernel(const half_t* __restri
     obase = (size_t)row * H;
   }
   const float inv_h = 1.0f / (float)H;
-  const int per = (np + 3) >> 2;
-  float a[4] = {0.f, 0.f, 0.f, 0.f}, b[4] = {0.f, 0.f, 0.f, 0.f};
+  const int half_np = (np + 1) >> 1;
+  float a0 = 0.f, b0 = 0.f, a1 = 0.f, b1 = 0.f;
   for (int q0 = 0; q0 < np; q0 += kWave) {  // lane q holds partial q0+q; added in index order via shuffles
     const float2 v = q0 + lane < np ? part[(size_t)row * np + q0 + lane] : make_float2(0.f, 0.f);
     const int n_here = min(np - q0, kWave);
     for (int q = 0; q < n_here; ++q) {
       const float x = __shfl(v.x, q, kWave), z = __shfl(v.y, q, kWave);
-      const int quarter = (q0 + q) / per;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        a[k] += quarter == k ? x : 0.f;
-        b[k] += quarter == k ? z : 0.f;
-      }
+      if (q0 + q < half_np) { a0 += x; b0 += z; } else { a1 += x; b1 += z; }
     }
   }
-  const float sum_z = (a[0] + a[1]) + (a[2] + a[3]), sum_z2 = (b[0] + b[1]) + (b[2] + b[3]);
-  const float mu = sum_z * inv_h;
-  const float rstd = rsqrtf(fmaxf(sum_z2 * inv_h - mu * mu, 0.f) + eps);
+  const float mu = (a0 + a1) * inv_h;
+  const float rstd = rsqrtf(fmaxf((b0 + b1) * inv_h - mu * mu, 0.f) + eps);
   const size_t base = (size_t)row * H;
   for (int c = lane; c < (H >> 3); c += kWave) {
     const half8_t u8 = *reinterpret_cast<const half8_t*>(u + base + c * 8);

@@ -877,3 +877,38 @@ def test_folded_stack_rows_with_a_large_common_offset(bt):
     ref = _oracle_each(wl, L, x, oracle_layers(wl, 2, True), [2])[2]
     assert np.abs(plain - ref).max() <= 2 * TOL_LAYER
     assert np.abs(got - ref).max() <= 2 * TOL_LAYER
+
+
+FOLD_BITS = [(768, 3072, 700, 1), (768, 3072, 1500, 2), (768, 3072, 2400, 1), (512, 2048, 3500, 2), (832, 3336, 1300, 1),
+             (1152, 4608, 900, 1)]
+
+
+def folded_stack_bits(bt, H, F, T, gelu_kind):
+    """SHA-256 of a two-layer folded stack's output (gelu_kind 1: erf as 0, 2: tanh as 1 of the layer descriptor)."""
+    import hashlib
+    rng = np.random.default_rng([H, F, T])
+    draw = lambda *s, mean=0.0, std=1.0: (mean + std * rng.standard_normal(s, dtype=np.float32)).astype(np.float16)
+    layers = [bt.Layer({"w_qkv": draw(3 * H, H, std=0.02), "b_qkv": draw(3 * H, std=0.1), "w_o": draw(H, H, std=0.02),
+                        "b_o": draw(H, std=0.1), "ln0_g": draw(H, mean=1.0, std=0.1), "ln0_b": draw(H, std=0.1),
+                        "w_1": draw(F, H, std=0.02), "b_1": draw(F, std=0.1), "w_2": draw(H, F, std=0.02),
+                        "b_2": draw(H, std=0.1), "ln1_g": draw(H, mean=1.0, std=0.1), "ln1_b": draw(H, std=0.1),
+                        "heads": H // 64}, gelu_kind=gelu_kind - 1) for _ in range(2)]
+    S = 128
+    L = np.full(-(-T // S), S, np.int32)
+    L[0] -= int(L.sum()) - T
+    cu = dev(np.concatenate([[0], np.cumsum(L)]).astype(np.int32))
+    x = dev(draw(T, H))
+    y, plain = bt.encoder_fwd(layers, x, cu, S, fold=bt.encoder_prepare(layers)), bt.encoder_fwd(layers, x, cu, S)
+    assert not np.array_equal(host(y), host(plain)), "not the folded pipeline"
+    assert np.abs(host(y).astype(np.float32) - host(plain)).max() <= TOL_12
+    return hashlib.sha256(host(y).tobytes()).hexdigest()
+
+
+@pytest.mark.parametrize("H,F,T,gelu_kind", FOLD_BITS)
+def test_folded_stack_keeps_its_bits(bt, H, F, T, gelu_kind):
+    """A row's sums are added in a fixed order (halves of the column tiles in index order), in every kernel that reads
+    them: the outputs have the bits on file, for 6 to 18 partial sums a row and each shape of the residual form."""
+    import os
+    path = os.path.join(os.path.dirname(__file__), "golden", "folded_stack_bits.txt")
+    want = {tuple(map(int, f[:4])): f[4] for f in (ln.split() for ln in open(path)) if len(f) == 5 and f[0].isdigit()}
+    assert folded_stack_bits(bt, H, F, T, gelu_kind) == want[H, F, T, gelu_kind]
