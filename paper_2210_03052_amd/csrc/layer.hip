@@ -226,12 +226,15 @@ static bt_status stack_fwd_folded(const bt_layer* layers, int n_layers, const fl
   return ln_finalize_dispatch(in, w.part2, np2, last->ln1_g, last->ln1_b, eps, T, H, y, st, io.out_idx, io.out_rows);
 }
 
-// Whether the folded pipeline is the faster one for T tokens (hidden width H, FFN width F).  Its residual
-// epilogue exists for the small tile shapes only (64 x 128 for the H-wide products); as long as those tiles fit
-// one round of the 256 compute units the two launches saved per layer win, beyond that the small tiles run in
-// several rounds and the plain 7-launch layer with its larger tiles is faster (measured: -4 % from 1 280 to
-// 2 560 tokens of width 768, -3 % at 2 048 tokens of width 1024; +7 ... +18 % beyond 5 400 tokens).  With so few tokens that the plain layer splits K of its
-// H-wide products, the plain layer wins again (the folded epilogue has no split-K form: +1.5 % at 186 tokens).
+// Whether fold vectors select the folded pipeline for T tokens (hidden width H, FFN width F): its residual epilogue exists for
+// the small tile shapes only (64 x 128 for the H-wide products), so not beyond one round of those on the 256 compute units,
+// and it has no split-K form, so not where the plain layer splits K of its H-wide products.
+// Six layers, folded against plain, in us on one card:
+//   width 768:  650 tokens 258 / 247,  900: 272 / 257,  1 280: 288 / 286,  1 500: 335 / 331,  2 308: 405 / 416,  2 560: 429 / 422
+//   width 1024: 600 tokens 321 / 283,  1 200: 400 / 393,  1 800: 470 / 461,  2 048: 489 / 485
+//   width 512:  1 040 tokens 220 / 212,  1 500: 234 / 230,  3 400: 326 / 326,  3 700: 342 / 358
+// The plain layer has caught up since the limits were drawn (its wide products were the slower ones then); folding leads by 1 to
+// 4 % where its tiles nearly fill the round and trails below.  The limits stay: the choice decides the results' last digits.
 static bool folded_pays(int T, int H, int F) {
   if ((long long)((T + 63) / 64) * ((H + 127) / 128) > 256) return false;
   return gemm_splitk_choice(T, H, F) == 1 && gemm_splitk_choice(T, H, H) == 1;
