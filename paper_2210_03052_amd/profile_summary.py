@@ -43,7 +43,7 @@ def template_args(name: str):
     return []
 
 
-STREAMING_GRID = 2_000_000      # threads: bench.py's 262 144-token pack launches 4 M of them, the workloads < 0.3 M
+STREAMING_GRID = 20_000_000     # threads: bench.py's 262 144-token pack launches 25 M of them, the workloads < 2 M
 
 
 def role_of(name: str, grid: int = 0):

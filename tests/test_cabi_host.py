@@ -57,6 +57,7 @@ def test_argument_errors_before_launch(lib):
     assert lib.bt_pack(one, one, -1, 8, one, None) == 1
     assert lib.bt_pack(one, one, 0, 8, one, None) == 0          # T == 0: no-op
     assert lib.bt_pack(odd, one, 4, 8, one, None) == 1          # misaligned
+    assert lib.bt_pack(one, one, 2**31 - 1, 1 << 20, one, None) == 2  # more chunks than a grid holds
     assert lib.bt_unpack(one, one, 100, 2, 8, 8, one, None) == 1  # T > B*S
     assert lib.bt_unpack(one, one, 0, 0, 8, 8, one, None) == 0
     # mha
