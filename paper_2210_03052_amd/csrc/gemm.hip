@@ -2,7 +2,8 @@
 // A [M,K] and W [N,K] are both K-contiguous, which is exactly the operand order
 // the gfx950 MFMA wants: every lane feeds 8 consecutive K values of one row.
 //
-// Narrow tiles (K % 64 == 0; 128 x 64 and smaller, and the forms that only they have): WGM x WGN wavefronts, block tile BM x BN x 64, wave tile
+// gemm_pipe_kernel (K % 64 == 0; the narrow tiles, 128 x 64 and smaller, the residual form, and larger tiles where the wide kernel
+// cannot go): WGM x WGN wavefronts, block tile BM x BN x 64, wave tile
 // (BM/WGM) x (BN/WGN) of 16x16x32 fp16 MFMA blocks with fp32 accumulators.  That block shape, not 32x32x16: with
 // every matrix core busy on ordinary data the chip runs at its power limit, and the shape decides how much
 // arithmetic the limit buys -- a register-only loop on normally distributed operands sustains 1 930 TFLOP/s with
@@ -553,7 +554,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(
   // These loads sit between the DMA of the first NS-1 slabs and of the later ones in the in-order queue the
   // hand-written waits count: a wait for slab k then also waits for as many of the younger entries as there
   // are loads here -- more than needed, never less, and only for the first slabs.
-  if constexpr (EPI == EPI_PLAIN) load_epi_vecs<NI, EPI>(ep, bias, N, n0 + wn * WN, lane, vec);
+  constexpr bool kEarlyBias = EPI == EPI_PLAIN && MI * NI < 16;  // the 256-row tile has no registers left to park it in
+  if constexpr (kEarlyBias) load_epi_vecs<NI, EPI>(ep, bias, N, n0 + wn * WN, lane, vec);
 
   // operand read offsets (halves): row*BK + ((4ks+quad) ^ swz(row))*8 ; swz depends on l16 only
   const int swz = (l16 >> 1) & (CPR - 1);
@@ -678,7 +680,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(
 #pragma unroll
     for (int i = 0; i < MI; ++i) { mu[i] = 0.f; rstd[i] = 1.f; }
   }
-  if constexpr (EPI == EPI_FOLD || EPI == EPI_RESID) load_epi_vecs<NI, EPI>(ep, bias, N, n0 + wn * WN, lane, vec);
+  if constexpr (!kEarlyBias && EPI != EPI_PARTIAL) load_epi_vecs<NI, EPI>(ep, bias, N, n0 + wn * WN, lane, vec);
   if constexpr (EPI == EPI_PARTIAL) {
     __builtin_amdgcn_s_barrier();  // every wave is done reading the last slab: LDS becomes staging space
     store_partial<MI, NI>(acc, ep.partial + (size_t)split * M * N, M, N, m0 + wm * WM, n0 + wn * WN, lane,
@@ -846,11 +848,16 @@ static bt_status launch_pipe(const half_t* A, const half_t* W, half_t* C, int M,
     }                                                                           \
   } while (0)
   if (epi == EPI_RESID) {
-    BT_LAUNCH(BT_ACT_NONE, EPI_RESID);
+    if constexpr (BM * BN <= 128 * 64) BT_LAUNCH(BT_ACT_NONE, EPI_RESID);  // narrow shapes, see gemm_resid_tile_choice
+    else return BT_ERR_UNSUPPORTED;
   } else if (epi == EPI_FOLD) {
-    if (act == BT_ACT_NONE) BT_LAUNCH(BT_ACT_NONE, EPI_FOLD);
-    else if (act == BT_ACT_GELU_ERF) BT_LAUNCH(BT_ACT_GELU_ERF, EPI_FOLD);
-    else BT_LAUNCH(BT_ACT_GELU_TANH, EPI_FOLD);
+    if constexpr (BM <= 128) {  // see gemm_shape_ok
+      if (act == BT_ACT_NONE) BT_LAUNCH(BT_ACT_NONE, EPI_FOLD);
+      else if (act == BT_ACT_GELU_ERF) BT_LAUNCH(BT_ACT_GELU_ERF, EPI_FOLD);
+      else BT_LAUNCH(BT_ACT_GELU_TANH, EPI_FOLD);
+    } else {
+      return BT_ERR_UNSUPPORTED;
+    }
   } else {
     if (act == BT_ACT_NONE) BT_LAUNCH(BT_ACT_NONE, EPI_PLAIN);
     else if (act == BT_ACT_GELU_ERF) BT_LAUNCH(BT_ACT_GELU_ERF, EPI_PLAIN);
@@ -891,14 +898,23 @@ static bt_status launch_simple(const half_t* A, const half_t* W, half_t* C, int 
 // slab0 is what a 64-deep slab costs a compute unit that has the chip to itself, slab_u what the other 255 add when all
 // of them fetch operands at once; act_us (one activation per output, vector work that nothing overlaps) adds to epi.
 // Its choice is within 1.1 % of the best shape on average over the measured points.  K % 64 == 0.
-struct GemmTile { int bm, bn; float start_us, slab0_us, slab_u_us, epi_us; bool wide; };
-constexpr int kGemmShapes = 9;
-static const GemmTile kGemmTiles[kGemmShapes] = {
-    {256, 128, 2.1f, 0.459f, 0.318f, 2.76f, true}, {224, 128, 1.6f, 0.402f, 0.242f, 3.2f, true},
-    {192, 128, 1.85f, 0.359f, 0.212f, 2.6f, true}, {160, 128, 1.7f, 0.319f, 0.177f, 2.29f, true},
-    {128, 128, 2.2f, 0.289f, 0.136f, 1.55f, true}, {96, 128, 2.2f, 0.285f, 0.078f, 1.08f, true},
-    {128, 64, 1.5f, 0.223f, 0.068f, 1.6f, false},  {64, 128, 1.55f, 0.224f, 0.059f, 1.61f, false},
-    {64, 64, 2.4f, 0.139f, 0.043f, 0.35f, false}};
+//
+// Where the wide kernel cannot take a product (fewer than four slabs, operands of 4 GiB and more) three eight-wavefront tiles
+// of gemm_pipe_kernel with three stages stand in for it.  Fitted at K = 128 and 192, 500 to 65 536 rows, 384 to 2 048
+// columns: the best shape at 36 of 44 points, within 3 % at the others.  65 536 x 1024 x 192 takes 44.8 us with them, 69.6 with
+// the narrow tiles; 700 000 x 768 x 3072 5.16 ms, 6.82 ms; 16 384 x 512 x 128 6.4 us, 8.7 us with the register-staged
+// kernel, which has the products that are shorter than the narrow tiles' pipeline.
+enum TileKind { kWide, kNarrow, kEightWaves, kRegisterStaged };
+struct GemmTile { int bm, bn; float start_us, slab0_us, slab_u_us, epi_us; TileKind kind; };
+static const GemmTile kGemmTiles[] = {
+    {256, 128, 2.1f, 0.459f, 0.318f, 2.76f, kWide},   {224, 128, 1.6f, 0.402f, 0.242f, 3.2f, kWide},
+    {192, 128, 1.85f, 0.359f, 0.212f, 2.6f, kWide},   {160, 128, 1.7f, 0.319f, 0.177f, 2.29f, kWide},
+    {128, 128, 2.2f, 0.289f, 0.136f, 1.55f, kWide},   {96, 128, 2.2f, 0.285f, 0.078f, 1.08f, kWide},
+    {128, 64, 1.5f, 0.223f, 0.068f, 1.6f, kNarrow},   {64, 128, 1.55f, 0.224f, 0.059f, 1.61f, kNarrow},
+    {64, 64, 2.4f, 0.139f, 0.043f, 0.35f, kNarrow},   {256, 128, 2.2f, 0.53f, 0.10f, 3.45f, kEightWaves},
+    {192, 128, 1.6f, 0.50f, 0.06f, 2.7f, kEightWaves}, {128, 128, 1.5f, 0.28f, 0.10f, 2.5f, kEightWaves},
+    {64, 64, 2.7f, 0.19f, 0.f, 0.35f, kRegisterStaged}};
+constexpr int kGemmShapes = sizeof(kGemmTiles) / sizeof(kGemmTiles[0]);
 constexpr float kActUs = 0.75e-4f;  // per output of a tile
 
 // gemm_wide_kernel: at least four slabs, 32-bit byte offsets into both operands.  Its residual epilogue does not exist: the
@@ -912,7 +928,9 @@ static bool gemm_wide_ok(long long a_rows, int N, int K, int epi) {
 // least three quarters of the chip: there they measured 3 to 4 % of a layer, and nothing elsewhere.  FOLD
 // exists for the other three wide shapes.
 static bool gemm_shape_ok(const GemmTile& t, int M, int N, int K, bt_act act, int epi, bool wide_ok) {
-  if (!t.wide) return true;
+  if (t.kind == kNarrow) return K / 64 >= 3;
+  if (t.kind == kRegisterStaged) return K / 64 < 3;
+  if (t.kind == kEightWaves) return !wide_ok && K / 64 >= 2 && (epi == EPI_PLAIN || t.bm == 128);  // FOLD would spill
   if (!wide_ok) return false;
   if (epi != EPI_PLAIN && t.bm != 256 && t.bm != 192 && t.bm != 128) return false;
   if (((t.bm == 160 || t.bm == 96) && act != BT_ACT_NONE && K < 1024) || (t.bm == 96 && K >= 2 * N)) {
@@ -928,7 +946,7 @@ static float gemm_shape_us(const GemmTile& t, int M, int N, int K, bt_act act) {
   const long long tiles = (long long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
   const float rounds = (float)((tiles + kComputeUnits - 1) / kComputeUnits), slabs = (float)(K / 64);
   const float epi = t.epi_us + (act != BT_ACT_NONE ? kActUs * t.bm * t.bn : 0.f);
-  const float full_us = t.wide && act == BT_ACT_NONE && tiles > 240 && tiles <= kComputeUnits ? 1.5f : 0.f;
+  const float full_us = t.kind == kWide && act == BT_ACT_NONE && tiles > 240 && tiles <= kComputeUnits ? 1.5f : 0.f;
   return t.start_us + rounds * (slabs * t.slab0_us + epi) + slabs * t.slab_u_us * (float)tiles / kComputeUnits + full_us;
 }
 
@@ -1003,7 +1021,11 @@ static bt_status gemm_launch_tile(int tile, const half_t* a, const half_t* w, ha
     case 5: return BT_WIDE(96, 128);
     case 6: return BT_PIPE(128, 64, 4, 2, 4);
     case 7: return BT_PIPE(64, 128, 2, 4, 4);
-    default: return BT_PIPE(64, 64, 2, 2, 4);
+    case 8: return BT_PIPE(64, 64, 2, 2, 4);
+    case 9: return BT_PIPE(256, 128, 4, 2, 3);
+    case 10: return BT_PIPE(192, 128, 2, 4, 3);
+    case 11: return BT_PIPE(128, 128, 2, 4, 3);
+    default: return launch_simple(a, w, c, M, N, K, act, epi, ep, st, np_out);
   }
 #undef BT_PIPE
 #undef BT_WIDE
@@ -1126,10 +1148,9 @@ extern "C" bt_status bt_gemm_row_split(int M, int N, int K, bt_act act, int* row
 extern "C" bt_status bt_gemm_tile_shape(int M, int N, int K, bt_act act, int* bm, int* bn) {
   if (M < 0 || N < 1 || K < 1 || (N % 8) != 0 || (K % 8) != 0 || !bm || !bn) return BT_ERR_INVALID_ARG;
   if (act != BT_ACT_NONE && act != BT_ACT_GELU_ERF && act != BT_ACT_GELU_TANH) return BT_ERR_INVALID_ARG;
-  *bm = *bn = 64;  // the register-staged fallback kernel: K not a multiple of 64, or shorter than the pipeline
+  *bm = *bn = 64;  // the register-staged fallback kernel: K not a multiple of 64
   if ((K % 64) != 0) return BT_OK;
   const bt::GemmTile& t = bt::kGemmTiles[bt::gemm_tile_choice(M, N, K, act, bt::EPI_PLAIN, bt::gemm_wide_ok(M, N, K, bt::EPI_PLAIN))];
-  if (K / 64 < 3) return BT_OK;  // shorter than the four stages of the narrow shapes
   *bm = t.bm;
   *bn = t.bn;
   return BT_OK;

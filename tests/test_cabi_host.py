@@ -212,6 +212,12 @@ def test_gemm_tile_shape_query_is_host_only():
     assert bt.gemm_tile_shape(2308, 768, 3072) == (64, 128)
     assert bt.gemm_tile_shape(2699, 768, 3072) == (128, 128)
     assert bt.gemm_tile_shape(100, 768, 72) == (64, 64)
+    # where the wide tiles cannot go -- two or three slabs, operands of 4 GiB -- many rows still get large tiles
+    assert bt.gemm_tile_shape(65536, 1024, 192) == bt.gemm_tile_shape(16384, 512, 128) == (256, 128)
+    assert bt.gemm_tile_shape(9894, 512, 192) == bt.gemm_tile_shape(9894, 512, 128) == (192, 128)
+    assert bt.gemm_tile_shape(9894, 384, 192) == bt.gemm_tile_shape(9894, 384, 128) == (128, 128)
+    assert bt.gemm_tile_shape(2000000, 768, 3072) == (256, 128)
+    assert bt.gemm_tile_shape(500, 384, 128) == bt.gemm_tile_shape(65536, 1024, 64) == (64, 64)
     for bad in ((10, 7, 64), (10, 8, 60), (-1, 8, 64)):
         with pytest.raises(bt.BtError):
             bt.gemm_tile_shape(*bad)

@@ -245,6 +245,53 @@ def test_gemm_wide_tiles(bt, tile, M, N, K, act):
     assert np.abs(got - ref).max() <= 2e-3 * max(1.0, np.abs(ref).max())
 
 
+@pytest.mark.parametrize("tile,M,N,K,act", [
+    (256, 16370, 504, 128, 1), (256, 16370, 504, 192, 0), (192, 9893, 504, 128, 2), (192, 9893, 504, 192, 1),
+    (128, 9893, 376, 128, 0), (128, 9893, 376, 192, 2)])
+def test_gemm_large_tiles_of_short_reductions(bt, tile, M, N, K, act):
+    """Two and three slabs, fewer than the wide kernel takes: ragged rows and columns of each eight-wavefront tile."""
+    assert bt.gemm_tile_shape(M, N, K, act) == (tile, 128)
+    rng = np.random.default_rng(M + N + K)
+    a = rng.normal(0, 1, (M, K)).astype(np.float16)
+    w = rng.normal(0, 0.05, (N, K)).astype(np.float16)
+    b = rng.normal(0, 0.5, N).astype(np.float16)
+    ref = a.astype(np.float32) @ w.astype(np.float32).T + b.astype(np.float32)
+    if act:
+        ref = (O.gelu if act == 1 else O.gelu_tanh)(ref.astype(np.float64))
+    got = host(bt.gemm_bias_act(dev(a), dev(w), dev(b), act)).astype(np.float64)
+    assert np.abs(got - ref).max() <= 2e-3 * max(1.0, np.abs(ref).max())
+
+
+def test_gemm_operand_past_4_gib(bt):
+    """Byte offsets into A that need more than 32 bits: the last rows against the same rows on their own."""
+    import torch
+    M, N, K = 700001, 136, 3072
+    assert 2 * M * K > 2 ** 32
+    g = torch.Generator(device="cuda:0").manual_seed(3)
+    a = torch.empty(M, K, dtype=torch.float16, device="cuda:0").normal_(generator=g)
+    w = torch.empty(N, K, dtype=torch.float16, device="cuda:0").normal_(0, 0.02, generator=g)
+    got = bt.gemm_bias_act(a, w)
+    for m in (0, 349000, M - 100):  # tile shapes agree to the bit: the same sums in the same order
+        assert torch.equal(got[m:m + 100], bt.gemm_bias_act(a[m:m + 100].clone(), w))
+
+
+def test_folded_stack_with_a_reduction_of_three_slabs(bt):
+    """Width 192: the folded products QKV and FFN-up run on eight-wavefront tiles.  Against the plain pipeline."""
+    rng = np.random.default_rng(192)
+    H, F, S, B = 192, 768, 100, 50
+    draw = lambda *s, mean=0.0, std=1.0: (mean + std * rng.standard_normal(s, dtype=np.float32)).astype(np.float16)
+    layers = [bt.Layer({"w_qkv": draw(3 * H, H, std=0.05), "b_qkv": draw(3 * H, std=0.1), "w_o": draw(H, H, std=0.05),
+                        "b_o": draw(H, std=0.1), "ln0_g": draw(H, mean=1.0, std=0.1), "ln0_b": draw(H, std=0.1),
+                        "w_1": draw(F, H, std=0.05), "b_1": draw(F, std=0.1), "w_2": draw(H, F, std=0.05),
+                        "b_2": draw(H, std=0.1), "ln1_g": draw(H, mean=1.0, std=0.1), "ln1_b": draw(H, std=0.1),
+                        "heads": H // 64}) for _ in range(2)]
+    x, cu = dev(draw(B * S, H)), dev(np.arange(B + 1, dtype=np.int32) * S)
+    got = host(bt.encoder_fwd(layers, x, cu, S, fold=bt.encoder_prepare(layers))).astype(np.float64)
+    plain = host(bt.encoder_fwd(layers, x, cu, S)).astype(np.float64)
+    assert not np.array_equal(got, plain)
+    assert np.abs(got - plain).max() <= 2 * TOL_LAYER
+
+
 @pytest.mark.parametrize("tile,M,N,K", [(96, 716, 2976, 256), (128, 3678, 3256, 256), (256, 4452, 3304, 256)])
 def test_gemm_wide_tiles_bias_alignment(bt, tile, M, N, K):
     """A bias that starts 8 bytes past a 16-byte boundary, the least alignment that is accepted: same bits."""
