@@ -234,6 +234,10 @@ def test_gemm_row_split_query_is_host_only():
     assert r == 2560                                                # 10 tile rows x 24 = 240 tiles, one round
     r = bt.gemm_row_split(6400, 4096, 1024, bt.ACT_GELU_ERF)
     assert 0 < r < 6400 and r % 64 == 0
+    # short reductions: only where the model promises more than its own error
+    for shape in ((14816, 2048, 512), (13056, 2048, 512), (10288, 2560, 640)):
+        assert bt.gemm_row_split(*shape, bt.ACT_GELU_ERF) == 0
+    assert bt.gemm_row_split(4160, 2048, 512, bt.ACT_GELU_ERF) == 4096
     assert bt.gemm_row_split(100, 768, 72) == 0                     # fallback kernel: never split
     with pytest.raises(bt.BtError):
         bt.gemm_row_split(10, 7, 64)
