@@ -923,19 +923,22 @@ static bool gemm_wide_ok(long long a_rows, int N, int K, int epi) {
   return K >= 256 && epi != EPI_RESID && (a_rows + 256) * K * 2 < (1LL << 32) && (N + 128LL) * K * 2 < (1LL << 32);
 }
 
-// The shapes whose row count is not a multiple of 64 smooth the staircase of the others.  160 and 96 rows for short
-// reductions with an activation, and 96 rows for deep reductions, are taken only where their last round of tiles fills at
-// least three quarters of the chip: there they measured 3 to 4 % of a layer, and nothing elsewhere.  FOLD
-// exists for the other three wide shapes.
+// The shapes whose row count is not a multiple of 64 smooth the staircase of the others.  160 and 96 rows for short reductions
+// with an activation, and 96 rows for deep reductions, are taken only where their last round of tiles fills at least three
+// quarters of the chip: there they measured 3 to 4 % of a layer, and nothing elsewhere (limits read off widths 768 and 1024).  One
+// round of 96-row tiles with an activation is the exception: 700 x 3072 x 768 with GELU 7.7 us, 8.9 with 128 rows (six
+// layers 247.9 -> 240.9 us), 1 040 x 2048 x 512 6.4 us, 7.5 (213.2 -> 208.8 us); 160 rows in one round moved the layers by
+// -1.5 to +2 %.  FOLD exists for the other three wide shapes.
 static bool gemm_shape_ok(const GemmTile& t, int M, int N, int K, bt_act act, int epi, bool wide_ok) {
   if (t.kind == kNarrow) return K / 64 >= 3;
   if (t.kind == kRegisterStaged) return K / 64 < 3;
   if (t.kind == kEightWaves) return !wide_ok && K / 64 >= 2 && (epi == EPI_PLAIN || t.bm == 128);  // FOLD would spill
   if (!wide_ok) return false;
   if (epi != EPI_PLAIN && t.bm != 256 && t.bm != 192 && t.bm != 128) return false;
-  if (((t.bm == 160 || t.bm == 96) && act != BT_ACT_NONE && K < 1024) || (t.bm == 96 && K >= 2 * N)) {
+  const bool short_act = (t.bm == 160 || t.bm == 96) && act != BT_ACT_NONE && K < 1024, deep = t.bm == 96 && K >= 2 * N;
+  if (short_act || deep) {
     const long long tiles = (long long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
-    return (tiles - 1) % kComputeUnits >= kComputeUnits * 3 / 4;
+    return (t.bm == 96 && !deep && tiles <= kComputeUnits) || (tiles - 1) % kComputeUnits >= kComputeUnits * 3 / 4;
   }
   return true;
 }

@@ -212,6 +212,8 @@ def test_gemm_tile_shape_query_is_host_only():
     assert bt.gemm_tile_shape(2308, 768, 3072) == (64, 128)
     assert bt.gemm_tile_shape(2699, 768, 3072) == (128, 128)
     assert bt.gemm_tile_shape(100, 768, 72) == (64, 64)
+    # one round of 96-row tiles instead of a third fewer 128-row tiles
+    assert bt.gemm_tile_shape(700, 3072, 768, bt.ACT_GELU_ERF) == bt.gemm_tile_shape(1040, 2048, 512, bt.ACT_GELU_ERF) == (96, 128)
     # where the wide tiles cannot go -- two or three slabs, operands of 4 GiB -- many rows still get large tiles
     assert bt.gemm_tile_shape(65536, 1024, 192) == bt.gemm_tile_shape(16384, 512, 128) == (256, 128)
     assert bt.gemm_tile_shape(9894, 512, 192) == bt.gemm_tile_shape(9894, 512, 128) == (192, 128)
