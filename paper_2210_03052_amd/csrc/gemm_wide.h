@@ -23,7 +23,10 @@
 // first store; the first hand-over of the next tile then needs no wait, and at the second the stores have drained.
 
 // DMA with the address split into a wave-uniform base and a 32-bit byte offset per lane; the LDS target is lds + OFF.  Two
-// parts, so that the hand-scheduled loop can put an MFMA into the wait state that the hardware wants between them.
+// parts, so that the hand-scheduled loop can put an MFMA into the wait state that the hardware wants between them.  No operand
+// ties the parts together (m0 cannot be one); a test reads off the library's listing that every pair is whole.  As one
+// statement with a wait state of its own (dma16_sv) the loop is slower: 9 894 x 768 x 3072 40.5 -> 41.0 us, 9 894 x 2304 x 768
+// 38.2 -> 38.9, 4 648 x 4096 x 1024 46.5 -> 46.8.
 template <int OFF>
 __device__ __forceinline__ void dma_target(uint32_t lds) {
   asm volatile("s_add_u32 m0, %0, %1" ::"s"(lds), "n"(OFF) : "m0", "scc");

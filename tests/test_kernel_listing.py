@@ -1,5 +1,6 @@
 """What the hand-scheduled product kernels rely on and the compiler does not know, read off the listing of the built library:
-loads that are requested in one place and collected in another by a hand-written wait."""
+loads that are requested in one place and collected in another by a hand-written wait, and DMA requests whose LDS target
+travels in a register (m0) that an earlier statement wrote."""
 import os
 import re
 import struct
@@ -41,12 +42,14 @@ def kernels():
         with tempfile.NamedTemporaryFile(suffix=".co") as f:
             f.write(code)
             f.flush()
-            text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", "--no-leading-addr", f.name], check=True,
-                                  capture_output=True, text=True).stdout
+            text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", "--no-leading-addr", "--symbolize-operands", f.name],
+                                  check=True, capture_output=True, text=True).stdout
         body = None
         for line in text.splitlines():
             m = re.match(r"<(\S+)>:", line)
-            if m:
+            if m and re.fullmatch(r"L\d+", m.group(1)) and body is not None:
+                body.append(m.group(1) + ":")
+            elif m:
                 body = found.setdefault(m.group(1), [])
             elif body is not None and line.strip():
                 body.append(line.split("//")[0].strip())
@@ -61,6 +64,24 @@ def registers(text):
         lo = int(m.group(2) or m.group(4))
         out |= {m.group(1) + str(r) for r in range(lo, int(m.group(3) or lo) + 1)}
     return out
+
+
+def dma_faults(body):
+    """DMA requests into LDS without a target of their own: m0 has to be written for each of them, in the same run of
+    instructions, with another instruction in between (the wait state between the write and its use)."""
+    bad, written = [], None
+    for i, ins in enumerate(body):
+        if ins.endswith(":") or re.match(r"s_(c?branch|setpc|swappc|call|endpgm)", ins):
+            written = None
+        elif ins.startswith("global_load_lds"):
+            if written is None or i - written < 2:
+                bad.append((i, ins))
+            written = None
+        elif re.match(r"\S+ m0\b", ins):
+            if written is not None:
+                bad.append((written, body[written]))
+            written = i
+    return bad
 
 
 def in_flight(body):
@@ -100,3 +121,22 @@ def test_folded_wide_row_sums_are_requested_ahead_of_the_last_slabs(kernels):
         touched, mfmas = in_flight(kernels[n])
         assert not touched, (n, touched[:4])
         assert mfmas >= 2 * (rows // 32) * 4, (n, mfmas)
+
+
+def test_dma_faults_finds_lost_and_hasty_targets():
+    to, load, mfma = "s_add_u32 m0, s4, 0x400", "global_load_lds_dwordx4 v2, s[2:3]", "v_mfma_f32_16x16x32_f16 a[0:3], v[10:13], v[14:17], a[0:3]"
+    assert dma_faults([to, mfma, load, to, "s_nop 0", load]) == []
+    assert dma_faults([to, load])                                      # no wait state
+    assert dma_faults([to, mfma, load, mfma, load])                    # second request without a target
+    assert dma_faults([to, "s_mov_b32 m0, s9", mfma, load])            # something else wrote m0 in between
+    assert dma_faults([to, "L3:", mfma, load])                         # another way into the request
+
+
+def test_every_dma_request_has_its_own_target(kernels):
+    """The hand-scheduled loop writes m0 in one statement and requests in another, with an MFMA between them that the
+    compiler could move: in the built library every pair is whole."""
+    seen = 0
+    for name, body in kernels.items():
+        assert not dma_faults(body), (name, dma_faults(body)[:3])
+        seen += sum(ins.startswith("global_load_lds") for ins in body)
+    assert seen > 1000
