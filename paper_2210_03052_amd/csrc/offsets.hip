@@ -65,7 +65,7 @@ __global__ __launch_bounds__(kOffsetsThreads) void offsets_lengths_kernel(const 
   const int gwave = (int)blockIdx.x * kOffsetsWaves + (tid >> 6), nwave = (int)gridDim.x * kOffsetsWaves;
   if (tid == 0) { s_bad = 0; s_max = 0; }
   int running = 0;
-  for (int b0 = 0; b0 < B || b0 == 0; b0 += kOffsetsThreads) {
+  for (int b0 = 0;; b0 += kOffsetsThreads) {  // left behind the last round: b0 + 1024 may not fit an int
     const int b = b0 + tid;
     int len = b < B ? lengths[b] : 0;
     const bool bad = len < 0 || len > S;
@@ -84,7 +84,7 @@ __global__ __launch_bounds__(kOffsetsThreads) void offsets_lengths_kernel(const 
     __syncthreads();
     if (blockIdx.x == 0) {
       if (b < B) cu[b] = base;
-      if (b0 + kOffsetsThreads >= B && tid == 0) {
+      if (B - b0 <= kOffsetsThreads && tid == 0) {
         cu[B] = s_bad ? -1 : running;
         publish_total(running, s_max, s_bad != 0, host_total, max_out);
       }
@@ -94,6 +94,7 @@ __global__ __launch_bounds__(kOffsetsThreads) void offsets_lengths_kernel(const 
       const int at = s_base[i], n = s_len[i], first = (b0 + i) * S;
       for (int t = lane; t < n; t += kWave) token_idx[at + t] = first + t;
     }
+    if (B - b0 <= kOffsetsThreads) break;
   }
 }
 
@@ -175,14 +176,14 @@ __global__ __launch_bounds__(kOffsetsThreads) void offsets_mask_kernel(const int
     auto prefix = [&](int at) {  // ones before flat index f0 + at, at < entries
       return s_pre[at >> 6] + __popcll(s_word[at >> 6] & ((1ull << (at & 63)) - 1ull));
     };
-    for (int b = (f0 + S - 1) / S + tid; b < B && (long long)b * S < (long long)f0 + entries; b += kOffsetsThreads)
-      cu[b] = prefix(b * S - f0);  // sentences that start in this round
+    for (unsigned b = (f0 + S - 1) / S + tid; b < (unsigned)B && (long long)b * S < (long long)f0 + entries; b += kOffsetsThreads)
+      cu[b] = prefix((int)b * S - f0);  // sentences that start in this round
     if (entries == n - f0) {  // last round: the total is known
       if (tid == 0) cu[B] = running;
       if (max_out) {
         __syncthreads();
         int m = 0;
-        for (int b = tid; b < B; b += kOffsetsThreads) m = max(m, cu[b + 1] - cu[b]);  // written by this workgroup
+        for (unsigned b = tid; b < (unsigned)B; b += kOffsetsThreads) m = max(m, cu[b + 1] - cu[b]);  // written by this workgroup
         m = wave_max(m);
         if (lane == 0) atomicMax(&s_max, m);
         __syncthreads();

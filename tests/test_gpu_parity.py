@@ -155,6 +155,20 @@ def test_offsets_lengths_edge_cases(bt):
         bt.build_offsets(mask=dev(np.array([[1, 2, 0]], np.int32)))         # mask entry not 0/1
 
 
+def test_offsets_largest_number_of_sentences(bt):
+    """B*S may be as large as 2^31 - 2: the last rounds of 1 024 sentences end at the border of the index type."""
+    import torch
+    B = 2**31 - 2
+    if torch.cuda.mem_get_info()[0] < 14 * B:
+        pytest.skip("not enough device memory")
+    lengths = torch.zeros(B, dtype=torch.int32, device="cuda:0")
+    at = torch.tensor([0, 1023, 1024, 2**31 - 1025, 2**31 - 1024, B - 1], device="cuda:0")
+    lengths[at] = 1
+    cu, tok, T = bt.build_offsets(lengths=lengths, S=1)
+    assert T == 6 and torch.equal(tok.long(), at)
+    assert cu[at].tolist() == [0, 1, 2, 3, 4, 5] and cu[B].item() == 6
+
+
 @pytest.mark.parametrize("B,S,H", [(3, 5, 8), (4, 64, 768), (16, 256, 768), (7, 100, 1024), (2, 33, 72), (1, 1, 8), (90, 100, 520)])
 def test_pack_unpack_bit_exact(bt, B, S, H):
     import torch
