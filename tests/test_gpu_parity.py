@@ -198,9 +198,9 @@ def test_unpack_all_padding(bt):
 @pytest.mark.parametrize("M,N", [(100, 768), (2308, 768), (2308, 2304), (2308, 3072), (2699, 768)])
 def test_gemm_slab_schedule_all_residues(bt, M, N):
     """The K loop splits its K/64 slabs into leading slabs, whole rounds of the pipeline depth and a tail;
-    every residue of K/64 modulo the depth (3 or 4 stages, one tile shape per (M,N) here: 64x64, 64x128,
-    192x128, 256x128, 128x128) and the
-    K < depth fallback must give the same product.  Ragged M, and N not a multiple of the tile."""
+    every residue of K/64 modulo the depth, and reductions shorter than the pipeline, must give the same product.  Which
+    kernels run: the register-staged one (one slab), eight-wavefront tiles of three stages where there are many rows (two and three
+    slabs), the narrow tiles of four stages and, from four slabs on, the wide ones.  Ragged M, and N not a multiple of the tile."""
     rng = np.random.default_rng(M * 7 + N)
     Kmax = 13 * 64
     a = rng.normal(0, 1, (M, Kmax)).astype(np.float16)
@@ -239,7 +239,8 @@ def test_gemm_bias_act(bt, M, N, K, act, bias):
 
 
 @pytest.mark.parametrize("tile,M,N,K,act", [
-    (96, 716, 2976, 256, 0), (96, 4491, 2008, 256, 1), (96, 2202, 1240, 768, 0), (128, 3678, 3256, 256, 1),
+    (96, 716, 2976, 256, 0), (96, 4491, 2008, 256, 1), (96, 2202, 1240, 768, 0), (96, 3635, 2480, 512, 2),
+    (224, 4190, 3288, 768, 2), (256, 6031, 2312, 320, 1), (128, 3678, 3256, 256, 1),
     (128, 6832, 1144, 384, 0), (128, 2852, 1344, 320, 2), (160, 7260, 1320, 256, 0), (160, 3583, 2768, 320, 2),
     (160, 4395, 856, 768, 0), (192, 6783, 1704, 256, 0), (192, 7870, 1376, 320, 2), (192, 3998, 1296, 768, 1),
     (224, 6686, 2088, 256, 0), (224, 8623, 1440, 320, 1), (224, 2010, 3040, 448, 2), (256, 4452, 3304, 256, 0),
@@ -917,6 +918,27 @@ def test_folded_stack_large_shape_in_its_token_range(bt):
     out = bt.encoder_fwd_padded(layers, xpad, tok, cu, fold=fold)
     want = bt.unpack(dev(got.astype(np.float16)), tok, 8, 300)
     assert torch.equal(out, want)
+
+
+@pytest.mark.parametrize("H,F,T", [(832, 3336, 1500), (1152, 4608, 1300)])
+def test_folded_stack_odd_head_counts(bt, H, F, T):
+    """Wide folded tiles whose last column tile is partial (13 heads: QKV 19.5 and FFN-up 26.06 tiles wide), and rows with
+    more partial sums than the requests cover (18 heads: 9 of them), against the oracle and the plain pipeline."""
+    import dataclasses
+    wl = dataclasses.replace(I.WORKLOADS["layer_b4_s64"], H=H, heads=H // 64, F=F, S=160, B=10)
+    assert bt.gemm_tile_shape(T, 3 * H, H)[0] in (128, 192) and bt.gemm_tile_shape(T, F, H, 1) == (192, 128)
+    L = I.uniform_lengths(wl.B, 120, 160, seed=H)
+    L[0] += T - int(L.sum())
+    assert 1 <= L[0] <= 400
+    x = I.make_hidden_packed(wl, T)
+    layers = [bt.Layer(I.make_layer_params(wl, i, True)) for i in range(2)]
+    cu = dev(np.concatenate([[0], np.cumsum(L)]).astype(np.int32))
+    got = host(bt.encoder_fwd(layers, dev(x), cu, 400, fold=bt.encoder_prepare(layers))).astype(np.float64)
+    plain = host(bt.encoder_fwd(layers, dev(x), cu, 400)).astype(np.float64)
+    assert not np.array_equal(got, plain)
+    ref = _oracle_each(wl, L, x, oracle_layers(wl, 2, True), [2])[2]
+    assert np.abs(plain - ref).max() <= 2 * TOL_LAYER
+    assert np.abs(got - ref).max() <= 2 * TOL_LAYER
 
 
 def test_folded_stack_rows_with_a_large_common_offset(bt):
