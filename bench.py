@@ -713,8 +713,8 @@ def main():
         out["layernorm_fold_vectors"] = dict(
             step_stats(wl.B, dtf, perf_, window=8), unit="sequences/s", step="encoder_fwd_masked(d_fold)",
             max_abs_diff_to_value_path=round(float((y_padded_f.float() - y_padded.float()).abs().max()), 5),
-            note="LayerNorms folded into the GEMM epilogues where the library finds that faster (a few hundred to "
-                 "about 2 700 tokens at hidden 768), else the same kernels as `value`")
+            note="LayerNorms folded into the GEMM epilogues in the library's range of token counts (about 600 to 2 700 at "
+                 "hidden 768), else the same kernels as `value`")
 
     # ---------------- the two library calls of the step made from Python one after the other (extra point; same bits)
     if not separate:
