@@ -223,34 +223,37 @@ __global__ __launch_bounds__(256) void pack_kernel(const uint4_t* __restrict__ p
   packed[i] = padded[(size_t)token_idx[tok] * chunks + c];
 }
 
-// A wavefront writes kUnpackRows consecutive padded rows.  One wave-wide search finds where they start in the
-// strictly increasing token_idx (three rounds of 64 probes for 2^18 tokens), the next kUnpackRows entries say
+// A wavefront writes ROWS consecutive padded rows.  One wave-wide search finds where they start in the
+// strictly increasing token_idx (three rounds of 64 probes for 2^18 tokens), the next ROWS entries say
 // which of the rows are valid and which packed row each one is.
-constexpr int kUnpackRows = 8;
+// Bound: latency up to some thousand rows, then memory.  Two rows a wavefront are the best or within 2 % of the best of 1, 2, 4, 8 from 32 to
+// 65 536 rows of 512 to 2048 halves (175 x 2048: 3.36 us, 4.93 with eight; 4 096 x 768: 3.98, 4.72; 65 536 x 768: 24.5, 24.9);
+// many narrow rows want eight, which share a search (65 536 x 64: 8.1 us, 11.6 with two; 8 192 x 64: the same).
+template <int ROWS>
 __global__ __launch_bounds__(256) void unpack_kernel(const uint4_t* __restrict__ packed,
                                                      const int32_t* __restrict__ token_idx, int T, int rows,
                                                      int chunks, uint4_t* __restrict__ padded) {
   const int lane = threadIdx.x & 63;
-  const int r0 = ((int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * kUnpackRows;
+  const int r0 = ((int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * ROWS;
   if (r0 >= rows) return;
   const int lo = wave_lower_bound(token_idx, T, r0, lane);
-  const int e = lane < kUnpackRows && lo + lane < T ? token_idx[lo + lane] - r0 : kUnpackRows;
-  int src[kUnpackRows];  // packed row of each padded row, -1: padding; wave-uniform
+  const int e = lane < ROWS && lo + lane < T ? token_idx[lo + lane] - r0 : ROWS;
+  int src[ROWS];  // packed row of each padded row, -1: padding; wave-uniform
 #pragma unroll
-  for (int k = 0; k < kUnpackRows; ++k) {
+  for (int k = 0; k < ROWS; ++k) {
     const unsigned long long hit = __ballot(e == k);
     src[k] = hit ? lo + __ffsll((long long)hit) - 1 : -1;
   }
   const uint4_t zero = {0u, 0u, 0u, 0u};
   for (int c = lane; c < chunks; c += kWave) {
-    uint4_t v[kUnpackRows];
+    uint4_t v[ROWS];
 #pragma unroll
-    for (int k = 0; k < kUnpackRows; ++k) {
+    for (int k = 0; k < ROWS; ++k) {
       v[k] = zero;
       if (src[k] >= 0) v[k] = packed[(size_t)src[k] * chunks + c];
     }
 #pragma unroll
-    for (int k = 0; k < kUnpackRows; ++k)
+    for (int k = 0; k < ROWS; ++k)
       if (r0 + k < rows) padded[(size_t)(r0 + k) * chunks + c] = v[k];
   }
 }
@@ -357,8 +360,11 @@ extern "C" bt_status bt_unpack(const bt_half* d_packed, const int32_t* d_token_i
   if (!d_padded || !aligned16(d_padded)) return BT_ERR_INVALID_ARG;
   if (T > 0 && (!d_packed || !d_token_idx || !aligned16(d_packed))) return BT_ERR_INVALID_ARG;
   const int rows = B * S;
-  constexpr int per = 4 * kUnpackRows;
-  unpack_kernel<<<(unsigned)(((size_t)rows + per - 1) / per), 256, 0, static_cast<hipStream_t>(stream)>>>(
-      reinterpret_cast<const uint4_t*>(d_packed), d_token_idx, T, rows, H / 8, reinterpret_cast<uint4_t*>(d_padded));
+  const uint4_t* const packed = reinterpret_cast<const uint4_t*>(d_packed);
+  uint4_t* const padded = reinterpret_cast<uint4_t*>(d_padded);
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  auto grid = [&](int per_wave) { return (unsigned)(((size_t)rows + 4 * per_wave - 1) / (4 * per_wave)); };
+  if (H < 512 && rows > 8192) unpack_kernel<8><<<grid(8), 256, 0, st>>>(packed, d_token_idx, T, rows, H / 8, padded);
+  else unpack_kernel<2><<<grid(2), 256, 0, st>>>(packed, d_token_idx, T, rows, H / 8, padded);
   return launch_status();
 }

@@ -169,7 +169,7 @@ def test_offsets_largest_number_of_sentences(bt):
     assert cu[at].tolist() == [0, 1, 2, 3, 4, 5] and cu[B].item() == 6
 
 
-@pytest.mark.parametrize("B,S,H", [(3, 5, 8), (4, 64, 768), (16, 256, 768), (7, 100, 1024), (2, 33, 72), (1, 1, 8), (90, 100, 520)])
+@pytest.mark.parametrize("B,S,H", [(3, 5, 8), (4, 64, 768), (16, 256, 768), (7, 100, 1024), (2, 33, 72), (1, 1, 8), (90, 100, 520), (91, 91, 264)])
 def test_pack_unpack_bit_exact(bt, B, S, H):
     import torch
     rng = np.random.default_rng(B + S + H)
