@@ -11,7 +11,9 @@ namespace bt {
 // slice order (the reduction of the split costs no kernel of its own); otherwise x is fp16 [T,H].
 // STREAM: the tensors exceed the memory-side cache, so rows are loaded and stored with the non-temporal
 // hint (measured +9 % on a 1.2 GB pass); at cache-resident sizes the next kernel wants the rows cached.
-template <int CPL, bool PART, bool STREAM>
+// UNPACK: y is the padded tensor (out_idx below).  A form of its own: with the search in the same code the packed form was slower,
+// 2 308 x 256 3.06 against 2.7 us, 0.04 us at the other widths.
+template <int CPL, bool PART, bool STREAM, bool UNPACK>
 __global__ __launch_bounds__(256) void bias_residual_ln_kernel(
     // Everything the kernel touches before its first batch of row loads is in flight comes first and fills exactly
     // the 14 dwords that are preloaded into SGPRs at wave launch: the output index (decides the first branch), the
@@ -29,11 +31,11 @@ __global__ __launch_bounds__(256) void bias_residual_ln_kernel(
   //   `lo` if out_idx[lo] == r (out_idx is increasing: one wave-wide search) and a zero row otherwise
   //   (unpack fused into the store, Sec. III-D).
   const int lane = threadIdx.x & 63;
-  int row = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int chunks = H >> 3;
   size_t obase;
-  if (out_idx) {
-    const int r = row;
+  if constexpr (UNPACK) {
+    const int r = __builtin_amdgcn_readfirstlane(row);
     if (r >= out_rows) return;
     const int lo = wave_lower_bound(out_idx, T, r, lane);
     obase = (size_t)r * H;
@@ -169,10 +171,10 @@ __global__ __launch_bounds__(256) void ln_finalize_kernel(const half_t* __restri
   // out_idx: y is the padded tensor [out_rows, H]; this wave owns padded row r, which is packed row `lo` if
   // out_idx[lo] == r and a zero row otherwise (unpack fused into the store, as in bias_residual_ln_kernel).
   const int lane = threadIdx.x & 63;
-  int row = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   size_t obase;
   if (out_idx) {
-    const int r = row;
+    const int r = __builtin_amdgcn_readfirstlane(row);
     if (r >= out_rows) return;
     const int lo = wave_lower_bound(out_idx, T, r, lane);
     obase = (size_t)r * H;
@@ -271,11 +273,16 @@ bt_status layernorm_dispatch(const bt_half* x, const float* xpart, int nsplit, c
   const int chunks = H / 8;
   dim3 grid(((out_idx ? out_rows : T) + 3) / 4), block(256);
   const bool stream = (size_t)T * H * 6 > ((size_t)256 << 20);  // three tensors larger than the 256 MB Infinity Cache
-#define BT_LN(CPL)                                                                                             \
+#define BT_LN_FORM(CPL, UNPACK)                                                                                \
   do {                                                                                                         \
-    if (xpart) bias_residual_ln_kernel<CPL, true, false><<<grid, block, 0, st>>>(xpart, pr, pg, pe, out_idx, res_rows, T, H, pb, py, nsplit, eps, out_rows); \
-    else if (stream) bias_residual_ln_kernel<CPL, false, true><<<grid, block, 0, st>>>(px, pr, pg, pe, out_idx, res_rows, T, H, pb, py, nsplit, eps, out_rows); \
-    else bias_residual_ln_kernel<CPL, false, false><<<grid, block, 0, st>>>(px, pr, pg, pe, out_idx, res_rows, T, H, pb, py, nsplit, eps, out_rows); \
+    if (xpart) bias_residual_ln_kernel<CPL, true, false, UNPACK><<<grid, block, 0, st>>>(xpart, pr, pg, pe, out_idx, res_rows, T, H, pb, py, nsplit, eps, out_rows); \
+    else if (stream) bias_residual_ln_kernel<CPL, false, true, UNPACK><<<grid, block, 0, st>>>(px, pr, pg, pe, out_idx, res_rows, T, H, pb, py, nsplit, eps, out_rows); \
+    else bias_residual_ln_kernel<CPL, false, false, UNPACK><<<grid, block, 0, st>>>(px, pr, pg, pe, out_idx, res_rows, T, H, pb, py, nsplit, eps, out_rows); \
+  } while (0)
+#define BT_LN(CPL)                        \
+  do {                                    \
+    if (out_idx) BT_LN_FORM(CPL, true);   \
+    else BT_LN_FORM(CPL, false);          \
   } while (0)
   if (chunks <= 64) BT_LN(1);
   else if (chunks <= 128) BT_LN(2);
@@ -283,6 +290,7 @@ bt_status layernorm_dispatch(const bt_half* x, const float* xpart, int nsplit, c
   else if (chunks <= 512) BT_LN(8);
   else BT_LN(16);
 #undef BT_LN
+#undef BT_LN_FORM
   return launch_status();
 }
 
