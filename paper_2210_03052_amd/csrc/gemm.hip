@@ -697,7 +697,9 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(
 // ---------------------------------------------------------------------------
 // Fallback kernel: register-staged, 64x64x64 tile, padded LDS rows, K tail zero-filled.
 // ---------------------------------------------------------------------------
-template <int ACT, int EPI>
+// SLABS (K > 64): the next slab's global loads travel under this slab's MFMAs.  A product of a single slab lives on the number of
+// workgroups in flight and goes without, at 72 registers instead of 80.
+template <int ACT, int EPI, bool SLABS>
 __global__ __launch_bounds__(kGemmThreads) void gemm_simple_kernel(const half_t* __restrict__ A,
                                                                    const half_t* __restrict__ W, const GemmEpi ep,
                                                                    half_t* __restrict__ C, int M, int N, int K,
@@ -716,9 +718,9 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_simple_kernel(const half_t*
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
   const uint4_t zero4 = {0u, 0u, 0u, 0u};
-  for (int k0 = 0; k0 < K; k0 += BK) {
+  uint4_t ra[CH], rb[CH];
+  auto load_slab = [&](int k0) {
     const bool in = (k0 + kc) < K;  // K % 8 == 0: a chunk is entirely inside or outside
-    uint4_t ra[CH], rb[CH];
 #pragma unroll
     for (int i = 0; i < CH; ++i) {
       const int row = (tid >> 3) + i * (kGemmThreads / 8);
@@ -726,6 +728,9 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_simple_kernel(const half_t*
       ra[i] = in ? *reinterpret_cast<const uint4_t*>(A + (size_t)(ep.a_rows ? ep.a_rows[ar] : ar) * K + k0 + kc) : zero4;
       rb[i] = in ? *reinterpret_cast<const uint4_t*>(W + (size_t)min(n0 + row, N - 1) * K + k0 + kc) : zero4;
     }
+  };
+  load_slab(0);
+  for (int k0 = 0; k0 < (SLABS ? K : 1); k0 += BK) {
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < CH; ++i) {
@@ -734,6 +739,7 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_simple_kernel(const half_t*
       *reinterpret_cast<uint4_t*>(&sB[row * LDS + kc]) = rb[i];
     }
     __syncthreads();
+    if (SLABS && k0 + BK < K) load_slab(k0 + BK);
 #pragma unroll
     for (int ks = 0; ks < BK / 32; ++ks) {
       half8_t fa[2], fb[2];
@@ -876,7 +882,11 @@ static bt_status launch_simple(const half_t* A, const half_t* W, half_t* C, int 
   const long long n_tiles = (long long)((M + 63) / 64) * tiles_n;
   if (n_tiles > 0x7fffffffLL) return BT_ERR_UNSUPPORTED;
   dim3 grid((unsigned)n_tiles), block(kGemmThreads);
-#define BT_LAUNCH(ACT, EPI) gemm_simple_kernel<ACT, EPI><<<grid, block, 0, st>>>(A, W, ep, C, M, N, K, tiles_n)
+#define BT_LAUNCH(ACT, EPI)                                                                       \
+  do {                                                                                           \
+    if (K > 64) gemm_simple_kernel<ACT, EPI, true><<<grid, block, 0, st>>>(A, W, ep, C, M, N, K, tiles_n); \
+    else gemm_simple_kernel<ACT, EPI, false><<<grid, block, 0, st>>>(A, W, ep, C, M, N, K, tiles_n);       \
+  } while (0)
   if (epi == EPI_RESID) {
     BT_LAUNCH(BT_ACT_NONE, EPI_RESID);
   } else if (epi == EPI_FOLD) {
