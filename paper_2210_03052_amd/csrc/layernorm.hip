@@ -11,8 +11,8 @@ namespace bt {
 // slice order (the reduction of the split costs no kernel of its own); otherwise x is fp16 [T,H].
 // STREAM: the tensors exceed the memory-side cache, so rows are loaded and stored with the non-temporal
 // hint (measured +9 % on a 1.2 GB pass); at cache-resident sizes the next kernel wants the rows cached.
-// UNPACK: y is the padded tensor (out_idx below).  A form of its own: with the search in the same code the packed form was slower,
-// 2 308 x 256 3.06 against 2.7 us, 0.04 us at the other widths.
+// UNPACK: y is the padded tensor (out_idx below).  A form of its own: with the search in the same code the packed form was 0.06 us
+// slower at every size (2 308 x 768 3.54 us, 3.47 without).
 template <int CPL, bool PART, bool STREAM, bool UNPACK>
 __global__ __launch_bounds__(256) void bias_residual_ln_kernel(
     // Everything the kernel touches before its first batch of row loads is in flight comes first and fills exactly
@@ -82,6 +82,9 @@ __global__ __launch_bounds__(256) void bias_residual_ln_kernel(
   const float bw = bias ? 1.f : 0.f;
 #pragma unroll
   for (int i = 0; i < CPL; ++i) bs[i] = *reinterpret_cast<const half8_t*>(bsrc + cc[i]);
+  // one chunk a lane: or the arithmetic on the first loads, and the wait for them, moves ahead of the bias (2 308 x 256 3.05 us
+  // instead of 2.74); with more chunks the compiler keeps the order and the barrier costs 0.05 us
+  if constexpr (CPL == 1) __builtin_amdgcn_sched_barrier(0);
   if constexpr (PART) {
     // K slices of the product, four at a time where the registers allow (slice indices past nsplit are clamped
     // and their values dropped): at the usual widths the up to eight slices cost two round trips, not one each

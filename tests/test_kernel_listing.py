@@ -140,3 +140,13 @@ def test_every_dma_request_has_its_own_target(kernels):
         assert not dma_faults(body), (name, dma_faults(body)[:3])
         seen += sum(ins.startswith("global_load_lds") for ins in body)
     assert seen > 1000
+
+
+def test_layernorm_rows_are_one_memory_round_trip(kernels):
+    """Packed rows up to 1024 wide: all five operands of a row (x, residual, gamma, beta, bias) are requested before the
+    first wait for any of them."""
+    for cpl in (1, 2):
+        body, = (b for n, b in kernels.items() if f"bias_residual_ln_kernelILi{cpl}ELb0ELb0ELb0E" in n)
+        first = next(i for i, ins in enumerate(body) if ins.startswith("global_load_dwordx4"))
+        wait = next(i for i, ins in enumerate(body) if i > first and ins.startswith("s_waitcnt") and "vmcnt" in ins)
+        assert sum(ins.startswith("global_load_dwordx4") for ins in body[first:wait]) == 5 * cpl, cpl
