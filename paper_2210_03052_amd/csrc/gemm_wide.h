@@ -34,11 +34,6 @@ __device__ __forceinline__ void dma_target(uint32_t lds) {
 __device__ __forceinline__ void dma_load(const void* sbase, uint32_t voff) {
   asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase) : "memory");
 }
-template <int OFF>
-__device__ __forceinline__ void dma16_sv(const void* sbase, uint32_t voff, uint32_t lds) {
-  asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(sbase), "n"(OFF)
-               : "memory", "m0", "scc");
-}
 __device__ __forceinline__ void dma4_sv(const void* sbase, uint32_t voff, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(voff), "s"(sbase) : "memory", "m0");
 }

@@ -4,6 +4,8 @@
 // Plain pipeline (7 launches per layer):
 //   GEMM0 (+bias) -> varlen MHA -> GEMM1 -> bias+residual+LN
 //   -> GEMM2 (+bias, GELU in the epilogue) -> GEMM3 -> bias+residual+LN
+// With few tokens bias+residual goes to the epilogue of the product in front and LN into the product behind it
+// (few_choice, few_tokens.hip): 5 or 6 launches per layer.
 //
 // Folded pipeline (bt_encoder_fwd with fold vectors, 5 launches per layer): the add-bias + residual
 // of Sec. III-C1 moves into the epilogue of GEMM1 / GEMM3, which also stores partial row sums of
@@ -26,6 +28,10 @@ bt_status layernorm_dispatch(const bt_half* x, const float* xpart, int nsplit, c
 int gemm_splitk_choice(int M, int N, int K);
 bt_status gemm_splitk_dispatch(const bt_half* A, const bt_half* W, int M, int N, int K, int ksplit, float* partial,
                                hipStream_t st);
+bt_status few_resid_gemm_dispatch(const bt_half* a, const bt_half* w, int T, int N, int K, const bt_half* resid,
+                                  const int32_t* resid_rows, const bt_half* bias, float* z, hipStream_t st);
+bt_status few_ln_gemm_dispatch(const float* z, const bt_half* w, int T, int N, int K, const bt_half* gamma, const bt_half* beta,
+                               const bt_half* bias, float eps, bt_act act, bt_half* c, bt_half* y, hipStream_t st);
 // slices * M * N of any split gemm_splitk_choice allows: at most 256 tiles of 64 x 64 outputs
 constexpr size_t kSplitKFloats = (size_t)256 * 64 * 64;
 bt_status ln_finalize_dispatch(const bt_half* u, const float2* part, int np, const bt_half* gamma,
@@ -113,15 +119,51 @@ struct LayerIo {
   int out_rows = 0;                   // every other row is zero-filled (last layer)
 };
 
+// How much of a layer runs in the form for few tokens (few_tokens.hip): kFewInner, LN0 inside FFN-up (6 launches);
+// kFewBoth, also LN1 inside the QKV product of the next layer (5 launches).
+//
+// Inner while the 32 x 128 tiles of FFN-up are one round of the compute units: up to there the product with the LayerNorm
+// inside is the faster, in the second round it pays for the rows every column tile normalises anew.  Both while FFN-down,
+// whose whole reduction is then one workgroup's, has at most 320 tiles of 16 x 32.
+// Microseconds per layer, six layers, seven launches / Inner / Both:
+//   width 512:    48 tokens 25.7 / 22.4 / 20.0, 128: 26.8 / 23.6 / 20.8, 256: 29.5 / 27.4 / 24.9, 320: 27.8 / 27.0 / 26.1,
+//                384: 28.3 / 27.2 / 27.6, 512: 29.4 / 27.8 / 29.0, 620: 31.6 / 34.5 / 35.5
+//   width 768:    48 tokens 29.2 / 25.5 / 22.4, 128: 31.0 / 28.1 / 25.7, 192: 31.7 / 30.1 / 29.3, 224: 31.7 / 29.9 / 29.9,
+//                256: 33.3 / 31.3 / 32.4, 320: 32.9 / 31.2 / 32.1, 384: 34.3 / 37.8 / 40.5
+//   width 1024:   48 tokens 31.2 / 27.4 / 24.7, 128: 32.9 / 30.3 / 28.7, 160: 33.3 / 32.1 / 31.9, 192: 33.5 / 32.4 / 33.6,
+//                256: 36.1 / 34.8 / 35.9, 288: 37.0 / 42.8 / 45.5
+// The widths are those the kernel is built for: a row is 2, 3 or 4 loads of a wavefront.
+enum Few { kFewNone = 0, kFewInner = 1, kFewBoth = 2 };
+static Few few_choice(int T, int H, int F) {
+  if ((H != 512 && H != 768 && H != 1024) || (F % 64) != 0 || (size_t)T * H > kSplitKFloats) return kFewNone;
+  if ((long long)F * H * 2 >= (1LL << 32) || (long long)T * F * 2 >= (1LL << 32)) return kFewNone;  // 32-bit byte offsets
+  auto tiles = [&](int n, int bm, int bn) { return (long long)((T + bm - 1) / bm) * ((n + bn - 1) / bn); };
+  if (tiles(F, 32, 128) > 256 || tiles(3 * H, 32, 128) > 256) return kFewNone;
+  return tiles(H, 16, 32) <= 320 ? kFewBoth : kFewInner;
+}
+
+// One layer.  prev: the layer in front of this one, whose output exists only as its LayerNorm's input w.splitk (form for few
+// tokens); next: this layer leaves its own output like that.
 static bt_status layer_fwd(const bt_layer* l, const bt_half* x, const int32_t* cu, int B, int T, int max_len,
-                           bt_half* y, const Workspace& w, hipStream_t st, const LayerIo& io = LayerIo()) {
+                           bt_half* y, const Workspace& w, hipStream_t st, const LayerIo& io = LayerIo(),
+                           const bt_layer* prev = nullptr, bool next = false) {
   const int H = l->H, F = l->F;
+  const Few few = few_choice(T, H, F);
+  const bt_act act = l->gelu_kind == 0 ? BT_ACT_GELU_ERF : BT_ACT_GELU_TANH;
+  float* const z = w.splitk;
   bt_status s;
   GemmEpi ep;
-  ep.a_rows = io.in_rows;
-  ep.a_rows_of = io.in_rows_of;
-  ep.bias = hp(l->b_qkv);
-  if ((s = gemm_dispatch(x, l->w_qkv, T, 3 * H, H, BT_ACT_NONE, EPI_PLAIN, ep, w.qkv, st, nullptr)) != BT_OK) return s;
+  if (prev) {
+    x = w.ping;
+    if ((s = few_ln_gemm_dispatch(z, l->w_qkv, T, 3 * H, H, prev->ln1_g, prev->ln1_b, l->b_qkv, prev->ln_eps, BT_ACT_NONE, w.qkv,
+                                  w.ping, st)) != BT_OK)
+      return s;
+  } else {
+    ep.a_rows = io.in_rows;
+    ep.a_rows_of = io.in_rows_of;
+    ep.bias = hp(l->b_qkv);
+    if ((s = gemm_dispatch(x, l->w_qkv, T, 3 * H, H, BT_ACT_NONE, EPI_PLAIN, ep, w.qkv, st, nullptr)) != BT_OK) return s;
+  }
   const float scale = 1.0f / sqrtf((float)l->head_dim);
   if ((s = mha_dispatch(w.qkv, w.qkv + H, w.qkv + 2 * H, 3 * (int64_t)H, nullptr, nullptr, nullptr, cu, B, T,
                         max_len, l->heads, scale, w.attn, st)) != BT_OK)
@@ -131,21 +173,27 @@ static bt_status layer_fwd(const bt_layer* l, const bt_half* x, const int32_t* c
   // Output projection and FFN-down: with few tokens the K loop is split over otherwise idle compute
   // units and the LayerNorm kernel adds the fp32 slices (no reduction kernel, no fp16 rounding in between).
   const int split1 = gemm_splitk_choice(T, H, H), split3 = gemm_splitk_choice(T, H, F);
-  if (split1 > 1) {
-    if ((s = gemm_splitk_dispatch(w.attn, l->w_o, T, H, H, split1, w.splitk, st)) != BT_OK) return s;
-    if ((s = layernorm_dispatch(nullptr, w.splitk, split1, l->b_o, x, l->ln0_g, l->ln0_b, l->ln_eps, T, H, w.y1, st,
-                                io.in_rows, nullptr, 0)) != BT_OK)
+  if (few != kFewNone) {
+    if ((s = few_resid_gemm_dispatch(w.attn, l->w_o, T, H, H, x, io.in_rows, l->b_o, z, st)) != BT_OK) return s;
+    if ((s = few_ln_gemm_dispatch(z, l->w_1, T, F, H, l->ln0_g, l->ln0_b, l->b_1, l->ln_eps, act, w.g, w.y1, st)) != BT_OK)
       return s;
+    if (next) return few_resid_gemm_dispatch(w.g, l->w_2, T, H, F, w.y1, nullptr, l->b_2, z, st);
   } else {
-    if ((s = gemm_dispatch(w.attn, l->w_o, T, H, H, BT_ACT_NONE, EPI_PLAIN, ep, w.proj, st, nullptr)) != BT_OK) return s;
-    if ((s = layernorm_dispatch(w.proj, nullptr, 0, l->b_o, x, l->ln0_g, l->ln0_b, l->ln_eps, T, H, w.y1, st,
-                                io.in_rows, nullptr, 0)) != BT_OK)
-      return s;
+    if (split1 > 1) {
+      if ((s = gemm_splitk_dispatch(w.attn, l->w_o, T, H, H, split1, w.splitk, st)) != BT_OK) return s;
+      if ((s = layernorm_dispatch(nullptr, w.splitk, split1, l->b_o, x, l->ln0_g, l->ln0_b, l->ln_eps, T, H, w.y1, st,
+                                  io.in_rows, nullptr, 0)) != BT_OK)
+        return s;
+    } else {
+      if ((s = gemm_dispatch(w.attn, l->w_o, T, H, H, BT_ACT_NONE, EPI_PLAIN, ep, w.proj, st, nullptr)) != BT_OK) return s;
+      if ((s = layernorm_dispatch(w.proj, nullptr, 0, l->b_o, x, l->ln0_g, l->ln0_b, l->ln_eps, T, H, w.y1, st,
+                                  io.in_rows, nullptr, 0)) != BT_OK)
+        return s;
+    }
+    ep.bias = hp(l->b_1);
+    if ((s = gemm_dispatch(w.y1, l->w_1, T, F, H, act, EPI_PLAIN, ep, w.g, st, nullptr)) != BT_OK) return s;
+    ep.bias = nullptr;
   }
-  const bt_act act = l->gelu_kind == 0 ? BT_ACT_GELU_ERF : BT_ACT_GELU_TANH;
-  ep.bias = hp(l->b_1);
-  if ((s = gemm_dispatch(w.y1, l->w_1, T, F, H, act, EPI_PLAIN, ep, w.g, st, nullptr)) != BT_OK) return s;
-  ep.bias = nullptr;
   if (split3 > 1) {
     if ((s = gemm_splitk_dispatch(w.g, l->w_2, T, H, F, split3, w.splitk, st)) != BT_OK) return s;
     return layernorm_dispatch(nullptr, w.splitk, split3, l->b_2, w.y1, l->ln1_g, l->ln1_b, l->ln_eps, T, H, y, st, nullptr,
@@ -154,6 +202,25 @@ static bt_status layer_fwd(const bt_layer* l, const bt_half* x, const int32_t* c
   if ((s = gemm_dispatch(w.g, l->w_2, T, H, F, BT_ACT_NONE, EPI_PLAIN, ep, w.proj, st, nullptr)) != BT_OK) return s;
   return layernorm_dispatch(w.proj, nullptr, 0, l->b_2, w.y1, l->ln1_g, l->ln1_b, l->ln_eps, T, H, y, st, nullptr,
                             io.out_idx, io.out_rows);
+}
+
+// The layers of a stack one after another.  in / out: packed tensors, or with io the padded ones.
+static bt_status stack_fwd(const bt_layer* layers, int n_layers, const bt_half* x, const int32_t* cu, int B, int T, int max_len,
+                           bt_half* y, const Workspace& w, hipStream_t st, const LayerIo& io = LayerIo()) {
+  const bool both = few_choice(T, layers[0].H, layers[0].F) == kFewBoth;
+  const bt_half* in = x;
+  for (int i = 0; i < n_layers; ++i) {
+    const bool last = i == n_layers - 1;
+    LayerIo here;
+    if (i == 0) { here.in_rows = io.in_rows; here.in_rows_of = io.in_rows_of; }
+    if (last) { here.out_idx = io.out_idx; here.out_rows = io.out_rows; }
+    bt_half* const outp = last ? y : ((i & 1) ? w.pong : w.ping);
+    const bt_status s = layer_fwd(&layers[i], in, cu, B, T, max_len, outp, w, st, here, both && i > 0 ? &layers[i - 1] : nullptr,
+                                  both && !last);
+    if (s != BT_OK) return s;
+    in = outp;
+  }
+  return BT_OK;
 }
 
 // Folded stack.  Between layers the activation lives as (u2 = gamma1 (.) z2, part2); inside a layer
@@ -369,13 +436,7 @@ extern "C" bt_status bt_encoder_fwd(const bt_layer* layers, int n_layers, const 
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (d_fold && folded_pays(T, layers[0].H, layers[0].F))
     return stack_fwd_folded(layers, n_layers, d_fold, d_x, d_cu_seqlens, B, T, max_len, d_y, w, st);
-  const bt_half* in = d_x;
-  for (int i = 0; i < n_layers; ++i) {
-    bt_half* outp = (i == n_layers - 1) ? d_y : ((i & 1) ? w.pong : w.ping);
-    if ((s = layer_fwd(&layers[i], in, d_cu_seqlens, B, T, max_len, outp, w, st)) != BT_OK) return s;
-    in = outp;
-  }
-  return BT_OK;
+  return stack_fwd(layers, n_layers, d_x, d_cu_seqlens, B, T, max_len, d_y, w, st);
 }
 
 extern "C" bt_status bt_encoder_fwd_padded(const bt_layer* layers, int n_layers, const float* d_fold,
@@ -398,25 +459,14 @@ extern "C" bt_status bt_encoder_fwd_padded(const bt_layer* layers, int n_layers,
   if (!d_ws || (reinterpret_cast<uintptr_t>(d_ws) & 255u)) return BT_ERR_WORKSPACE;
   const Workspace w = carve(d_ws, T, H, layers[0].F);
   if (ws_bytes < w.bytes) return BT_ERR_WORKSPACE;
-  if (d_fold && folded_pays(T, H, layers[0].F)) {
-    LayerIo io;
-    io.in_rows = d_token_idx;
-    io.in_rows_of = B * S;
-    io.out_idx = d_token_idx;
-    io.out_rows = B * S;
+  LayerIo io;
+  io.in_rows = d_token_idx;
+  io.in_rows_of = B * S;
+  io.out_idx = d_token_idx;
+  io.out_rows = B * S;
+  if (d_fold && folded_pays(T, H, layers[0].F))
     return stack_fwd_folded(layers, n_layers, d_fold, d_x_padded, d_cu_seqlens, B, T, S, d_y_padded, w, st, io);
-  }
-  const bt_half* in = d_x_padded;
-  for (int i = 0; i < n_layers; ++i) {
-    const bool last = i == n_layers - 1;
-    LayerIo io;
-    if (i == 0) { io.in_rows = d_token_idx; io.in_rows_of = B * S; }
-    if (last) { io.out_idx = d_token_idx; io.out_rows = B * S; }
-    bt_half* outp = last ? d_y_padded : ((i & 1) ? w.pong : w.ping);
-    if ((s = layer_fwd(&layers[i], in, d_cu_seqlens, B, T, S, outp, w, st, io)) != BT_OK) return s;
-    in = outp;
-  }
-  return BT_OK;
+  return stack_fwd(layers, n_layers, d_x_padded, d_cu_seqlens, B, T, S, d_y_padded, w, st, io);
 }
 
 // bt_build_offsets followed by bt_encoder_fwd_padded in one call: the token count the first call waits for

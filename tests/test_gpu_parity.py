@@ -893,6 +893,39 @@ def test_folded_stack_vs_oracle(bt, name, n_layers, stress):
     assert max(np.abs(b[cuh[i]: cuh[i + 1]] - ref[i]).max() for i in seqs) <= tol
 
 
+@pytest.mark.parametrize("H,F,T", [
+    # one token; every row count at which one of the four products changes its tile shape or a tile gains its first row
+    (768, 3072, 1), (768, 3072, 17), (768, 3072, 80), (768, 3072, 81), (768, 3072, 113), (768, 3072, 160), (768, 3072, 161),
+    # the last and first token counts of the three forms (5, 6 and 7 launches per layer)
+    (768, 3072, 208), (768, 3072, 209), (768, 3072, 320), (768, 3072, 321), (512, 2048, 320), (512, 2048, 321), (512, 2048, 512),
+    (1024, 4096, 48), (1024, 4096, 160), (1024, 4096, 161), (1024, 4096, 256), (1024, 4096, 257),
+    # a reduction of one slab (wavefronts without work), of 13 (an uneven share), a partial last column tile
+    (512, 64, 33), (512, 832, 130), (768, 1600, 97)])
+def test_few_tokens_stack_vs_oracle(bt, H, F, T):
+    """Stacks of the token counts at which LayerNorms run inside the products behind them: three layers against the oracle
+    (one layer's bound for each), from a workspace full of NaN patterns; the padded entry point bit for bit, both GELU forms."""
+    import dataclasses
+    import torch
+    wl = dataclasses.replace(I.WORKLOADS["layer_b4_s64"], H=H, heads=H // 64, F=F, S=T)
+    L = np.array([T] if T < 3 else [T - T // 3 - T // 5, T // 5, T // 3], np.int32)
+    x = I.make_hidden_packed(wl, T)
+    n = 3
+    S = int(L.max())
+    cu, tok, t = bt.build_offsets(lengths=dev(L), S=S)
+    assert t == T
+    layers = [bt.Layer(I.make_layer_params(wl, i, True), gelu_kind=T & 1) for i in range(n)]
+    ow = [O.LayerWeights(**I.make_layer_params(wl, i, True), gelu_kind="tanh" if T & 1 else "erf") for i in range(n)]
+    ws = torch.empty(bt.layer_workspace_bytes(layers[0], T, len(L), S), dtype=torch.uint8, device="cuda:0").fill_(0xFF)
+    got = bt.encoder_fwd(layers, dev(x), cu, S, ws=ws)
+    ref, cuh = _oracle_on(wl, L, x, ow, list(range(len(L))))
+    assert np.abs(host(got).astype(np.float64) - np.concatenate(ref)).max() <= n * TOL_LAYER
+    ws.fill_(0xFF)
+    out = bt.encoder_fwd_padded(layers, dev(I.pad_rows(x, L, S, fill=5.0)), tok, cu, ws=ws)
+    assert torch.equal(out, bt.unpack(got, tok, len(L), S))
+    one = bt.encoder_layer_fwd(layers[0], dev(x), cu, S)
+    assert torch.equal(one, bt.encoder_fwd(layers[:1], dev(x), cu, S))
+
+
 def test_folded_stack_large_shape_in_its_token_range(bt):
     """Hidden 1024 / FFN 4096 / 16 heads with 1 455 tokens: inside the range where fold vectors select the folded
     pipeline at this width (enough tokens not to split K, few enough for one round of 64 x 128 tiles).  Every
