@@ -266,6 +266,12 @@ __global__ __launch_bounds__(WK * 64) void few_resid_gemm_kernel(
     fa += 64;
     fb += 64;
   };
+  // the residual piece this thread adds at the end, requested ahead of the slabs (clamped where it has none)
+  const int r = tid / C4, c = (tid - r * C4) * 4, m = m0 + r, n = n0 + c;
+  const bool mine = tid < Q && m < T && n < N;
+  const int rm = min(m, T - 1), rn = min(n, N - 4);
+  const half4_t r4 = *reinterpret_cast<const half4_t*>(resid + (size_t)(resid_rows ? resid_rows[rm] : rm) * N + rn);
+  const half4_t b4 = *reinterpret_cast<const half4_t*>(bias + rn);
 #pragma unroll
   for (int s = 0; s < NS; ++s)
     if (s < my) fetch(s);
@@ -327,13 +333,6 @@ __global__ __launch_bounds__(WK * 64) void few_resid_gemm_kernel(
   for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int j = 0; j < NI; ++j) *reinterpret_cast<float4_t*>(part + (i * 16 + l16) * ACC_LD + j * 16 + 4 * quad) = acc[i][j];
-  const int r = tid / C4, c = (tid - r * C4) * 4, m = m0 + r, n = n0 + c;
-  const bool mine = tid < Q && m < T && n < N;
-  half4_t r4, b4;
-  if (mine) {
-    r4 = *reinterpret_cast<const half4_t*>(resid + (size_t)(resid_rows ? resid_rows[m] : m) * N + n);
-    b4 = *reinterpret_cast<const half4_t*>(bias + n);
-  }
   __syncthreads();
   if (mine) {
     float4_t s = {0.f, 0.f, 0.f, 0.f};
