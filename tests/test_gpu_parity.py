@@ -69,6 +69,28 @@ def test_offsets_rounds_and_alignment(bt, B, S, offset):
         bt.build_offsets(mask=given)
 
 
+@pytest.mark.parametrize("B,S", [(1, 1), (4095, 1), (4096, 1), (4097, 1), (1366, 3), (17, 4096), (129, 511), (255, 4096), (256, 4096),
+                                 (257, 4096)])
+@pytest.mark.parametrize("skew", [0, 1])
+def test_offsets_from_mask_across_chunks(bt, B, S, skew):
+    """Masks with holes around a multiple of the 4 096 entries a workgroup owns, sentences shorter than its threads' four
+    entries, the largest size of that kernel and the first beyond it, 16-byte aligned and not; a wrong entry is
+    reported wherever it stands."""
+    rng = np.random.default_rng([B, S, skew])
+    given = dev(np.zeros(B * S + skew, np.int32))[skew:].view(B, S)
+    for density in (0.0, 0.4, 1.0):
+        mask = (rng.random((B, S)) < density).astype(np.int32)
+        given.copy_(dev(mask))
+        cu, tok, T = bt.build_offsets(mask=given)
+        rcu, rtok, rT = O.build_offsets(mask)
+        assert T == rT and np.array_equal(host(cu), rcu) and np.array_equal(host(tok), rtok)
+    for at in {0, B * S // 2, B * S - 1}:
+        given.view(-1)[at] = 2
+        with pytest.raises(bt.BtError):
+            bt.build_offsets(mask=given)
+        given.view(-1)[at] = 1
+
+
 @pytest.mark.parametrize("name", list(I.WORKLOADS))
 def test_offsets_from_lengths_workloads(bt, name):
     wl = I.WORKLOADS[name]
