@@ -15,7 +15,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.environ.get("BT_LIB_OUT") or os.path.join(PKG, "libbt.so")   # BT_LIB_OUT: build a variant elsewhere
-SOURCES = ["offsets.hip", "gemm.hip", "few_tokens.hip", "layernorm.hip", "mha.hip", "layer.hip"]
+SOURCES = ["offsets.hip", "gemm.hip", "layernorm.hip", "mha.hip", "layer.hip"]
 PEAKS_LIB = os.path.join(PKG, "libbt_peaks.so")
 PEAKS_SOURCES = ["peaks.hip", "unfused.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -34,8 +34,7 @@ FLAGS = [
 # GEMM epilogue: the last fused multiply-add of an activation and its conversion to fp16 become one instruction with one
 # rounding.  The SLP vectoriser pairs some of the conversions first, which leaves those elements two roundings, other
 # ones in every tile shape; without it the result of an element does not depend on the tile that holds it.
-EXTRA_FLAGS = {"mha.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"], "gemm.hip": ["-fno-slp-vectorize"],
-               "few_tokens.hip": ["-fno-slp-vectorize"]}
+EXTRA_FLAGS = {"mha.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"], "gemm.hip": ["-fno-slp-vectorize"]}
 
 
 def _compile(src: str) -> str:

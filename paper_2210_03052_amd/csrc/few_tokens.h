@@ -7,8 +7,8 @@
 //                           out and add their parts through LDS in wavefront order)
 //   few_ln_gemm_kernel      C = act(LN(z) W^T + bias): every workgroup normalises the rows it multiplies, 16 or 32 of them,
 //                           while the first slabs of its weights are on their way
+// Included at the end of gemm.hip.
 // z stays fp32 between the two, so nothing is rounded that the LayerNorm kernel over K slices did not round either.
-#include "gemm_util.h"
 
 namespace bt {
 

@@ -5,7 +5,7 @@
 //   GEMM0 (+bias) -> varlen MHA -> GEMM1 -> bias+residual+LN
 //   -> GEMM2 (+bias, GELU in the epilogue) -> GEMM3 -> bias+residual+LN
 // With few tokens bias+residual goes to the epilogue of the product in front and LN into the product behind it
-// (few_choice, few_tokens.hip): 5 or 6 launches per layer.
+// (few_choice, few_tokens.h): 5 or 6 launches per layer.
 //
 // Folded pipeline (bt_encoder_fwd with fold vectors, 5 launches per layer): the add-bias + residual
 // of Sec. III-C1 moves into the epilogue of GEMM1 / GEMM3, which also stores partial row sums of
@@ -119,7 +119,7 @@ struct LayerIo {
   int out_rows = 0;                   // every other row is zero-filled (last layer)
 };
 
-// How much of a layer runs in the form for few tokens (few_tokens.hip): kFewInner, LN0 inside FFN-up (6 launches);
+// How much of a layer runs in the form for few tokens (few_tokens.h): kFewInner, LN0 inside FFN-up (6 launches);
 // kFewBoth, also LN1 inside the QKV product of the next layer (5 launches).
 //
 // Inner while the 32 x 128 tiles of FFN-up are one round of the compute units: up to there the product with the LayerNorm
