@@ -76,8 +76,13 @@ def role_of(name: str, grid: int = 0):
     if "bias_residual_ln_kernel" in name:
         stream = len(a) >= 3 and a[2] == 1
         return ("bias_residual_ln_streaming" if stream else "bias_residual_ln"), f"bias_residual_ln<{','.join(map(str, a[:3]))}>"
+    if "few_resid_gemm_kernel" in name:
+        return "few_gemm_resid", f"few_resid_gemm<{','.join(map(str, a[:4]))}>"
+    if "few_ln_gemm_kernel" in name:
+        return ("few_ln_gemm2_bias_gelu" if len(a) >= 5 and a[4] else "few_ln_gemm0_qkv"), f"few_ln_gemm<{','.join(map(str, a[:5]))}>"
     for key, role in (("ln_finalize_kernel", "ln_finalize"), ("unpack_kernel", "unpack"), ("pack_kernel", "pack"),
-                      ("offsets_lengths_kernel", "offsets"), ("offsets_mask_kernel", "offsets"), ("fold_vectors_kernel", "fold_vectors"),
+                      ("offsets_lengths_kernel", "offsets"), ("offsets_mask_kernel", "offsets"),
+                      ("offsets_mask_chunks_kernel", "offsets"), ("fold_vectors_kernel", "fold_vectors"),
                       ("peak_mfma_kernel", "peak_mfma"), ("peak_read_kernel", "peak_read"),
                       ("copyBuffer", "device_copy")):
         if key in name:
@@ -217,14 +222,12 @@ def sweep_summary(path_json: str, out: str) -> None:
         md.append(f"| {r['batch']} | {r['max_seq']} | {r['valid_tokens']} | {r['ms_packed']:.3f} | "
                   f"{r['ms_all_tokens_valid']:.3f} | {r['speedup_from_removing_padding']:.2f}x |")
     md += ["",
-           f"Below about 600 tokens the forward is bound by its 85 dependent launches (offsets + 12 x 7): {min(small):.2f}-{max(small):.2f} ms, "
-           f"about {1e3 * min(small) / 85:.1f} us",
-           "per launch, of which about 2.5 us is the gap between dependent launches and the rest a kernel whose K loop a few dozen",
-           "tiles walk alone (a HIP-graph replay of the same launches takes the same time: the gaps are on the GPU side). The",
-           "output projection and FFN-down run split over K there (2-6 slices, added by the LayerNorm kernel that follows).",
-           "What remains per layer: GEMM #0, attention, GEMM #1, add-bias+residual+LayerNorm, GEMM #2 (+GELU), GEMM #3,",
-           "add-bias+residual+LayerNorm. The LayerNorm-folded pipeline (5 launches) does not help here: its residual epilogue has no",
-           "split-K form, so FFN-down walks K = 3072 on a dozen tiles (measured +1.5 % at 186 tokens); a whole-layer persistent",
+           f"Below about 600 tokens the forward is bound by its dependent launches: {min(small):.2f}-{max(small):.2f} ms. About 2.5 us of each is",
+           "the gap between dependent launches and the rest a kernel whose K loop a few dozen tiles walk alone (a HIP-graph",
+           "replay of the same launches takes the same time: the gaps are on the GPU side). Up to 208 tokens a layer is 5",
+           "launches, up to 320 it is 6 (LayerNorms inside the products that read them), beyond that 7: output projection and",
+           "FFN-down then run split over K, the slices added by the LayerNorm kernel that follows. The LayerNorm-folded",
+           "pipeline (5 launches) does not help here: its residual epilogue has no split-K form; a whole-layer persistent",
            "kernel needs grid-wide barriers, which cost more than the launch gaps they would replace.", "",
            "## Single encoder layer, batch 1 (the two absolute times the paper prints, Table III, A100 FP16)", "",
            "| seq | ms, layer only (`bt_encoder_layer_fwd`, HIP events, 200 launches) | ms, whole step (+ build_offsets, pack / unpack fused) | paper, A100 |",
