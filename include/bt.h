@@ -268,9 +268,8 @@ bt_status bt_encoder_prepare(const bt_layer* layers, int n_layers, float* d_fold
  * H / heads / F / ln_eps.  The workspace (sized by bt_layer_workspace_bytes) also
  * holds the ping-pong buffer between layers; d_x is not modified; d_y receives
  * the last layer's output.
- * d_fold == NULL: each layer runs as bt_encoder_layer_fwd does (7 launches per layer, 6 or 5 with few tokens, where the
- * LayerNorms run inside the products that read them; between layers the 5 round once less than bt_encoder_layer_fwd in a
- * loop would -- same function, last digits differ).
+ * d_fold == NULL: the result is that of bt_encoder_layer_fwd layer by layer, bit for bit (7 launches per layer, 6 or 5 with
+ * few tokens, where the LayerNorms run inside the products that read them).
  * d_fold from bt_encoder_prepare: the library MAY fold the LayerNorms into the GEMM epilogues
  * (5 launches per layer plus one normalisation at the end) and does so while
  * ceil(T/64) * ceil(H/128) <= 256 (up to about 2 700 tokens at H = 768) and there are

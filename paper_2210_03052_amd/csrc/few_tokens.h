@@ -8,7 +8,8 @@
 //   few_ln_gemm_kernel      C = act(LN(z) W^T + bias): every workgroup normalises the rows it multiplies, 16 or 32 of them,
 //                           while the first slabs of its weights are on their way
 // Included at the end of gemm.hip.
-// z stays fp32 between the two, so nothing is rounded that the LayerNorm kernel over K slices did not round either.
+// z stays fp32 between the two and is summed in the order of the product over K slices and the LayerNorm kernel behind it, the
+// statistics in the order of that kernel: a layer's output is the same bits in 5, 6 and 7 launches.
 
 namespace bt {
 
@@ -20,6 +21,37 @@ __device__ __forceinline__ void wait_younger(int younger) {
   else wait_younger<MAX - 1, TOT>(younger);
 }
 __device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(0xc07f); }  // lgkmcnt(0), other counters untouched
+
+// The LayerNorm kernel's arithmetic (layernorm.hip) with the roundings the compiler gives it there written out: a row normalised
+// here and one normalised by that kernel are the same bits.  Deviations are fused from the row sum; the output of rows of more
+// than one piece a lane starts from the rounded mean instead; the output's last multiply-add and its conversion to fp16 round
+// once, but twice from the third element on where a lane has one piece.
+__device__ __forceinline__ float ln_square(float v, float sum, float inv_h, float sq) {
+  const float d = __builtin_fmaf(-inv_h, sum, v);
+  return __builtin_fmaf(d, d, sq);
+}
+template <bool ONE_PIECE>
+__device__ __forceinline__ half8_t ln_out(const float4_t (&v)[2], float sum, float inv_h, float rstd, uint4_t gamma, uint4_t beta) {
+#pragma clang fp contract(off)
+  const half8_t g8 = __builtin_bit_cast(half8_t, gamma), b8 = __builtin_bit_cast(half8_t, beta);
+  const float mean = sum * inv_h;
+  half8_t o;
+  static_for<8>([&](auto e_c) {
+#pragma clang fp contract(off)
+    constexpr int e = decltype(e_c)::value;
+    const float x = v[e / 4][e % 4], d = ONE_PIECE ? __builtin_fmaf(-inv_h, sum, x) : x - mean;
+    float y = __builtin_fmaf(d * rstd, (float)g8[e], (float)b8[e]);
+    if constexpr (ONE_PIECE && e >= 2) asm volatile("" : "+v"(y));
+    o[e] = (half_t)y;
+  });
+  return o;
+}
+// Lower halves of two registers side by side, and the upper ones; a second swap puts them back.
+__device__ __forceinline__ void swap_halves(float& a, float& b) {
+  const auto t = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b), false, false);
+  a = __builtin_bit_cast(float, (unsigned)t[0]);
+  b = __builtin_bit_cast(float, (unsigned)t[1]);
+}
 
 // C [T,N] = act(LN(z) W^T + bias), y [T,K] = LN(z); z fp32 [T,K], K = 256 NL, N % 16 == 0.
 // NW wavefronts, block tile 16 MI x 16 NW; a wavefront owns 16 columns: its slabs of W (16 rows, 64 deep) go through a ring of
@@ -37,7 +69,10 @@ __global__ __launch_bounds__(NW * 64) void few_ln_gemm_kernel(
     half_t* __restrict__ C, half_t* __restrict__ y) {
   constexpr int K = 256 * NL, BM = MI * 16, RW = BM / NW;  // rows a wavefront normalises
   constexpr int SLAB = 2048, NCH = NL * 2;                 // bytes of a slab, chunks of a reduction
-  constexpr int PITCH = K * 2 + 16;                        // of a normalised row in LDS: 16 rows start in different banks
+  constexpr int PITCH = K * 2 + 16;                        // of a normalised row in LDS
+  // A lane holds pieces of eight columns, piece lane + 64 i of a row, as in the LayerNorm kernel: its sums are then the same
+  // sums.  The second pieces of 768 columns fill half a wavefront, so two rows share one (one row each: 1 us a layer more).
+  constexpr int SHARE = NL == 3 ? 2 : 1, TAILS = NL == 2 ? 0 : RW / SHARE;  // rows to a second piece, second pieces
   static_assert(RW == 2 || RW == 4, "rows per wavefront");
   static_assert(NC <= NCH, "ring");
   __shared__ __attribute__((aligned(1024))) char s_ring[NW * NC * 2 * SLAB];
@@ -57,21 +92,33 @@ __global__ __launch_bounds__(NW * 64) void few_ln_gemm_kernel(
 
   // Rows, gamma, beta and bias, behind them the whole ring, and the wait for all but the ring, as ONE statement: the compiler does
   // not count the DMA requests and would wait for them too before it touches a row.
-  const uint32_t vz = lane * 16, vh = lane * 8, vb = (uint32_t)min(n0 + 4 * quad, N - 4) * 2;
+  const int tail_lane = lane & (kWave / SHARE - 1), tail_row = lane / (kWave / SHARE);
+  const uint32_t vh = lane * 16, vz = vh * 2, th = (kWave + tail_lane) * 16;
+  const uint32_t vb = (uint32_t)min(n0 + 4 * quad, N - 4) * 2;
   const int row0 = m0 + wave * RW;
-  const float* zr[4];
+  auto clamped = [&](int r) { return min(row0 + r, T - 1); };  // rows past T: never stored
+  const float *zr[RW], *zt[4];
+  uint32_t tz[4];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) zr[r] = z + (size_t)min(row0 + min(r, RW - 1), T - 1) * K;  // rows past T: clamped, never stored
-  float4_t v[4][4];
-  uint2_t gm[4], be[4], bs;
-#define BT_ROW_1(r) "global_load_dwordx4 %[z" #r "0], %[vz], %[b" #r "]\n\t"
-#define BT_ROW_2(r) BT_ROW_1(r) "global_load_dwordx4 %[z" #r "1], %[vz], %[b" #r "] offset:1024\n\t"
-#define BT_ROW_3(r) BT_ROW_2(r) "global_load_dwordx4 %[z" #r "2], %[vz], %[b" #r "] offset:2048\n\t"
-#define BT_ROW_4(r) BT_ROW_3(r) "global_load_dwordx4 %[z" #r "3], %[vz], %[b" #r "] offset:3072\n\t"
-#define BT_VEC_1(x) "global_load_dwordx2 %[" #x "0], %[vh], %[" #x "]\n\t"
-#define BT_VEC_2(x) BT_VEC_1(x) "global_load_dwordx2 %[" #x "1], %[vh], %[" #x "] offset:512\n\t"
-#define BT_VEC_3(x) BT_VEC_2(x) "global_load_dwordx2 %[" #x "2], %[vh], %[" #x "] offset:1024\n\t"
-#define BT_VEC_4(x) BT_VEC_3(x) "global_load_dwordx2 %[" #x "3], %[vh], %[" #x "] offset:1536\n\t"
+  for (int r = 0; r < RW; ++r) zr[r] = z + (size_t)clamped(r) * K;
+#pragma unroll
+  for (int p = 0; p < TAILS; ++p) {
+    zt[p] = zr[p * SHARE];
+    tz[p] = th * 2 + (tail_row ? (uint32_t)(clamped(p * SHARE + 1) - clamped(p * SHARE)) * (K * 4) : 0u);
+  }
+  float4_t v[RW][2], t[4][2];
+  uint4_t gm[2], be[2];
+  uint2_t bs;
+#define BT_ROW(r) "global_load_dwordx4 %[z" #r "0], %[vz], %[b" #r "]\n\tglobal_load_dwordx4 %[z" #r "1], %[vz], %[b" #r "] offset:16\n\t"
+#define BT_TAIL(p) "global_load_dwordx4 %[t" #p "0], %[u" #p "], %[c" #p "]\n\tglobal_load_dwordx4 %[t" #p "1], %[u" #p "], %[c" #p "] offset:16\n\t"
+#define BT_VEC "global_load_dwordx4 %[g0], %[vh], %[g]\n\tglobal_load_dwordx4 %[e0], %[vh], %[e]\n\t"
+#define BT_TAIL_VEC "global_load_dwordx4 %[g1], %[th], %[g]\n\tglobal_load_dwordx4 %[e1], %[th], %[e]\n\t"
+#define BT_ROWS_2 BT_ROW(0) BT_ROW(1) BT_VEC
+#define BT_ROWS_4 BT_ROW(0) BT_ROW(1) BT_ROW(2) BT_ROW(3) BT_VEC
+#define BT_TAILS_0
+#define BT_TAILS_1 BT_TAIL(0) BT_TAIL_VEC
+#define BT_TAILS_2 BT_TAIL(0) BT_TAIL(1) BT_TAIL_VEC
+#define BT_TAILS_4 BT_TAIL(0) BT_TAIL(1) BT_TAIL(2) BT_TAIL(3) BT_TAIL_VEC
 #define BT_RING                                    \
   "global_load_dwordx2 %[bs], %[vb], %[bias]\n\t"  \
   ".set bt_ring_at, 0\n\t"                         \
@@ -86,75 +133,90 @@ __global__ __launch_bounds__(NW * 64) void few_ln_gemm_kernel(
   ".set bt_ring_at, bt_ring_at + 0x800\n\t"        \
   ".endr\n\t"                                      \
   "s_waitcnt vmcnt(%c[dma])"
-#define BT_ROW_OUT_1(r) [z##r##0] "=&v"(v[r][0])
-#define BT_ROW_OUT_2(r) BT_ROW_OUT_1(r), [z##r##1] "=&v"(v[r][1])
-#define BT_ROW_OUT_3(r) BT_ROW_OUT_2(r), [z##r##2] "=&v"(v[r][2])
-#define BT_ROW_OUT_4(r) BT_ROW_OUT_3(r), [z##r##3] "=&v"(v[r][3])
-#define BT_VEC_OUT_1(x, a) [x##0] "=&v"(a[0])
-#define BT_VEC_OUT_2(x, a) BT_VEC_OUT_1(x, a), [x##1] "=&v"(a[1])
-#define BT_VEC_OUT_3(x, a) BT_VEC_OUT_2(x, a), [x##2] "=&v"(a[2])
-#define BT_VEC_OUT_4(x, a) BT_VEC_OUT_3(x, a), [x##3] "=&v"(a[3])
-#define BT_IN                                                                                                    \
-  [vz] "v"(vz), [vh] "v"(vh), [vb] "v"(vb), [b0] "s"(zr[0]), [b1] "s"(zr[1]), [g] "s"(gamma), [e] "s"(beta),     \
-      [bias] "s"(bias), [w] "s"(W), [lds] "s"(ring), [slabs] "n"(2 * NC), [dma] "n"(4 * NC)
-#define BT_LOAD_2(L)                                                                                             \
-  asm volatile(BT_ROW_##L(0) BT_ROW_##L(1) BT_VEC_##L(g) BT_VEC_##L(e) BT_RING                                   \
-               : BT_ROW_OUT_##L(0), BT_ROW_OUT_##L(1), BT_VEC_OUT_##L(g, gm), BT_VEC_OUT_##L(e, be),             \
-                 [bs] "=&v"(bs), [w0] "+&v"(w0), [w1] "+&v"(w1)                                                  \
-               : BT_IN                                                                                           \
+#define BT_ROW_OUT(r) [z##r##0] "=&v"(v[r][0]), [z##r##1] "=&v"(v[r][1])
+#define BT_TAIL_OUT(p) , [t##p##0] "=&v"(t[p][0]), [t##p##1] "=&v"(t[p][1])
+#define BT_TAIL_VEC_OUT , [g1] "=&v"(gm[1]), [e1] "=&v"(be[1])
+#define BT_ROWS_OUT_2 BT_ROW_OUT(0), BT_ROW_OUT(1)
+#define BT_ROWS_OUT_4 BT_ROW_OUT(0), BT_ROW_OUT(1), BT_ROW_OUT(2), BT_ROW_OUT(3)
+#define BT_TAILS_OUT_0
+#define BT_TAILS_OUT_1 BT_TAIL_OUT(0) BT_TAIL_VEC_OUT
+#define BT_TAILS_OUT_2 BT_TAIL_OUT(0) BT_TAIL_OUT(1) BT_TAIL_VEC_OUT
+#define BT_TAILS_OUT_4 BT_TAIL_OUT(0) BT_TAIL_OUT(1) BT_TAIL_OUT(2) BT_TAIL_OUT(3) BT_TAIL_VEC_OUT
+#define BT_ROWS_IN_2 [b0] "s"(zr[0]), [b1] "s"(zr[1])
+#define BT_ROWS_IN_4 BT_ROWS_IN_2, [b2] "s"(zr[2]), [b3] "s"(zr[3])
+#define BT_TAIL_IN(p) , [u##p] "v"(tz[p]), [c##p] "s"(zt[p])
+#define BT_TAILS_IN_0
+#define BT_TAILS_IN_1 , [th] "v"(th) BT_TAIL_IN(0)
+#define BT_TAILS_IN_2 BT_TAILS_IN_1 BT_TAIL_IN(1)
+#define BT_TAILS_IN_4 BT_TAILS_IN_2 BT_TAIL_IN(2) BT_TAIL_IN(3)
+#define BT_LOAD(R, P)                                                                                                          \
+  asm volatile(BT_ROWS_##R BT_TAILS_##P BT_RING                                                                                \
+               : BT_ROWS_OUT_##R BT_TAILS_OUT_##P, [g0] "=&v"(gm[0]), [e0] "=&v"(be[0]), [bs] "=&v"(bs), [w0] "+&v"(w0), [w1] "+&v"(w1) \
+               : BT_ROWS_IN_##R BT_TAILS_IN_##P, [vz] "v"(vz), [vh] "v"(vh), [vb] "v"(vb), [g] "s"(gamma), [e] "s"(beta),      \
+                 [bias] "s"(bias), [w] "s"(W), [lds] "s"(ring), [slabs] "n"(2 * NC), [dma] "n"(4 * NC)                         \
                : "memory", "m0", "scc")
-#define BT_LOAD_4(L)                                                                                             \
-  asm volatile(BT_ROW_##L(0) BT_ROW_##L(1) BT_ROW_##L(2) BT_ROW_##L(3) BT_VEC_##L(g) BT_VEC_##L(e) BT_RING       \
-               : BT_ROW_OUT_##L(0), BT_ROW_OUT_##L(1), BT_ROW_OUT_##L(2), BT_ROW_OUT_##L(3),                     \
-                 BT_VEC_OUT_##L(g, gm), BT_VEC_OUT_##L(e, be), [bs] "=&v"(bs), [w0] "+&v"(w0), [w1] "+&v"(w1)    \
-               : BT_IN, [b2] "s"(zr[2]), [b3] "s"(zr[3])                                                         \
-               : "memory", "m0", "scc")
-  if constexpr (RW == 2) {
-    if constexpr (NL == 2) BT_LOAD_2(2);
-    else if constexpr (NL == 3) BT_LOAD_2(3);
-    else BT_LOAD_2(4);
-  } else {
-    if constexpr (NL == 2) BT_LOAD_4(2);
-    else if constexpr (NL == 3) BT_LOAD_4(3);
-    else BT_LOAD_4(4);
-  }
-#undef BT_LOAD_2
-#undef BT_LOAD_4
+  if constexpr (RW == 2 && TAILS == 0) BT_LOAD(2, 0);
+  if constexpr (RW == 2 && TAILS == 1) BT_LOAD(2, 1);
+  if constexpr (RW == 2 && TAILS == 2) BT_LOAD(2, 2);
+  if constexpr (RW == 4 && TAILS == 0) BT_LOAD(4, 0);
+  if constexpr (RW == 4 && TAILS == 2) BT_LOAD(4, 2);
+  if constexpr (RW == 4 && TAILS == 4) BT_LOAD(4, 4);
+#undef BT_LOAD
 
-  // two-pass statistics in fp32, normalised rows to LDS in fp16
+  // Two-pass statistics in fp32, normalised rows to LDS in fp16.  tails(s, add): add(p, s) goes on with the sums s of the rows of
+  // second piece p, in the lanes that hold them.
   constexpr float inv_k = 1.0f / (float)K;
-  float rstd[RW];
+  auto tails = [&](float (&s)[RW], auto&& add) {
+    static_for<TAILS>([&](auto p_c) {
+      constexpr int a = decltype(p_c)::value * SHARE, b = a + SHARE - 1;
+      if constexpr (SHARE == 2) swap_halves(s[a], s[b]);  // the lanes 0 to 31 of both rows
+      add(p_c, s[a]);
+      if constexpr (SHARE == 2) swap_halves(s[a], s[b]);
+    });
+  };
+  auto of_tail = [&](const float (&s)[RW], auto p_c) {
+    constexpr int a = decltype(p_c)::value * SHARE, b = a + SHARE - 1;
+    return tail_row ? s[b] : s[a];
+  };
+  float sum[RW], sq[RW], rstd[RW];
 #pragma unroll
   for (int r = 0; r < RW; ++r) {
-    float s = 0.f;
+    sum[r] = 0.f;
 #pragma unroll
-    for (int l = 0; l < NL; ++l) s += (v[r][l][0] + v[r][l][1]) + (v[r][l][2] + v[r][l][3]);
-    const float mean = wave_sum(s) * inv_k;
-#pragma unroll
-    for (int l = 0; l < NL; ++l)
-#pragma unroll
-      for (int t = 0; t < 4; ++t) v[r][l][t] -= mean;
+    for (int e = 0; e < 8; ++e) sum[r] += v[r][e / 4][e % 4];
   }
+  tails(sum, [&](auto p_c, float& s) {
+    constexpr int p = decltype(p_c)::value;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s += t[p][e / 4][e % 4];
+  });
 #pragma unroll
   for (int r = 0; r < RW; ++r) {
-    float q = 0.f;
+    sum[r] = wave_sum(sum[r]);
+    sq[r] = 0.f;
 #pragma unroll
-    for (int l = 0; l < NL; ++l)
-#pragma unroll
-      for (int t = 0; t < 4; ++t) q = __builtin_fmaf(v[r][l][t], v[r][l][t], q);
-    rstd[r] = rsqrtf(wave_sum(q) * inv_k + eps);
-  }
-#pragma unroll
-  for (int l = 0; l < NL; ++l) {
-    const half4_t g4 = __builtin_bit_cast(half4_t, gm[l]), b4 = __builtin_bit_cast(half4_t, be[l]);
-#pragma unroll
-    for (int r = 0; r < RW; ++r) {
-      half4_t o;
-#pragma unroll
-      for (int t = 0; t < 4; ++t) o[t] = (half_t)(v[r][l][t] * rstd[r] * (float)g4[t] + (float)b4[t]);
-      *reinterpret_cast<half4_t*>(s_a + (wave * RW + r) * PITCH + lane * 8 + l * 512) = o;
+    for (int k = 0; k < 8; ++k) {
+      const int e = k < 2 ? 1 - k : k;  // the first two the other way round, as there
+      sq[r] = ln_square(v[r][e / 4][e % 4], sum[r], inv_k, sq[r]);
     }
   }
+  tails(sq, [&](auto p_c, float& q) {
+    constexpr int p = decltype(p_c)::value;
+    const float s = of_tail(sum, p_c);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) q = ln_square(t[p][e / 4][e % 4], s, inv_k, q);
+  });
+#pragma unroll
+  for (int r = 0; r < RW; ++r) rstd[r] = rsqrtf(__builtin_fmaf(inv_k, wave_sum(sq[r]), eps));
+  char* const rows_at = s_a + wave * RW * PITCH;
+#pragma unroll
+  for (int r = 0; r < RW; ++r)
+    *reinterpret_cast<half8_t*>(rows_at + r * PITCH + vh) = ln_out<TAILS == 0>(v[r], sum[r], inv_k, rstd[r], gm[0], be[0]);
+  static_for<TAILS>([&](auto p_c) {
+    constexpr int p = decltype(p_c)::value;
+    *reinterpret_cast<half8_t*>(rows_at + (p * SHARE + tail_row) * PITCH + th) =
+        ln_out<false>(t[p], of_tail(sum, p_c), inv_k, of_tail(rstd, p_c), gm[1], be[1]);
+  });
   wait_lds();
   __builtin_amdgcn_s_barrier();
 
@@ -229,13 +291,15 @@ __global__ __launch_bounds__(NW * 64) void few_ln_gemm_kernel(
 
 // z [T,N] = A W^T + residual + bias, fp32; A fp16 [T,K], K % 64 == 0, N % 8 == 0; row m of the residual is row
 // resid_rows[m] of `resid` where given (pack fused into the read).
-// WK wavefronts, block tile 16 MI x 16 NI: every wavefront multiplies the whole tile over its share of the K/64 slabs, from a ring
-// of NS slabs of its own (no barrier until the parts are added).
+// WK wavefronts, block tile 16 MI x 16 NI: a wavefront multiplies the whole tile over one slice of the reduction, `per` of the K/64
+// slabs, from a ring of NS slabs of its own (no barrier until the parts are added).  The slices are those of the product over K
+// slices and are added in their order, then residual, then bias: z is what the LayerNorm kernel over K slices normalises, bit for
+// bit, and a layer's output does not depend on which form made it.  Wavefronts past the last slice add zeros.
 // Bound: operand bytes per compute unit.  768 columns, K = 768 / 3072: 30 tokens 2.7 / 4.4 us, 90 tokens 3.1 / 5.4 us, 256 tokens 3.3 /
 // 6.4 us; the products over K slices 3.0 / 4.1, 3.0 / 4.2 and 3.4 / 5.1 us, but they leave 4 to 8 slices to be added.
 template <int MI, int NI, int WK, int NS>
 __global__ __launch_bounds__(WK * 64) void few_resid_gemm_kernel(
-    const half_t* __restrict__ A, const half_t* __restrict__ W, int T, int N, int K, int tiles_m,
+    const half_t* __restrict__ A, const half_t* __restrict__ W, int T, int N, int K, int per,
     const half_t* __restrict__ resid, const int32_t* __restrict__ resid_rows, const half_t* __restrict__ bias,
     float* __restrict__ z) {
   constexpr int BM = MI * 16, BN = NI * 16, LA = BM / 8, LB = BN / 8, TOT = LA + LB;
@@ -247,9 +311,9 @@ __global__ __launch_bounds__(WK * 64) void few_resid_gemm_kernel(
   __shared__ __attribute__((aligned(1024))) char smem[WK * NS * SLAB];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, quad = lane >> 4;
-  const int id = xcd_remap(blockIdx.x, gridDim.x);
+  const int id = xcd_remap(blockIdx.x, gridDim.x), tiles_m = (T + BM - 1) / BM;
   const int tn = id / tiles_m, m0 = (id - tn * tiles_m) * BM, n0 = tn * BN;
-  const int nk = K / 64, s0 = wave * nk / WK, my = (wave + 1) * nk / WK - s0;
+  const int s0 = wave * per, my = s0 < K / 64 ? per : 0;
 
   const int r8 = lane >> 3;
   const uint32_t chunk = (uint32_t)((lane & 7) ^ (r8 >> 1)) * 16;
@@ -382,17 +446,25 @@ bt_status few_ln_gemm_dispatch(const float* z, const bt_half* w, int T, int N, i
   return launch_status();
 }
 
-bt_status few_resid_gemm_dispatch(const bt_half* a, const bt_half* w, int T, int N, int K, const bt_half* resid,
+// slices: as gemm_splitk_choice gives them, 2 to 8 and a divisor of K/64
+bt_status few_resid_gemm_dispatch(const bt_half* a, const bt_half* w, int T, int N, int K, int slices, const bt_half* resid,
                                   const int32_t* resid_rows, const bt_half* bias, float* z, hipStream_t st) {
   auto h = [](const bt_half* p) { return reinterpret_cast<const half_t*>(p); };
+  if (slices < 1 || slices > 8 || K % (64 * slices) != 0) return BT_ERR_UNSUPPORTED;
 #define BT_LAUNCH(MI, NI, WK, NS)                                                                                   \
   do {                                                                                                              \
     const int tm = (T + MI * 16 - 1) / (MI * 16), tn = (N + NI * 16 - 1) / (NI * 16);                               \
-    few_resid_gemm_kernel<MI, NI, WK, NS><<<tm * tn, WK * 64, 0, st>>>(h(a), h(w), T, N, K, tm, h(resid), resid_rows, h(bias), z); \
+    few_resid_gemm_kernel<MI, NI, WK, NS><<<tm * tn, WK * 64, 0, st>>>(h(a), h(w), T, N, K, K / 64 / slices, h(resid), resid_rows, h(bias), z); \
   } while (0)
-  if (few_tiles(T, N, 16, 16) <= kFewRound) BT_LAUNCH(1, 1, 4, 3);
-  else if (few_tiles(T, N, 16, 32) <= kFewRound && K >= 2 * N) BT_LAUNCH(1, 2, 8, 3);
-  else BT_LAUNCH(2, 2, 4, 2);
+#define BT_SLICES(MI, NI, NS)                      \
+  do {                                             \
+    if (slices <= 4) BT_LAUNCH(MI, NI, 4, NS);     \
+    else BT_LAUNCH(MI, NI, 8, NS);                 \
+  } while (0)
+  if (few_tiles(T, N, 16, 16) <= kFewRound) BT_SLICES(1, 1, 3);
+  else if (few_tiles(T, N, 16, 32) <= kFewRound && K >= 2 * N) BT_SLICES(1, 2, 3);
+  else BT_SLICES(2, 2, 2);
+#undef BT_SLICES
 #undef BT_LAUNCH
   return launch_status();
 }

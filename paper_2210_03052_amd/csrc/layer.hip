@@ -28,8 +28,8 @@ bt_status layernorm_dispatch(const bt_half* x, const float* xpart, int nsplit, c
 int gemm_splitk_choice(int M, int N, int K);
 bt_status gemm_splitk_dispatch(const bt_half* A, const bt_half* W, int M, int N, int K, int ksplit, float* partial,
                                hipStream_t st);
-bt_status few_resid_gemm_dispatch(const bt_half* a, const bt_half* w, int T, int N, int K, const bt_half* resid,
-                                  const int32_t* resid_rows, const bt_half* bias, float* z, hipStream_t st);
+bt_status few_resid_gemm_dispatch(const bt_half* a, const bt_half* w, int T, int N, int K, int slices,
+                                  const bt_half* resid, const int32_t* resid_rows, const bt_half* bias, float* z, hipStream_t st);
 bt_status few_ln_gemm_dispatch(const float* z, const bt_half* w, int T, int N, int K, const bt_half* gamma, const bt_half* beta,
                                const bt_half* bias, float eps, bt_act act, bt_half* c, bt_half* y, hipStream_t st);
 // slices * M * N of any split gemm_splitk_choice allows: at most 256 tiles of 64 x 64 outputs
@@ -132,13 +132,15 @@ struct LayerIo {
 //                256: 33.3 / 31.3 / 32.4, 320: 32.9 / 31.2 / 32.1, 384: 34.3 / 37.8 / 40.5
 //   width 1024:   48 tokens 31.2 / 27.4 / 24.7, 128: 32.9 / 30.3 / 28.7, 160: 33.3 / 32.1 / 31.9, 192: 33.5 / 32.4 / 33.6,
 //                256: 36.1 / 34.8 / 35.9, 288: 37.0 / 42.8 / 45.5
-// The widths are those the kernel is built for: a row is 2, 3 or 4 loads of a wavefront.
+// The widths are those the kernel is built for: a row is 2, 3 or 4 loads of a wavefront.  Only where the other form splits both
+// products over K: an unsplit product leaves fp16, which z does not.
 enum Few { kFewNone = 0, kFewInner = 1, kFewBoth = 2 };
 static Few few_choice(int T, int H, int F) {
   if ((H != 512 && H != 768 && H != 1024) || (F % 64) != 0 || (size_t)T * H > kSplitKFloats) return kFewNone;
   if ((long long)F * H * 2 >= (1LL << 32) || (long long)T * F * 2 >= (1LL << 32)) return kFewNone;  // 32-bit byte offsets
   auto tiles = [&](int n, int bm, int bn) { return (long long)((T + bm - 1) / bm) * ((n + bn - 1) / bn); };
   if (tiles(F, 32, 128) > 256 || tiles(3 * H, 32, 128) > 256) return kFewNone;
+  if (gemm_splitk_choice(T, H, H) == 1 || gemm_splitk_choice(T, H, F) == 1) return kFewNone;
   return tiles(H, 16, 32) <= 320 ? kFewBoth : kFewInner;
 }
 
@@ -174,10 +176,10 @@ static bt_status layer_fwd(const bt_layer* l, const bt_half* x, const int32_t* c
   // units and the LayerNorm kernel adds the fp32 slices (no reduction kernel, no fp16 rounding in between).
   const int split1 = gemm_splitk_choice(T, H, H), split3 = gemm_splitk_choice(T, H, F);
   if (few != kFewNone) {
-    if ((s = few_resid_gemm_dispatch(w.attn, l->w_o, T, H, H, x, io.in_rows, l->b_o, z, st)) != BT_OK) return s;
+    if ((s = few_resid_gemm_dispatch(w.attn, l->w_o, T, H, H, split1, x, io.in_rows, l->b_o, z, st)) != BT_OK) return s;
     if ((s = few_ln_gemm_dispatch(z, l->w_1, T, F, H, l->ln0_g, l->ln0_b, l->b_1, l->ln_eps, act, w.g, w.y1, st)) != BT_OK)
       return s;
-    if (next) return few_resid_gemm_dispatch(w.g, l->w_2, T, H, F, w.y1, nullptr, l->b_2, z, st);
+    if (next) return few_resid_gemm_dispatch(w.g, l->w_2, T, H, F, split3, w.y1, nullptr, l->b_2, z, st);
   } else {
     if (split1 > 1) {
       if ((s = gemm_splitk_dispatch(w.attn, l->w_o, T, H, H, split1, w.splitk, st)) != BT_OK) return s;

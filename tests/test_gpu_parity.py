@@ -948,6 +948,45 @@ def test_few_tokens_stack_vs_oracle(bt, H, F, T):
     assert torch.equal(one, bt.encoder_fwd(layers[:1], dev(x), cu, S))
 
 
+@pytest.mark.parametrize("H,F", [(512, 2048), (768, 3072), (1024, 4096), (512, 1152), (512, 1344), (768, 1600), (1024, 1024)])
+@pytest.mark.parametrize("T", [1, 16, 17, 64, 65, 129, 160, 193, 209, 257, 320, 321, 449])
+def test_few_tokens_forms_keep_every_bit(bt, H, F, T):
+    """How many launches a layer takes is no matter of its result: a stack equals its layers called one by one, and a layer
+    equals the exported products, attention and LayerNorm over K slices in a row, bit for bit, at token counts on both sides
+    of every change of form, tile or number of slices (2 to 8)."""
+    import dataclasses
+    import torch
+    wl = dataclasses.replace(I.WORKLOADS["layer_b4_s64"], H=H, heads=H // 64, F=F, S=T)
+    L = np.array([T] if T < 3 else [T - T // 3 - T // 5, T // 5, T // 3], np.int32)
+    S, tanh = int(L.max()), T & 1
+    x = dev(I.make_hidden_packed(wl, T))
+    cu, tok, _ = bt.build_offsets(lengths=dev(L), S=S)
+    layers = [bt.Layer(I.make_layer_params(wl, i, True), gelu_kind=tanh) for i in range(3)]
+
+    def from_parts(layer, x):
+        t = layer.tensors
+
+        def normalised(a, w, bias, residual, gamma, beta):
+            y, slices = bt.gemm_kslices(a, w)
+            if slices is None:
+                return bt.add_bias_residual_layernorm(y, bias, residual, gamma, beta, layer.eps)
+            return bt.add_bias_residual_layernorm_kslices(slices, bias, residual, gamma, beta, layer.eps)
+
+        attn = bt.varlen_mha(bt.gemm_bias_act(x, t["w_qkv"], t["b_qkv"]), cu, S, layer.heads)
+        y1 = normalised(attn, t["w_o"], t["b_o"], x, t["ln0_g"], t["ln0_b"])
+        g = bt.gemm_bias_act(y1, t["w_1"], t["b_1"], bt.ACT_GELU_TANH if tanh else bt.ACT_GELU_ERF)
+        return normalised(g, t["w_2"], t["b_2"], y1, t["ln1_g"], t["ln1_b"])
+
+    ws = torch.empty(bt.layer_workspace_bytes(layers[0], T, len(L), S), dtype=torch.uint8, device="cuda:0").fill_(0xFF)
+    loop = x
+    for layer in layers:
+        parts = from_parts(layer, loop)
+        loop = bt.encoder_layer_fwd(layer, loop, cu, S, ws=ws)
+        assert torch.equal(loop, parts)
+    ws.fill_(0xFF)
+    assert torch.equal(bt.encoder_fwd(layers, x, cu, S, ws=ws), loop)
+
+
 def test_folded_stack_large_shape_in_its_token_range(bt):
     """Hidden 1024 / FFN 4096 / 16 heads with 1 455 tokens: inside the range where fold vectors select the folded
     pipeline at this width (enough tokens not to split K, few enough for one round of 64 x 128 tiles).  Every
