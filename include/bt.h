@@ -69,10 +69,13 @@ const char* bt_status_string(bt_status s);
  *     the total there as soon as it is known and the host polls for it; the stream is
  *     NOT synchronised (d_cu_seqlens / d_token_idx are ready for later work on the same
  *     stream, as for any other call).  About 20 us less host latency per batch.  Each
- *     thread that calls concurrently needs its own h_total.
+ *     thread that calls concurrently needs its own h_total.  On return d_mask has been read
+ *     in full and may be refilled from anywhere; d_lengths of more than 16 sentences may
+ *     still be read, and both outputs written, until the stream has passed the call.
  * A length outside [0,S] or a mask entry outside {0,1} is detected on the device and
- * reported as BT_ERR_INVALID_ARG after the kernel has run (*h_total = 0, the other
- * outputs are then unspecified).  Requires 1 <= S <= BT_MAX_SEQ, B*S < 2^31.
+ * reported as BT_ERR_INVALID_ARG (*h_total = 0; the other outputs are then unspecified and,
+ * with a pinned h_total, may still be written until the stream has passed the call).
+ * Requires 1 <= S <= BT_MAX_SEQ, B*S < 2^31.
  * Because the call waits for a device result it cannot be recorded into a HIP graph:
  * on a stream that is being captured it returns BT_ERR_UNSUPPORTED and enqueues nothing
  * (build the offsets before the capture; every other call of this library captures as it is).

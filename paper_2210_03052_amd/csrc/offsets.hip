@@ -1,5 +1,6 @@
 // Zero-padding algorithm (Sec. III-D, Fig. 4): prefix sum of the mask matrix,
 // position array, pack and unpack.  Integer / byte work: bit-exact.
+#include <atomic>
 #include <chrono>
 
 #include "common.h"
@@ -98,7 +99,7 @@ __global__ __launch_bounds__(kOffsetsThreads) void offsets_lengths_kernel(const 
   }
 }
 
-// Mask, more than 2^20 entries or with the per-sentence maximum.  One workgroup; the mask is read once and kept as bits in
+// Mask of 4 097 to 16 384 or more than 2^20 entries, or with the per-sentence maximum.  One workgroup; the mask is read once and kept as bits in
 // LDS.  A token's entry in token_idx is its flat index b*S + t, and its position is the number of ones before it in flat
 // order, so the mask is taken as
 // one flat string of 64-bit words whatever S is: one prefix sum over the popcounts of the words gives the base of
@@ -260,19 +261,28 @@ __global__ __launch_bounds__(256) void unpack_kernel(const uint4_t* __restrict__
 }
 
 // Mask, without the per-sentence maximum.  Workgroup w owns entries [w, w+1) * kMaskChunk, four a thread, and counts the ones
-// ahead of them itself: nothing is handed from one workgroup to the next.  The last one has read every entry and reports.
-// Bound: the last workgroup's read rate (about 90 GB/s).  The one-workgroup kernel above reads as much, then packs bits and
-// writes every position: 65 536 entries 16.4 us there, 5.5 us here; the whole call at 4 096 entries 14.7 / 12.4 us, at 65 536
-// 19.1 / 15.0, at 2^20 216 / 45.
+// ahead of them itself: nothing is handed from one workgroup to the next.  The last one has read every entry and knows the total,
+// but the host may refill the mask once it has that, so the total goes out with whichever workgroup has read its entries last:
+// each adds one to a counter, the last chunk's also the total, and the one that completes the count reports and clears it.
+// Bound: the last workgroup's read rate (2^20 entries, 4 MiB: 33 us more than the smallest call, 125 GB/s).  The one-workgroup kernel
+// above reads as much, then packs bits and writes every position: 65 536 entries 16.4 us there, 5.5 us here; the whole call at
+// 4 096 entries 14.6 / 12.7 us, at 65 536 18.9 / 16.1, at 2^20 213 / 46.  The counter is 0.6 to 0.9 us of that, so two to four
+// chunks stay with the kernel above (8 192 entries 15.0 / 15.2, 12 288 15.4 / 15.7, 16 384 15.7 / 15.7, 32 768 16.5 / 16.2).
 constexpr int kMaskChunk = 4 * kOffsetsThreads;
 // 2^20 entries: one workgroup per compute unit, all resident at once.  The entries read grow with the square of the chunks, and the
 // packed counts have 24 bits; larger masks stay with the kernel above.
-constexpr int kMaskChunksMax = 256;
+constexpr int kMaskChunksMax = 256, kMaskChunksFew = 4;
+// Counters of calls under way, zero in between; bits 0 to 15 workgroups, 16 to 47 the total, 48 an invalid entry.  A call holds one
+// from its launch until the total has arrived (a call beyond as many at a time takes the kernel above).
+constexpr int kMaskCounters = 64;
+__device__ unsigned long long mask_counters[kMaskCounters];
 
+// ONE: a single chunk, whose workgroup has nobody to wait for.
+template <bool ONE>
 __global__ __launch_bounds__(kOffsetsThreads) void offsets_mask_chunks_kernel(const int32_t* __restrict__ mask, int n, int B,
                                                                              int S, int32_t* __restrict__ cu,
                                                                              int32_t* __restrict__ token_idx,
-                                                                             int32_t* host_total) {
+                                                                             int32_t* host_total, int counter) {
   typedef int int4_t __attribute__((ext_vector_type(4)));
   constexpr int kAhead = 16, kBadBit = 24;  // loads in flight; the counts stay below 2^24
   __shared__ int s_part[kOffsetsWaves], s_before[kOffsetsWaves];
@@ -327,10 +337,20 @@ __global__ __launch_bounds__(kOffsetsThreads) void offsets_mask_chunks_kernel(co
   q += __builtin_amdgcn_update_dpp(0, q, 0x118, 0xf, 0xf, false);
   const int ahead = __builtin_amdgcn_readlane(q, 15), first = ahead & ((1 << kBadBit) - 1);
   const int total = first + __builtin_amdgcn_readlane(p, 15);
+  const bool bad = ahead >> kBadBit;
   if (tid == 0 && chunk == (int)gridDim.x - 1) {
-    const bool bad = ahead >> kBadBit;
     cu[B] = bad ? -1 : total;
-    publish_total(total, 0, bad, host_total, nullptr);
+    if (ONE) publish_total(total, 0, bad, host_total, nullptr);
+  }
+  if (!ONE && tid == 0 && host_total) {  // behind the barrier: every wavefront has its entries in registers
+    unsigned long long* const slot = mask_counters + counter;
+    unsigned long long count = 1;
+    if (chunk == (int)gridDim.x - 1) count += ((unsigned long long)total << 16) + ((unsigned long long)bad << 48);
+    count += __hip_atomic_fetch_add(slot, count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((count & 0xffff) == gridDim.x) {
+      __hip_atomic_store(slot, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ahead of the report, which releases it
+      publish_total((int)(count >> 16), 0, count >> 48 != 0, host_total, nullptr);
+    }
   }
   int at = first + (wave ? __builtin_amdgcn_readlane(p, wave - 1) : 0) + x - ones;
   int b = flat / S, r = flat - b * S;
@@ -348,6 +368,30 @@ __global__ __launch_bounds__(kOffsetsThreads) void offsets_mask_chunks_kernel(co
 }  // namespace bt
 
 using namespace bt;
+
+// One of the counters of offsets_mask_chunks_kernel, held by one call; index -1: all are held, or none was asked for.
+class MaskCounter {
+ public:
+  explicit MaskCounter(bool wanted) {
+    uint64_t b = wanted ? held.load(std::memory_order_relaxed) : ~0ull;
+    while (~b && index < 0) {
+      const int i = __builtin_ctzll(~b);
+      if (held.compare_exchange_weak(b, b | 1ull << i, std::memory_order_acquire)) index = i;
+    }
+  }
+  ~MaskCounter() {
+    if (index >= 0 && !lost) held.fetch_and(~(1ull << index), std::memory_order_release);
+  }
+  MaskCounter(const MaskCounter&) = delete;
+  MaskCounter& operator=(const MaskCounter&) = delete;
+  int index = -1;
+  bool lost = false;  // the kernel may not have ended: never handed out again
+
+ private:
+  static std::atomic<uint64_t> held;
+};
+std::atomic<uint64_t> MaskCounter::held{0};
+static_assert(kMaskCounters == 64, "a bit each");
 
 // Shared body of bt_build_offsets / bt_build_offsets_stats.  h_out[0] receives the total; with `stats`
 // h_out[1] receives the largest per-sentence count and d_cu_seqlens has B+2 entries (the last one is
@@ -380,10 +424,12 @@ static bt_status build_offsets_impl(const int32_t* d_mask, const int32_t* d_leng
   if (h_dev) *slot = kPending;
   // B == 0 runs the same kernel: it writes cu[0] = 0 and a total of 0 (no memset, no special case)
   int32_t* const d_max = stats ? d_cu_seqlens + B + 1 : nullptr;
-  const int n = B * S;
-  if (d_mask && !stats && n > 0 && n <= kMaskChunksMax * kMaskChunk) {
-    offsets_mask_chunks_kernel<<<(n + kMaskChunk - 1) / kMaskChunk, kOffsetsThreads, 0, st>>>(d_mask, n, B, S, d_cu_seqlens,
-                                                                                             d_token_idx, h_dev);
+  const int n = B * S, chunks = (int)(((int64_t)n + kMaskChunk - 1) / kMaskChunk);
+  const bool by_chunks = d_mask && !stats && n > 0 && (chunks == 1 || chunks > kMaskChunksFew) && chunks <= kMaskChunksMax;
+  MaskCounter counter(by_chunks && chunks > 1 && h_dev);
+  if (by_chunks && (chunks == 1 || !h_dev || counter.index >= 0)) {
+    auto* const kernel = chunks == 1 ? offsets_mask_chunks_kernel<true> : offsets_mask_chunks_kernel<false>;
+    kernel<<<chunks, kOffsetsThreads, 0, st>>>(d_mask, n, B, S, d_cu_seqlens, d_token_idx, h_dev, counter.index);
   } else if (d_mask) {
     offsets_mask_kernel<<<1, kOffsetsThreads, 0, st>>>(d_mask, B, S, d_cu_seqlens, d_token_idx, h_dev, d_max);
   } else {  // one wavefront per sentence, up to one workgroup per compute unit
@@ -391,7 +437,7 @@ static bt_status build_offsets_impl(const int32_t* d_mask, const int32_t* d_leng
     offsets_lengths_kernel<<<wgs < 1 ? 1 : (wgs > 256 ? 256 : wgs), kOffsetsThreads, 0, st>>>(
         d_lengths, B, S, d_cu_seqlens, d_token_idx, h_dev, d_max);
   }
-  if (hipGetLastError() != hipSuccess) return BT_ERR_HIP;
+  if (hipGetLastError() != hipSuccess) return counter.lost = true, BT_ERR_HIP;
   int32_t res[2] = {kPending, 0};
   if (h_dev) {
     const auto t0 = std::chrono::steady_clock::now();
@@ -407,8 +453,8 @@ static bt_status build_offsets_impl(const int32_t* d_mask, const int32_t* d_leng
   if (res[0] == kPending) {  // pageable h_out, or the store has not shown up: copy and synchronise
     if (hipMemcpyAsync(res, d_cu_seqlens + B, (stats ? 2 : 1) * sizeof(int32_t), hipMemcpyDeviceToHost, st) !=
         hipSuccess)
-      return BT_ERR_HIP;
-    if (hipStreamSynchronize(st) != hipSuccess) return BT_ERR_HIP;
+      return counter.lost = true, BT_ERR_HIP;
+    if (hipStreamSynchronize(st) != hipSuccess) return counter.lost = true, BT_ERR_HIP;
   }
   h_out[0] = res[0] < 0 ? 0 : res[0];
   if (stats) h_out[1] = res[0] < 0 ? 0 : res[1];

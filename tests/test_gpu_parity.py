@@ -91,6 +91,47 @@ def test_offsets_from_mask_across_chunks(bt, B, S, skew):
         given.view(-1)[at] = 1
 
 
+def test_mask_may_be_refilled_on_return(bt):
+    """With a pinned total the mask has been read in full when the call returns: refilled at once on another stream, offsets and
+    positions are still those of the batch.  Several threads with streams of their own, one to 256 workgroups a call, calls with
+    an invalid entry among them."""
+    import threading
+    import torch
+    bt.build_offsets(mask=dev(np.ones((2, 8), np.int32)))
+    failed = []
+
+    def caller(k):
+        rng = np.random.default_rng(k)
+        mine, other = torch.cuda.Stream(), torch.cuda.Stream()
+        with torch.cuda.stream(mine):
+            for B, S in [(3, 100), (4, 4096), (4097, 4), (64, 1024), (256, 4096), (9, 4095)] * 3:
+                mask = (rng.random((B, S)) < 0.6).astype(np.int32)
+                given = dev(mask)
+                spoilt = dev(1 - mask)
+                bad = given.clone()
+                bad.view(-1)[int(rng.integers(B * S))] = 3
+                mine.synchronize()
+                cu, tok, T = bt.build_offsets(mask=given)
+                with torch.cuda.stream(other):
+                    given.copy_(spoilt)
+                rcu, rtok, rT = O.build_offsets(mask)
+                if not (T == rT and np.array_equal(host(cu), rcu) and np.array_equal(host(tok), rtok)):
+                    failed.append((k, B, S))
+                try:
+                    bt.build_offsets(mask=bad)
+                    failed.append((k, B, S, "accepted"))
+                except bt.BtError:
+                    pass
+                other.synchronize()
+
+    threads = [threading.Thread(target=caller, args=(k,)) for k in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failed
+
+
 @pytest.mark.parametrize("name", list(I.WORKLOADS))
 def test_offsets_from_lengths_workloads(bt, name):
     wl = I.WORKLOADS[name]

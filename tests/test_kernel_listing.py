@@ -150,3 +150,16 @@ def test_layernorm_rows_are_one_memory_round_trip(kernels):
         first = next(i for i, ins in enumerate(body) if ins.startswith("global_load_dwordx4"))
         wait = next(i for i, ins in enumerate(body) if i > first and ins.startswith("s_waitcnt") and "vmcnt" in ins)
         assert sum(ins.startswith("global_load_dwordx4") for ins in body[first:wait]) == 5 * cpl, cpl
+
+
+def test_mask_total_is_reported_behind_every_workgroup(kernels):
+    """The kernel with a workgroup per 4 096 mask entries may tell the host the total only when all of them have read theirs, since
+    the host is free to refill the mask then: the workgroup that reports is the one whose counter increment came back complete."""
+    bodies = {n: b for n, b in kernels.items() if "offsets_mask_chunks_kernel" in n}
+    assert bodies
+    for name, body in bodies.items():
+        counted = [i for i, t in enumerate(body) if t.startswith("global_atomic_add_x2") and "sc0" in t]  # sc0: returns the old value
+        reported = [i for i, t in enumerate(body) if re.match(r"(global|flat)_store_dword\b", t) and "sc0 sc1" in t]  # system scope
+        one_workgroup = "ILb1E" in name
+        assert reported and len(counted) == (0 if one_workgroup else 1), name
+        assert one_workgroup or min(reported) > counted[0], name
