@@ -50,7 +50,8 @@ static inline const half_t* hp(const bt_half* p) { return reinterpret_cast<const
 //   qkv [T,3H] | attn [T,H] | proj [T,H] (GEMM1 and GEMM3 output) | y1 [T,H] | g [T,F] | ping [T,H] |
 //   pong [T,H] | part1 [T, H/64] float2 | part2 [T, H/64] float2   (partial row sums of the two LayerNorms;
 //   a column tile of the producing GEMM is at least 64 wide, so H/64 slots per row always suffice)
-//   | splitk fp32 [kSplitKFloats]   (K slices of GEMM1 / GEMM3 when the token count is small)
+//   | splitk fp32 [kSplitKFloats]   (with few tokens: K slices of GEMM1 / GEMM3, or z [T,H], the input of a LayerNorm that runs in
+//   the product behind it, between two launches and between two layers)
 struct Workspace {
   bt_half *qkv, *attn, *proj, *y1, *g, *ping, *pong;
   float2 *part1, *part2;
@@ -123,15 +124,21 @@ struct LayerIo {
 // kFewBoth, also LN1 inside the QKV product of the next layer (5 launches).
 //
 // Inner while the 32 x 128 tiles of FFN-up are one round of the compute units: up to there the product with the LayerNorm
-// inside is the faster, in the second round it pays for the rows every column tile normalises anew.  Both while FFN-down,
-// whose whole reduction is then one workgroup's, has at most 320 tiles of 16 x 32.
-// Microseconds per layer, six layers, seven launches / Inner / Both:
-//   width 512:    48 tokens 25.7 / 22.4 / 20.0, 128: 26.8 / 23.6 / 20.8, 256: 29.5 / 27.4 / 24.9, 320: 27.8 / 27.0 / 26.1,
-//                384: 28.3 / 27.2 / 27.6, 512: 29.4 / 27.8 / 29.0, 620: 31.6 / 34.5 / 35.5
-//   width 768:    48 tokens 29.2 / 25.5 / 22.4, 128: 31.0 / 28.1 / 25.7, 192: 31.7 / 30.1 / 29.3, 224: 31.7 / 29.9 / 29.9,
-//                256: 33.3 / 31.3 / 32.4, 320: 32.9 / 31.2 / 32.1, 384: 34.3 / 37.8 / 40.5
-//   width 1024:   48 tokens 31.2 / 27.4 / 24.7, 128: 32.9 / 30.3 / 28.7, 160: 33.3 / 32.1 / 31.9, 192: 33.5 / 32.4 / 33.6,
-//                256: 36.1 / 34.8 / 35.9, 288: 37.0 / 42.8 / 45.5
+// inside is the faster, in the second round it pays for the rows every column tile normalises anew.  Both while FFN-down has at
+// most 320 tiles of 16 x 32, and while what one of its workgroups reads stays below 640 KB: it walks the whole reduction, where
+// the other form's read a slice.
+// Microseconds per layer, graph replays of six layers, seven launches / Inner / Both:
+//   width 512,  F 2048:  48 tokens 26.1 / 22.8 / 20.2, 128: 26.8 / 23.8 / 21.0, 256: 28.6 / 26.6 / 24.0, 320: 28.2 / 27.1 / 25.8,
+//                        384: 28.7 / 27.7 / 27.5, 512: 29.7 / 28.3 / 28.7, 576: 30.9 / 33.6 / 34.2
+//   width 768,  F 3072:  48 tokens 29.7 / 26.1 / 23.1, 128: 31.6 / 28.9 / 25.9, 192: 32.5 / 30.7 / 29.8, 208: 31.9 / 30.2 / 29.7,
+//                        224: 32.2 / 30.4 / 30.0, 256: 32.7 / 30.7 / 31.4, 320: 33.3 / 31.6 / 32.2, 352: 34.2 / 37.7 / 39.4
+//   width 1024, F 4096:  48 tokens 31.9 / 27.8 / 24.9, 128: 33.5 / 30.7 / 28.6, 160: 33.6 / 32.2 / 31.8, 192: 34.0 / 32.7 / 33.2,
+//                        256: 35.3 / 33.5 / 33.8, 288: 36.9 / 42.5 / 44.6
+// F other than 4 H, in front of / behind each line: 1024, F 6144, 160 tokens (590 KB) 36.1 / 34.3 / 34.3, 192: 36.6 / 41.4 / 42.9;
+// 1024, F 8192, 64 tokens (524 KB) 34.2 / 31.1 / 28.8, 80 (786 KB): 36.9 / 36.6 / 37.6; 768, F 12288, 16 tokens (786 KB)
+// 34.7 / 31.2 / 34.4; 1024, F 16384, 16 tokens (1 MB) 43.8 / 40.8 / 44.6, 80: 46.9 / 53.2 / 60.5; 1024, F 2048, 256 tokens
+// 34.5 / 30.8 / 30.5, 320: 34.0 / 34.0 / 34.7; 768, F 2304, 448 tokens 33.6 / 33.0 / 33.4, 480: 35.6 / 39.9 / 44.4.  Where F is below
+// 4 H Both would hold to a few more tokens (512, F 512, 384: 26.5 / 24.7 / 23.6).
 // The widths are those the kernel is built for: a row is 2, 3 or 4 loads of a wavefront.  Only where the other form splits both
 // products over K: an unsplit product leaves fp16, which z does not.
 enum Few { kFewNone = 0, kFewInner = 1, kFewBoth = 2 };
@@ -141,7 +148,8 @@ static Few few_choice(int T, int H, int F) {
   auto tiles = [&](int n, int bm, int bn) { return (long long)((T + bm - 1) / bm) * ((n + bn - 1) / bn); };
   if (tiles(F, 32, 128) > 256 || tiles(3 * H, 32, 128) > 256) return kFewNone;
   if (gemm_splitk_choice(T, H, H) == 1 || gemm_splitk_choice(T, H, F) == 1) return kFewNone;
-  return tiles(H, 16, 32) <= 320 ? kFewBoth : kFewInner;
+  const long long down_bytes = (16 + (tiles(H, 16, 16) <= 256 ? 16 : 32)) * 2LL * F;  // of a workgroup, both operands
+  return tiles(H, 16, 32) <= 320 && down_bytes <= 640 * 1024 ? kFewBoth : kFewInner;
 }
 
 // One layer.  prev: the layer in front of this one, whose output exists only as its LayerNorm's input w.splitk (form for few

@@ -989,7 +989,8 @@ def test_few_tokens_stack_vs_oracle(bt, H, F, T):
     assert torch.equal(one, bt.encoder_fwd(layers[:1], dev(x), cu, S))
 
 
-@pytest.mark.parametrize("H,F", [(512, 2048), (768, 3072), (1024, 4096), (512, 1152), (512, 1344), (768, 1600), (1024, 1024)])
+@pytest.mark.parametrize("H,F", [(512, 2048), (768, 3072), (1024, 4096), (512, 1152), (512, 1344), (768, 1600), (1024, 1024),
+                                 (512, 8192), (1024, 8192)])
 @pytest.mark.parametrize("T", [1, 16, 17, 64, 65, 129, 160, 193, 209, 257, 320, 321, 449])
 def test_few_tokens_forms_keep_every_bit(bt, H, F, T):
     """How many launches a layer takes is no matter of its result: a stack equals its layers called one by one, and a layer
