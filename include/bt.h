@@ -219,6 +219,13 @@ typedef struct {
 size_t bt_layer_workspace_bytes(const bt_layer* layer, int T, int B, int max_len);
 
 /*
+ * How many launches a layer of width H and FFN width F takes for T packed tokens inside a stack without fold vectors
+ * (host only, nothing is launched): 7, or with few tokens 6 or 5, where LayerNorms run inside the products behind them.  The
+ * last layer of a stack, and a layer on its own, takes 6 where this says 5.  For reports; results do not depend on it.
+ */
+bt_status bt_layer_launches(int T, int H, int F, int* launches);
+
+/*
  * One padding-free post-LN BERT encoder layer on packed tokens, Fig. 2(c):
  *   QKV = x W_qkv^T + b_qkv;  A = varlen MHA(QKV);  y1 = LN(A W_o^T + b_o + x);
  *   y  = LN(GELU(y1 W_1^T + b_1) W_2^T + b_2 + y1).

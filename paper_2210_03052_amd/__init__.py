@@ -61,6 +61,7 @@ _SIGNATURES = {
                                                           _c.c_void_p, _c.c_float, _c.c_int, _c.c_int, _c.c_void_p,
                                                           _c.c_void_p]),
     "bt_layer_workspace_bytes": (_c.c_size_t, [_c.POINTER(bt_layer), _c.c_int, _c.c_int, _c.c_int]),
+    "bt_layer_launches": (_c.c_int, [_c.c_int, _c.c_int, _c.c_int, _c.POINTER(_c.c_int)]),
     "bt_encoder_layer_fwd": (_c.c_int, [_c.POINTER(bt_layer), _c.c_void_p, _c.c_void_p, _c.c_int, _c.c_int,
                                         _c.c_int, _c.c_void_p, _c.c_void_p, _c.c_size_t, _c.c_void_p]),
     "bt_encoder_layer_fwd_static": (_c.c_int, [_c.POINTER(bt_layer), _c.c_void_p, _c.c_void_p, _c.c_int, _c.c_int,
@@ -367,6 +368,13 @@ class Layer:
 
 def layer_workspace_bytes(layer: Layer, T, B, max_len):
     return int(load_library().bt_layer_workspace_bytes(_c.byref(layer.desc), T, B, max_len))
+
+
+def layer_launches(T, H, F):
+    """bt_layer_launches: launches a layer takes for T tokens inside a stack (7, with few tokens 6 or 5)."""
+    n = _c.c_int(0)
+    _call("bt_layer_launches", int(T), int(H), int(F), _c.byref(n))
+    return n.value
 
 
 def _workspace(layer, T, B, max_len, device):

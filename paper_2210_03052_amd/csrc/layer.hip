@@ -378,6 +378,12 @@ extern "C" size_t bt_layer_workspace_bytes(const bt_layer* layer, int T, int B, 
   return carve(nullptr, T, layer->H, layer->F).bytes;
 }
 
+extern "C" bt_status bt_layer_launches(int T, int H, int F, int* launches) {
+  if (T < 1 || H < 8 || F < 8 || (H % 8) != 0 || (F % 8) != 0 || !launches) return BT_ERR_INVALID_ARG;
+  *launches = 7 - (int)few_choice(T, H, F);
+  return BT_OK;
+}
+
 extern "C" bt_status bt_encoder_layer_fwd(const bt_layer* layer, const bt_half* d_x, const int32_t* d_cu_seqlens,
                                           int B, int T, int max_len, bt_half* d_y, void* d_ws, size_t ws_bytes,
                                           bt_stream stream) {

@@ -300,6 +300,13 @@ def main():
         if plain in work:
             work[folded] = work[plain]
 
+    # with few tokens: the same products with a LayerNorm in front or the residual behind (the latter is one kernel for two of
+    # them in a stack of five launches a layer)
+    for fused, plain in (("few_ln_gemm2_bias_gelu", "gemm2_bias_gelu"), ("few_ln_gemm0_qkv", "gemm0_qkv_bias"),
+                         ("few_gemm_resid", "gemm1_proj")):
+        if plain in work and (fused != "few_gemm_resid" or fused in bench.get("algorithmic_bytes", {})):
+            work[fused] = work[plain]
+
     md = [f"# rocprofv3 summary: bench.py, workload `{args.workload}`", ""]
     if bench.get("config"):
         c = bench["config"]

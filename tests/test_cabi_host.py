@@ -225,6 +225,21 @@ def test_gemm_tile_shape_query_is_host_only():
             bt.gemm_tile_shape(*bad)
 
 
+def test_layer_launches_query_is_host_only():
+    """bt_layer_launches: the last and first token counts of the three forms at the usual widths, and where the forms for few
+    tokens do not apply or stop early: K that is not split, other widths, a wide F whose FFN-down would read too much."""
+    for H, both, inner in ((512, 320, 512), (768, 208, 320), (1024, 160, 256)):
+        got = [bt.layer_launches(t, H, 4 * H) for t in (1, both, both + 1, inner, inner + 1, 5000)]
+        assert got == [5, 5, 6, 6, 7, 7], H
+    assert bt.layer_launches(100, 768, 3072 + 8) == bt.layer_launches(100, 640, 2560) == 7
+    assert bt.layer_launches(100, 512, 64) == bt.layer_launches(100, 512, 832) == 7       # one slab, thirteen slabs
+    assert bt.layer_launches(64, 1024, 8192) == bt.layer_launches(160, 1024, 6144) == 5
+    assert bt.layer_launches(65, 1024, 8192) == bt.layer_launches(16, 768, 12288) == bt.layer_launches(16, 1024, 16384) == 6
+    for bad in ((0, 768, 3072), (10, 7, 64), (10, 768, 60)):
+        with pytest.raises(bt.BtError):
+            bt.layer_launches(*bad)
+
+
 def test_gemm_row_split_query_is_host_only():
     """bt_gemm_row_split: products whose tile grid fills its rounds run as one launch (the four products of the
     headline layer, the long and the large workload's FFN-down); a grid a little past a whole number of rounds
