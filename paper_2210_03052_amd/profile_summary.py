@@ -216,7 +216,7 @@ def sweep_summary(path_json: str, out: str) -> None:
           "same kernels on the same batch with every sequence at full length, i.e. what a padded pipeline computes;",
           "the ratio is the gain from removing padding (Sec. III-D; the paper reports +24 % per layer at mean 0.6 max on A100).",
           "Each figure is the whole step (`bt_encoder_fwd_masked` = `bt_build_offsets` + `bt_encoder_fwd_padded`: 12 layers with pack / unpack fused into the",
-          "first / last kernels), 50 timed iterations.", "",
+          "first / last kernels), median of 50 timed steps.", "",
           "| batch | max_seq | valid tokens | ms packed | ms all tokens valid | gain |", "|---|---|---|---|---|---|"]
     for r in rows:
         md.append(f"| {r['batch']} | {r['max_seq']} | {r['valid_tokens']} | {r['ms_packed']:.3f} | "
