@@ -56,10 +56,12 @@ __device__ __forceinline__ void swap_halves(float& a, float& b) {
 // C [T,N] = act(LN(z) W^T + bias), y [T,K] = LN(z); z fp32 [T,K], K = 256 NL, N % 16 == 0.
 // NW wavefronts, block tile 16 MI x 16 NW; a wavefront owns 16 columns: its slabs of W (16 rows, 64 deep) go through a ring of
 // its own, NC chunks of two slabs, so that nothing but the normalised rows is shared and one barrier is all there is.
-// Bound: operand bytes per compute unit (z in fp32 and 16 NW rows of W at about 110 GB/s) behind one launch and one round trip.
-// Per launch, weights of twelve layers in turn, width 768, z to 2304 / 3072 + GELU columns: 48 tokens 5.1 / 5.2 us, 90 tokens
-// 5.1 / 5.6 us, 256 tokens 7.4 / 7.5 us, where the LayerNorm kernel over K slices (3.2 to 3.9 us) and the product (4.7 / 5.1 us)
-// took 8 to 9 us together.  One slab per hand-over without fragments read ahead took 6.3 us, a ring of 64-deep slabs
+// Bound: a chain of launch, round trip to z, row statistics and a K loop of its own per wavefront; no single unit is full.  186 tokens,
+// FFN-up of width 768: 7.4 us, in which LDS is active for 1.8 us of a compute unit's time, 0.6 of them bank conflicts of the reads of
+// the normalised rows (4 cycles a read, and all NW wavefronts read every row).
+// Per launch, weights of twelve layers in turn, graph replays, width 768, z to 2304 / 3072 + GELU columns: 48 tokens 5.2 / 5.2 us,
+// 90 tokens 5.2 / 5.8 us, 256 tokens 7.2 / 7.5 us, where the LayerNorm kernel over K slices (3.2 to 3.8 us) and the product (5.0 /
+// 5.4 us) take 8 to 9 us together.  One slab per hand-over without fragments read ahead took 6.3 us, a ring of 64-deep slabs
 // twice as long 5.4 us.
 template <int MI, int NW, int NC, int NL, int ACT>
 __global__ __launch_bounds__(NW * 64) void few_ln_gemm_kernel(
@@ -295,8 +297,8 @@ __global__ __launch_bounds__(NW * 64) void few_ln_gemm_kernel(
 // slabs, from a ring of NS slabs of its own (no barrier until the parts are added).  The slices are those of the product over K
 // slices and are added in their order, then residual, then bias: z is what the LayerNorm kernel over K slices normalises, bit for
 // bit, and a layer's output does not depend on which form made it.  Wavefronts past the last slice add zeros.
-// Bound: operand bytes per compute unit.  768 columns, K = 768 / 3072: 30 tokens 2.7 / 4.4 us, 90 tokens 3.1 / 5.4 us, 256 tokens 3.3 /
-// 6.4 us; the products over K slices 3.0 / 4.1, 3.0 / 4.2 and 3.4 / 5.1 us, but they leave 4 to 8 slices to be added.
+// Bound: operand bytes per compute unit.  768 columns, K = 768 / 3072, graph replays: 30 tokens 2.9 / 4.8 us, 90 tokens 3.3 / 5.7 us,
+// 256 tokens 3.4 / 6.6 us; the products over K slices 3.3 / 4.4, 3.4 / 4.4 and 3.6 / 5.3 us, but they leave 4 to 8 slices to be added.
 template <int MI, int NI, int WK, int NS>
 __global__ __launch_bounds__(WK * 64) void few_resid_gemm_kernel(
     const half_t* __restrict__ A, const half_t* __restrict__ W, int T, int N, int K, int per,

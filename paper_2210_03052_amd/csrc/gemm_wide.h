@@ -164,9 +164,9 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(
     constexpr int NM = MI * NI, NR = MI + NI;
     constexpr int RSPAN = NM * 3 / 4;  // the reads go into the first three quarters: they are back when the step ends
     static_for<NM>([&](auto m_c) {
-      // Back and forth over the columns: the MFMAs on both sides of a turn share both a row and, with the one before, a column
-      // fragment, and operands that do not change cost no switching.  On ordinary data the chip runs at its power limit, so
-      // that is time: 8 232 x 3072 x 768 42.9 -> 42.2 us, K = 1536 74.9 -> 74.2 (160 rows), 77 -> 76.1 (224 rows); on zeros level.
+      // Back and forth over the columns: at a turn the column fragment stays and the row changes, elsewhere the row stays, and
+      // operands that do not change cost no switching.  On ordinary data the chip runs at its power limit, so that is time, if
+      // little: 8 232 x 3072 x 768 42.9 -> 42.2 us on one card, level on zeros; whole stacks 0 to 1 % by card and run.
       constexpr int m = decltype(m_c)::value, i = m / NI, j = (i & 1) ? NI - 1 - m % NI : m % NI;
       constexpr int dlo = Q0 + m * (Q1 - Q0) / NM, dhi = Q0 + (m + 1) * (Q1 - Q0) / NM;
       static_assert(dhi - dlo <= 1, "at most one request per MFMA");

@@ -222,13 +222,14 @@ def sweep_summary(path_json: str, out: str) -> None:
         md.append(f"| {r['batch']} | {r['max_seq']} | {r['valid_tokens']} | {r['ms_packed']:.3f} | "
                   f"{r['ms_all_tokens_valid']:.3f} | {r['speedup_from_removing_padding']:.2f}x |")
     md += ["",
+           f"Slowest single step of the sweep: {d.get('slowest_step_ms', float('nan')):.1f} ms (a collection of the interpreter's garbage; the medians leave it out).", "",
            f"Below about 600 tokens the forward is bound by its dependent launches: {min(small):.2f}-{max(small):.2f} ms. About 2.5 us of each is",
            "the gap between dependent launches and the rest a kernel whose K loop a few dozen tiles walk alone (a HIP-graph",
            "replay of the same launches takes the same time: the gaps are on the GPU side). Up to 208 tokens a layer is 5",
            "launches, up to 320 it is 6 (LayerNorms inside the products that read them), beyond that 7: output projection and",
            "FFN-down then run split over K, the slices added by the LayerNorm kernel that follows. The LayerNorm-folded",
            "pipeline (5 launches) does not help here: its residual epilogue has no split-K form; a whole-layer persistent",
-           "kernel needs grid-wide barriers, which cost more than the launch gaps they would replace.", "",
+           "kernel needs grid-wide barriers, of which only a naive one was measured (15-18 us each, more than the gaps).", "",
            "## Single encoder layer, batch 1 (the two absolute times the paper prints, Table III, A100 FP16)", "",
            "| seq | ms, layer only (`bt_encoder_layer_fwd`, HIP events, 200 launches) | ms, whole step (+ build_offsets, pack / unpack fused) | paper, A100 |",
            "|---|---|---|---|"]
