@@ -269,8 +269,8 @@ __global__ __launch_bounds__(256) void unpack_kernel(const uint4_t* __restrict__
 // 4 096 entries 14.6 / 12.7 us, at 65 536 18.9 / 16.1, at 2^20 213 / 46.  The counter is 0.6 to 0.9 us of that, so two to four
 // chunks stay with the kernel above (8 192 entries 15.0 / 15.2, 12 288 15.4 / 15.7, 16 384 15.7 / 15.7, 32 768 16.5 / 16.2).
 constexpr int kMaskChunk = 4 * kOffsetsThreads;
-// 2^20 entries: one workgroup per compute unit, all resident at once.  The entries read grow with the square of the chunks, and the
-// packed counts have 24 bits; larger masks stay with the kernel above.
+// 2^20 entries: one workgroup per compute unit, all resident at once.  The entries read grow with the square of the chunks (0.5 GB
+// in all at 2^20, from the caches) and the packed counts have 24 bits; larger masks stay with the kernel above.
 constexpr int kMaskChunksMax = 256, kMaskChunksFew = 4;
 // Counters of calls under way, zero in between; bits 0 to 15 workgroups, 16 to 47 the total, 48 an invalid entry.  A call holds one
 // from its launch until the total has arrived (a call beyond as many at a time takes the kernel above).
