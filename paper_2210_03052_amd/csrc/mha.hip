@@ -2,7 +2,7 @@
 //
 // One kernel for every sequence length: a workgroup owns one (sequence, head,
 // tile of BQ = 32*NW query rows); it walks the sequence's own keys in tiles of
-// 64 and keeps the running row maximum / row sum (online softmax), so the
+// 64 and keeps a reference for the exponentials / row sum (online softmax), so the
 // L x L logit matrix never exists in memory and no padded row or column is
 // touched -- the valid range comes from cu_seqlens, the prefix sum of Sec. III-D.
 //
@@ -23,6 +23,8 @@
 // in memory.  Biases: b_q is added to the Q registers; b_k shifts every logit of
 // a row by the same amount and cancels in the softmax; b_v is added to the
 // output (the probabilities of a row sum to one).
+#include <type_traits>
+
 #include "common.h"
 
 namespace bt {
@@ -71,8 +73,8 @@ __device__ __forceinline__ FragAddr make_frag_addr(int lane) {
 }
 
 // One 64-key tile for the 32 query rows of a wavefront, step by step:  S^T = K Q^T (qk_tile);  mask of a
-// ragged last tile;  running maximum and rescale (softmax_max);  P = exp2(S - m), row sums, fp16 P
-// (softmax_exp);  O^T += V^T P^T (pv_tile).
+// ragged last tile;  then, per block of 32 keys, P = exp2(S - m), row sums, fp16 P (softmax_exp) and
+// O^T += V^T P^T (pv_block).
 __device__ __forceinline__ void qk_tile(const half_t* sk, const half8_t (&qf)[4], const FragAddr& fa,
                                         float16_t (&s)[2]) {
 #pragma unroll
@@ -108,31 +110,30 @@ __device__ __forceinline__ void both_halves(float x, float& lo, float& hi) {
   hi = __builtin_bit_cast(float, (unsigned)sw[1]);
 }
 
-// m_run is kept in the scaled log2 domain and is only raised when the tile maximum exceeds it by
-// more than 8 (a factor 256: probabilities stay <= 256, exact in fp16/fp32 terms), so the rescale
-// of the accumulators is skipped for most tiles; any reference maximum gives the same softmax.
-__device__ __forceinline__ void softmax_max(const float16_t (&s)[2], float scale_log2e, float& m_run, float& l_run,
-                                            float16_t (&o_acc)[2]) {
-  // four independent chains, then the exchange between the two 32-lane halves by the lane-swap
-  // instruction of gfx950 (a VALU operation: no trip through the LDS queue behind the fragment reads)
-  float c[4];
+// m_run, the reference of the exponentials, is kept in the scaled log2 domain; any reference gives the same softmax.  It is
+// the maximum of a sequence's first tile and stays there until the probabilities of a block outgrow it (see process_tile).
+// Largest logit of a 32-key block in this lane: two independent chains of three-operand maxima.
+__device__ __forceinline__ float block_max(const float16_t& t) {
+  float c[2];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const float16_t& t = s[j >> 1];
-    const int o = 8 * (j & 1);
-    float m = fmaxf(fmaxf(t[o], t[o + 1]), t[o + 2]);  // three-operand maxima
+  for (int j = 0; j < 2; ++j) {
+    const int o = 8 * j;
+    float m = fmaxf(fmaxf(t[o], t[o + 1]), t[o + 2]);
     m = fmaxf(fmaxf(m, t[o + 3]), t[o + 4]);
     m = fmaxf(fmaxf(m, t[o + 5]), t[o + 6]);
     c[j] = fmaxf(m, t[o + 7]);
   }
-  float mx = fmaxf(fmaxf(fmaxf(c[0], c[1]), c[2]), c[3]);
-  {
-    float lo, hi;
-    both_halves(mx, lo, hi);
-    mx = fmaxf(lo, hi);
-  }
-  const float mx_s = mx * scale_log2e;            // finite: every tile holds at least one valid key
-  const bool raise = mx_s > m_run + 8.0f;         // same in both halves of a query column
+  return fmaxf(c[0], c[1]);
+}
+
+// Raises the reference to mx (a lane's maximum; the two halves of a query column agree on the larger one) where that is
+// above it, and rescales what has been summed so far.
+__device__ __forceinline__ void raise_reference(float mx, float scale_log2e, float& m_run, float& l_run,
+                                                float16_t (&o_acc)[2]) {
+  float lo, hi;
+  both_halves(mx, lo, hi);
+  const float mx_s = fmaxf(lo, hi) * scale_log2e;
+  const bool raise = mx_s > m_run;  // same in both halves of a query column
   if (__builtin_amdgcn_ballot_w64(raise)) {
     const float m_new = raise ? mx_s : m_run;
     const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
@@ -145,36 +146,34 @@ __device__ __forceinline__ void softmax_max(const float16_t (&s)[2], float scale
   }
 }
 
-__device__ __forceinline__ void softmax_exp(const float16_t (&s)[2], float scale_log2e, float m_run, float& l_run,
-                                            half8_t (&pf)[2][2]) {
-  // The row sum is taken over the fp16 probabilities, the values the second product multiplies, two per
-  // instruction (dot product with (1, 1), fp32 accumulate) instead of one fp32 add per probability.
+// P = exp2(S - m) of a 32-key block, to fp16.  The row sum is taken over the fp16 probabilities, the values the second
+// product multiplies, two per instruction (dot product with (1, 1), fp32 accumulate) instead of one fp32 add per
+// probability.  Returns this half's row sum.
+__device__ __forceinline__ float softmax_exp(const float16_t& s, float scale_log2e, float m_run, half8_t (&pf)[2]) {
   typedef __fp16 fp16x2_t __attribute__((ext_vector_type(2)));
   const fp16x2_t ones = {(__fp16)1.0f, (__fp16)1.0f};
-  float psum0 = 0.f, psum1 = 0.f;
+  float psum = 0.f;
 #pragma unroll
-  for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-    for (int r = 0; r < 16; r += 2) {
-      const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][r], scale_log2e, -m_run));
-      const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][r + 1], scale_log2e, -m_run));
-      const half2_t h = {(half_t)p0, (half_t)p1};
-      pf[kb][r >> 3][r & 7] = h[0];
-      pf[kb][r >> 3][(r & 7) + 1] = h[1];
-      if (kb == 0) psum0 = __builtin_amdgcn_fdot2(__builtin_bit_cast(fp16x2_t, h), ones, psum0, false);
-      else psum1 = __builtin_amdgcn_fdot2(__builtin_bit_cast(fp16x2_t, h), ones, psum1, false);
-    }
-  l_run += psum0 + psum1;
+  for (int r = 0; r < 16; r += 2) {
+    const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], scale_log2e, -m_run));
+    const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r + 1], scale_log2e, -m_run));
+    const half2_t h = {(half_t)p0, (half_t)p1};
+    pf[r >> 3][r & 7] = h[0];
+    pf[r >> 3][(r & 7) + 1] = h[1];
+    psum = __builtin_amdgcn_fdot2(__builtin_bit_cast(fp16x2_t, h), ones, psum, false);
+  }
+  return psum;
 }
 
-// O^T += V^T P^T ; 16-key step ks covers S^T registers 8*(ks%2)..+7 of block ks/2, i.e. keys
+// O^T += V^T P^T for block kb of 32 keys; 16-key step ks covers S^T registers 8*(ks%2)..+7 of block ks/2, i.e. keys
 // 16ks + {0..3, 8..11} + 4hf, the order the two transposing reads deliver.
-__device__ __forceinline__ void pv_tile(const half_t* sv, const FragAddr& fa, const half8_t (&pf)[2][2],
-                                        float16_t (&o_acc)[2]) {
+__device__ __forceinline__ void pv_block(const half_t* sv, int kb, const FragAddr& fa, const half8_t (&pf)[2],
+                                         float16_t (&o_acc)[2]) {
 #pragma unroll
-  for (int db = 0; db < 2; ++db) {
+  for (int k = 0; k < 2; ++k) {
+    const int ks = 2 * kb + k;
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
+    for (int db = 0; db < 2; ++db) {
       half8_t a;
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
@@ -185,21 +184,40 @@ __device__ __forceinline__ void pv_tile(const half_t* sv, const FragAddr& fa, co
 #pragma unroll
         for (int e = 0; e < 4; ++e) a[4 * t + e] = x[e];
       }
-      o_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, pf[ks >> 1][ks & 1], o_acc[db], 0, 0, 0);
+      o_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, pf[k], o_acc[db], 0, 0, 0);
     }
   }
 }
 
+// The maximum is only taken where it is needed: on a sequence's first tile, and where a block's row sum (fp32, over 16
+// probabilities of a lane) says that one of them may be above 256.  A sum of up to 256 means probabilities of up to 256, so
+// nothing comes near the fp16 range; an overflow or a NaN fails the comparison as well.  The row then gets the block's
+// maximum as its reference and the block's exponentials are taken again (a sum of more than 256 means a logit above the
+// reference).  Without it a tile is 32 multiply-adds, 32 exponentials, 16 conversions and 16 dot products, the first
+// exponentials do not wait for the last product of the tile, and the second block's run under the first one's V^T P^T:
+// 8 sequences of 1024 to 4096 tokens, 16 heads 409.1 -> 392.4 us against a maximum per tile; one short batch (16 x up to 256) level.
 __device__ __forceinline__ void process_tile(const half_t* sk, const half_t* sv, const half8_t (&qf)[4], int k0, int L,
-                                             float scale_log2e, const FragAddr& fa, float& m_run, float& l_run,
+                                             bool first, float scale_log2e, const FragAddr& fa, float& m_run, float& l_run,
                                              float16_t (&o_acc)[2]) {
   float16_t s[2];
   qk_tile(sk, qf, fa, s);
   if (k0 + kKT > L) mask_ragged(s, k0, L, fa.hf);  // wave-uniform
-  softmax_max(s, scale_log2e, m_run, l_run, o_acc);
-  half8_t pf[2][2];
-  softmax_exp(s, scale_log2e, m_run, l_run, pf);
-  pv_tile(sv, fa, pf, o_acc);
+  if (first) raise_reference(fmaxf(block_max(s[0]), block_max(s[1])), scale_log2e, m_run, l_run, o_acc);
+  float tile_sum = 0.f;
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb) {
+    half8_t pf[2];
+    float psum = softmax_exp(s[kb], scale_log2e, m_run, pf);
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(psum <= 256.f)) != 0, 0)) {
+      l_run += tile_sum;  // the first block's share is rescaled with the rest
+      tile_sum = 0.f;
+      raise_reference(block_max(s[kb]), scale_log2e, m_run, l_run, o_acc);
+      psum = softmax_exp(s[kb], scale_log2e, m_run, pf);
+    }
+    tile_sum += psum;
+    pv_block(sv, kb, fa, pf, o_acc);
+  }
+  l_run += tile_sum;
 }
 
 // Locate the (sequence, q-tile) a workgroup owns.  Results are wave-uniform (readfirstlane).
@@ -262,7 +280,7 @@ __device__ __forceinline__ bool locate_tile(const int32_t* __restrict__ cu, int 
 }
 
 template <int NW, int NS>
-__global__ __launch_bounds__(NW * 64) void varlen_mha_kernel(
+__global__ __launch_bounds__(NW * 64, 4) void varlen_mha_kernel(
     // in the order of first use: the first 14 dwords are preloaded into SGPRs at wave launch
     const int32_t* __restrict__ cu, int B, int heads, float scale_log2e, const half_t* __restrict__ Q,
     const half_t* __restrict__ K, const half_t* __restrict__ V, int64_t row_stride, half_t* __restrict__ out,
@@ -305,36 +323,27 @@ __global__ __launch_bounds__(NW * 64) void varlen_mha_kernel(
   //   V: (i%8) ^ (4*((r>>1)&1))  (the 4-row x 64-byte windows of the transposing read do)
   const half_t* kbase = K + (size_t)tok0 * row_stride + hofs;
   const half_t* vbase = V + (size_t)tok0 * row_stride + hofs;
-  int k_chunk[PER], v_chunk[PER], t_row[PER];
   uint32_t k_off[PER], v_off[PER];  // byte offsets of this lane's 16 bytes inside a tile that lies fully inside the sequence
 #pragma unroll
   for (int p = 0; p < PER; ++p) {
     const int r = (wave * PER + p) * 8 + (lane >> 3);
-    t_row[p] = r;
-    k_chunk[p] = ((lane & 7) ^ ((r >> 1) & 7)) * 8;
-    v_chunk[p] = ((lane & 7) ^ (((r >> 1) & 1) << 2)) * 8;
-    k_off[p] = (uint32_t)(((int64_t)r * row_stride + k_chunk[p]) * 2);  // < 64 rows x row pitch: fits 32 bits (checked by the host)
-    v_off[p] = (uint32_t)(((int64_t)r * row_stride + v_chunk[p]) * 2);
+    const int k_chunk = ((lane & 7) ^ ((r >> 1) & 7)) * 8, v_chunk = ((lane & 7) ^ (((r >> 1) & 1) << 2)) * 8;
+    k_off[p] = (uint32_t)(((int64_t)r * row_stride + k_chunk) * 2);  // < 64 rows x row pitch: fits 32 bits (checked by the host)
+    v_off[p] = (uint32_t)(((int64_t)r * row_stride + v_chunk) * 2);
   }
   const uint32_t lds_k = (uint32_t)(uintptr_t)(BT_AS3 const void*)sK + wave * PER * 1024;
   const uint32_t lds_v = (uint32_t)(uintptr_t)(BT_AS3 const void*)sV + wave * PER * 1024;
   const int64_t tile_pitch = (int64_t)kKT * row_stride;  // elements between consecutive key tiles
-  auto issue_tile = [&](int kt, int stage) {
-    if ((kt + 1) * kKT <= L) {  // wave-uniform: the whole tile lies inside the sequence -> scalar base, fixed lane offsets
-      const half_t* kb_ = kbase + kt * tile_pitch;
-      const half_t* vb_ = vbase + kt * tile_pitch;
+  auto issue_tile = [&](int kt, int stage) {  // scalar base, lane offsets
+    const half_t* kb_ = kbase + kt * tile_pitch;
+    const half_t* vb_ = vbase + kt * tile_pitch;
+    const int rows = L - kt * kKT;  // wave-uniform, >= 1
 #pragma unroll
-      for (int p = 0; p < PER; ++p) {
-        mha_dma16_sv(kb_, k_off[p], lds_k + stage * (TILE * 2) + p * 1024);
-        mha_dma16_sv(vb_, v_off[p], lds_v + stage * (TILE * 2) + p * 1024);
-      }
-    } else {
-#pragma unroll
-      for (int p = 0; p < PER; ++p) {
-        const size_t row = (size_t)min(kt * kKT + t_row[p], L - 1) * row_stride;  // rows past L: clamped, masked later
-        mha_dma16(kbase + row + k_chunk[p], lds_k + stage * (TILE * 2) + p * 1024);
-        mha_dma16(vbase + row + v_chunk[p], lds_v + stage * (TILE * 2) + p * 1024);
-      }
+    for (int p = 0; p < PER; ++p) {
+      uint32_t back = 0;  // rows past the end of the sequence: the last row again, masked later
+      if (rows < kKT) back = (uint32_t)max((wave * PER + p) * 8 + (lane >> 3) - (rows - 1), 0) * (uint32_t)(row_stride * 2);
+      mha_dma16_sv(kb_, k_off[p] - back, lds_k + stage * (TILE * 2) + p * 1024);
+      mha_dma16_sv(vb_, v_off[p] - back, lds_v + stage * (TILE * 2) + p * 1024);
     }
   };
 #pragma unroll
@@ -366,8 +375,9 @@ __global__ __launch_bounds__(NW * 64) void varlen_mha_kernel(
 
   const FragAddr fa = make_frag_addr(lane);
 
-  int stage = 0;
-  for (int kt = 0; kt < ntiles; ++kt) {
+  // unrolled over the stages: every LDS address of a tile is a lane constant plus an immediate
+  auto tile = [&](int kt, auto stage_c) {
+    constexpr int STAGE = decltype(stage_c)::value;
     {  // tile kt landed (at most min(ntiles-1-kt, NS-2) younger tiles in flight) and is published
       const int younger = min(ntiles - 1 - kt, NS - 2);
       if (NS >= 4 && younger >= 2) mha_wait_vmcnt<(NS >= 4 ? 2 : 0) * TOT>();
@@ -375,12 +385,15 @@ __global__ __launch_bounds__(NW * 64) void varlen_mha_kernel(
       else mha_wait_vmcnt<0>();
       __builtin_amdgcn_s_barrier();
     }
-    if (kt + NS - 1 < ntiles) issue_tile(kt + NS - 1, stage == 0 ? NS - 1 : stage - 1);
-    const int k0 = kt * kKT;
-
+    if (kt + NS - 1 < ntiles) issue_tile(kt + NS - 1, STAGE == 0 ? NS - 1 : STAGE - 1);
     if (wave_active)
-      process_tile(sK + stage * TILE, sV + stage * TILE, qf, k0, L, scale_log2e, fa, m_run, l_run, o_acc);
-    stage = stage + 1 == NS ? 0 : stage + 1;
+      process_tile(sK + STAGE * TILE, sV + STAGE * TILE, qf, kt * kKT, L, STAGE == 0 && kt == 0, scale_log2e, fa, m_run, l_run,
+                   o_acc);
+  };
+  static_assert(NS == 2, "two stages, see mha_dispatch");
+  for (int kt = 0; kt < ntiles; kt += NS) {
+    tile(kt, std::integral_constant<int, 0>{});
+    if (kt + 1 < ntiles) tile(kt + 1, std::integral_constant<int, 1>{});
   }
 
   // Output.  A lane holds 4 consecutive values of one row per register group, so stored directly a
@@ -533,8 +546,8 @@ __global__ __launch_bounds__(NK * 64) void varlen_mha_splitkey_kernel(
       if (it + NS - 1 < my_tiles) issue_tile(kt + (NS - 1) * NK, stage == 0 ? NS - 1 : stage - 1);
     }
     const int k0 = kt * kKT;
-    process_tile(my_lds + stage * (2 * TILE), my_lds + stage * (2 * TILE) + TILE, qf, k0, L, scale_log2e, fa, m_run,
-                 l_run, o_acc);
+    process_tile(my_lds + stage * (2 * TILE), my_lds + stage * (2 * TILE) + TILE, qf, k0, L, it == 0, scale_log2e, fa,
+                 m_run, l_run, o_acc);
     if (NS > 1) stage = stage + 1 == NS ? 0 : stage + 1;
   }
 

@@ -540,6 +540,27 @@ def test_varlen_mha_maximum_length(bt):
     assert _mha_case(bt, [4096, 3, 4095], 2, seed=4096) <= 4e-3
 
 
+@pytest.mark.parametrize("lengths,heads", [([256] * 12 + [200, 77, 130, 300], 12), ([120, 128, 65, 97, 33, 128] * 5, 12), ([300, 65, 97, 161], 2)])
+@pytest.mark.parametrize("step", [3.0, 5.0, 40.0, -40.0])
+def test_varlen_mha_logits_that_outgrow_the_reference(bt, lengths, heads, step):
+    """Logits that rise by `step` every 24 keys (about the first half of the rows; fall for the others): the reference of the
+    exponentials is raised in either block of a tile, on some rows of a wavefront only, or stays.  One case for each of the
+    three kernels.  Error of an output: fp16 probabilities (2^-11 of |v| <= 5 each, averaged) and its own rounding."""
+    d = 64
+    rng = np.random.default_rng(11)
+    T = int(np.sum(lengths))
+    cu = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    qkv = rng.normal(0, 1, (T, 3, heads, d)).astype(np.float32)
+    key = np.concatenate([np.arange(n) for n in lengths]) // 24
+    sign = np.where(rng.random((T, heads)) < 0.5, 1.0, -1.0)
+    qkv[:, 0, :, 0] = 8.0 * sign                            # logit = (q . k) / 8: the first component carries the staircase
+    qkv[:, 1, :, 0] = (step * key)[:, None]
+    qkv = qkv.reshape(T, -1).astype(np.float16)
+    got = host(bt.varlen_mha(dev(qkv), dev(cu), max(lengths), heads)).astype(np.float64)
+    ref = O.varlen_mha_packed(qkv, cu, heads, d)
+    assert np.abs(got - ref).max() <= 5e-3
+
+
 def test_varlen_mha_many_sequences(bt):
     """More than 64 sequences (plain sequence order path), two-wave kernel."""
     rng = np.random.default_rng(5)
