@@ -74,7 +74,7 @@ __device__ __forceinline__ FragAddr make_frag_addr(int lane) {
 
 // One 64-key tile for the 32 query rows of a wavefront, step by step:  S^T = K Q^T (qk_tile);  mask of a
 // ragged last tile;  then, per block of 32 keys, P = exp2(S - m), row sums, fp16 P (softmax_exp) and
-// O^T += V^T P^T (pv_block).
+// O^T += V^T P^T (pv_step).
 __device__ __forceinline__ void qk_tile(const half_t* sk, const half8_t (&qf)[4], const FragAddr& fa,
                                         float16_t (&s)[2]) {
 #pragma unroll
@@ -126,14 +126,29 @@ __device__ __forceinline__ float block_max(const float16_t& t) {
   return fmaxf(c[0], c[1]);
 }
 
+// Of the whole tile: four chains.
+__device__ __forceinline__ float tile_max(const float16_t (&s)[2]) {
+  float c[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const float16_t& t = s[j >> 1];
+    const int o = 8 * (j & 1);
+    float m = fmaxf(fmaxf(t[o], t[o + 1]), t[o + 2]);
+    m = fmaxf(fmaxf(m, t[o + 3]), t[o + 4]);
+    m = fmaxf(fmaxf(m, t[o + 5]), t[o + 6]);
+    c[j] = fmaxf(m, t[o + 7]);
+  }
+  return fmaxf(fmaxf(fmaxf(c[0], c[1]), c[2]), c[3]);
+}
+
 // Raises the reference to mx (a lane's maximum; the two halves of a query column agree on the larger one) where that is
-// above it, and rescales what has been summed so far.
-__device__ __forceinline__ void raise_reference(float mx, float scale_log2e, float& m_run, float& l_run,
+// more than `slack` above it, and rescales what has been summed so far.
+__device__ __forceinline__ void raise_reference(float mx, float slack, float scale_log2e, float& m_run, float& l_run,
                                                 float16_t (&o_acc)[2]) {
   float lo, hi;
   both_halves(mx, lo, hi);
   const float mx_s = fmaxf(lo, hi) * scale_log2e;
-  const bool raise = mx_s > m_run;  // same in both halves of a query column
+  const bool raise = mx_s > m_run + slack;  // same in both halves of a query column
   if (__builtin_amdgcn_ballot_w64(raise)) {
     const float m_new = raise ? mx_s : m_run;
     const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
@@ -165,44 +180,52 @@ __device__ __forceinline__ float softmax_exp(const float16_t& s, float scale_log
   return psum;
 }
 
-// O^T += V^T P^T for block kb of 32 keys; 16-key step ks covers S^T registers 8*(ks%2)..+7 of block ks/2, i.e. keys
+// O^T += V^T P^T, 16-key step ks, output dimensions 32 db ..+31: it covers S^T registers 8*(ks%2)..+7 of block ks/2, i.e. keys
 // 16ks + {0..3, 8..11} + 4hf, the order the two transposing reads deliver.
-__device__ __forceinline__ void pv_block(const half_t* sv, int kb, const FragAddr& fa, const half8_t (&pf)[2],
-                                         float16_t (&o_acc)[2]) {
+__device__ __forceinline__ void pv_step(const half_t* sv, int ks, int db, const FragAddr& fa, const half8_t& p,
+                                        float16_t& o_acc) {
+  half8_t a;
 #pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int ks = 2 * kb + k;
+  for (int t = 0; t < 2; ++t) {
+    const int row = 16 * ks + 8 * t + fa.v_row;
+    const int chunk = (4 * db + fa.v_c) ^ (((row >> 1) & 1) << 2);
+    const half4_t x = __builtin_bit_cast(
+        half4_t, __builtin_amdgcn_ds_read_tr16_b64_v4f16((BT_AS3 fp16x4_t*)(sv + row * kD + chunk * 8 + fa.v_in)));
 #pragma unroll
-    for (int db = 0; db < 2; ++db) {
-      half8_t a;
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const int row = 16 * ks + 8 * t + fa.v_row;
-        const int chunk = (4 * db + fa.v_c) ^ (((row >> 1) & 1) << 2);
-        const half4_t x = __builtin_bit_cast(
-            half4_t, __builtin_amdgcn_ds_read_tr16_b64_v4f16((BT_AS3 fp16x4_t*)(sv + row * kD + chunk * 8 + fa.v_in)));
-#pragma unroll
-        for (int e = 0; e < 4; ++e) a[4 * t + e] = x[e];
-      }
-      o_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, pf[k], o_acc[db], 0, 0, 0);
-    }
+    for (int e = 0; e < 4; ++e) a[4 * t + e] = x[e];
   }
+  o_acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, p, o_acc, 0, 0, 0);
 }
 
-// The maximum is only taken where it is needed: on a sequence's first tile, and where a block's row sum (fp32, over 16
+// Two forms.  TALL (the kernel for long sequences): the maximum is only taken where it is needed: on a sequence's first tile, and where a block's row sum (fp32, over 16
 // probabilities of a lane) says that one of them may be above 256.  A sum of up to 256 means probabilities of up to 256, so
 // nothing comes near the fp16 range; an overflow or a NaN fails the comparison as well.  The row then gets the block's
 // maximum as its reference and the block's exponentials are taken again (a sum of more than 256 means a logit above the
 // reference).  Without it a tile is 32 multiply-adds, 32 exponentials, 16 conversions and 16 dot products, the first
 // exponentials do not wait for the last product of the tile, and the second block's run under the first one's V^T P^T:
-// 8 sequences of 1024 to 4096 tokens, 16 heads 409.1 -> 392.4 us against a maximum per tile; one short batch (16 x up to 256) level.
+// 8 sequences of 1024 to 4096 tokens, 16 heads 409.1 -> 392.4 us against a maximum per tile, 16 x up to 256, 12 heads 6.85 -> 6.51.
+// The others: a maximum per tile, which raises the reference where it is more than 8 (a factor 256) above it.  They run
+// where a wavefront has one or two tiles, and the pieces of a tile that the checks separate cost more than the maximum of the second:
+// 16 x up to 128 5.32 us, in the form above 5.47; 8 x up to 128 5.03, 5.15; one of 256 4.85, 4.94.
+template <bool TALL>
 __device__ __forceinline__ void process_tile(const half_t* sk, const half_t* sv, const half8_t (&qf)[4], int k0, int L,
                                              bool first, float scale_log2e, const FragAddr& fa, float& m_run, float& l_run,
                                              float16_t (&o_acc)[2]) {
   float16_t s[2];
   qk_tile(sk, qf, fa, s);
   if (k0 + kKT > L) mask_ragged(s, k0, L, fa.hf);  // wave-uniform
-  if (first) raise_reference(fmaxf(block_max(s[0]), block_max(s[1])), scale_log2e, m_run, l_run, o_acc);
+  if constexpr (!TALL) {
+    raise_reference(tile_max(s), 8.f, scale_log2e, m_run, l_run, o_acc);
+    half8_t pf[2][2];
+    const float sum0 = softmax_exp(s[0], scale_log2e, m_run, pf[0]), sum1 = softmax_exp(s[1], scale_log2e, m_run, pf[1]);
+    l_run += sum0 + sum1;
+#pragma unroll
+    for (int db = 0; db < 2; ++db)
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) pv_step(sv, ks, db, fa, pf[ks >> 1][ks & 1], o_acc[db]);
+    return;
+  }
+  if (first) raise_reference(tile_max(s), 0.f, scale_log2e, m_run, l_run, o_acc);
   float tile_sum = 0.f;
 #pragma unroll
   for (int kb = 0; kb < 2; ++kb) {
@@ -211,11 +234,14 @@ __device__ __forceinline__ void process_tile(const half_t* sk, const half_t* sv,
     if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(psum <= 256.f)) != 0, 0)) {
       l_run += tile_sum;  // the first block's share is rescaled with the rest
       tile_sum = 0.f;
-      raise_reference(block_max(s[kb]), scale_log2e, m_run, l_run, o_acc);
+      raise_reference(block_max(s[kb]), 0.f, scale_log2e, m_run, l_run, o_acc);
       psum = softmax_exp(s[kb], scale_log2e, m_run, pf);
     }
     tile_sum += psum;
-    pv_block(sv, kb, fa, pf, o_acc);
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+      for (int db = 0; db < 2; ++db) pv_step(sv, 2 * kb + k, db, fa, pf[k], o_acc[db]);
   }
   l_run += tile_sum;
 }
@@ -387,7 +413,7 @@ __global__ __launch_bounds__(NW * 64, 4) void varlen_mha_kernel(
     }
     if (kt + NS - 1 < ntiles) issue_tile(kt + NS - 1, STAGE == 0 ? NS - 1 : STAGE - 1);
     if (wave_active)
-      process_tile(sK + STAGE * TILE, sV + STAGE * TILE, qf, kt * kKT, L, STAGE == 0 && kt == 0, scale_log2e, fa, m_run, l_run,
+      process_tile<(NW == 4)>(sK + STAGE * TILE, sV + STAGE * TILE, qf, kt * kKT, L, STAGE == 0 && kt == 0, scale_log2e, fa, m_run, l_run,
                    o_acc);
   };
   static_assert(NS == 2, "two stages, see mha_dispatch");
@@ -546,7 +572,7 @@ __global__ __launch_bounds__(NK * 64) void varlen_mha_splitkey_kernel(
       if (it + NS - 1 < my_tiles) issue_tile(kt + (NS - 1) * NK, stage == 0 ? NS - 1 : stage - 1);
     }
     const int k0 = kt * kKT;
-    process_tile(my_lds + stage * (2 * TILE), my_lds + stage * (2 * TILE) + TILE, qf, k0, L, it == 0, scale_log2e, fa,
+    process_tile<false>(my_lds + stage * (2 * TILE), my_lds + stage * (2 * TILE) + TILE, qf, k0, L, it == 0, scale_log2e, fa,
                  m_run, l_run, o_acc);
     if (NS > 1) stage = stage + 1 == NS ? 0 : stage + 1;
   }
