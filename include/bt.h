@@ -320,13 +320,12 @@ bt_status bt_encoder_fwd_padded(const bt_layer* layers, int n_layers, const floa
  * and the packed layers it feeds).  Same kernels, same results, same arguments with the same meaning as in the two
  * calls: d_mask / d_lengths (exactly one non-NULL), d_cu_seqlens [B+1] and d_token_idx [B*S] are written as by
  * bt_build_offsets, *h_total receives the token count (host memory; pinned and device-mapped memory avoids a stream
- * synchronisation), d_y_padded as by bt_encoder_fwd_padded.  What the single call saves is host time: the count that
- * the host waits for goes into the launches of the layers without returning to the caller first, and while the
- * host holds that count without having launched, the device has nothing to do (about 10 us per batch through a
- * scripting-language binding).  The workspace must be large enough for every count: at least
+ * synchronisation), d_y_padded as by bt_encoder_fwd_padded.  What the single call saves is time in which the device has
+ * nothing to do: the count goes into the launches of the layers without returning to the caller first, and the first
+ * layer's QKV product, which reads the count on the device, runs while the host waits for it.  The workspace must be large enough for every count: at least
  * bt_layer_workspace_bytes(layers, B*S, B, S).  Errors the host can see are reported before anything runs; a
  * length outside [0, S] is found by the prefix-sum kernel and reported as by bt_build_offsets, and then no layer
- * is launched.  Like
+ * runs (the QKV product finds no rows and ends).  Like
  * bt_build_offsets this call waits on the host and is refused (BT_ERR_UNSUPPORTED) on a capturing stream.
  */
 bt_status bt_encoder_fwd_masked(const bt_layer* layers, int n_layers, const float* d_fold,

@@ -392,14 +392,11 @@ __device__ __forceinline__ void load_resid(const half_t* __restrict__ resid, con
 // SHAPE (0 = fan-out, N >= 2K; 1 = neither; 2 = deep reduction, K >= 2N) changes nothing in the code: it is
 // part of the kernel's name, so that a kernel trace tells the four products of an encoder layer apart
 // (QKV and FFN-up are fan-out, the output projection is square, FFN-down is deep) when they share a tile shape.
-template <int BM, int BN, int WGM, int WGN, int NS, int ACT, int EPI, int SHAPE>
-__global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(
-    // Argument order: what the prologue and the K loop need comes first and fits the 14 dwords that are
-    // preloaded into SGPRs at wave launch (-amdgpu-kernarg-preload-count), so the first DMA does not
-    // wait for a scalar load of the kernel arguments; the epilogue descriptor is fetched behind it.
-    const half_t* __restrict__ A, const half_t* __restrict__ W, const int32_t* __restrict__ a_rows /* = ep.a_rows */,
-    const half_t* __restrict__ bias /* = ep.bias */, int M, int N, int K, int tiles_n, int tiles_m, int group_m,
-    half_t* __restrict__ C, const GemmEpi ep) {
+template <int BM, int BN, int WGM, int WGN, int NS, int ACT, int EPI>
+__device__ __forceinline__ void gemm_pipe_tile(const half_t* __restrict__ A, const half_t* __restrict__ W,
+                                               const int32_t* __restrict__ a_rows, const half_t* __restrict__ bias, int M, int N,
+                                               int K, int tiles_n, int tiles_m, int group_m, half_t* __restrict__ C,
+                                               const GemmEpi& ep) {
   constexpr int BK = 64, KS = BK / 32;
   constexpr int NWAVES = WGM * WGN;
   constexpr int WM = BM / WGM, WN = BN / WGN;   // wave tile
@@ -659,7 +656,51 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(
   }
 }
 
+template <int BM, int BN, int WGM, int WGN, int NS, int ACT, int EPI, int SHAPE>
+__global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(
+    // Argument order: what the prologue and the K loop need comes first and fits the 14 dwords that are
+    // preloaded into SGPRs at wave launch (-amdgpu-kernarg-preload-count), so the first DMA does not
+    // wait for a scalar load of the kernel arguments; the epilogue descriptor is fetched behind it.
+    const half_t* __restrict__ A, const half_t* __restrict__ W, const int32_t* __restrict__ a_rows /* = ep.a_rows */,
+    const half_t* __restrict__ bias /* = ep.bias */, int M, int N, int K, int tiles_n, int tiles_m, int group_m,
+    half_t* __restrict__ C, const GemmEpi ep) {
+  gemm_pipe_tile<BM, BN, WGM, WGN, NS, ACT, EPI>(A, W, a_rows, bias, M, N, K, tiles_n, tiles_m, group_m, C, ep);
+}
+
 #include "gemm_wide.h"
+
+// The plain product with its number of rows in device memory: launched behind the kernel that counts them, before the host
+// knows the count (gemm_counted_dispatch).  The grid covers the largest count there can be; what is not needed ends at once.
+struct CountedTiles { int m, n, group; };
+template <int BM, int BN>
+__device__ __forceinline__ CountedTiles counted_tiles(int M, int N) {
+  CountedTiles t;
+  t.m = (M + BM - 1) / BM;
+  t.n = (N + BN - 1) / BN;
+  // as strip_rows; only the order of the tiles depends on it
+  t.group = min(max(__builtin_amdgcn_readfirstlane((int)(sqrtf((float)(t.m * t.n) * (0.125f * BN / BM)) + 0.5f)), 1), t.m);
+  return t;
+}
+template <int BM, int BN, int WGM, int WGN, int NS>
+__global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_counted_kernel(
+    const half_t* __restrict__ A, const half_t* __restrict__ W, const int32_t* __restrict__ a_rows,
+    const half_t* __restrict__ bias, const int32_t* __restrict__ rows, int N, int K, half_t* __restrict__ C) {
+  const int M = *rows;  // 0 or -1 (an invalid mask): nothing to do
+  if (M < 1) return;
+  const CountedTiles t = counted_tiles<BM, BN>(M, N);
+  if ((int)blockIdx.x >= t.m * t.n) return;
+  gemm_pipe_tile<BM, BN, WGM, WGN, NS, BT_ACT_NONE, EPI_PLAIN>(A, W, a_rows, bias, M, N, K, t.n, t.m, t.group, C, GemmEpi());
+}
+template <int BM, int BN>
+__global__ __launch_bounds__(256, 1) void gemm_wide_counted_kernel(
+    const half_t* __restrict__ A, const half_t* __restrict__ W, const int32_t* __restrict__ a_rows,
+    const half_t* __restrict__ bias, const int32_t* __restrict__ rows, int N, int K, half_t* __restrict__ C) {
+  const int M = *rows;
+  if (M < 1) return;
+  const CountedTiles t = counted_tiles<BM, BN>(M, N);
+  if ((int)blockIdx.x >= t.m * t.n) return;
+  gemm_wide_tiles<BM, BN, BT_ACT_NONE, EPI_PLAIN>(A, W, a_rows, bias, M, N, K, t.n, t.m, t.group, C, GemmEpi());
+}
 
 // ---------------------------------------------------------------------------
 // Fallback kernel: register-staged, 64x64x64 tile, padded LDS rows, K tail zero-filled.
@@ -1037,6 +1078,44 @@ bt_status gemm_dispatch(const bt_half* A, const bt_half* W, int M, int N, int K,
     }
   }
   return gemm_launch_tile(gemm_tile_choice(M, N, K, act, epi, wide_ok), a, w, c, M, N, K, act, epi, ep, st, np_out);
+}
+
+// C = A[a_rows] W^T + bias with the number of rows, *rows <= rows_max, in device memory.  For the first product of a stack: the
+// host waits for the count before it can size a launch, and the device would wait for that launch; this one is sized by
+// rows_max and reads the count itself, so the device has work until the host has caught up.  The shape is taken for five
+// eighths of rows_max (sentences of even lengths fill a little more than half of a padded batch); a row's result is the same in
+// every shape.  What it buys is the time until the host's first launch arrives, less the round trip of the count into the
+// kernel's registers: masked calls, both builds in one process: one layer, 4 x up to 64, 36.6 -> 31.8 us; 12 layers, 1 x up to
+// 128, 271.5 -> 267.0, 8 x up to 128 462.9 -> 457.3, 16 x up to 256 775.2 -> 768.3; full batches, for which the shape is taken too
+// small, no less (25 x 185, six layers 642.4 -> 630.4).  Narrow tiles of which most would find no rows are not launched by the
+// thousand (the limit is sixteen rounds).  BT_ERR_UNSUPPORTED: no form for these sizes, nothing enqueued.
+bt_status gemm_counted_dispatch(const bt_half* A, const bt_half* W, const int32_t* a_rows, const bt_half* bias,
+                                const int32_t* rows, int rows_max, int N, int K, bt_half* C, hipStream_t st) {
+  if ((K % 64) != 0 || K < 256) return BT_ERR_UNSUPPORTED;
+  static constexpr int kShapes[] = {0, 2, 4, 7, 8};
+  const int expected = (int)((long long)rows_max * 5 / 8) + 1;
+  int best = -1;
+  float best_us = 0.f;
+  for (const int c : kShapes) {
+    if (!gemm_shape_ok(kGemmTiles[c], expected, N, K, BT_ACT_NONE, EPI_PLAIN, gemm_wide_ok(rows_max, N, K, EPI_PLAIN))) continue;
+    const float us = gemm_shape_us(kGemmTiles[c], expected, N, K, BT_ACT_NONE);
+    if (best < 0 || us < best_us) { best = c; best_us = us; }
+  }
+  if (best < 0) return BT_ERR_UNSUPPORTED;
+  const GemmTile& t = kGemmTiles[best];
+  const long long tiles = (long long)((rows_max + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+  if (t.kind == kNarrow && tiles > 16 * kComputeUnits) return BT_ERR_UNSUPPORTED;
+  const unsigned grid = (unsigned)(t.kind == kWide && tiles > kComputeUnits ? kComputeUnits : tiles);
+  const half_t *a = reinterpret_cast<const half_t*>(A), *w = reinterpret_cast<const half_t*>(W), *b = reinterpret_cast<const half_t*>(bias);
+  half_t* const c = reinterpret_cast<half_t*>(C);
+  switch (best) {
+    case 0: gemm_wide_counted_kernel<256, 128><<<grid, 256, 0, st>>>(a, w, a_rows, b, rows, N, K, c); break;
+    case 2: gemm_wide_counted_kernel<192, 128><<<grid, 256, 0, st>>>(a, w, a_rows, b, rows, N, K, c); break;
+    case 4: gemm_wide_counted_kernel<128, 128><<<grid, 256, 0, st>>>(a, w, a_rows, b, rows, N, K, c); break;
+    case 7: gemm_pipe_counted_kernel<64, 128, 2, 4, 4><<<grid, 512, 0, st>>>(a, w, a_rows, b, rows, N, K, c); break;
+    default: gemm_pipe_counted_kernel<64, 64, 2, 2, 4><<<grid, 256, 0, st>>>(a, w, a_rows, b, rows, N, K, c); break;
+  }
+  return launch_status();
 }
 
 // Split-K for token counts so small that the tile grid leaves most compute units idle and every tile

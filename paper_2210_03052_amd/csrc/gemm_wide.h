@@ -50,12 +50,11 @@ struct WideTile {
   static_assert(TOT < 32, "vmcnt range");
 };
 
-template <int BM, int BN, int ACT, int EPI, int SHAPE>
-__global__ __launch_bounds__(256, 1) void gemm_wide_kernel(
-    // in the order of first use: the first 14 dwords are preloaded into SGPRs at wave launch
-    const half_t* __restrict__ A, const half_t* __restrict__ W, const int32_t* __restrict__ a_rows /* = ep.a_rows */,
-    const half_t* __restrict__ bias /* = ep.bias */, int M, int N, int K, int tiles_n, int tiles_m, int group_m,
-    half_t* __restrict__ C, const GemmEpi ep) {
+template <int BM, int BN, int ACT, int EPI>
+__device__ __forceinline__ void gemm_wide_tiles(const half_t* __restrict__ A, const half_t* __restrict__ W,
+                                                const int32_t* __restrict__ a_rows, const half_t* __restrict__ bias, int M, int N,
+                                                int K, int tiles_n, int tiles_m, int group_m, half_t* __restrict__ C,
+                                                const GemmEpi& ep) {
   using T = WideTile<BM, BN>;
   constexpr int MI = T::MI, NI = T::NI, LA = T::LA, LB = T::LB, TOT = T::TOT, STAGE = T::STAGE;
   static_assert(EPI == EPI_PLAIN || EPI == EPI_FOLD, "epilogue form");
@@ -326,4 +325,13 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(
       offsets_of(nm0, nn0, nva, nvb);
     }
   }
+}
+
+template <int BM, int BN, int ACT, int EPI, int SHAPE>
+__global__ __launch_bounds__(256, 1) void gemm_wide_kernel(
+    // in the order of first use: the first 14 dwords are preloaded into SGPRs at wave launch
+    const half_t* __restrict__ A, const half_t* __restrict__ W, const int32_t* __restrict__ a_rows /* = ep.a_rows */,
+    const half_t* __restrict__ bias /* = ep.bias */, int M, int N, int K, int tiles_n, int tiles_m, int group_m,
+    half_t* __restrict__ C, const GemmEpi ep) {
+  gemm_wide_tiles<BM, BN, ACT, EPI>(A, W, a_rows, bias, M, N, K, tiles_n, tiles_m, group_m, C, ep);
 }

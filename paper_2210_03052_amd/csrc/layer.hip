@@ -21,6 +21,11 @@
 namespace bt {
 bt_status gemm_dispatch(const bt_half* A, const bt_half* W, int M, int N, int K, bt_act act, int epi,
                         const GemmEpi& ep, bt_half* C, hipStream_t st, int* np_out);
+bt_status gemm_counted_dispatch(const bt_half* A, const bt_half* W, const int32_t* a_rows, const bt_half* bias,
+                                const int32_t* rows, int rows_max, int N, int K, bt_half* C, hipStream_t st);
+bt_status build_offsets(const int32_t* d_mask, const int32_t* d_lengths, int B, int S, int32_t* d_cu_seqlens,
+                        int32_t* d_token_idx, int32_t* h_out, bool stats, bt_stream stream, void (*meanwhile)(void*),
+                        void* context);
 bt_status layernorm_dispatch(const bt_half* x, const float* xpart, int nsplit, const bt_half* bias,
                              const bt_half* residual, const bt_half* gamma, const bt_half* beta, float eps, int T,
                              int H, bt_half* y, hipStream_t st, const int32_t* res_rows, const int32_t* out_idx,
@@ -118,6 +123,7 @@ struct LayerIo {
   int in_rows_of = 0;                 // rows of that tensor
   const int32_t* out_idx = nullptr;   // y is the PADDED tensor [out_rows, H]; packed row i goes to row out_idx[i],
   int out_rows = 0;                   // every other row is zero-filled (last layer)
+  bool qkv_ready = false;             // the QKV product of the (first) layer has been launched already
 };
 
 // How much of a layer runs in the form for few tokens (few_tokens.h): kFewInner, LN0 inside FFN-up (6 launches);
@@ -168,7 +174,7 @@ static bt_status layer_fwd(const bt_layer* l, const bt_half* x, const int32_t* c
     if ((s = few_ln_gemm_dispatch(z, l->w_qkv, T, 3 * H, H, prev->ln1_g, prev->ln1_b, l->b_qkv, prev->ln_eps, BT_ACT_NONE, w.qkv,
                                   w.ping, st)) != BT_OK)
       return s;
-  } else {
+  } else if (!io.qkv_ready) {
     ep.a_rows = io.in_rows;
     ep.a_rows_of = io.in_rows_of;
     ep.bias = hp(l->b_qkv);
@@ -222,7 +228,7 @@ static bt_status stack_fwd(const bt_layer* layers, int n_layers, const bt_half* 
   for (int i = 0; i < n_layers; ++i) {
     const bool last = i == n_layers - 1;
     LayerIo here;
-    if (i == 0) { here.in_rows = io.in_rows; here.in_rows_of = io.in_rows_of; }
+    if (i == 0) { here.in_rows = io.in_rows; here.in_rows_of = io.in_rows_of; here.qkv_ready = io.qkv_ready; }
     if (last) { here.out_idx = io.out_idx; here.out_rows = io.out_rows; }
     bt_half* const outp = last ? y : ((i & 1) ? w.pong : w.ping);
     const bt_status s = layer_fwd(&layers[i], in, cu, B, T, max_len, outp, w, st, here, both && i > 0 ? &layers[i - 1] : nullptr,
@@ -254,7 +260,7 @@ static bt_status stack_fwd_folded(const bt_layer* layers, int n_layers, const fl
     const bt_layer* prev = i > 0 ? &layers[i - 1] : nullptr;
     const float* fv = fold + (size_t)i * per_layer;
     bt_half* u2 = (i & 1) ? w.pong : w.ping;
-    {  // GEMM0: QKV projection of LN1_{i-1}(z2) (folded) or of the plain input
+    if (prev || !io.qkv_ready) {  // GEMM0: QKV projection of LN1_{i-1}(z2) (folded) or of the plain input
       GemmEpi ep;
       if (prev) {
         ep.ln_part = w.part2; ep.ln_np = np2; ep.fold_c = fv; ep.fold_d = fv + 3 * H; ep.inv_h = inv_h; ep.eps = eps;
@@ -455,10 +461,9 @@ extern "C" bt_status bt_encoder_fwd(const bt_layer* layers, int n_layers, const 
   return stack_fwd(layers, n_layers, d_x, d_cu_seqlens, B, T, max_len, d_y, w, st);
 }
 
-extern "C" bt_status bt_encoder_fwd_padded(const bt_layer* layers, int n_layers, const float* d_fold,
-                                           const bt_half* d_x_padded, const int32_t* d_token_idx,
-                                           const int32_t* d_cu_seqlens, int B, int T, int S, bt_half* d_y_padded,
-                                           void* d_ws, size_t ws_bytes, bt_stream stream) {
+static bt_status fwd_padded(const bt_layer* layers, int n_layers, const float* d_fold, const bt_half* d_x_padded,
+                            const int32_t* d_token_idx, const int32_t* d_cu_seqlens, int B, int T, int S, bt_half* d_y_padded,
+                            void* d_ws, size_t ws_bytes, bt_stream stream, bool qkv_ready) {
   bt_status s = check_stack(layers, n_layers);
   if (s != BT_OK) return s;
   if (B < 0 || T < 0 || S < 0) return BT_ERR_INVALID_ARG;
@@ -480,14 +485,24 @@ extern "C" bt_status bt_encoder_fwd_padded(const bt_layer* layers, int n_layers,
   io.in_rows_of = B * S;
   io.out_idx = d_token_idx;
   io.out_rows = B * S;
+  io.qkv_ready = qkv_ready;
   if (d_fold && folded_pays(T, H, layers[0].F))
     return stack_fwd_folded(layers, n_layers, d_fold, d_x_padded, d_cu_seqlens, B, T, S, d_y_padded, w, st, io);
   return stack_fwd(layers, n_layers, d_x_padded, d_cu_seqlens, B, T, S, d_y_padded, w, st, io);
 }
 
+extern "C" bt_status bt_encoder_fwd_padded(const bt_layer* layers, int n_layers, const float* d_fold,
+                                           const bt_half* d_x_padded, const int32_t* d_token_idx,
+                                           const int32_t* d_cu_seqlens, int B, int T, int S, bt_half* d_y_padded,
+                                           void* d_ws, size_t ws_bytes, bt_stream stream) {
+  return fwd_padded(layers, n_layers, d_fold, d_x_padded, d_token_idx, d_cu_seqlens, B, T, S, d_y_padded, d_ws, ws_bytes, stream,
+                    false);
+}
+
 // bt_build_offsets followed by bt_encoder_fwd_padded in one call: the token count the first call waits for
-// goes straight into the launches of the second, with no host code of the caller in between (while the host
-// holds the count and has not launched yet, the device is idle).
+// goes straight into the launches of the second, with no host code of the caller in between.  While the count travels to
+// the host and the first launch back, the device would be idle for 8 to 10 us; the first layer's QKV product needs no count on the
+// host (gemm_counted_dispatch) and runs in that time.
 extern "C" bt_status bt_encoder_fwd_masked(const bt_layer* layers, int n_layers, const float* d_fold,
                                            const bt_half* d_x_padded, const int32_t* d_mask,
                                            const int32_t* d_lengths, int B, int S, int32_t* d_cu_seqlens,
@@ -504,8 +519,23 @@ extern "C" bt_status bt_encoder_fwd_masked(const bt_layer* layers, int n_layers,
     if (!d_ws || (reinterpret_cast<uintptr_t>(d_ws) & 255u)) return BT_ERR_WORKSPACE;
     if (ws_bytes < carve(d_ws, B * S, layers[0].H, layers[0].F).bytes) return BT_ERR_WORKSPACE;  // any count fits
   }
-  if ((s = bt_build_offsets(d_mask, d_lengths, B, S, d_cu_seqlens, d_token_idx, h_total, stream)) != BT_OK) return s;
-  return bt_encoder_fwd_padded(layers, n_layers, d_fold, d_x_padded, d_token_idx, d_cu_seqlens, B, h_total[0], S,
-                               d_y_padded, d_ws, ws_bytes, stream);
+  auto first_product = [&]() {  // the QKV rows stand at the front of the workspace, whatever the count
+    const bt_layer& l = layers[0];
+    return gemm_counted_dispatch(d_x_padded, l.w_qkv, d_token_idx, l.b_qkv, d_cu_seqlens + B, B * S, 3 * l.H, l.H,
+                                 carve(d_ws, B * S, l.H, l.F).qkv, static_cast<hipStream_t>(stream));
+  };
+  struct Meanwhile {
+    decltype(first_product)* launch;
+    bool done;
+  } meanwhile{&first_product, false};
+  auto run = [](void* m) {
+    auto* const w = static_cast<Meanwhile*>(m);
+    w->done = (*w->launch)() == BT_OK;
+  };
+  if ((s = build_offsets(d_mask, d_lengths, B, S, d_cu_seqlens, d_token_idx, h_total, false, stream, B > 0 && S > 0 ? +run : nullptr,
+                         &meanwhile)) != BT_OK)
+    return s;
+  return fwd_padded(layers, n_layers, d_fold, d_x_padded, d_token_idx, d_cu_seqlens, B, h_total[0], S, d_y_padded, d_ws, ws_bytes,
+                    stream, meanwhile.done);
 }
 

@@ -6,6 +6,9 @@
 #include "common.h"
 
 namespace bt {
+bt_status build_offsets(const int32_t* d_mask, const int32_t* d_lengths, int B, int S, int32_t* d_cu_seqlens,
+                        int32_t* d_token_idx, int32_t* h_out, bool stats, bt_stream stream, void (*meanwhile)(void*),
+                        void* context);
 
 constexpr int kOffsetsThreads = 1024;  // 16 wavefronts
 constexpr int kOffsetsWaves = kOffsetsThreads / kWave;
@@ -396,9 +399,10 @@ static_assert(kMaskCounters == 64, "a bit each");
 // Shared body of bt_build_offsets / bt_build_offsets_stats.  h_out[0] receives the total; with `stats`
 // h_out[1] receives the largest per-sentence count and d_cu_seqlens has B+2 entries (the last one is
 // the device copy of that maximum).
-static bt_status build_offsets_impl(const int32_t* d_mask, const int32_t* d_lengths, int B, int S,
-                                    int32_t* d_cu_seqlens, int32_t* d_token_idx, int32_t* h_out, bool stats,
-                                    bt_stream stream) {
+// meanwhile(context) runs between the launch and the wait: work for the device that does not need the total on the host.
+bt_status bt::build_offsets(const int32_t* d_mask, const int32_t* d_lengths, int B, int S, int32_t* d_cu_seqlens,
+                            int32_t* d_token_idx, int32_t* h_out, bool stats, bt_stream stream, void (*meanwhile)(void*),
+                            void* context) {
   if ((d_mask == nullptr) == (d_lengths == nullptr)) return BT_ERR_INVALID_ARG;
   if (!d_cu_seqlens || !d_token_idx || !h_out || B < 0 || S < 1) return BT_ERR_INVALID_ARG;
   if (S > BT_MAX_SEQ || (int64_t)B * S >= (int64_t)INT32_MAX) return BT_ERR_UNSUPPORTED;
@@ -438,6 +442,7 @@ static bt_status build_offsets_impl(const int32_t* d_mask, const int32_t* d_leng
         d_lengths, B, S, d_cu_seqlens, d_token_idx, h_dev, d_max);
   }
   if (hipGetLastError() != hipSuccess) return counter.lost = true, BT_ERR_HIP;
+  if (meanwhile) meanwhile(context);
   int32_t res[2] = {kPending, 0};
   if (h_dev) {
     const auto t0 = std::chrono::steady_clock::now();
@@ -464,13 +469,13 @@ static bt_status build_offsets_impl(const int32_t* d_mask, const int32_t* d_leng
 extern "C" bt_status bt_build_offsets(const int32_t* d_mask, const int32_t* d_lengths, int B, int S,
                                       int32_t* d_cu_seqlens, int32_t* d_token_idx, int32_t* h_total,
                                       bt_stream stream) {
-  return build_offsets_impl(d_mask, d_lengths, B, S, d_cu_seqlens, d_token_idx, h_total, false, stream);
+  return build_offsets(d_mask, d_lengths, B, S, d_cu_seqlens, d_token_idx, h_total, false, stream, nullptr, nullptr);
 }
 
 extern "C" bt_status bt_build_offsets_stats(const int32_t* d_mask, const int32_t* d_lengths, int B, int S,
                                             int32_t* d_cu_seqlens, int32_t* d_token_idx, int32_t* h_total_max,
                                             bt_stream stream) {
-  return build_offsets_impl(d_mask, d_lengths, B, S, d_cu_seqlens, d_token_idx, h_total_max, true, stream);
+  return build_offsets(d_mask, d_lengths, B, S, d_cu_seqlens, d_token_idx, h_total_max, true, stream, nullptr, nullptr);
 }
 
 extern "C" bt_status bt_pack(const bt_half* d_padded, const int32_t* d_token_idx, int T, int H,

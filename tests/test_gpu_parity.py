@@ -836,6 +836,35 @@ def test_encoder_fwd_masked_equals_the_two_calls(bt, use_mask, folded):
     assert float((untouched - 3.0).abs().sum()) == 0.0
 
 
+@pytest.mark.parametrize("B,S,H", [(3, 21, 768), (2, 128, 512), (9, 130, 768), (16, 129, 1024), (16, 256, 768), (13, 640, 512),
+                                   (30, 512, 768), (5, 40, 192)])
+def test_first_product_ahead_of_the_count(bt, B, S, H):
+    """The masked call launches its first product before the host knows the number of tokens, in a shape taken for five eighths of
+    the padded rows: the same bits as with the count known, for a single token, one more than a tile, ragged and full batches, in
+    each of its shapes and where there is none (width 192); rows that hold no token are neither read nor written."""
+    import torch
+    rng = np.random.default_rng([B, S, H])
+    w = lambda *s: dev(rng.normal(0, 0.02, s).astype(np.float16))
+    one, zero = dev(np.ones(H, np.float16)), dev(np.zeros(H, np.float16))
+    layer = bt.Layer({"w_qkv": w(3 * H, H), "b_qkv": w(3 * H), "w_o": w(H, H), "b_o": w(H), "ln0_g": one, "ln0_b": zero,
+                      "w_1": w(4 * H, H), "b_1": w(4 * H), "w_2": w(H, 4 * H), "b_2": w(H), "ln1_g": one, "ln1_b": zero,
+                      "heads": H // 64})
+    ragged = rng.integers(0, S + 1, B).astype(np.int32)
+    single = np.where(np.arange(B) == B - 1, 1, 0).astype(np.int32)
+    tile = np.minimum(np.maximum(257 - S * np.arange(B), 0), S).astype(np.int32)      # 257 tokens at the front, where they fit
+    for L in (ragged, single, tile, np.full(B, S, np.int32), np.full(B, max(1, S // 5), np.int32)):
+        x = rng.normal(0, 1, (B, S, H)).astype(np.float16)
+        x[np.arange(S)[None, :] >= L[:, None]] = np.nan                                # a pad that is read shows
+        x = dev(x)
+        cu, tok, T = bt.build_offsets(lengths=dev(L), S=S)
+        want = bt.encoder_fwd_padded([layer], x, tok, cu)
+        ws = torch.full((bt.layer_workspace_bytes(layer, B * S, B, S),), 17, dtype=torch.uint8, device="cuda")
+        got, _, _, t = bt.encoder_fwd_masked([layer], x, lengths=dev(L), ws=ws)
+        assert t == T and torch.equal(got, want), L
+        need = bt.layer_workspace_bytes(layer, T, B, S)
+        assert T == B * S or bool((ws[need:] == 17).all())
+
+
 def test_padded_stack_where_the_first_gemm_runs_as_two_row_ranges(bt):
     """8 200 tokens at width 768: the QKV product's tile grid is a little past two rounds, so it runs as two
     launches over row ranges -- with the pack fused into its operand load the second launch must continue in
