@@ -699,7 +699,7 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_counted_kernel(
   if (M < 1) return;
   const CountedTiles t = counted_tiles<BM, BN>(M, N);
   if ((int)blockIdx.x >= t.m * t.n) return;
-  gemm_wide_tiles<BM, BN, BT_ACT_NONE, EPI_PLAIN>(A, W, a_rows, bias, M, N, K, t.n, t.m, t.group, C, GemmEpi());
+  gemm_wide_tiles<BM, BN, BT_ACT_NONE, EPI_PLAIN, 3>(A, W, a_rows, bias, M, N, K, t.n, t.m, t.group, C, GemmEpi());
 }
 
 // ---------------------------------------------------------------------------
@@ -791,6 +791,7 @@ static int strip_rows(long long n_tiles, int tiles_m, int bm, int bn) {
   return gm < 1 ? 1 : (gm > tiles_m ? tiles_m : gm);
 }
 
+// Shape class 2 has four stages on the smaller tiles, which want five slabs.
 template <int BM, int BN>
 static bt_status launch_wide(const half_t* A, const half_t* W, half_t* C, int M, int N, int K, bt_act act, int epi,
                              GemmEpi ep, hipStream_t st, int* np_out) {
@@ -806,7 +807,7 @@ static bt_status launch_wide(const half_t* A, const half_t* W, half_t* C, int M,
   do {                                                           \
     if constexpr ((ACT) == BT_ACT_NONE) {                        \
       if (N >= 2 * K) BT_LAUNCH_S(ACT, EPI, 0);                  \
-      else if (K >= 2 * N) BT_LAUNCH_S(ACT, EPI, 2);             \
+      else if (K >= 2 * N && K > 256) BT_LAUNCH_S(ACT, EPI, 2); \
       else BT_LAUNCH_S(ACT, EPI, 1);                             \
     } else {                                                     \
       BT_LAUNCH_S(ACT, EPI, 1);                                  \
@@ -827,6 +828,18 @@ static bt_status launch_wide(const half_t* A, const half_t* W, half_t* C, int M,
   }
 #undef BT_LAUNCH
 #undef BT_LAUNCH_S
+  return launch_status();
+}
+
+// Tiles of 96 columns: one round, deep reductions without an activation, plain epilogue (see gemm_shape_ok).
+template <int BM>
+static bt_status launch_wide_deep(const half_t* A, const half_t* W, half_t* C, int M, int N, int K, bt_act act, int epi,
+                                  const GemmEpi& ep, hipStream_t st, int* np_out) {
+  const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + 95) / 96, n_tiles = tiles_m * tiles_n;
+  if (act != BT_ACT_NONE || epi != EPI_PLAIN || K <= 256) return BT_ERR_UNSUPPORTED;
+  if (np_out) *np_out = tiles_n;
+  gemm_wide_kernel<BM, 96, BT_ACT_NONE, EPI_PLAIN, 2><<<n_tiles < kComputeUnits ? n_tiles : kComputeUnits, 256, 0, st>>>(
+      A, W, ep.a_rows, ep.bias, M, N, K, tiles_n, tiles_m, strip_rows(n_tiles, tiles_m, BM, 96), C, ep);
   return launch_status();
 }
 
@@ -931,7 +944,8 @@ static const GemmTile kGemmTiles[] = {
     {128, 64, 1.5f, 0.223f, 0.068f, 1.6f, kNarrow},   {64, 128, 1.55f, 0.224f, 0.059f, 1.61f, kNarrow},
     {64, 64, 2.4f, 0.139f, 0.043f, 0.35f, kNarrow},   {256, 128, 2.2f, 0.53f, 0.10f, 3.45f, kEightWaves},
     {192, 128, 1.6f, 0.50f, 0.06f, 2.7f, kEightWaves}, {128, 128, 1.5f, 0.28f, 0.10f, 2.5f, kEightWaves},
-    {64, 64, 2.7f, 0.19f, 0.f, 0.35f, kRegisterStaged}};
+    {64, 64, 2.7f, 0.19f, 0.f, 0.35f, kRegisterStaged},
+    {96, 96, 2.0f, 0.20f, 0.089f, 1.1f, kWide},        {64, 96, 2.3f, 0.165f, 0.055f, 0.8f, kWide}};
 constexpr int kGemmShapes = sizeof(kGemmTiles) / sizeof(kGemmTiles[0]);
 constexpr float kActUs = 0.75e-4f;  // per output of a tile
 
@@ -947,11 +961,21 @@ static bool gemm_wide_ok(long long a_rows, int N, int K, int epi) {
 // round of 96-row tiles with an activation is the exception: 700 x 3072 x 768 with GELU 7.7 us, 8.9 with 128 rows (six
 // layers 247.9 -> 240.9 us), 1 040 x 2048 x 512 6.4 us, 7.5 (213.2 -> 208.8 us); 160 rows in one round moved the layers by
 // -1.5 to +2 %.  FOLD exists for the other three wide shapes.
+//
+// 96 columns (four stages, see wide_stages) fill a round of deep reductions where 128-wide tiles leave a part of the chip idle or
+// start a second one: 64 x 96 wherever the model has it ahead in one round, 96 x 96 only where it fills at least 15/16 of it (below
+// it is level with 64 x 128).  us, before / now: 1 700 x 768 x 3072 15.3 / 13.5, 2 048: 15.9 / 14.0, 1 400 x 1024 x 4096 18.6 / 16.6,
+// 2 200 x 512 x 2048 10.2 / 9.5 (64 x 96); 2 800 x 768 x 3072 21.0 / 16.7, 2 192 x 1024 x 4096 25.4 / 20.9 (96 x 96).
 static bool gemm_shape_ok(const GemmTile& t, int M, int N, int K, bt_act act, int epi, bool wide_ok) {
   if (t.kind == kNarrow) return K / 64 >= 3;
   if (t.kind == kRegisterStaged) return K / 64 < 3;
   if (t.kind == kEightWaves) return !wide_ok && K / 64 >= 2 && (epi == EPI_PLAIN || t.bm == 128);  // FOLD would spill
   if (!wide_ok) return false;
+  if (t.bn == 96) {
+    if (epi != EPI_PLAIN || act != BT_ACT_NONE || K < 2 * N || K <= 256) return false;
+    const long long tiles = (long long)((M + t.bm - 1) / t.bm) * ((N + 95) / 96);
+    return tiles <= kComputeUnits && (t.bm == 64 || tiles >= kComputeUnits * 15 / 16);
+  }
   if (epi != EPI_PLAIN && t.bm != 256 && t.bm != 192 && t.bm != 128) return false;
   const bool short_act = (t.bm == 160 || t.bm == 96) && act != BT_ACT_NONE && K < 1024, deep = t.bm == 96 && K >= 2 * N;
   if (short_act || deep) {
@@ -1051,6 +1075,8 @@ static bt_status gemm_launch_tile(int tile, const half_t* a, const half_t* w, ha
     case 9: return BT_PIPE(256, 128, 4, 2, 3);
     case 10: return BT_PIPE(192, 128, 2, 4, 3);
     case 11: return BT_PIPE(128, 128, 2, 4, 3);
+    case 13: return launch_wide_deep<96>(a, w, c, M, N, K, act, epi, ep, st, np_out);
+    case 14: return launch_wide_deep<64>(a, w, c, M, N, K, act, epi, ep, st, np_out);
     default: return launch_simple(a, w, c, M, N, K, act, epi, ep, st, np_out);
   }
 #undef BT_PIPE

@@ -1,7 +1,8 @@
 // The wide-tile product kernel (included by gemm.hip).
 //
 //   C = epilogue(A W^T),  block tile BM x BN x 64, four wavefronts in a 2 x 2 grid (one per SIMD), wave tile
-//   (BM/2) x (BN/2) of 16x16x32 MFMA blocks, three operand stages in LDS, tiles taken one after another.
+//   (BM/2) x (BN/2) of 16x16x32 MFMA blocks, three operand stages in LDS (NS; four for some, see wide_stages), tiles taken
+//   one after another.
 //
 // What it is built around:
 //  - LDS traffic.  With eight wavefronts of 64 x 64 the fragment reads of a 256 x 128 x 64 slab are 128 KB and, with the
@@ -13,10 +14,11 @@
 //    the last slabs of a tile already fetch the first ones of the next, which land during the epilogue.  The
 //    epilogue stages 16 rows at a time in LDS of its own, so the ring keeps its contents.
 //
-// Slab g of the stream lives in stage g mod 3.  Its two k-steps (32 deep):
+// Slab g of the stream lives in stage g mod NS.  Its two k-steps (32 deep), with three stages (with four everything is
+// requested one slab earlier, and one more may be in flight):
 //    k-step 0   MFMAs on fragments in registers; reads the fragments of k-step 1; requests the second half of slab g+2
-//    hand-over  every fragment of slab g is in registers, slab g+1 has landed (vmcnt), barrier: stage g mod 3 is free
-//    k-step 1   MFMAs; reads the first fragments of slab g+1; requests the first half of slab g+3 into stage g mod 3
+//    hand-over  every fragment of slab g is in registers, slab g+1 has landed (vmcnt), barrier: its stage is free
+//    k-step 1   MFMAs; reads the first fragments of slab g+1; requests the first half of slab g+3 into that stage
 // A wait "at most TOT memory instructions in flight" at the hand-over is exact: what may still be in flight
 // is slab g+2.  Additional older requests (the bias of a tile) only make it stricter.  Loads return in order
 // among themselves, but stores may overtake them, so the epilogue waits for every request in flight before its
@@ -38,24 +40,31 @@ __device__ __forceinline__ void dma4_sv(const void* sbase, uint32_t voff, uint32
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(voff), "s"(sbase) : "memory", "m0");
 }
 
-template <int BM, int BN>
+// Stages.  Three hold all that LDS has room for from 192 rows on.  Deep reductions (SHAPE 2) on smaller tiles take four: a slab of
+// theirs is multiplied in a third to two thirds of the time its operands travel, and what the fourth stage costs, a slab's
+// requests ahead of the first product, they do not notice.  us, three stages / four: 1 400 x 1024 x 4096 with 96 x 128 tiles 22.8 / 20.7,
+// 128 x 128 24.5 / 23.3; 2 192 x 768 x 3072 18.7 / 18.0, 20.3 / 20.2; with 96 x 96 17.1 / 15.8.  Five and six are level with four, 160 rows level
+// (33.8 / 33.8), and K = 768 has nothing of it (1 200 x 2304, 128 x 128: 7.70 / 7.96; 160 x 128 8.73 / 8.93).
+constexpr int wide_stages(int bm, int epi, int shape) { return shape == 2 && epi == EPI_PLAIN && bm <= 128 ? 4 : 3; }
+
+template <int BM, int BN, int STAGES>
 struct WideTile {
   static constexpr int WM = BM / 2, WN = BN / 2, MI = WM / 16, NI = WN / 16;
   static constexpr int LA = BM / 32, LB = BN / 32, TOT = LA + LB;  // DMA instructions (8 rows each) per wave and slab
-  static constexpr int NS = 3, STAGE = (BM + BN) * 128;           // bytes per stage
+  static constexpr int NS = STAGES, STAGE = (BM + BN) * 128;  // operand stages, bytes per stage
   static constexpr int EPI_LD = WN + 8;                           // row pitch of the epilogue's staging rows, halves
   static constexpr int EPI_BYTES = 16 * EPI_LD * 2, BIAS_BYTES = 1024;
   static constexpr int LDS = NS * STAGE + 4 * EPI_BYTES + 2 * BIAS_BYTES;
   static_assert(LDS <= 160 * 1024, "LDS");
-  static_assert(TOT < 32, "vmcnt range");
+  static_assert((NS - 2) * TOT + TOT / 2 < 64, "vmcnt range");
 };
 
-template <int BM, int BN, int ACT, int EPI>
+template <int BM, int BN, int ACT, int EPI, int NS>
 __device__ __forceinline__ void gemm_wide_tiles(const half_t* __restrict__ A, const half_t* __restrict__ W,
                                                 const int32_t* __restrict__ a_rows, const half_t* __restrict__ bias, int M, int N,
                                                 int K, int tiles_n, int tiles_m, int group_m, half_t* __restrict__ C,
                                                 const GemmEpi& ep) {
-  using T = WideTile<BM, BN>;
+  using T = WideTile<BM, BN, NS>;
   constexpr int MI = T::MI, NI = T::NI, LA = T::LA, LB = T::LB, TOT = T::TOT, STAGE = T::STAGE;
   static_assert(EPI == EPI_PLAIN || EPI == EPI_FOLD, "epilogue form");
   // Several tiles per workgroup; FOLD: one.  It runs in one round of tiles nearly everywhere; where it does not (192- and
@@ -94,7 +103,7 @@ __device__ __forceinline__ void gemm_wide_tiles(const half_t* __restrict__ A, co
   };
   const uint32_t lds0 = lds_addr(smem);
   const uint32_t dma_a = lds0 + wave * LA * 1024, dma_b = lds0 + BM * 128 + wave * LB * 1024;
-  const int nk = K / 64;  // >= 4 (checked by the launcher)
+  const int nk = K / 64;  // > NS (checked by the launcher)
 
   // ---- fetch cursor: the slab whose requests are being issued
   uint32_t va[LA], vb[LB], nva[LA], nvb[LB];
@@ -112,9 +121,9 @@ __device__ __forceinline__ void gemm_wide_tiles(const half_t* __restrict__ A, co
   // PLAIN: BN bias values, a pair per lane (a bias is 8-byte aligned, not 16).  FOLD: BN values of fold_c, then BN of
   // fold_d = fold_c + N.
   auto request_bias = [&](int n_first, int parity) {
-    const uint32_t to = lds0 + T::NS * STAGE + 4 * T::EPI_BYTES + parity * T::BIAS_BYTES;
+    const uint32_t to = lds0 + NS * STAGE + 4 * T::EPI_BYTES + parity * T::BIAS_BYTES;
     if constexpr (EPI == EPI_PLAIN) {
-      static_assert(BN == 128, "one DMA instruction: 64 pairs");
+      static_assert(BN <= 128, "one DMA instruction: 64 pairs");
       if (bias && wave == 0) dma4_sv(bias, (uint32_t)min(n_first + lane * 2, N - 2) * 2u, to);
     } else {
       static_assert(BN == 128, "one DMA instruction: 32 lanes for each vector");
@@ -124,7 +133,7 @@ __device__ __forceinline__ void gemm_wide_tiles(const half_t* __restrict__ A, co
   auto advance = [&]() {
     fa_base += 64;
     fb_base += 64;
-    fstage = fstage == 2u * STAGE ? 0u : fstage + STAGE;
+    fstage = fstage == (NS - 1u) * STAGE ? 0u : fstage + STAGE;
   };
 
   request_bias(n0, 0);
@@ -132,8 +141,10 @@ __device__ __forceinline__ void gemm_wide_tiles(const half_t* __restrict__ A, co
   advance();
   // the requests of slab 0 of every wavefront go ahead of those of slab 1: the pipeline starts half a slab earlier
   __builtin_amdgcn_s_barrier();
-  static_for<TOT>(request);
-  advance();
+  static_for<NS - 2>([&](auto) {
+    static_for<TOT>(request);
+    advance();
+  });
   constexpr int HALF = TOT / 2;
   static_for<HALF>(request);
   int nm0 = 0, nn0 = 0;  // the tile after this one
@@ -200,10 +211,10 @@ __device__ __forceinline__ void gemm_wide_tiles(const half_t* __restrict__ A, co
     constexpr bool F0 = decltype(fetch0_c)::value, LAST = decltype(last_c)::value;
     kstep(integral_constant<int, 0>{}, zero_c, yes{}, integral_constant<int, HALF>{},
           integral_constant<int, F0 ? TOT : HALF>{}, row_a + rstage + co1, row_b + rstage + co1);
-    rstage = rstage == 2u * STAGE ? 0u : rstage + STAGE;
+    rstage = rstage == (NS - 1u) * STAGE ? 0u : rstage + STAGE;
     if constexpr (!LAST) {
       __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
-      if (wait) wait_vmcnt<(F0 ? TOT : 0) + decltype(younger_c)::value>();
+      if (wait) wait_vmcnt<(F0 ? (NS - 2) * TOT : 0) + decltype(younger_c)::value>();
       __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -219,7 +230,7 @@ __device__ __forceinline__ void gemm_wide_tiles(const half_t* __restrict__ A, co
       for (int q = 0; q < LB; ++q) vb[q] = nvb[q];
       request_bias(nn0, next_parity);
     }
-    if constexpr (F1 > 0) fstage = fstage == 2u * STAGE ? 0u : fstage + STAGE;
+    if constexpr (F1 > 0) fstage = fstage == (NS - 1u) * STAGE ? 0u : fstage + STAGE;
     __builtin_amdgcn_sched_barrier(0);
     kstep(integral_constant<int, 1>{}, no{}, integral_constant<bool, !LAST>{}, integral_constant<int, 0>{},
           integral_constant<int, (F1 > 0 ? HALF : 0)>{}, row_a + rstage + co0, row_b + rstage + co0);
@@ -227,12 +238,12 @@ __device__ __forceinline__ void gemm_wide_tiles(const half_t* __restrict__ A, co
   };
 
   // first fragments of slab 0 (slab 1 and half of slab 2 may be in flight)
-  wait_vmcnt<TOT + HALF>();
+  wait_vmcnt<(NS - 2) * TOT + HALF>();
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_sched_barrier(0);
   static_for<MI + NI>([&](auto i_c) { read_one(i_c, integral_constant<int, 0>{}, row_a + co0, row_b + co0); });
 
-  half_t* const stage = reinterpret_cast<half_t*>(smem + T::NS * STAGE + wave * T::EPI_BYTES);
+  half_t* const stage = reinterpret_cast<half_t*>(smem + NS * STAGE + wave * T::EPI_BYTES);
   bool first = true;
   for (int parity = 0;; parity ^= 1) {
     const bool last = !STREAM || id + (int)gridDim.x >= n_tiles;
@@ -241,7 +252,7 @@ __device__ __forceinline__ void gemm_wide_tiles(const half_t* __restrict__ A, co
     using none = integral_constant<int, 0>;
     float2 psum[EPI == EPI_FOLD ? MI : 1][row_sum_requests(BM, BN)];
     slab(yes{}, yes{}, next{}, no{}, none{}, first, 0);
-    for (int k = nk - 4; k > 0; --k) slab(no{}, yes{}, next{}, no{}, none{}, true, 0);
+    for (int k = nk - NS - 1; k > 0; --k) slab(no{}, yes{}, next{}, no{}, none{}, true, 0);
     if (last) {
       slab(no{}, yes{}, none{}, no{}, none{}, true, 0);
       // FOLD: the row sums arrive under the last two slabs.  They are younger than the last operand requests, and the only
@@ -250,18 +261,21 @@ __device__ __forceinline__ void gemm_wide_tiles(const half_t* __restrict__ A, co
       // Requested behind the last slab, their round trip stood alone in every tile: six folded layers of width 768 at 2 308
       // tokens 408.3 -> 405.4 us, at 1 500 tokens 340.2 -> 335.0 us; width 1024 at 1 600 tokens 452.6 -> 443.7 us.
       if constexpr (EPI == EPI_FOLD) request_row_sums(ep.ln_part, ep.ln_np, M, m0 + wm * T::WM, l16, quad, psum);
-      slab(no{}, no{}, none{}, no{}, integral_constant<int, EPI == EPI_FOLD ? MI * row_sum_requests(BM, BN) : 0>{}, true, 0);
+      static_for<NS - 2>([&](auto t_c) {  // the slabs behind the next one may be in flight
+        slab(no{}, no{}, none{}, no{},
+             integral_constant<int, (EPI == EPI_FOLD ? MI * row_sum_requests(BM, BN) : 0) + (NS - 3 - decltype(t_c)::value) * TOT>{}, true, 0);
+      });
       slab(no{}, no{}, none{}, yes{}, none{}, true, 0);
     } else {
       slab(no{}, yes{}, switch_tile{}, no{}, none{}, true, parity ^ 1);
-      for (int k = 2; k > 0; --k) slab(no{}, yes{}, next{}, no{}, none{}, true, 0);
+      for (int k = NS - 1; k > 0; --k) slab(no{}, yes{}, next{}, no{}, none{}, true, 0);
     }
     first = false;
 
     // ---- epilogue: acc[i][j][t] = C[m][n], m = m_base + i*16 + l16, n = n_base + j*16 + 4 quad + t
     const int m_base = m0 + wm * T::WM, n_base = n0 + wn * T::WN;
     float mu[MI], rstd[MI];
-    const char* const col_lds = smem + T::NS * STAGE + 4 * T::EPI_BYTES + parity * T::BIAS_BYTES;
+    const char* const col_lds = smem + NS * STAGE + 4 * T::EPI_BYTES + parity * T::BIAS_BYTES;
     float4_t c4[NI], d4[NI];  // PLAIN: d4 = bias;  FOLD: c4, d4
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
@@ -294,8 +308,7 @@ __device__ __forceinline__ void gemm_wide_tiles(const half_t* __restrict__ A, co
         }
       }
     };
-    constexpr int LPR = T::WN / 8, RPP = 64 / LPR;  // lanes per row of the row-contiguous pass, rows per pass
-    const int rr = lane / LPR, cc = (lane % LPR) * 8;
+    constexpr int LPR = T::WN / 8;  // 16-byte pieces of a row in the row-contiguous pass
     // The arithmetic runs MI/2 blocks ahead of the stores: the requests in flight for the next tile land under it.
     // (FOLD has waited for them already, with its row sums.)
     constexpr int AHEAD = EPI == EPI_FOLD ? 0 : MI / 2;
@@ -310,9 +323,11 @@ __device__ __forceinline__ void gemm_wide_tiles(const half_t* __restrict__ A, co
       for (int j = 0; j < NI; ++j) *reinterpret_cast<half4_t*>(stage + l16 * T::EPI_LD + j * 16 + 4 * quad) = out[i][j];
       // same wavefront reads what it wrote: LDS operations of a wave complete in order
 #pragma unroll
-      for (int r0 = 0; r0 < 16; r0 += RPP) {
-        const int mr = m_base + i * 16 + r0 + rr, n = n_base + cc;
-        const uint4_t o4 = *reinterpret_cast<const uint4_t*>(stage + (r0 + rr) * T::EPI_LD + cc);
+      for (int p0 = 0; p0 < 16 * LPR; p0 += 64) {
+        const int piece = p0 + lane, rr = piece / LPR, cc = (piece % LPR) * 8;
+        const int mr = m_base + i * 16 + rr, n = n_base + cc;
+        if (16 * LPR % 64 != 0 && rr >= 16) continue;
+        const uint4_t o4 = *reinterpret_cast<const uint4_t*>(stage + rr * T::EPI_LD + cc);
         if (mr < M && n < N) store_through(C + ((size_t)mr * N + n), o4);  // written through: see store_tile
       }
     }
@@ -333,5 +348,5 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(
     const half_t* __restrict__ A, const half_t* __restrict__ W, const int32_t* __restrict__ a_rows /* = ep.a_rows */,
     const half_t* __restrict__ bias /* = ep.bias */, int M, int N, int K, int tiles_n, int tiles_m, int group_m,
     half_t* __restrict__ C, const GemmEpi ep) {
-  gemm_wide_tiles<BM, BN, ACT, EPI>(A, W, a_rows, bias, M, N, K, tiles_n, tiles_m, group_m, C, ep);
+  gemm_wide_tiles<BM, BN, ACT, EPI, wide_stages(BM, EPI, SHAPE)>(A, W, a_rows, bias, M, N, K, tiles_n, tiles_m, group_m, C, ep);
 }

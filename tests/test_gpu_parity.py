@@ -323,6 +323,32 @@ def test_gemm_wide_tiles(bt, tile, M, N, K, act):
     assert np.abs(got - ref).max() <= 2e-3 * max(1.0, np.abs(ref).max())
 
 
+@pytest.mark.parametrize("bm,bn,M,N,K", [
+    (64, 96, 4726, 224, 1280), (64, 96, 4339, 288, 832), (64, 96, 4146, 264, 896), (64, 96, 6488, 144, 1216), (64, 96, 14755, 80, 320),
+    (96, 96, 11673, 176, 768), (96, 96, 5953, 368, 1344), (96, 96, 11991, 136, 1152), (96, 96, 11558, 176, 960), (96, 96, 11440, 152, 320),
+    (96, 128, 7389, 328, 1280), (96, 128, 6888, 272, 576), (96, 128, 7400, 312, 1152), (96, 128, 9363, 248, 704), (96, 128, 18773, 120, 320),
+    (128, 128, 10782, 648, 1536), (128, 128, 9525, 344, 1088), (128, 128, 10781, 672, 1408), (128, 128, 10831, 664, 1472),
+    (128, 128, 13046, 136, 320), (64, 96, 2048, 768, 3072), (96, 96, 2192, 1024, 4096)])
+def test_gemm_four_stage_tiles(bt, bm, bn, M, N, K):
+    """Deep reductions on the tiles with four stages: every residue of the slabs modulo the ring, the shortest (five slabs), ragged
+    rows and columns, several tiles to a workgroup, columns in tiles of 96.  The bits of the narrow tiles."""
+    import torch
+    assert bt.gemm_tile_shape(M, N, K) == (bm, bn) and bt.gemm_row_split(M, N, K) == 0
+    rng = np.random.default_rng(M + N + K)
+    a = rng.normal(0, 1, (M, K)).astype(np.float16)
+    w = rng.normal(0, 0.05, (N, K)).astype(np.float16)
+    b = rng.normal(0, 0.5, N).astype(np.float16)
+    ad, wd, bd = dev(a), dev(w), dev(b)
+    guard = torch.full((M + 1, N), 9.0, dtype=torch.float16, device="cuda")
+    got = bt.gemm_bias_act(ad, wd, bd, out=guard[:M])
+    assert bool((guard[M] == 9.0).all())
+    narrow = torch.cat([bt.gemm_bias_act(ad[m:m + 128], wd, bd) for m in range(0, M, 128)])
+    assert bt.gemm_tile_shape(128, N, K) == (64, 64) and torch.equal(got, narrow)
+    rows = rng.integers(0, M, 400)
+    ref = a[rows].astype(np.float64) @ w.astype(np.float64).T + b.astype(np.float64)
+    assert np.abs(host(got).astype(np.float64)[rows] - ref).max() <= 2e-3 * max(1.0, np.abs(ref).max())
+
+
 @pytest.mark.parametrize("tile,M,N,K,act", [
     (256, 16370, 504, 128, 1), (256, 16370, 504, 192, 0), (192, 9893, 504, 128, 2), (192, 9893, 504, 192, 1),
     (128, 9893, 376, 128, 0), (128, 9893, 376, 192, 2)])
