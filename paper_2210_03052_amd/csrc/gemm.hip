@@ -946,7 +946,9 @@ static const GemmTile kGemmTiles[] = {
     {192, 128, 1.6f, 0.50f, 0.06f, 2.7f, kEightWaves}, {128, 128, 1.5f, 0.28f, 0.10f, 2.5f, kEightWaves},
     {64, 64, 2.7f, 0.19f, 0.f, 0.35f, kRegisterStaged},
     {96, 96, 2.0f, 0.20f, 0.089f, 1.1f, kWide},        {64, 96, 2.3f, 0.165f, 0.055f, 0.8f, kWide}};
-constexpr int kGemmShapes = sizeof(kGemmTiles) / sizeof(kGemmTiles[0]);
+constexpr int kGemmShapes = sizeof(kGemmTiles) / sizeof(kGemmTiles[0]), kDeepShapes = 2;
+// The last two are for deep reductions only; the others do not pay for looking at them.
+static bool gemm_deep(int N, int K, bt_act act, int epi) { return epi == EPI_PLAIN && act == BT_ACT_NONE && K >= 2 * N && K > 256; }
 constexpr float kActUs = 0.75e-4f;  // per output of a tile
 
 // gemm_wide_kernel: at least four slabs, 32-bit byte offsets into both operands.  Its residual epilogue does not exist: the
@@ -966,13 +968,13 @@ static bool gemm_wide_ok(long long a_rows, int N, int K, int epi) {
 // start a second one: 64 x 96 wherever the model has it ahead in one round, 96 x 96 only where it fills at least 15/16 of it (below
 // it is level with 64 x 128).  us, before / now: 1 700 x 768 x 3072 15.3 / 13.5, 2 048: 15.9 / 14.0, 1 400 x 1024 x 4096 18.6 / 16.6,
 // 2 200 x 512 x 2048 10.2 / 9.5 (64 x 96); 2 800 x 768 x 3072 21.0 / 16.7, 2 192 x 1024 x 4096 25.4 / 20.9 (96 x 96).
-static bool gemm_shape_ok(const GemmTile& t, int M, int N, int K, bt_act act, int epi, bool wide_ok) {
+// Inlined: their time is idle time of the device where a launch waits for the host.
+__attribute__((always_inline)) static inline bool gemm_shape_ok(const GemmTile& t, int M, int N, int K, bt_act act, int epi, bool wide_ok) {
   if (t.kind == kNarrow) return K / 64 >= 3;
   if (t.kind == kRegisterStaged) return K / 64 < 3;
   if (t.kind == kEightWaves) return !wide_ok && K / 64 >= 2 && (epi == EPI_PLAIN || t.bm == 128);  // FOLD would spill
   if (!wide_ok) return false;
-  if (t.bn == 96) {
-    if (epi != EPI_PLAIN || act != BT_ACT_NONE || K < 2 * N || K <= 256) return false;
+  if (t.bn == 96) {  // gemm_deep
     const long long tiles = (long long)((M + t.bm - 1) / t.bm) * ((N + 95) / 96);
     return tiles <= kComputeUnits && (t.bm == 64 || tiles >= kComputeUnits * 15 / 16);
   }
@@ -987,7 +989,7 @@ static bool gemm_shape_ok(const GemmTile& t, int M, int N, int K, bt_act act, in
 
 // A single round of wide tiles on nearly every compute unit, all of them storing at once, costs more inside an encoder layer
 // than the model says (1.5 to 3.7 us on the products without an activation): full_us.
-static float gemm_shape_us(const GemmTile& t, int M, int N, int K, bt_act act) {
+__attribute__((always_inline)) static inline float gemm_shape_us(const GemmTile& t, int M, int N, int K, bt_act act) {
   const long long tiles = (long long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
   const float rounds = (float)((tiles + kComputeUnits - 1) / kComputeUnits), slabs = (float)(K / 64);
   const float epi = t.epi_us + (act != BT_ACT_NONE ? kActUs * t.bm * t.bn : 0.f);
@@ -1015,7 +1017,8 @@ static int gemm_tile_choice(int M, int N, int K, bt_act act, int epi, bool wide_
   if (epi == EPI_RESID) return gemm_resid_tile_choice(M, N, K);
   int best = -1;
   float best_us = 0.f;
-  for (int c = 0; c < kGemmShapes; ++c) {
+  const int shapes = gemm_deep(N, K, act, epi) ? kGemmShapes : kGemmShapes - kDeepShapes;
+  for (int c = 0; c < shapes; ++c) {
     if (!gemm_shape_ok(kGemmTiles[c], M, N, K, act, epi, wide_ok)) continue;
     const float us = gemm_shape_us(kGemmTiles[c], M, N, K, act);
     if (best < 0 || us < best_us) { best = c; best_us = us; }
@@ -1038,7 +1041,7 @@ static int gemm_msplit_choice(int M, int N, int K, bt_act act, bool wide_ok, int
   (void)gemm_tile_choice(M, N, K, act, EPI_PLAIN, wide_ok, &best_us);
   if (K < 768) best_us *= 0.96f;
   int best_rows = 0;
-  for (int c = 0; c < kGemmShapes; ++c) {
+  for (int c = 0; c < kGemmShapes - kDeepShapes; ++c) {  // those two are never more than a round
     const GemmTile& t = kGemmTiles[c];
     if (!gemm_shape_ok(t, M, N, K, act, EPI_PLAIN, wide_ok)) continue;
     const long long tn = (N + t.bn - 1) / t.bn, tm = (M + t.bm - 1) / t.bm, tiles = tm * tn;
@@ -1108,24 +1111,31 @@ bt_status gemm_dispatch(const bt_half* A, const bt_half* W, int M, int N, int K,
 
 // C = A[a_rows] W^T + bias with the number of rows, *rows <= rows_max, in device memory.  For the first product of a stack: the
 // host waits for the count before it can size a launch, and the device would wait for that launch; this one is sized by
-// rows_max and reads the count itself, so the device has work until the host has caught up.  The shape is taken for five
-// eighths of rows_max (sentences of even lengths fill a little more than half of a padded batch); a row's result is the same in
-// every shape.  What it buys is the time until the host's first launch arrives, less the round trip of the count into the
+// rows_max and reads the count itself, so the device has work until the host has caught up.  Its shape is the one that
+// loses least against the best for three, five or eight eighths of rows_max (a few long sentences, even lengths, full ones),
+// and there is none where that loss may reach kCountedLossUs: beyond ten thousand rows of width 512 the wrong shape cost more than the
+// wait (one layer, 16 269 rows, taken for five eighths alone: 191.7 -> 197.0 us).  A row's result is the same in every shape.  What it buys is the time until the host's first launch arrives, less the round trip of the count into the
 // kernel's registers: masked calls, both builds in one process: one layer, 4 x up to 64, 36.6 -> 31.8 us; 12 layers, 1 x up to
-// 128, 271.5 -> 267.0, 8 x up to 128 462.9 -> 457.3, 16 x up to 256 775.2 -> 768.3; full batches, for which the shape is taken too
-// small, no less (25 x 185, six layers 642.4 -> 630.4).  Narrow tiles of which most would find no rows are not launched by the
+// 128, 271.5 -> 267.0, 8 x up to 128 462.9 -> 457.3, 16 x up to 256 775.2 -> 768.3.  Narrow tiles of which most would find no rows are not launched by the
 // thousand (the limit is sixteen rounds).  BT_ERR_UNSUPPORTED: no form for these sizes, nothing enqueued.
+constexpr float kCountedLossUs = 4.f;
 bt_status gemm_counted_dispatch(const bt_half* A, const bt_half* W, const int32_t* a_rows, const bt_half* bias,
                                 const int32_t* rows, int rows_max, int N, int K, bt_half* C, hipStream_t st) {
   if ((K % 64) != 0 || K < 256) return BT_ERR_UNSUPPORTED;
-  static constexpr int kShapes[] = {0, 2, 4, 7, 8};
-  const int expected = (int)((long long)rows_max * 5 / 8) + 1;
+  static constexpr int kShapes[] = {0, 2, 4, 7, 8}, kEighths[] = {3, 5, 8};
+  const bool wide_ok = gemm_wide_ok(rows_max, N, K, EPI_PLAIN);
   int best = -1;
-  float best_us = 0.f;
+  float best_us = kCountedLossUs;
   for (const int c : kShapes) {
-    if (!gemm_shape_ok(kGemmTiles[c], expected, N, K, BT_ACT_NONE, EPI_PLAIN, gemm_wide_ok(rows_max, N, K, EPI_PLAIN))) continue;
-    const float us = gemm_shape_us(kGemmTiles[c], expected, N, K, BT_ACT_NONE);
-    if (best < 0 || us < best_us) { best = c; best_us = us; }
+    float loss = 0.f;
+    for (const int e : kEighths) {
+      const int rows = (int)((long long)rows_max * e / 8) + 1;
+      float us = 0.f;
+      (void)gemm_tile_choice(rows, N, K, BT_ACT_NONE, EPI_PLAIN, wide_ok, &us);
+      const bool ok = gemm_shape_ok(kGemmTiles[c], rows, N, K, BT_ACT_NONE, EPI_PLAIN, wide_ok);
+      loss = fmaxf(loss, ok ? gemm_shape_us(kGemmTiles[c], rows, N, K, BT_ACT_NONE) - us : 2.f * kCountedLossUs);
+    }
+    if (loss < best_us) { best = c; best_us = loss; }
   }
   if (best < 0) return BT_ERR_UNSUPPORTED;
   const GemmTile& t = kGemmTiles[best];
