@@ -308,7 +308,8 @@ __device__ __forceinline__ void gemm_wide_tiles(const half_t* __restrict__ A, co
         }
       }
     };
-    constexpr int LPR = T::WN / 8;  // 16-byte pieces of a row in the row-contiguous pass
+    constexpr int LPR = T::WN / 8, RPP = 64 / LPR;  // lanes per row of the row-contiguous pass, rows per pass
+    const int rr = lane / LPR, cc = (lane % LPR) * 8;
     // The arithmetic runs MI/2 blocks ahead of the stores: the requests in flight for the next tile land under it.
     // (FOLD has waited for them already, with its row sums.)
     constexpr int AHEAD = EPI == EPI_FOLD ? 0 : MI / 2;
@@ -323,11 +324,10 @@ __device__ __forceinline__ void gemm_wide_tiles(const half_t* __restrict__ A, co
       for (int j = 0; j < NI; ++j) *reinterpret_cast<half4_t*>(stage + l16 * T::EPI_LD + j * 16 + 4 * quad) = out[i][j];
       // same wavefront reads what it wrote: LDS operations of a wave complete in order
 #pragma unroll
-      for (int p0 = 0; p0 < 16 * LPR; p0 += 64) {
-        const int piece = p0 + lane, rr = piece / LPR, cc = (piece % LPR) * 8;
-        const int mr = m_base + i * 16 + rr, n = n_base + cc;
-        if (16 * LPR % 64 != 0 && rr >= 16) continue;
-        const uint4_t o4 = *reinterpret_cast<const uint4_t*>(stage + rr * T::EPI_LD + cc);
+      for (int r0 = 0; r0 < 16; r0 += RPP) {  // 96 columns: six lanes a row, ten rows a pass, the last four lanes idle
+        if (RPP * LPR != 64 && (rr >= RPP || r0 + rr >= 16)) continue;
+        const int mr = m_base + i * 16 + r0 + rr, n = n_base + cc;
+        const uint4_t o4 = *reinterpret_cast<const uint4_t*>(stage + (r0 + rr) * T::EPI_LD + cc);
         if (mr < M && n < N) store_through(C + ((size_t)mr * N + n), o4);  // written through: see store_tile
       }
     }

@@ -865,8 +865,8 @@ def test_encoder_fwd_masked_equals_the_two_calls(bt, use_mask, folded):
 @pytest.mark.parametrize("B,S,H", [(3, 21, 768), (2, 128, 512), (9, 130, 768), (16, 129, 1024), (16, 256, 768), (13, 640, 512),
                                    (30, 512, 768), (5, 40, 192)])
 def test_first_product_ahead_of_the_count(bt, B, S, H):
-    """The masked call launches its first product before the host knows the number of tokens, in a shape taken for five eighths of
-    the padded rows: the same bits as with the count known, for a single token, one more than a tile, ragged and full batches, in
+    """The masked call launches its first product before the host knows the number of tokens, in a shape chosen for a range of
+    counts: the same bits as with the count known, for a single token, one more than a tile, ragged and full batches, in
     each of its shapes and where there is none (width 192); rows that hold no token are neither read nor written."""
     import torch
     rng = np.random.default_rng([B, S, H])
