@@ -73,8 +73,8 @@ __device__ __forceinline__ FragAddr make_frag_addr(int lane) {
 }
 
 // One 64-key tile for the 32 query rows of a wavefront, step by step:  S^T = K Q^T (qk_tile);  mask of a
-// ragged last tile;  then, per block of 32 keys, P = exp2(S - m), row sums, fp16 P (softmax_exp) and
-// O^T += V^T P^T (pv_step).
+// ragged last tile;  reference of the exponentials (raise_reference);  P = exp2(S - m), row sums, fp16 P
+// (softmax_exp);  O^T += V^T P^T (pv_step).
 __device__ __forceinline__ void qk_tile(const half_t* sk, const half8_t (&qf)[4], const FragAddr& fa,
                                         float16_t (&s)[2]) {
 #pragma unroll
@@ -110,23 +110,7 @@ __device__ __forceinline__ void both_halves(float x, float& lo, float& hi) {
   hi = __builtin_bit_cast(float, (unsigned)sw[1]);
 }
 
-// m_run, the reference of the exponentials, is kept in the scaled log2 domain; any reference gives the same softmax.  It is
-// the maximum of a sequence's first tile and stays there until the probabilities of a block outgrow it (see process_tile).
-// Largest logit of a 32-key block in this lane: two independent chains of three-operand maxima.
-__device__ __forceinline__ float block_max(const float16_t& t) {
-  float c[2];
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int o = 8 * j;
-    float m = fmaxf(fmaxf(t[o], t[o + 1]), t[o + 2]);
-    m = fmaxf(fmaxf(m, t[o + 3]), t[o + 4]);
-    m = fmaxf(fmaxf(m, t[o + 5]), t[o + 6]);
-    c[j] = fmaxf(m, t[o + 7]);
-  }
-  return fmaxf(c[0], c[1]);
-}
-
-// Of the whole tile: four chains.
+// Largest logit of the tile in this lane: four independent chains of three-operand maxima.
 __device__ __forceinline__ float tile_max(const float16_t (&s)[2]) {
   float c[4];
 #pragma unroll
@@ -141,14 +125,14 @@ __device__ __forceinline__ float tile_max(const float16_t (&s)[2]) {
   return fmaxf(fmaxf(fmaxf(c[0], c[1]), c[2]), c[3]);
 }
 
-// Raises the reference to mx (a lane's maximum; the two halves of a query column agree on the larger one) where that is
-// more than `slack` above it, and rescales what has been summed so far.
-__device__ __forceinline__ void raise_reference(float mx, float slack, float scale_log2e, float& m_run, float& l_run,
-                                                float16_t (&o_acc)[2]) {
+// m_run, the reference of a row's exponentials, is kept in the scaled log2 domain; any reference gives the same softmax.  It is
+// the maximum of the first tile and raised where the maximum of a tile exceeds it by more than 8 (a factor 256: probabilities
+// stay at or below 256), so the sums are hardly ever rescaled.  mx: a lane's maximum of the tile.
+__device__ __forceinline__ void raise_reference(float mx, float scale_log2e, float& m_run, float& l_run, float16_t (&o_acc)[2]) {
   float lo, hi;
   both_halves(mx, lo, hi);
-  const float mx_s = fmaxf(lo, hi) * scale_log2e;
-  const bool raise = mx_s > m_run + slack;  // same in both halves of a query column
+  const float mx_s = fmaxf(lo, hi) * scale_log2e;  // finite: every tile holds at least one valid key
+  const bool raise = mx_s > m_run + 8.0f;          // same in both halves of a query column
   if (__builtin_amdgcn_ballot_w64(raise)) {
     const float m_new = raise ? mx_s : m_run;
     const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
@@ -161,23 +145,25 @@ __device__ __forceinline__ void raise_reference(float mx, float slack, float sca
   }
 }
 
-// P = exp2(S - m) of a 32-key block, to fp16.  The row sum is taken over the fp16 probabilities, the values the second
-// product multiplies, two per instruction (dot product with (1, 1), fp32 accumulate) instead of one fp32 add per
-// probability.  Returns this half's row sum.
-__device__ __forceinline__ float softmax_exp(const float16_t& s, float scale_log2e, float m_run, half8_t (&pf)[2]) {
+// P = exp2(S - m), to fp16.  The row sum is taken over the fp16 probabilities, the values the second product multiplies, two
+// per instruction (dot product with (1, 1), fp32 accumulate) instead of one fp32 add per probability.  Returns this half's
+// row sum.
+__device__ __forceinline__ float softmax_exp(const float16_t (&s)[2], float scale_log2e, float m_run, half8_t (&pf)[2][2]) {
   typedef __fp16 fp16x2_t __attribute__((ext_vector_type(2)));
   const fp16x2_t ones = {(__fp16)1.0f, (__fp16)1.0f};
-  float psum = 0.f;
+  float psum[2] = {0.f, 0.f};
 #pragma unroll
-  for (int r = 0; r < 16; r += 2) {
-    const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], scale_log2e, -m_run));
-    const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r + 1], scale_log2e, -m_run));
-    const half2_t h = {(half_t)p0, (half_t)p1};
-    pf[r >> 3][r & 7] = h[0];
-    pf[r >> 3][(r & 7) + 1] = h[1];
-    psum = __builtin_amdgcn_fdot2(__builtin_bit_cast(fp16x2_t, h), ones, psum, false);
-  }
-  return psum;
+  for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+    for (int r = 0; r < 16; r += 2) {
+      const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][r], scale_log2e, -m_run));
+      const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][r + 1], scale_log2e, -m_run));
+      const half2_t h = {(half_t)p0, (half_t)p1};
+      pf[kb][r >> 3][r & 7] = h[0];
+      pf[kb][r >> 3][(r & 7) + 1] = h[1];
+      psum[kb] = __builtin_amdgcn_fdot2(__builtin_bit_cast(fp16x2_t, h), ones, psum[kb], false);
+    }
+  return psum[0] + psum[1];
 }
 
 // O^T += V^T P^T, 16-key step ks, output dimensions 32 db ..+31: it covers S^T registers 8*(ks%2)..+7 of block ks/2, i.e. keys
@@ -197,53 +183,39 @@ __device__ __forceinline__ void pv_step(const half_t* sv, int ks, int db, const 
   o_acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, p, o_acc, 0, 0, 0);
 }
 
-// Two forms.  TALL (the kernel for long sequences): the maximum is only taken where it is needed: on a sequence's first tile, and where a block's row sum (fp32, over 16
-// probabilities of a lane) says that one of them may be above 256.  A sum of up to 256 means probabilities of up to 256, so
-// nothing comes near the fp16 range; an overflow or a NaN fails the comparison as well.  The row then gets the block's
-// maximum as its reference and the block's exponentials are taken again (a sum of more than 256 means a logit above the
-// reference).  Without it a tile is 32 multiply-adds, 32 exponentials, 16 conversions and 16 dot products, the first
-// exponentials do not wait for the last product of the tile, and the second block's run under the first one's V^T P^T:
-// 8 sequences of 1024 to 4096 tokens, 16 heads 409.1 -> 392.4 us against a maximum per tile, 16 x up to 256, 12 heads 6.85 -> 6.51.
-// The others: a maximum per tile, which raises the reference where it is more than 8 (a factor 256) above it.  They run
-// where a wavefront has one or two tiles, and the pieces of a tile that the checks separate cost more than the maximum of the second:
-// 16 x up to 128 5.32 us, in the form above 5.47; 8 x up to 128 5.03, 5.15; one of 256 4.85, 4.94.
-template <bool TALL>
+// GUESS: `calm` says that the reference has been good enough so far; the exponentials are then taken without a look at the
+// tile's maximum, and the row sums tell whether that was right.  A lane's sum below 192 means probabilities below 192, a
+// maximum that raise_reference would have left alone (its limit is 256), and what has been computed is what it would have
+// been; an overflow or a NaN fails the comparison.  Else the tile's exponentials are taken again behind raise_reference, and
+// the wavefront looks at the maximum from then on.  So the guess changes no bit, a row's result does not depend on the other
+// rows of its wavefront, and where logits keep rising it costs the exponentials of one tile per wavefront, once.
+// A guess in every tile, with the reference raised per block of 32 keys where a sum asked for it, was 2 to 5 % faster on
+// N(0,1) logits but up to 45 % slower where logits rise along the keys (8 sequences of 1024 to 4096 tokens, 16 heads, us,
+// maximum in every tile / that / this: N(0,1) logits 320.6 / 306.6 / 304.5, N(0,9) 325.3 / 315.8 / 326.7, rows that attend
+// near themselves 300.5 / 367.8 / 303.6, logits that rise every 24 keys 321.8 / 475.4 / 323.6).
+template <bool GUESS>
 __device__ __forceinline__ void process_tile(const half_t* sk, const half_t* sv, const half8_t (&qf)[4], int k0, int L,
-                                             bool first, float scale_log2e, const FragAddr& fa, float& m_run, float& l_run,
+                                             float scale_log2e, const FragAddr& fa, bool& calm, float& m_run, float& l_run,
                                              float16_t (&o_acc)[2]) {
   float16_t s[2];
   qk_tile(sk, qf, fa, s);
   if (k0 + kKT > L) mask_ragged(s, k0, L, fa.hf);  // wave-uniform
-  if constexpr (!TALL) {
-    raise_reference(tile_max(s), 8.f, scale_log2e, m_run, l_run, o_acc);
-    half8_t pf[2][2];
-    const float sum0 = softmax_exp(s[0], scale_log2e, m_run, pf[0]), sum1 = softmax_exp(s[1], scale_log2e, m_run, pf[1]);
-    l_run += sum0 + sum1;
-#pragma unroll
-    for (int db = 0; db < 2; ++db)
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) pv_step(sv, ks, db, fa, pf[ks >> 1][ks & 1], o_acc[db]);
-    return;
+  half8_t pf[2][2];
+  float sum = 0.f;
+  bool ready = false;
+  if (GUESS && calm) {
+    sum = softmax_exp(s, scale_log2e, m_run, pf);
+    calm = ready = __builtin_amdgcn_ballot_w64(!(sum < 192.f)) == 0;
   }
-  if (first) raise_reference(tile_max(s), 0.f, scale_log2e, m_run, l_run, o_acc);
-  float tile_sum = 0.f;
-#pragma unroll
-  for (int kb = 0; kb < 2; ++kb) {
-    half8_t pf[2];
-    float psum = softmax_exp(s[kb], scale_log2e, m_run, pf);
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(psum <= 256.f)) != 0, 0)) {
-      l_run += tile_sum;  // the first block's share is rescaled with the rest
-      tile_sum = 0.f;
-      raise_reference(block_max(s[kb]), 0.f, scale_log2e, m_run, l_run, o_acc);
-      psum = softmax_exp(s[kb], scale_log2e, m_run, pf);
-    }
-    tile_sum += psum;
-#pragma unroll
-    for (int k = 0; k < 2; ++k)
-#pragma unroll
-      for (int db = 0; db < 2; ++db) pv_step(sv, 2 * kb + k, db, fa, pf[k], o_acc[db]);
+  if (!ready) {
+    raise_reference(tile_max(s), scale_log2e, m_run, l_run, o_acc);
+    sum = softmax_exp(s, scale_log2e, m_run, pf);
   }
-  l_run += tile_sum;
+  l_run += sum;
+#pragma unroll
+  for (int db = 0; db < 2; ++db)
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) pv_step(sv, ks, db, fa, pf[ks >> 1][ks & 1], o_acc[db]);
 }
 
 // Locate the (sequence, q-tile) a workgroup owns.  Results are wave-uniform (readfirstlane).
@@ -314,8 +286,7 @@ __global__ __launch_bounds__(NW * 64, 4) void varlen_mha_kernel(
   constexpr int BQ = NW * 32;
   constexpr int TILE = kKT * kD;            // halves per K (or V) tile
   constexpr int PER = 8 / NW;               // DMA instructions per wave per operand tile (8 rows each)
-  constexpr int TOT = 2 * PER;              // ... per stage
-  static_assert(NW == 1 || NW == 2 || NW == 4, "NW");
+  static_assert((NW == 1 || NW == 2 || NW == 4) && NS == 2, "wavefronts, stages (see mha_dispatch)");
 
   __shared__ __attribute__((aligned(1024))) half_t sK[NS * TILE];
   __shared__ __attribute__((aligned(1024))) half_t sV[NS * TILE];
@@ -401,25 +372,35 @@ __global__ __launch_bounds__(NW * 64, 4) void varlen_mha_kernel(
 
   const FragAddr fa = make_frag_addr(lane);
 
-  // unrolled over the stages: every LDS address of a tile is a lane constant plus an immediate
-  auto tile = [&](int kt, auto stage_c) {
-    constexpr int STAGE = decltype(stage_c)::value;
-    {  // tile kt landed (at most min(ntiles-1-kt, NS-2) younger tiles in flight) and is published
-      const int younger = min(ntiles - 1 - kt, NS - 2);
-      if (NS >= 4 && younger >= 2) mha_wait_vmcnt<(NS >= 4 ? 2 : 0) * TOT>();
-      else if (NS >= 3 && younger == 1) mha_wait_vmcnt<(NS >= 3 ? 1 : 0) * TOT>();
-      else mha_wait_vmcnt<0>();
-      __builtin_amdgcn_s_barrier();
-    }
-    if (kt + NS - 1 < ntiles) issue_tile(kt + NS - 1, STAGE == 0 ? NS - 1 : STAGE - 1);
+  bool calm = false;  // see process_tile
+  auto tile = [&](int kt, auto stage, auto guess) {
+    mha_wait_vmcnt<0>();  // tile kt has landed ...
+    __builtin_amdgcn_s_barrier();  // ... and is published
+    if (kt + 1 < ntiles) issue_tile(kt + 1, stage ^ 1);
     if (wave_active)
-      process_tile<(NW == 4)>(sK + STAGE * TILE, sV + STAGE * TILE, qf, kt * kKT, L, STAGE == 0 && kt == 0, scale_log2e, fa, m_run, l_run,
-                   o_acc);
+      process_tile<decltype(guess)::value>(sK + stage * TILE, sV + stage * TILE, qf, kt * kKT, L, scale_log2e, fa, calm, m_run,
+                                           l_run, o_acc);
   };
-  static_assert(NS == 2, "two stages, see mha_dispatch");
-  for (int kt = 0; kt < ntiles; kt += NS) {
-    tile(kt, std::integral_constant<int, 0>{});
-    if (kt + 1 < ntiles) tile(kt + 1, std::integral_constant<int, 1>{});
+  using even = std::integral_constant<int, 0>;
+  using odd = std::integral_constant<int, 1>;
+  // By the length of the sequence.  From six tiles on the loop is unrolled over the two stages, and every LDS address is a lane
+  // constant plus an immediate; below, the larger code costs more than that gives.  us, unrolled / not: 16 x up to 256, 12 heads
+  // 7.02 / 6.75, 16 x 100 to 512 13.2 / 13.3, 16 x 128 to 1024 29.6 / 30.2, 8 x 1024 to 4096, 16 heads 334 / 339.
+  // From 2 048 keys on the exponentials do not wait for the maximum (process_tile).  A wrong guess stops the other wavefronts of the
+  // workgroup too, in up to four tiles: with it from 1 024 keys on, N(0,9) logits at 16 x 128 to 1024 took 31.9 us, without 31.0.
+  if (NW == 4 && ntiles >= 32) {
+    for (int kt = 0; kt < ntiles; kt += 2) {
+      tile(kt, even{}, std::true_type{});
+      if (kt == 0) calm = true;
+      if (kt + 1 < ntiles) tile(kt + 1, odd{}, std::true_type{});
+    }
+  } else if (NW == 4 && ntiles >= 6) {
+    for (int kt = 0; kt < ntiles; kt += 2) {
+      tile(kt, even{}, std::false_type{});
+      if (kt + 1 < ntiles) tile(kt + 1, odd{}, std::false_type{});
+    }
+  } else {
+    for (int kt = 0; kt < ntiles; ++kt) tile(kt, kt & 1, std::false_type{});
   }
 
   // Output.  A lane holds 4 consecutive values of one row per register group, so stored directly a
@@ -557,6 +538,7 @@ __global__ __launch_bounds__(NK * 64) void varlen_mha_splitkey_kernel(
 
   const FragAddr fa = make_frag_addr(lane);
 
+  bool calm = false;  // not used by this form
   int stage = 0;
   for (int it = 0; it < my_tiles; ++it) {
     const int kt = wave + it * NK;
@@ -571,9 +553,8 @@ __global__ __launch_bounds__(NK * 64) void varlen_mha_splitkey_kernel(
       // the stage refilled now was read in iteration it-1; those reads completed before its MFMAs issued
       if (it + NS - 1 < my_tiles) issue_tile(kt + (NS - 1) * NK, stage == 0 ? NS - 1 : stage - 1);
     }
-    const int k0 = kt * kKT;
-    process_tile<false>(my_lds + stage * (2 * TILE), my_lds + stage * (2 * TILE) + TILE, qf, k0, L, it == 0, scale_log2e, fa,
-                 m_run, l_run, o_acc);
+    process_tile<false>(my_lds + stage * (2 * TILE), my_lds + stage * (2 * TILE) + TILE, qf, kt * kKT, L, scale_log2e, fa, calm,
+                        m_run, l_run, o_acc);
     if (NS > 1) stage = stage + 1 == NS ? 0 : stage + 1;
   }
 
@@ -681,7 +662,7 @@ bt_status mha_dispatch(const bt_half* q, const bt_half* k, const bt_half* v, int
   // against 8.5 us with 2-wave tiles at 16 sequences of up to 256 tokens, 408 workgroups; 39 against 55 us
   // at 16 x up to 1024).  2-wave tiles give more workgroups below that; with too few of those to occupy the
   // SIMDs, the split-key kernel puts two waves on every 32 query rows.  Two K/V stages (32 KB of LDS per
-  // workgroup) rather than three: the 120 VGPRs of the kernel allow four waves per SIMD and the third
+  // workgroup) rather than three: the 121 VGPRs of the kernel allow four waves per SIMD and the third
   // stage would cap residency at three; measured 2-8 % faster from 256 to 1024 keys, never slower.
   auto blocks = [&](int bqt) { return ((long long)T / bqt + B) * heads; };
   if (max_len > 128 && blocks(128) >= 256) return launch_mha<4, 2>(BT_MHA_ARGS);

@@ -566,12 +566,12 @@ def test_varlen_mha_maximum_length(bt):
     assert _mha_case(bt, [4096, 3, 4095], 2, seed=4096) <= 4e-3
 
 
-@pytest.mark.parametrize("lengths,heads", [([256] * 12 + [200, 77, 130, 300], 12), ([120, 128, 65, 97, 33, 128] * 5, 12), ([300, 65, 97, 161], 2)])
+@pytest.mark.parametrize("lengths,heads", [([256] * 12 + [200, 77, 130, 300], 12), ([120, 128, 65, 97, 33, 128] * 5, 12), ([300, 65, 97, 161], 2), ([2100, 700, 300], 12)])
 @pytest.mark.parametrize("step", [3.0, 5.0, 40.0, -40.0])
 def test_varlen_mha_logits_that_outgrow_the_reference(bt, lengths, heads, step):
     """Logits that rise by `step` every 24 keys (about the first half of the rows; fall for the others): the reference of the
-    exponentials is raised in either block of a tile, on some rows of a wavefront only, or stays.  One case for each of the
-    three kernels.  Error of an output: fp16 probabilities (2^-11 of |v| <= 5 each, averaged) and its own rounding."""
+    exponentials is raised in a tile or stays, on some rows of a wavefront only.  One case for each of the three kernels, one
+    that is long enough for exponentials ahead of the maximum.  Error of an output: fp16 probabilities (2^-11 of |v| <= 5 each, averaged) and its own rounding."""
     d = 64
     rng = np.random.default_rng(11)
     T = int(np.sum(lengths))
@@ -585,6 +585,27 @@ def test_varlen_mha_logits_that_outgrow_the_reference(bt, lengths, heads, step):
     got = host(bt.varlen_mha(dev(qkv), dev(cu), max(lengths), heads)).astype(np.float64)
     ref = O.varlen_mha_packed(qkv, cu, heads, d)
     assert np.abs(got - ref).max() <= 5e-3
+
+
+@pytest.mark.parametrize("lengths,heads", [([2100, 700, 300], 12), ([2048, 1984, 130], 16), ([120, 128, 65, 97, 33, 128] * 5, 12), ([300, 65, 97, 161], 2)])
+def test_varlen_mha_rows_do_not_depend_on_each_other(bt, lengths, heads):
+    """One query row of each sequence gets logits far above those of its first keys, half way along the sequence and at its end: the
+    reference of its exponentials is raised there.  Every other row keeps every bit, also those of the same wavefront."""
+    import torch
+    rng = np.random.default_rng(len(lengths))
+    T = int(np.sum(lengths))
+    cu = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    qkv = rng.normal(0, 1, (T, 3, heads, 64)).astype(np.float32)
+    plain = bt.varlen_mha(dev(qkv.reshape(T, -1).astype(np.float16)), dev(cu), max(lengths), heads)
+    rows = [int(c + n // 3) for c, n in zip(cu, lengths)]
+    for r, c, n in zip(rows, cu, lengths):
+        qkv[r, 0] = 3.0 * qkv[c + n - 1, 1] + 2.0 * qkv[c + n // 2, 1]
+    packed = qkv.reshape(T, -1).astype(np.float16)
+    sharp = bt.varlen_mha(dev(packed), dev(cu), max(lengths), heads)
+    others = np.setdiff1d(np.arange(T), rows)
+    assert torch.equal(plain[others], sharp[others])
+    ref = O.varlen_mha_packed(packed, cu, heads, 64)
+    assert np.abs(host(sharp).astype(np.float64) - ref).max() <= 5e-3
 
 
 def test_varlen_mha_many_sequences(bt):
