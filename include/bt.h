@@ -170,6 +170,14 @@ bt_status bt_gemm_tile_shape(int M, int N, int K, bt_act act, int* bm, int* bn);
 bt_status bt_gemm_row_split(int M, int N, int K, bt_act act, int* rows_first);
 
 /*
+ * The block tile of the first product of bt_encoder_fwd_masked (host only, nothing is launched) for a batch of `rows` tokens
+ * where there could be rows_max = B*S: the product is launched before the host knows the count and chooses its tiles on the
+ * device.  *behind_us: what that choice takes longer, by the cost model, than the launch or launches made with
+ * the count known (a grid that would run as two row ranges runs as one here).  *bm = *bn = 0: such a product waits for the count.
+ */
+bt_status bt_gemm_counted_shape(int rows_max, int rows, int N, int K, int* bm, int* bn, float* behind_us);
+
+/*
  * Fused add-bias + residual + LayerNorm, Sec. III-C1:
  *   y[i,:] = LN(x[i,:] + bias + residual[i,:]) * gamma + beta,   one pass over memory.
  * x, residual, y fp16 [T,H]; bias, gamma, beta fp16 [H]; bias may be NULL.

@@ -72,6 +72,8 @@ _SIGNATURES = {
                                   _c.c_int, _c.c_int, _c.c_void_p, _c.c_void_p, _c.c_size_t, _c.c_void_p]),
     "bt_gemm_tile_shape": (_c.c_int, [_c.c_int, _c.c_int, _c.c_int, _c.c_int, _c.POINTER(_c.c_int), _c.POINTER(_c.c_int)]),
     "bt_gemm_row_split": (_c.c_int, [_c.c_int, _c.c_int, _c.c_int, _c.c_int, _c.POINTER(_c.c_int)]),
+    "bt_gemm_counted_shape": (_c.c_int, [_c.c_int, _c.c_int, _c.c_int, _c.c_int, _c.POINTER(_c.c_int), _c.POINTER(_c.c_int),
+                                         _c.POINTER(_c.c_float)]),
     "bt_encoder_fwd_padded": (_c.c_int, [_c.POINTER(bt_layer), _c.c_int, _c.c_void_p, _c.c_void_p, _c.c_void_p,
                                          _c.c_void_p, _c.c_int, _c.c_int, _c.c_int, _c.c_void_p, _c.c_void_p,
                                          _c.c_size_t, _c.c_void_p]),
@@ -297,6 +299,14 @@ def gemm_tile_shape(M, N, K, act=ACT_NONE):
     bm, bn = _c.c_int(0), _c.c_int(0)
     _call("bt_gemm_tile_shape", int(M), int(N), int(K), int(act), _c.byref(bm), _c.byref(bn))
     return bm.value, bn.value
+
+
+def gemm_counted_shape(rows_max, rows, N, K):
+    """bt_gemm_counted_shape: (BM, BN, us behind a launch that knows the count) of encoder_fwd_masked's first product where the
+    batch holds `rows` of at most `rows_max` tokens, None where the product waits for the count."""
+    bm, bn, behind = _c.c_int(0), _c.c_int(0), _c.c_float(0)
+    _call("bt_gemm_counted_shape", int(rows_max), int(rows), int(N), int(K), _c.byref(bm), _c.byref(bn), _c.byref(behind))
+    return (bm.value, bn.value, behind.value) if bm.value else None
 
 
 def add_bias_residual_layernorm(x, bias, residual, gamma, beta, eps, out=None):

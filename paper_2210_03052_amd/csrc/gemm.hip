@@ -392,11 +392,14 @@ __device__ __forceinline__ void load_resid(const half_t* __restrict__ resid, con
 // SHAPE (0 = fan-out, N >= 2K; 1 = neither; 2 = deep reduction, K >= 2N) changes nothing in the code: it is
 // part of the kernel's name, so that a kernel trace tells the four products of an encoder layer apart
 // (QKV and FFN-up are fan-out, the output projection is square, FFN-down is deep) when they share a tile shape.
-template <int BM, int BN, int WGM, int WGN, int NS, int ACT, int EPI>
-__device__ __forceinline__ void gemm_pipe_tile(const half_t* __restrict__ A, const half_t* __restrict__ W,
-                                               const int32_t* __restrict__ a_rows, const half_t* __restrict__ bias, int M, int N,
-                                               int K, int tiles_n, int tiles_m, int group_m, half_t* __restrict__ C,
-                                               const GemmEpi& ep) {
+template <int BM, int BN, int WGM, int WGN, int NS, int ACT, int EPI, int SHAPE>
+__global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(
+    // Argument order: what the prologue and the K loop need comes first and fits the 14 dwords that are
+    // preloaded into SGPRs at wave launch (-amdgpu-kernarg-preload-count), so the first DMA does not
+    // wait for a scalar load of the kernel arguments; the epilogue descriptor is fetched behind it.
+    const half_t* __restrict__ A, const half_t* __restrict__ W, const int32_t* __restrict__ a_rows /* = ep.a_rows */,
+    const half_t* __restrict__ bias /* = ep.bias */, int M, int N, int K, int tiles_n, int tiles_m, int group_m,
+    half_t* __restrict__ C, const GemmEpi ep) {
   constexpr int BK = 64, KS = BK / 32;
   constexpr int NWAVES = WGM * WGN;
   constexpr int WM = BM / WGM, WN = BN / WGN;   // wave tile
@@ -656,51 +659,7 @@ __device__ __forceinline__ void gemm_pipe_tile(const half_t* __restrict__ A, con
   }
 }
 
-template <int BM, int BN, int WGM, int WGN, int NS, int ACT, int EPI, int SHAPE>
-__global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(
-    // Argument order: what the prologue and the K loop need comes first and fits the 14 dwords that are
-    // preloaded into SGPRs at wave launch (-amdgpu-kernarg-preload-count), so the first DMA does not
-    // wait for a scalar load of the kernel arguments; the epilogue descriptor is fetched behind it.
-    const half_t* __restrict__ A, const half_t* __restrict__ W, const int32_t* __restrict__ a_rows /* = ep.a_rows */,
-    const half_t* __restrict__ bias /* = ep.bias */, int M, int N, int K, int tiles_n, int tiles_m, int group_m,
-    half_t* __restrict__ C, const GemmEpi ep) {
-  gemm_pipe_tile<BM, BN, WGM, WGN, NS, ACT, EPI>(A, W, a_rows, bias, M, N, K, tiles_n, tiles_m, group_m, C, ep);
-}
-
 #include "gemm_wide.h"
-
-// The plain product with its number of rows in device memory: launched behind the kernel that counts them, before the host
-// knows the count (gemm_counted_dispatch).  The grid covers the largest count there can be; what is not needed ends at once.
-struct CountedTiles { int m, n, group; };
-template <int BM, int BN>
-__device__ __forceinline__ CountedTiles counted_tiles(int M, int N) {
-  CountedTiles t;
-  t.m = (M + BM - 1) / BM;
-  t.n = (N + BN - 1) / BN;
-  // as strip_rows; only the order of the tiles depends on it
-  t.group = min(max(__builtin_amdgcn_readfirstlane((int)(sqrtf((float)(t.m * t.n) * (0.125f * BN / BM)) + 0.5f)), 1), t.m);
-  return t;
-}
-template <int BM, int BN, int WGM, int WGN, int NS>
-__global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_counted_kernel(
-    const half_t* __restrict__ A, const half_t* __restrict__ W, const int32_t* __restrict__ a_rows,
-    const half_t* __restrict__ bias, const int32_t* __restrict__ rows, int N, int K, half_t* __restrict__ C) {
-  const int M = *rows;  // 0 or -1 (an invalid mask): nothing to do
-  if (M < 1) return;
-  const CountedTiles t = counted_tiles<BM, BN>(M, N);
-  if ((int)blockIdx.x >= t.m * t.n) return;
-  gemm_pipe_tile<BM, BN, WGM, WGN, NS, BT_ACT_NONE, EPI_PLAIN>(A, W, a_rows, bias, M, N, K, t.n, t.m, t.group, C, GemmEpi());
-}
-template <int BM, int BN>
-__global__ __launch_bounds__(256, 1) void gemm_wide_counted_kernel(
-    const half_t* __restrict__ A, const half_t* __restrict__ W, const int32_t* __restrict__ a_rows,
-    const half_t* __restrict__ bias, const int32_t* __restrict__ rows, int N, int K, half_t* __restrict__ C) {
-  const int M = *rows;
-  if (M < 1) return;
-  const CountedTiles t = counted_tiles<BM, BN>(M, N);
-  if ((int)blockIdx.x >= t.m * t.n) return;
-  gemm_wide_tiles<BM, BN, BT_ACT_NONE, EPI_PLAIN, 3>(A, W, a_rows, bias, M, N, K, t.n, t.m, t.group, C, GemmEpi());
-}
 
 // ---------------------------------------------------------------------------
 // Fallback kernel: register-staged, 64x64x64 tile, padded LDS rows, K tail zero-filled.
@@ -937,7 +896,7 @@ static bt_status launch_simple(const half_t* A, const half_t* W, half_t* C, int 
 // kernel, which has the products that are shorter than the narrow tiles' pipeline.
 enum TileKind { kWide, kNarrow, kEightWaves, kRegisterStaged };
 struct GemmTile { int bm, bn; float start_us, slab0_us, slab_u_us, epi_us; TileKind kind; };
-static const GemmTile kGemmTiles[] = {
+static constexpr GemmTile kGemmTiles[] = {
     {256, 128, 2.1f, 0.459f, 0.318f, 2.76f, kWide},   {224, 128, 1.6f, 0.402f, 0.242f, 3.2f, kWide},
     {192, 128, 1.85f, 0.359f, 0.212f, 2.6f, kWide},   {160, 128, 1.7f, 0.319f, 0.177f, 2.29f, kWide},
     {128, 128, 2.2f, 0.289f, 0.136f, 1.55f, kWide},   {96, 128, 2.2f, 0.285f, 0.078f, 1.08f, kWide},
@@ -989,11 +948,12 @@ __attribute__((always_inline)) static inline bool gemm_shape_ok(const GemmTile& 
 
 // A single round of wide tiles on nearly every compute unit, all of them storing at once, costs more inside an encoder layer
 // than the model says (1.5 to 3.7 us on the products without an activation): full_us.
+constexpr float kFullUs = 1.5f;
 __attribute__((always_inline)) static inline float gemm_shape_us(const GemmTile& t, int M, int N, int K, bt_act act) {
   const long long tiles = (long long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
   const float rounds = (float)((tiles + kComputeUnits - 1) / kComputeUnits), slabs = (float)(K / 64);
   const float epi = t.epi_us + (act != BT_ACT_NONE ? kActUs * t.bm * t.bn : 0.f);
-  const float full_us = t.kind == kWide && act == BT_ACT_NONE && tiles > 240 && tiles <= kComputeUnits ? 1.5f : 0.f;
+  const float full_us = t.kind == kWide && act == BT_ACT_NONE && tiles > 240 && tiles <= kComputeUnits ? kFullUs : 0.f;
   return t.start_us + rounds * (slabs * t.slab0_us + epi) + slabs * t.slab_u_us * (float)tiles / kComputeUnits + full_us;
 }
 
@@ -1036,9 +996,10 @@ static int gemm_tile_choice(int M, int N, int K, bt_act act, int epi, bool wide_
 // K = 512 -1.6 %, 640 -0.5 %, 768 +0.3 %, 1024 +1.1 %, 1280 to 8192 +1.7 %.  Hence the bar for reductions shorter than 768, where
 // those above it gained 3 to 5 %, and none for longer ones.
 // Returns the number of leading rows for the first launch and its shape, or 0: one launch.
-static int gemm_msplit_choice(int M, int N, int K, bt_act act, bool wide_ok, int* main_tile) {
+static int gemm_msplit_choice(int M, int N, int K, bt_act act, bool wide_ok, int* main_tile, float* us_out = nullptr) {
   float best_us = 0.f;
   (void)gemm_tile_choice(M, N, K, act, EPI_PLAIN, wide_ok, &best_us);
+  if (us_out) *us_out = best_us;
   if (K < 768) best_us *= 0.96f;
   int best_rows = 0;
   for (int c = 0; c < kGemmShapes - kDeepShapes; ++c) {  // those two are never more than a round
@@ -1058,6 +1019,7 @@ static int gemm_msplit_choice(int M, int N, int K, bt_act act, bool wide_ok, int
       *main_tile = c;
     }
   }
+  if (us_out && best_rows) *us_out = best_us;
   return best_rows;
 }
 
@@ -1110,47 +1072,110 @@ bt_status gemm_dispatch(const bt_half* A, const bt_half* W, int M, int N, int K,
 }
 
 // C = A[a_rows] W^T + bias with the number of rows, *rows <= rows_max, in device memory.  For the first product of a stack: the
-// host waits for the count before it can size a launch, and the device would wait for that launch; this one is sized by
-// rows_max and reads the count itself, so the device has work until the host has caught up.  Its shape is the one that
-// loses least against the best for three, five or eight eighths of rows_max (a few long sentences, even lengths, full ones),
-// and there is none where that loss may reach kCountedLossUs: beyond ten thousand rows of width 512 the wrong shape cost more than the
-// wait (one layer, 16 269 rows, taken for five eighths alone: 191.7 -> 197.0 us).  A row's result is the same in every shape.  What it buys is the time until the host's first launch arrives, less the round trip of the count into the
-// kernel's registers: masked calls, both builds in one process: one layer, 4 x up to 64, 36.6 -> 31.8 us; 12 layers, 1 x up to
-// 128, 271.5 -> 267.0, 8 x up to 128 462.9 -> 457.3, 16 x up to 256 775.2 -> 768.3.  Narrow tiles of which most would find no rows are not launched by the
-// thousand (the limit is sixteen rounds).  BT_ERR_UNSUPPORTED: no form for these sizes, nothing enqueued.
-constexpr float kCountedLossUs = 4.f;
+// host waits for the count before it can size a launch, and the device would wait for that launch; this kernel is launched
+// behind the one that counts, takes the count from device memory and chooses its tiles by it, with the costs that the host
+// would use.  Every shape has four wavefronts, so one kernel holds them all behind a uniform branch; 64-row tiles are wide
+// tiles here, with three stages (four: 2 x 128 full sentences of width 1024 39.5 -> 38.9 us, 700 tokens of width 512 39.9 -> 40.9).
+// A row's result is the same in every shape.
+//
+// Masked calls of one layer, all libraries in one process, us: product behind the count / ahead of it in one shape for all
+// counts / ahead of it in the shape for the count.  4 x up to 64, width 768: 38.7 / 34.7 / 34.4; 16 x up to 256: 100 tokens
+// 41.8 / 40.5 / 37.8, 2 308: 78.9 / 73.7 / 74.5, 2 700: 92.6 / 93.7 / 88.1, 3 300: 97.2 / 94.6 / 90.8; width 1024: 1 100 tokens
+// 69.6 / 70.0 / 65.0, 2 625: 113.7 / 113.2 / 107.7; 24 x up to 512, 2 600 tokens 115.7 / 116.4 / 109.5.
+constexpr int kCountedShapes[] = {0, 1, 2, 3, 4, 5, 7, 8}, kCountedN = 8;  // of kGemmTiles, the largest first
+template <int C>
+struct CountedTile {
+  static constexpr GemmTile t = kGemmTiles[kCountedShapes[C]];
+  using Tile = WideTile<t.bm, t.bn, 3>;
+};
+constexpr int kCountedLds = CountedTile<0>::Tile::LDS;
+
+// The choice on the device: a shape per lane, all eight at once, and the smallest by three lane exchanges.  What comes ahead of
+// the first operand request is fetched cold in every launch, so its length counts: the product is 0.3 to 0.5 us longer than with
+// its shape given, 0.6 to 1.0 with eight shapes one after another (190 instructions).  The costs come from memory, in the time in
+// which the count does.
+struct CountedCost { float start_us, slab0_us, slab_u_us, epi_us; unsigned bm, of_32_rows, log2_bn; float full_us; };
+struct CountedCosts { CountedCost of[kCountedN]; };
+static constexpr CountedCosts counted_costs() {
+  CountedCosts c{};
+  for (int i = 0; i < kCountedN; ++i) {
+    const GemmTile& t = kGemmTiles[kCountedShapes[i]];
+    c.of[i] = {t.start_us, t.slab0_us, t.slab_u_us / kComputeUnits, t.epi_us, (unsigned)t.bm,
+               (unsigned)(((1ull << 32) + t.bm / 32 - 1) / (t.bm / 32)), t.bn == 128 ? 7u : 6u, t.kind == kWide ? kFullUs : 0.f};
+  }
+  return c;
+}
+static __constant__ CountedCosts kCountedCosts = counted_costs();
+
+__device__ __forceinline__ int counted_choice(int M, int N, int K, const CountedCost& c) {
+  // n / (bm / 32) as the upper half of a product: exact for n < 2^29
+  const unsigned tiles_m = __umulhi(((unsigned)M + c.bm - 1) >> 5, c.of_32_rows);
+  const unsigned tiles = tiles_m * (((unsigned)N + (1u << c.log2_bn) - 1) >> c.log2_bn);  // fits: see gemm_counted_ok
+  const float rounds = (float)((tiles + kComputeUnits - 1) / kComputeUnits), slabs = (float)((unsigned)K / 64);  // as gemm_shape_us
+  float us = c.start_us + rounds * (slabs * c.slab0_us + c.epi_us) + slabs * c.slab_u_us * (float)tiles;
+  us += tiles - 241u < 16u ? c.full_us : 0.f;
+  // positive floats order like their bits; the lowest three make room for the lane
+  int key = (__builtin_bit_cast(int, us) & ~7) | (int)(threadIdx.x & 7);
+  key = min(key, __builtin_amdgcn_update_dpp(key, key, 0xb1, 0xf, 0xf, false));   // lane ^ 1
+  key = min(key, __builtin_amdgcn_update_dpp(key, key, 0x4e, 0xf, 0xf, false));   // lane ^ 2
+  key = min(key, __builtin_amdgcn_update_dpp(key, key, 0x141, 0xf, 0xf, false));  // 7 - lane: the other four
+  return __builtin_amdgcn_readfirstlane(key) & 7;
+}
+static int counted_shape(int M, int N, int K, float* us_out) {  // the same on the host, for reports
+  int best = 0;
+  for (int c = 0; c < kCountedN; ++c) {
+    const float us = gemm_shape_us(kGemmTiles[kCountedShapes[c]], M, N, K, BT_ACT_NONE);
+    if (c == 0 || us < *us_out) { best = c; *us_out = us; }
+  }
+  return best;
+}
+
+__global__ __launch_bounds__(256, 1) void gemm_counted_kernel(
+    const half_t* __restrict__ A, const half_t* __restrict__ W, const int32_t* __restrict__ a_rows,
+    const half_t* __restrict__ bias, const int32_t* __restrict__ rows, int N, int K, half_t* __restrict__ C) {
+  __shared__ __attribute__((aligned(1024))) char smem[kCountedLds];
+  const CountedCost cost = kCountedCosts.of[threadIdx.x & 7];
+  const int M = *rows;
+  const int shape = counted_choice(M, N, K, cost);
+  if (M < 1) return;  // 0, or -1 for an invalid mask: nothing to do.  (Behind the choice, so that both loads are under way)
+  auto run = [&](auto c) {
+    using S = CountedTile<decltype(c)::value>;
+    static_assert(S::Tile::LDS <= kCountedLds, "the first shape is the largest");
+    const int tiles_m = (int)(((unsigned)M + S::t.bm - 1) / S::t.bm), tiles_n = (int)(((unsigned)N + S::t.bn - 1) / S::t.bn);
+    if ((int)blockIdx.x >= tiles_m * tiles_n) return;
+    // as strip_rows; only the order of the tiles depends on it
+    const float strip = __builtin_amdgcn_sqrtf((float)(tiles_m * tiles_n) * (0.125f * S::t.bn / S::t.bm)) + 0.5f;
+    const int group_m = min(max(__builtin_amdgcn_readfirstlane((int)strip), 1), tiles_m);
+    gemm_wide_tiles<S::t.bm, S::t.bn, BT_ACT_NONE, EPI_PLAIN, 3>(smem, A, W, a_rows, bias, M, N, K, tiles_n, tiles_m, group_m, C,
+                                                                 GemmEpi());
+  };
+  using std::integral_constant;
+  switch (shape) {
+    case 0: return run(integral_constant<int, 0>{});
+    case 1: return run(integral_constant<int, 1>{});
+    case 2: return run(integral_constant<int, 2>{});
+    case 3: return run(integral_constant<int, 3>{});
+    case 4: return run(integral_constant<int, 4>{});
+    case 5: return run(integral_constant<int, 5>{});
+    case 6: return run(integral_constant<int, 6>{});
+    default: return run(integral_constant<int, 7>{});
+  }
+}
+
+// Up to about 100 GFLOP: what a single grid loses against two row ranges (gemm_msplit_choice) grows with the rounds, to 3 us by
+// the model here (at K <= 1024 and 12 288 rows 1.4), and what the early launch gains does not: 64 x 512 full sentences of width
+// 768 took 645.7 us behind the count, 648.3 ahead of it.
+static bool gemm_counted_ok(int rows_max, int N, int K) {
+  return (K % 64) == 0 && gemm_wide_ok(rows_max, N, K, EPI_PLAIN) && (double)rows_max * N * K <= 52e9;
+}
+
 bt_status gemm_counted_dispatch(const bt_half* A, const bt_half* W, const int32_t* a_rows, const bt_half* bias,
                                 const int32_t* rows, int rows_max, int N, int K, bt_half* C, hipStream_t st) {
-  if ((K % 64) != 0 || K < 256) return BT_ERR_UNSUPPORTED;
-  static constexpr int kShapes[] = {0, 2, 4, 7, 8}, kEighths[] = {3, 5, 8};
-  const bool wide_ok = gemm_wide_ok(rows_max, N, K, EPI_PLAIN);
-  int best = -1;
-  float best_us = kCountedLossUs;
-  for (const int c : kShapes) {
-    float loss = 0.f;
-    for (const int e : kEighths) {
-      const int rows = (int)((long long)rows_max * e / 8) + 1;
-      float us = 0.f;
-      (void)gemm_tile_choice(rows, N, K, BT_ACT_NONE, EPI_PLAIN, wide_ok, &us);
-      const bool ok = gemm_shape_ok(kGemmTiles[c], rows, N, K, BT_ACT_NONE, EPI_PLAIN, wide_ok);
-      loss = fmaxf(loss, ok ? gemm_shape_us(kGemmTiles[c], rows, N, K, BT_ACT_NONE) - us : 2.f * kCountedLossUs);
-    }
-    if (loss < best_us) { best = c; best_us = loss; }
-  }
-  if (best < 0) return BT_ERR_UNSUPPORTED;
-  const GemmTile& t = kGemmTiles[best];
-  const long long tiles = (long long)((rows_max + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
-  if (t.kind == kNarrow && tiles > 16 * kComputeUnits) return BT_ERR_UNSUPPORTED;
-  const unsigned grid = (unsigned)(t.kind == kWide && tiles > kComputeUnits ? kComputeUnits : tiles);
-  const half_t *a = reinterpret_cast<const half_t*>(A), *w = reinterpret_cast<const half_t*>(W), *b = reinterpret_cast<const half_t*>(bias);
-  half_t* const c = reinterpret_cast<half_t*>(C);
-  switch (best) {
-    case 0: gemm_wide_counted_kernel<256, 128><<<grid, 256, 0, st>>>(a, w, a_rows, b, rows, N, K, c); break;
-    case 2: gemm_wide_counted_kernel<192, 128><<<grid, 256, 0, st>>>(a, w, a_rows, b, rows, N, K, c); break;
-    case 4: gemm_wide_counted_kernel<128, 128><<<grid, 256, 0, st>>>(a, w, a_rows, b, rows, N, K, c); break;
-    case 7: gemm_pipe_counted_kernel<64, 128, 2, 4, 4><<<grid, 512, 0, st>>>(a, w, a_rows, b, rows, N, K, c); break;
-    default: gemm_pipe_counted_kernel<64, 64, 2, 2, 4><<<grid, 256, 0, st>>>(a, w, a_rows, b, rows, N, K, c); break;
-  }
+  if (!gemm_counted_ok(rows_max, N, K)) return BT_ERR_UNSUPPORTED;
+  const long long tiles = (long long)((rows_max + 63) / 64) * ((N + 63) / 64);  // the smallest shape has the most
+  gemm_counted_kernel<<<(unsigned)(tiles < kComputeUnits ? tiles : kComputeUnits), 256, 0, st>>>(
+      reinterpret_cast<const half_t*>(A), reinterpret_cast<const half_t*>(W), a_rows, reinterpret_cast<const half_t*>(bias), rows, N, K,
+      reinterpret_cast<half_t*>(C));
   return launch_status();
 }
 
@@ -1255,5 +1280,20 @@ extern "C" bt_status bt_gemm_tile_shape(int M, int N, int K, bt_act act, int* bm
   const bt::GemmTile& t = bt::kGemmTiles[bt::gemm_tile_choice(M, N, K, act, bt::EPI_PLAIN, bt::gemm_wide_ok(M, N, K, bt::EPI_PLAIN))];
   *bm = t.bm;
   *bn = t.bn;
+  return BT_OK;
+}
+
+extern "C" bt_status bt_gemm_counted_shape(int rows_max, int rows, int N, int K, int* bm, int* bn, float* behind_us) {
+  if (rows < 1 || rows_max < rows || N < 1 || K < 1 || (N % 8) != 0 || (K % 8) != 0 || !bm || !bn || !behind_us) return BT_ERR_INVALID_ARG;
+  *bm = *bn = 0;
+  *behind_us = 0.f;
+  if (!bt::gemm_counted_ok(rows_max, N, K)) return BT_OK;
+  float us = 0.f, known_us = 0.f;
+  int tile = 0;
+  const int shape = bt::counted_shape(rows, N, K, &us);
+  (void)bt::gemm_msplit_choice(rows, N, K, BT_ACT_NONE, bt::gemm_wide_ok(rows_max, N, K, bt::EPI_PLAIN), &tile, &known_us);
+  *bm = bt::kGemmTiles[bt::kCountedShapes[shape]].bm;
+  *bn = bt::kGemmTiles[bt::kCountedShapes[shape]].bn;
+  *behind_us = us - known_us;
   return BT_OK;
 }

@@ -59,8 +59,9 @@ struct WideTile {
   static_assert((NS - 2) * TOT + TOT / 2 < 64, "vmcnt range");
 };
 
+// smem: WideTile<BM, BN, NS>::LDS bytes, 1024-byte aligned.
 template <int BM, int BN, int ACT, int EPI, int NS>
-__device__ __forceinline__ void gemm_wide_tiles(const half_t* __restrict__ A, const half_t* __restrict__ W,
+__device__ __forceinline__ void gemm_wide_tiles(char* smem, const half_t* __restrict__ A, const half_t* __restrict__ W,
                                                 const int32_t* __restrict__ a_rows, const half_t* __restrict__ bias, int M, int N,
                                                 int K, int tiles_n, int tiles_m, int group_m, half_t* __restrict__ C,
                                                 const GemmEpi& ep) {
@@ -70,7 +71,6 @@ __device__ __forceinline__ void gemm_wide_tiles(const half_t* __restrict__ A, co
   // Several tiles per workgroup; FOLD: one.  It runs in one round of tiles nearly everywhere; where it does not (192- and
   // 128-row tiles at 2 561 to 2 688 tokens of width 768) the second round starts anew.
   constexpr bool STREAM = EPI == EPI_PLAIN;
-  __shared__ __attribute__((aligned(1024))) char smem[T::LDS];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1, l16 = lane & 15, quad = lane >> 4;
@@ -348,5 +348,7 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(
     const half_t* __restrict__ A, const half_t* __restrict__ W, const int32_t* __restrict__ a_rows /* = ep.a_rows */,
     const half_t* __restrict__ bias /* = ep.bias */, int M, int N, int K, int tiles_n, int tiles_m, int group_m,
     half_t* __restrict__ C, const GemmEpi ep) {
-  gemm_wide_tiles<BM, BN, ACT, EPI, wide_stages(BM, EPI, SHAPE)>(A, W, a_rows, bias, M, N, K, tiles_n, tiles_m, group_m, C, ep);
+  constexpr int NS = wide_stages(BM, EPI, SHAPE);
+  __shared__ __attribute__((aligned(1024))) char smem[WideTile<BM, BN, NS>::LDS];
+  gemm_wide_tiles<BM, BN, ACT, EPI, NS>(smem, A, W, a_rows, bias, M, N, K, tiles_n, tiles_m, group_m, C, ep);
 }

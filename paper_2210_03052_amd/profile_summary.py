@@ -67,8 +67,8 @@ def role_of(name: str, grid: int = 0):
         if epi == 2:   # bias + residual + row sums in the epilogue (5-launch pipeline)
             return ("gemm3_ffn_down_resid" if shape == 2 else "gemm1_proj_resid"), label
         return {0: "gemm0_qkv_bias", 1: "gemm1_proj", 2: "gemm3_ffn_down"}.get(shape, "gemm"), label
-    if "gemm_wide_counted_kernel" in name or "gemm_pipe_counted_kernel" in name:   # first product of a masked call
-        return "gemm0_qkv_counted", f"gemm_{'wide' if 'wide' in name else 'pipe'}_counted<{'x'.join(map(str, a[:2]))}>"
+    if "gemm_counted_kernel" in name:   # first product of a masked call: its shape follows the count, on the device
+        return "gemm0_qkv_counted", "gemm_counted"
     if "gemm_simple_kernel" in name:
         return "gemm_fallback", "gemm_simple"
     if "varlen_mha_splitkey_kernel" in name:

@@ -225,6 +225,26 @@ def test_gemm_tile_shape_query_is_host_only():
             bt.gemm_tile_shape(*bad)
 
 
+def test_first_product_ahead_of_the_count_costs_little_at_every_count():
+    """bt_gemm_counted_shape: the product that is launched before the count is known is, by the cost model and at every count
+    there can be, at most 1.5 us behind the launch or launches that know it up to 8 192 rows of the usual widths, and at
+    most 3.5 us anywhere (a grid that would run as two row ranges).  Counts: both sides of every tile edge."""
+    for H in (256, 512, 640, 768, 1024, 1280, 2048, 4096):
+        for rows_max in (1, 40, 512, 1200, 4096, 8192, 12288, 16384, 32768, 65536):
+            counts = sorted({1, rows_max, *range(32, rows_max + 1, 32), *range(33, rows_max + 1, 32)} - {0})
+            if bt.gemm_counted_shape(rows_max, 1, 3 * H, H) is None:
+                assert rows_max * 3 * H * H > 52e9
+                continue
+            worst = max(bt.gemm_counted_shape(rows_max, t, 3 * H, H)[2] for t in counts)
+            assert worst <= (1.5 if H <= 1024 and rows_max <= 8192 else 3.5), (H, rows_max, worst)
+    # waits for the count: short reductions, K not a multiple of 64, operands of 4 GiB, more than about 100 GFLOP
+    for bad in ((100, 50, 576, 192), (100, 50, 2304, 200), (3 << 20, 50, 2304, 768), (32768, 50, 2304, 768)):
+        assert bt.gemm_counted_shape(*bad) is None
+    for bad in ((10, 0, 2304, 768), (10, 11, 2304, 768), (10, 5, 7, 64), (10, 5, 64, 60)):
+        with pytest.raises(bt.BtError):
+            bt.gemm_counted_shape(*bad)
+
+
 def test_layer_launches_query_is_host_only():
     """bt_layer_launches: the last and first token counts of the three forms at the usual widths, and where the forms for few
     tokens do not apply or stop early: K that is not split, other widths, a wide F whose FFN-down would read too much."""

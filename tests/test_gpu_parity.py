@@ -883,19 +883,23 @@ def test_encoder_fwd_masked_equals_the_two_calls(bt, use_mask, folded):
     assert float((untouched - 3.0).abs().sum()) == 0.0
 
 
+def _plain_layer(bt, rng, H):
+    w = lambda *s: dev(rng.normal(0, 0.02, s).astype(np.float16))
+    one, zero = dev(np.ones(H, np.float16)), dev(np.zeros(H, np.float16))
+    return bt.Layer({"w_qkv": w(3 * H, H), "b_qkv": w(3 * H), "w_o": w(H, H), "b_o": w(H), "ln0_g": one, "ln0_b": zero,
+                     "w_1": w(4 * H, H), "b_1": w(4 * H), "w_2": w(H, 4 * H), "b_2": w(H), "ln1_g": one, "ln1_b": zero,
+                     "heads": H // 64})
+
+
 @pytest.mark.parametrize("B,S,H", [(3, 21, 768), (2, 128, 512), (9, 130, 768), (16, 129, 1024), (16, 256, 768), (13, 640, 512),
                                    (30, 512, 768), (5, 40, 192)])
 def test_first_product_ahead_of_the_count(bt, B, S, H):
-    """The masked call launches its first product before the host knows the number of tokens, in a shape chosen for a range of
-    counts: the same bits as with the count known, for a single token, one more than a tile, ragged and full batches, in
-    each of its shapes and where there is none (width 192); rows that hold no token are neither read nor written."""
+    """The masked call launches its first product before the host knows the number of tokens: the same bits as with the count
+    known, for a single token, one more than a tile, ragged and full batches, and where the product waits for the count
+    (width 192); rows that hold no token are neither read nor written."""
     import torch
     rng = np.random.default_rng([B, S, H])
-    w = lambda *s: dev(rng.normal(0, 0.02, s).astype(np.float16))
-    one, zero = dev(np.ones(H, np.float16)), dev(np.zeros(H, np.float16))
-    layer = bt.Layer({"w_qkv": w(3 * H, H), "b_qkv": w(3 * H), "w_o": w(H, H), "b_o": w(H), "ln0_g": one, "ln0_b": zero,
-                      "w_1": w(4 * H, H), "b_1": w(4 * H), "w_2": w(H, 4 * H), "b_2": w(H), "ln1_g": one, "ln1_b": zero,
-                      "heads": H // 64})
+    layer = _plain_layer(bt, rng, H)
     ragged = rng.integers(0, S + 1, B).astype(np.int32)
     single = np.where(np.arange(B) == B - 1, 1, 0).astype(np.int32)
     tile = np.minimum(np.maximum(257 - S * np.arange(B), 0), S).astype(np.int32)      # 257 tokens at the front, where they fit
@@ -910,6 +914,33 @@ def test_first_product_ahead_of_the_count(bt, B, S, H):
         assert t == T and torch.equal(got, want), L
         need = bt.layer_workspace_bytes(layer, T, B, S)
         assert T == B * S or bool((ws[need:] == 17).all())
+        # the rows of a tile behind a single token would reach far into the last region, which the rest of the layer hardly uses
+        assert T > 1 or bool((ws[128 << 10:] == 17).all())
+
+
+@pytest.mark.parametrize("bm,bn,T,B,S,H", [
+    (64, 64, 448, 32, 256, 768), (64, 128, 449, 32, 256, 768), (64, 128, 896, 32, 256, 768), (96, 128, 897, 32, 256, 768),
+    (96, 128, 1248, 32, 256, 768), (128, 128, 1249, 32, 256, 768), (160, 128, 1665, 32, 256, 768), (192, 128, 2081, 32, 256, 768),
+    (224, 128, 2497, 32, 256, 768), (256, 128, 3328, 32, 256, 768), (128, 128, 3329, 32, 256, 768), (160, 128, 4480, 32, 256, 768),
+    (192, 128, 4481, 32, 256, 768), (224, 128, 6272, 32, 256, 768), (256, 128, 6273, 32, 256, 768), (64, 64, 1344, 16, 256, 256),
+    (64, 128, 2688, 16, 256, 256), (96, 128, 2689, 16, 256, 256), (64, 64, 33, 2, 48, 512), (96, 128, 1345, 8, 256, 512),
+    (128, 128, 2560, 16, 256, 512), (256, 128, 4705, 8, 640, 1024), (192, 128, 4032, 8, 640, 1024)])
+def test_first_product_in_each_of_its_shapes(bt, bm, bn, T, B, S, H):
+    """The shape of that product follows the count, on the device: every shape, in one round of tiles and in several, at the edges of
+    its range of counts.  The bits of the launch that knows the count."""
+    import torch
+    assert bt.gemm_counted_shape(B * S, T, 3 * H, H)[:2] == (bm, bn)
+    rng = np.random.default_rng([T, H])
+    L = np.full(B, T // B, np.int32)
+    L[: T - int(L.sum())] += 1
+    L = rng.permutation(L)
+    layer = _plain_layer(bt, rng, H)
+    x = dev(rng.normal(0, 1, (B, S, H)).astype(np.float16))
+    cu, tok, t = bt.build_offsets(lengths=dev(L), S=S)
+    want = bt.encoder_fwd_padded([layer], x, tok, cu)
+    for _ in range(2):
+        got, _, _, t = bt.encoder_fwd_masked([layer], x, lengths=dev(L))
+        assert t == T and torch.equal(got, want)
 
 
 def test_padded_stack_where_the_first_gemm_runs_as_two_row_ranges(bt):
