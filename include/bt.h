@@ -329,11 +329,12 @@ bt_status bt_encoder_fwd_padded(const bt_layer* layers, int n_layers, const floa
  * calls: d_mask / d_lengths (exactly one non-NULL), d_cu_seqlens [B+1] and d_token_idx [B*S] are written as by
  * bt_build_offsets, *h_total receives the token count (host memory; pinned and device-mapped memory avoids a stream
  * synchronisation), d_y_padded as by bt_encoder_fwd_padded.  What the single call saves is time in which the device has
- * nothing to do: the count goes into the launches of the layers without returning to the caller first, and the first
- * layer's QKV product, which reads the count on the device, runs while the host waits for it.  The workspace must be large enough for every count: at least
- * bt_layer_workspace_bytes(layers, B*S, B, S).  Errors the host can see are reported before anything runs; a
- * length outside [0, S] is found by the prefix-sum kernel and reported as by bt_build_offsets, and then no layer
- * runs (the QKV product finds no rows and ends).  Like
+ * nothing to do: the count goes into the launches of the layers without returning to the caller first, and, with a pinned
+ * h_total, the first layer's QKV product, which reads the count on the device, runs while the host waits for it.  The workspace
+ * must be large enough for every count: at least bt_layer_workspace_bytes(layers, B*S, B, S).  Errors the host can see are
+ * reported before anything runs; a length outside [0, S] is found by the prefix-sum kernel and reported as by
+ * bt_build_offsets, and then no layer runs.  With a pinned h_total the QKV product may then still be queued behind that kernel: it
+ * reads d_cu_seqlens[B], finds no rows and ends, so d_cu_seqlens must stay allocated until the stream has passed the call.  Like
  * bt_build_offsets this call waits on the host and is refused (BT_ERR_UNSUPPORTED) on a capturing stream.
  */
 bt_status bt_encoder_fwd_masked(const bt_layer* layers, int n_layers, const float* d_fold,

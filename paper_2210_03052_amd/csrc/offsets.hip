@@ -399,7 +399,8 @@ static_assert(kMaskCounters == 64, "a bit each");
 // Shared body of bt_build_offsets / bt_build_offsets_stats.  h_out[0] receives the total; with `stats`
 // h_out[1] receives the largest per-sentence count and d_cu_seqlens has B+2 entries (the last one is
 // the device copy of that maximum).
-// meanwhile(context) runs between the launch and the wait: work for the device that does not need the total on the host.
+// meanwhile(context) runs between the launch and the wait, if the host polls for the total: work for the device that does not need
+// the total on the host.
 bt_status bt::build_offsets(const int32_t* d_mask, const int32_t* d_lengths, int B, int S, int32_t* d_cu_seqlens,
                             int32_t* d_token_idx, int32_t* h_out, bool stats, bt_stream stream, void (*meanwhile)(void*),
                             void* context) {
@@ -442,7 +443,9 @@ bt_status bt::build_offsets(const int32_t* d_mask, const int32_t* d_lengths, int
         d_lengths, B, S, d_cu_seqlens, d_token_idx, h_dev, d_max);
   }
   if (hipGetLastError() != hipSuccess) return counter.lost = true, BT_ERR_HIP;
-  if (meanwhile) meanwhile(context);
+  // Not with ordinary host memory: the copy of the total would queue up behind that work, the host would wait for both and the
+  // device be idle afterwards all the same (masked call of one layer, 9 894 tokens: 251.1 us so, 247.7 without).
+  if (meanwhile && h_dev) meanwhile(context);
   int32_t res[2] = {kPending, 0};
   if (h_dev) {
     const auto t0 = std::chrono::steady_clock::now();
