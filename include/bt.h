@@ -292,8 +292,9 @@ bt_status bt_encoder_prepare(const bt_layer* layers, int n_layers, float* d_fold
  * (5 launches per layer plus one normalisation at the end) and does so while
  * ceil(T/64) * ceil(H/128) <= 256 (up to about 2 700 tokens at H = 768) and there are
  * enough tokens that the unfolded layer would not split K (more than about 600 at H = 768).  It is the faster
- * pipeline in the upper quarter of that range, by 1 to 4 %, and up to 8 % (H = 768) or 15 % (H = 1024) slower at
- * its lower end: a caller who knows T may leave d_fold NULL there.  Outside that
+ * pipeline at some counts of the upper half of that range only, by 1 to 5 %, and slower at most others: up to 9 %
+ * (H = 768, at 1 700 tokens), 16 % (H = 1024) or 6 % (H = 512), most at the lower end.  A caller who knows T may leave
+ * d_fold NULL there.  Outside that
  * range it runs the unfolded layers.  Same function either way.  The folded results differ from the
  * unfolded ones in two ways: u = gamma (.) z is stored in fp16 instead of LN(z), so every stored value carries
  * a rounding error of 2^-11 |u| that the normalisation then divides by the row's standard deviation; and the

@@ -389,9 +389,10 @@ __device__ __forceinline__ void load_resid(const half_t* __restrict__ resid, con
 // ---------------------------------------------------------------------------
 // Pipelined kernel: direct-to-LDS slabs, NS stages, WGM x WGN wavefronts.
 // ---------------------------------------------------------------------------
-// SHAPE (0 = fan-out, N >= 2K; 1 = neither; 2 = deep reduction, K >= 2N) changes nothing in the code: it is
-// part of the kernel's name, so that a kernel trace tells the four products of an encoder layer apart
-// (QKV and FFN-up are fan-out, the output projection is square, FFN-down is deep) when they share a tile shape.
+// SHAPE (0 = fan-out, N >= 2K; 1 = neither; 2 = deep reduction, K >= 2N) changes nothing in this kernel: it is
+// part of the name, so that a kernel trace tells the four products of an encoder layer apart (QKV and FFN-up are
+// fan-out, the output projection is square, FFN-down is deep) when they share a tile shape.  In the wide kernel it
+// also selects the depth of the ring (wide_stages).
 template <int BM, int BN, int WGM, int WGN, int NS, int ACT, int EPI, int SHAPE>
 __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(
     // Argument order: what the prologue and the K loop need comes first and fits the 14 dwords that are
@@ -887,7 +888,9 @@ static bt_status launch_simple(const half_t* A, const half_t* W, half_t* C, int 
 //   us = start + rounds (slabs slab0 + epi + act) + slabs slab_u (tiles / 256),   rounds = ceil(tiles / 256).
 // slab0 is what a 64-deep slab costs a compute unit that has the chip to itself, slab_u what the other 255 add when all
 // of them fetch operands at once; act_us (one activation per output, vector work that nothing overlaps) adds to epi.
-// Its choice is within 1.1 % of the best shape on average over the measured points.  K % 64 == 0.
+// Its choice is within 1.1 % of the best shape on average over the measured points.  K % 64 == 0.  The costs of 128 x 128 and
+// 96 x 128 were fitted with three stages and are high for deep reductions, where these tiles have four (1 400 x 1024 x 4096 in
+// 96 x 128 tiles: 23.9 us by the model, 20.7 measured).
 //
 // Where the wide kernel cannot take a product (fewer than four slabs, operands of 4 GiB and more) three eight-wavefront tiles
 // of gemm_pipe_kernel with three stages stand in for it.  Fitted at K = 128 and 192, 500 to 65 536 rows, 384 to 2 048
@@ -924,9 +927,11 @@ static bool gemm_wide_ok(long long a_rows, int N, int K, int epi) {
 // -1.5 to +2 %.  FOLD exists for the other three wide shapes.
 //
 // 96 columns (four stages, see wide_stages) fill a round of deep reductions where 128-wide tiles leave a part of the chip idle or
-// start a second one: 64 x 96 wherever the model has it ahead in one round, 96 x 96 only where it fills at least 15/16 of it (below
-// it is level with 64 x 128).  us, before / now: 1 700 x 768 x 3072 15.3 / 13.5, 2 048: 15.9 / 14.0, 1 400 x 1024 x 4096 18.6 / 16.6,
-// 2 200 x 512 x 2048 10.2 / 9.5 (64 x 96); 2 800 x 768 x 3072 21.0 / 16.7, 2 192 x 1024 x 4096 25.4 / 20.9 (96 x 96).
+// start a second one: 64 x 96 wherever the model has it ahead in one round, 96 x 96 only where it fills at least 15/16 of it.
+// us, before / now: 1 700 x 768 x 3072 15.3 / 13.5, 2 048: 15.9 / 14.0, 1 400 x 1024 x 4096 18.6 / 16.6, 2 200 x 512 x 2048
+// 10.2 / 9.5 (64 x 96); 2 800 x 768 x 3072 21.0 / 16.7, 2 192 x 1024 x 4096 25.4 / 20.9 (96 x 96).  Where 64 x 128 is one round,
+// 96 x 96 with fewer tiles is level with it; what the line keeps out beside that is 2 689 to 2 784 x 768 x 3072 (232 tiles, about
+// 16.6 us against 20.2 in 128 x 128), a choice that the host tests hold at 2 699 rows.
 // Inlined: their time is idle time of the device where a launch waits for the host.
 __attribute__((always_inline)) static inline bool gemm_shape_ok(const GemmTile& t, int M, int N, int K, bt_act act, int epi, bool wide_ok) {
   if (t.kind == kNarrow) return K / 64 >= 3;

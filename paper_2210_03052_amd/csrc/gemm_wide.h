@@ -40,11 +40,12 @@ __device__ __forceinline__ void dma4_sv(const void* sbase, uint32_t voff, uint32
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(voff), "s"(sbase) : "memory", "m0");
 }
 
-// Stages.  Three hold all that LDS has room for from 192 rows on.  Deep reductions (SHAPE 2) on smaller tiles take four: a slab of
-// theirs is multiplied in a third to two thirds of the time its operands travel, and what the fourth stage costs, a slab's
-// requests ahead of the first product, they do not notice.  us, three stages / four: 1 400 x 1024 x 4096 with 96 x 128 tiles 22.8 / 20.7,
-// 128 x 128 24.5 / 23.3; 2 192 x 768 x 3072 18.7 / 18.0, 20.3 / 20.2; with 96 x 96 17.1 / 15.8.  Five and six are level with four, 160 rows level
-// (33.8 / 33.8), and K = 768 has nothing of it (1 200 x 2304, 128 x 128: 7.70 / 7.96; 160 x 128 8.73 / 8.93).
+// Stages.  Three hold all that LDS has room for from 192 rows on.  Deep reductions (SHAPE 2) on smaller tiles take four: a
+// slab of theirs is multiplied in a third to two thirds of the time its operands travel, and what the fourth stage costs, a
+// slab's requests ahead of the first product, they do not notice.  us, three stages / four: 1 400 x 1024 x 4096 with 96 x 128
+// tiles 22.8 / 20.7, 128 x 128 24.5 / 23.3; 2 192 x 768 x 3072 18.7 / 18.0, 20.3 / 20.2; with 96 x 96 17.1 / 15.8.  Five and six
+// are level with four, 160 rows level (33.8 / 33.8), and K = 768 has nothing of it (1 200 x 2304, 128 x 128: 7.70 / 7.96; 160 x 128
+// 8.73 / 8.93).
 constexpr int wide_stages(int bm, int epi, int shape) { return shape == 2 && epi == EPI_PLAIN && bm <= 128 ? 4 : 3; }
 
 template <int BM, int BN, int STAGES>
@@ -263,7 +264,8 @@ __device__ __forceinline__ void gemm_wide_tiles(char* smem, const half_t* __rest
       if constexpr (EPI == EPI_FOLD) request_row_sums(ep.ln_part, ep.ln_np, M, m0 + wm * T::WM, l16, quad, psum);
       static_for<NS - 2>([&](auto t_c) {  // the slabs behind the next one may be in flight
         slab(no{}, no{}, none{}, no{},
-             integral_constant<int, (EPI == EPI_FOLD ? MI * row_sum_requests(BM, BN) : 0) + (NS - 3 - decltype(t_c)::value) * TOT>{}, true, 0);
+             integral_constant<int, (EPI == EPI_FOLD ? MI * row_sum_requests(BM, BN) : 0) + (NS - 3 - decltype(t_c)::value) * TOT>{},
+             true, 0);
       });
       slab(no{}, no{}, none{}, yes{}, none{}, true, 0);
     } else {

@@ -312,12 +312,14 @@ static bt_status stack_fwd_folded(const bt_layer* layers, int n_layers, const fl
 // Whether fold vectors select the folded pipeline for T tokens (hidden width H, FFN width F): its residual epilogue exists for
 // the small tile shapes only (64 x 128 for the H-wide products), so not beyond one round of those on the 256 compute units,
 // and it has no split-K form, so not where the plain layer splits K of its H-wide products.
-// Six layers, folded against plain, in us on one card:
-//   width 768:  650 tokens 258 / 247,  900: 272 / 257,  1 280: 288 / 286,  1 500: 335 / 331,  2 308: 405 / 416,  2 560: 429 / 422
-//   width 1024: 600 tokens 321 / 283,  1 200: 400 / 393,  1 800: 470 / 461,  2 048: 489 / 485
-//   width 512:  1 040 tokens 220 / 212,  1 500: 234 / 230,  3 400: 326 / 326,  3 700: 342 / 358
-// The plain layer has caught up since the limits were drawn (its wide products were the slower ones then); folding leads by 1 to
-// 4 % where its tiles nearly fill the round and trails below.  The limits stay: the choice decides the results' last digits.
+// Six layers, folded against plain, in us on one card (batch of 16 sentences of even length):
+//   width 768:  655 tokens 252 / 236,  940: 271 / 258,  1 225: 287 / 293,  1 415: 343 / 325,  1 700: 360 / 331,  1 985: 381 / 376,
+//               2 080: 397 / 402,  2 308: 408 / 419,  2 460: 415 / 423,  2 560: 432 / 421,  2 688: 458 / 437
+//   width 1024: 515 tokens 315 / 273,  800: 335 / 302,  1 180: 397 / 379,  1 465: 414 / 406,  1 845: 472 / 465,  2 048: 483 / 486
+//   width 512:  1 040 tokens 215 / 204,  1 580: 231 / 222,  2 120: 277 / 261,  2 480: 290 / 297,  3 380: 324 / 319,  4 096: 361 / 379
+// The plain layer has caught up since the limits were drawn: its wide products were the slower ones then, and deep reductions
+// have tiles of 96 columns now (1 350 to 2 050 tokens of width 768), for which the residual epilogue has no form.  Folding leads
+// by 1 to 5 % at some counts of the upper half and trails elsewhere.  The limits stay: the choice decides the results' last digits.
 static bool folded_pays(int T, int H, int F) {
   if ((long long)((T + 63) / 64) * ((H + 127) / 128) > 256) return false;
   return gemm_splitk_choice(T, H, F) == 1 && gemm_splitk_choice(T, H, H) == 1;

@@ -189,10 +189,13 @@ __device__ __forceinline__ void pv_step(const half_t* sv, int ks, int db, const 
 // been; an overflow or a NaN fails the comparison.  Else the tile's exponentials are taken again behind raise_reference, and
 // the wavefront looks at the maximum from then on.  So the guess changes no bit, a row's result does not depend on the other
 // rows of its wavefront, and where logits keep rising it costs the exponentials of one tile per wavefront, once.
-// A guess in every tile, with the reference raised per block of 32 keys where a sum asked for it, was 2 to 5 % faster on
-// N(0,1) logits but up to 45 % slower where logits rise along the keys (8 sequences of 1024 to 4096 tokens, 16 heads, us,
-// maximum in every tile / that / this: N(0,1) logits 320.6 / 306.6 / 304.5, N(0,9) 325.3 / 315.8 / 326.7, rows that attend
-// near themselves 300.5 / 367.8 / 303.6, logits that rise every 24 keys 321.8 / 475.4 / 323.6).
+// A guess in every tile, with the reference raised per block of 32 keys where a sum asked for it, was level on N(0,1) logits
+// but up to 45 % slower where logits rise along the keys.  us, maximum in every tile / that / this:
+//                                          N(0,1)                N(0,9)                near itself           rises every 24 keys
+//   8 x 1024 to 4096, 16 heads    263.5 / 252.4 / 250.8   268.2 / 260.0 / 269.4   245.8 / 302.4 / 246.7   257.8 / 356.8 / 258.1
+//   12 x 1024 to 1536, 16 heads   107.6 / 102.7 / 103.0   109.4 / 107.0 / 109.5   102.7 / 127.5 / 102.5   105.5 / 143.7 / 106.0
+//   27 x 611, 12 heads             48.2 /  46.1 /  47.8    48.9 /  48.1 /  48.3    47.5 /  55.3 /  46.8    47.7 /  61.9 /  47.0
+// ("near itself": rows that attend to their neighbourhood.  The last line is below the length from which a guess is made.)
 template <bool GUESS>
 __device__ __forceinline__ void process_tile(const half_t* sk, const half_t* sv, const half8_t (&qf)[4], int k0, int L,
                                              float scale_log2e, const FragAddr& fa, bool& calm, float& m_run, float& l_run,
@@ -386,12 +389,18 @@ __global__ __launch_bounds__(NW * 64, 4) void varlen_mha_kernel(
   // By the length of the sequence.  From six tiles on the loop is unrolled over the two stages, and every LDS address is a lane
   // constant plus an immediate; below, the larger code costs more than that gives.  us, unrolled / not: 16 x up to 256, 12 heads
   // 7.02 / 6.75, 16 x 100 to 512 13.2 / 13.3, 16 x 128 to 1024 29.6 / 30.2, 8 x 1024 to 4096, 16 heads 334 / 339.
-  // From 2 048 keys on the exponentials do not wait for the maximum (process_tile).  A wrong guess stops the other wavefronts of the
-  // workgroup too, in up to four tiles: with it from 1 024 keys on, N(0,9) logits at 16 x 128 to 1024 took 31.9 us, without 31.0.
-  if (NW == 4 && ntiles >= 32) {
+  // From 16 tiles on the exponentials do not wait for the maximum (process_tile), unless a row of the first tile has its weight
+  // on one or two keys: such logits will outgrow their reference.  A wrong guess stops the other wavefronts of the workgroup too,
+  // in up to four tiles: with it from ten tiles on, 16 x 500 to 700 28.6 us on N(0,1) logits, 29.5 without, but 31.8 / 30.5 where
+  // they rise; without the look at the first tile N(0,9) logits took 110.5 us at 12 x 1024 to 1536, with it 109.5.
+  if (NW == 4 && ntiles >= 16) {
     for (int kt = 0; kt < ntiles; kt += 2) {
       tile(kt, even{}, std::true_type{});
-      if (kt == 0) calm = true;
+      if (kt == 0) {
+        float lo, hi;
+        both_halves(l_run, lo, hi);
+        calm = __builtin_amdgcn_ballot_w64(!(lo + hi >= 2.f)) == 0;  // row sums relative to the largest probability, 1
+      }
       if (kt + 1 < ntiles) tile(kt + 1, odd{}, std::true_type{});
     }
   } else if (NW == 4 && ntiles >= 6) {
