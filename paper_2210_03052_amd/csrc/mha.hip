@@ -187,8 +187,9 @@ __device__ __forceinline__ void pv_step(const half_t* sv, int ks, int db, const 
 // tile's maximum, and the row sums tell whether that was right.  A lane's sum below 192 means probabilities below 192, a
 // maximum that raise_reference would have left alone (its limit is 256), and what has been computed is what it would have
 // been; an overflow or a NaN fails the comparison.  Else the tile's exponentials are taken again behind raise_reference, and
-// the wavefront looks at the maximum from then on.  So the guess changes no bit, a row's result does not depend on the other
-// rows of its wavefront, and where logits keep rising it costs the exponentials of one tile per wavefront, once.
+// the wavefront looks at the maximum from then on.  So the guess changes no bit (while fp32 resolves the distance of the two
+// limits, 0.4 in the exponent: logits below 2^21), a row's result does not depend on the other rows of its wavefront, and
+// where logits keep rising it costs the exponentials of one tile per wavefront, once.
 // A guess in every tile, with the reference raised per block of 32 keys where a sum asked for it, was level on N(0,1) logits
 // but up to 45 % slower where logits rise along the keys.  us, maximum in every tile / that / this:
 //                                          N(0,1)                N(0,9)                near itself           rises every 24 keys
